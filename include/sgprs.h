@@ -177,14 +177,15 @@ int sgprs_pack_conv_weights(const sgprs_conv_desc_t *d, const float *w_oihw, voi
                             size_t bytes);
 int sgprs_unpack_conv_weights(const sgprs_conv_desc_t *d, const void *w_packed, size_t bytes,
                               float *w_oihw);
-/* Split-K scratch needed on a partition of partition_cus CUs (0 when the
- * launch is not split). */
+/* Split-K scratch needed on a partition of partition_cus CUs (0 when no kernel
+ * that splits K over workgroups is a candidate for the launch). */
 int sgprs_conv2d_workspace(const sgprs_conv_desc_t *d, int partition_cus, size_t *bytes);
 /* Which kernel sgprs_conv2d would launch for this shape on a partition of
  * partition_cus CUs, with or without a residual (host logic only, nothing is
  * enqueued).  family: 0 implicit GEMM, 1 LDS-patch 3x3, 2 stride-2 LDS-patch
  * 3x3, 3 row-streaming 3x3 (64 -> 64 channels, 56-pixel rows), 4 the 7x7 stem;
- * detail: the tile variant, or the output rows per stream and job of family 3. */
+ * detail: the tile variant (family 0: from 8 on, those that split K over the
+ * wavefronts of a workgroup), or the output rows per stream and job of family 3. */
 int sgprs_conv2d_plan(const sgprs_conv_desc_t *d, int partition_cus, int has_residual, int *family,
                       int *detail);
 /* y = act( scale[k] * conv(x, w)[.,k] + shift[k] (+ residual) ).
@@ -201,7 +202,9 @@ int sgprs_conv2d(const sgprs_conv_desc_t *d, const void *x, const void *w_packed
  * (default); 0: implicit GEMM only; 1: the stride-1 LDS-patch kernel with the
  * given tile variant (0..4) and split factor where the shape allows it; 2:
  * automatic, but implicit-GEMM launches use tile variant `variant` (0..3)
- * wherever it divides cout, with split-K factor `splits` (0: planner's choice);
+ * wherever it divides cout, with split-K factor `splits` (0: planner's choice),
+ * and with `variant` 8..17 every 3x3 and 1x1 layer uses that tile of the kernel
+ * that splits K over a workgroup's wavefronts;
  * 3: automatic, plus the stride-2 LDS-patch kernel (not chosen otherwise) with
  * tile variant `variant` (0: 256 rows, 1: 128 rows) wherever the shape allows
  * it; variant 2 switches it off again; 4: automatic, but stage 0 of a bf16

@@ -798,19 +798,41 @@ static bool patch_geometry_uncached(const sgprs_conv_desc_t& d, int v, int split
 static std::atomic<int> g_force_variant{-1}, g_force_splits{0};
 void patch_force(int variant, int splits) { g_force_variant = variant; g_force_splits = splits; }
 
+// Rounds of work items the busiest workgroup runs on a partition of `cus` CUs, and the grid.  The
+// die-keyed item order pads its index space (row tiles to a multiple of 8); where that costs a
+// round (a few row tiles on a small partition: 2 x 4 tiles of one 14x14x256 image on 8 CUs took 4
+// rounds, 41 us) the plain order is used instead.
+static int patch_rounds(PatchArgs* a, int cus, int occ, int* grid)
+{
+    const long long room = (long long)cus * occ;
+    int g = (int)std::min<long long>(a->n_slots, room);
+    if (a->xcd_groups && g >= 8) g -= g % 8;  // a multiple of 8 keeps every workgroup on one die across its items
+    int rounds = (a->n_slots + g - 1) / g;
+    if (a->xcd_groups) {
+        const int items = a->n_mtiles * a->n_ntiles * a->splits, gp = (int)std::min<long long>(items, room), plain = (items + gp - 1) / gp;
+        if (plain < rounds) {
+            a->xcd_groups = 0;
+            a->n_slots = items;
+            g = gp;
+            rounds = plain;
+        }
+    }
+    *grid = g;
+    return rounds;
+}
+
 // Picks the tile variant: the candidate with the smallest estimated time
 // rounds(items / CUs) * (chunks * cost-per-chunk + cost-per-item); the costs (in
 // microseconds, whole-GPU measurements at batch 64) only rank candidates.
-// When a shape offers too few work items to fill the partition and is deep in K
-// this kernel declines and the implicit-GEMM path (with its split-K) takes over.
-bool plan_patch(const sgprs_conv_desc_t& d, int cus, int* variant, int* splits)
+// The caller compares the winner's time with those of the other kernel families.
+bool plan_patch(const sgprs_conv_desc_t& d, int cus, int* variant, int* splits, double* cost_us)
 {
     if (!patch_eligible(d)) return false;
     PatchArgs a;
     const int fv = g_force_variant.load(), fs = g_force_splits.load();
     if (fv >= 0) {
         if (fv >= kNumPatchVariants || !patch_geometry(d, fv, std::max(1, fs), &a)) return false;
-        *variant = fv; *splits = std::max(1, fs);
+        *variant = fv; *splits = std::max(1, fs); *cost_us = 0.0;
         return true;
     }
     // {variant, microseconds per chunk, microseconds per work item}
@@ -823,16 +845,14 @@ bool plan_patch(const sgprs_conv_desc_t& d, int cus, int* variant, int* splits)
         // occupy the partition
         for (int sp = 1; sp <= 2; ++sp) {
             if (!patch_geometry(d, c.v, sp, &a)) continue;
-            const long long items = (long long)a.n_mtiles * a.n_ntiles * sp;
-            // far fewer items than CUs: the partition's time is one workgroup's serial K loop. A shallow
-            // one (up to four chunks, Cin <= 128) is over before a split implicit GEMM plus its reduction
-            // pass would be (batch 1 on 256 CUs: 6.0 against 6.9-9.8 us at 56x56x64, 7.8 against 10.2 us
-            // at 28x28x128); a deep one is left to the implicit GEMM's wider split-K
-            if (items * 3 < cus && (sp > 1 || a.chunks_per_split > 4)) continue;
-            const long long rounds = (items + cus - 1) / cus;
+            // far fewer items than CUs and deep in K: the partition's time would be one workgroup's
+            // serial chain, which the kernels that split K shorten
+            if ((long long)a.n_mtiles * a.n_ntiles * sp * 3 < cus && (sp > 1 || a.chunks_per_split > 4)) continue;
+            int grid = 0;
+            const int rounds = patch_rounds(&a, cus, 1, &grid);
             double cost = rounds * (a.chunks_per_split * c.step + c.item);
             if (sp > 1) cost += 9.0 + (double)d.n * d.h * d.w * d.cout * 4.0 * (sp + 1) / (3.0e6 * cus / 256.0);
-            if (cost < best) { best = cost; *variant = c.v; *splits = sp; found = true; }
+            if (cost < best) { best = cost; *variant = c.v; *splits = sp; *cost_us = cost; found = true; }
         }
     }
     return found;
@@ -891,9 +911,8 @@ int launch_conv3x3_patch(const sgprs_conv_desc_t& d, int variant, int splits, co
     a.x_bytes = (unsigned)((size_t)d.n * d.h * d.w * d.cin * 2); a.w_bytes = (unsigned)((size_t)d.cout * 9 * d.cin * 2);
     a.y_bytes = (unsigned)((size_t)d.n * d.h * d.w * d.cout * 2);
     const int occ = variant == kPatchDlPairVariant ? 2 : 1;  // small enough for two workgroups per CU
-    // a multiple of 8 keeps every workgroup on one die across its items
-    int grid = (int)std::min<long long>(a.n_slots, (long long)cus * occ);
-    if (a.xcd_groups && grid >= 8) grid -= grid % 8;
+    int grid = 0;
+    patch_rounds(&a, cus, occ, &grid);
     const bool stat = variant != kPatchDlPairVariant && a.n_chunks == 2 && a.n_ntiles == 1 && a.splits == 1;  // resident weights
     const double M = (double)d.n * d.h * d.w;
     const double flops = 2.0 * M * d.cout * 9.0 * d.cin;

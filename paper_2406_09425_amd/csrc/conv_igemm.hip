@@ -480,6 +480,7 @@ const char* igemm_pair_variant_name(int v)
 {
     static char buf[8][96];
     static int next = 0;
+    if (v >= kKsplitNames) return ksplit_variant_name(v - kKsplitNames);
     if (v < 0 || v >= 16 || (v & 7) >= 4) return "?";
     const int* t = kIgemmShape[v & 7];
     char* out = buf[next++ & 7];
@@ -492,6 +493,7 @@ const char* igemm_variant_name(int v)
 {
     static char buf[8][96];
     static int next = 0;
+    if (v >= kKsplitNames) return ksplit_variant_name(v - kKsplitNames);
     if (v < 0 || v >= 32 || (v & 7) >= 4) return "?";
     const int* t = kIgemmShape[v & 7];
     char* out = buf[next++ & 7];
@@ -561,6 +563,10 @@ int launch_conv_pair(const sgprs_conv_desc_t& d0, const void* w0, const float* s
     *done = false;
     if (d0.dtype != d1.dtype || d0.n != d1.n || d0.h != d1.h || d0.w != d1.w || d0.cin != d1.cin) return SGPRS_OK;
     const ConvPlan p0 = plan_conv(d0, cus);
+    if (p0.bm != 0 && p0.kind == 4 && ksplit_fits(d1, p0.variant) && d1.cout == d0.cout && d1.stride == d0.stride && d1.pad == d1.r / 2 && d0.pad == d0.r / 2) {
+        *done = true;
+        return launch_conv_ksplit(d0, p0.variant, x, w0, scale0, shift0, nullptr, y0, &d1, w1, scale1, shift1, y1, stream, prof);
+    }
     ConvPlan p1 = plan_conv(d1, cus);
     if (p0.bm == 0 || p0.kind != 0 || p0.splits != 1 || p1.bm == 0 || p1.kind != 0) return SGPRS_OK;
     // the second problem takes the first one's tile shape
@@ -596,6 +602,8 @@ int launch_conv(const sgprs_conv_desc_t& d, const void* x, const void* w, const 
     if (p.kind == 1)
         return launch_conv3x3_patch(d, p.variant, p.splits, x, w, scale, shift, residual, y, ws, ws_bytes, stream, cus,
                                     prof);
+    if (p.kind == 4)
+        return launch_conv_ksplit(d, p.variant, x, w, scale, shift, residual, y, nullptr, nullptr, nullptr, nullptr, nullptr, stream, prof);
     if (p.kind == 3) return launch_conv3x3_rows(d, p.variant, x, w, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 2) {
         return launch_conv3x3s2_patch(d, p.variant, x, w, scale, shift, y, nullptr, nullptr, nullptr, nullptr, nullptr, stream, cus,

@@ -159,7 +159,8 @@ extern std::atomic<int> g_plan_generation;  // bumped whenever a tuning override
 
 // Tile configuration of one implicit-GEMM launch.
 struct ConvPlan {
-    int kind = 0;      // 0: implicit GEMM, 1: LDS-patch 3x3 kernel, 2: its stride-2 variant, 3: row streaming
+    int kind = 0;      // 0: implicit GEMM, 1: LDS-patch 3x3 kernel, 2: its stride-2 variant, 3: row streaming,
+                       // 4: implicit GEMM with K split over a workgroup's wavefronts
     int variant = 0;   // index into the kernel's tile table (row streaming: output rows per stream and job)
     int bm = 0, bn = 0;
     int splits = 1;    // split-K factor (grid.z)
@@ -244,7 +245,7 @@ int launch_stem_pool(int dtype, int n, int h, int w, const void* x, const void* 
                      const float* scale, const float* shift, void* y, hipStream_t stream, int cus, Profiler* prof);
 
 // LDS-patch 3x3 kernel (bf16, stride 1)
-bool plan_patch(const sgprs_conv_desc_t& d, int cus, int* variant, int* splits);
+bool plan_patch(const sgprs_conv_desc_t& d, int cus, int* variant, int* splits, double* cost_us);
 void patch_force(int variant, int splits);
 const char* patch_variant_name(int variant);
 int launch_conv3x3_patch(const sgprs_conv_desc_t& d, int variant, int splits, const void* x, const void* w,
@@ -265,6 +266,15 @@ bool plan_rows(const sgprs_conv_desc_t& d, int cus, int* rows_per_stream);
 void rows_force_off(bool off);
 int launch_conv3x3_rows(const sgprs_conv_desc_t& d, int rows_per_stream, const void* x, const void* w, const float* scale,
                         const float* shift, const void* residual, void* y, hipStream_t stream, int cus, Profiler* prof);
+// implicit GEMM with the K range split over the wavefronts of a workgroup (few output tiles)
+bool plan_ksplit(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us);
+int ksplit_num_variants();
+const char* ksplit_variant_name(int v);
+constexpr int kKsplitNames = 32;  // launches of this kernel are recorded as implicit GEMM (or pair), variant 32 + 16 * dtype + tile
+bool ksplit_fits(const sgprs_conv_desc_t& d, int variant);
+int launch_conv_ksplit(const sgprs_conv_desc_t& d, int variant, const void* x, const void* w, const float* scale, const float* shift,
+                       const void* res, void* y, const sgprs_conv_desc_t* d1, const void* w1, const float* scale1,
+                       const float* shift1, void* y1, hipStream_t stream, Profiler* prof);
 // tuning override: kind -1 automatic, 0 implicit GEMM only, 1 force patch (variant, splits)
 extern std::atomic<int> g_conv_force_kind;
 extern std::atomic<int> g_igemm_force_variant, g_igemm_force_splits;

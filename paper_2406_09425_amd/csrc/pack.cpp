@@ -60,7 +60,7 @@ std::atomic<int> g_igemm_force_splits{0};
 
 std::atomic<int> g_plan_generation{0};
 
-static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual);
+static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit);
 
 ConvPlan plan_conv(const sgprs_conv_desc_t& d, int cus, bool has_residual)
 {
@@ -70,13 +70,18 @@ ConvPlan plan_conv(const sgprs_conv_desc_t& d, int cus, bool has_residual)
     Key k;
     memset(&k, 0, sizeof(k));
     k.d = d; k.cus = cus; k.res = has_residual; k.gen = g_plan_generation.load();
-    return memo.get(local, k, [&]() { return plan_conv_uncached(d, cus, has_residual); });
+    return memo.get(local, k, [&]() { return plan_conv_uncached(d, cus, has_residual, true); });
 }
 
-static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual)
+static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit)
 {
     const int force_kind = g_conv_force_kind.load(), force_variant = g_igemm_force_variant.load(),
               force_splits = g_igemm_force_splits.load();
+    if (force_variant >= 8 && ksplit_fits(d, force_variant - 8)) {
+        ConvPlan p;
+        p.kind = 4; p.variant = force_variant - 8; p.bm = 1;
+        return p;
+    }
     if (force_kind == -1) {
         int rows = 0;
         if (plan_rows(d, cus < 1 ? 1 : cus, &rows)) {
@@ -86,19 +91,29 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
             return p;
         }
     }
+    if (cus < 1) cus = 1;
+    ConvPlan best;
+    double best_cost = 1e30;
     if (force_kind != 0) {
         int v = 0, s = 1;
-        if (plan_patch(d, cus < 1 ? 1 : cus, &v, &s)) {
-            ConvPlan p;
-            p.kind = 1; p.variant = v; p.splits = s;
-            p.bm = 1;  // marks a valid plan
-            return p;
+        double cost = 0.0;
+        if (plan_patch(d, cus, &v, &s, &cost)) {
+            best.kind = 1; best.variant = v; best.splits = s;
+            best.bm = 1;  // marks a valid plan
+            best_cost = cost;
+            if (force_kind == 1) return best;
         }
-        if (force_kind != 1 && !has_residual && plan_s2patch(d, cus < 1 ? 1 : cus, &v)) {
-            ConvPlan p;
-            p.kind = 2; p.variant = v; p.splits = 1;
-            p.bm = 1;
-            return p;
+        if (force_kind != 1 && !has_residual && plan_s2patch(d, cus, &v)) {
+            best.kind = 2; best.variant = v; best.splits = 1;
+            best.bm = 1;
+            return best;
+        }
+        // a forced implicit-GEMM tile is for the layers that would take that family anyway
+        if (best.bm && force_variant >= 0) return best;
+        if (ksplit && force_variant < 0 && force_kind != 1 && plan_ksplit(d, cus, &v, &cost) && cost < best_cost) {
+            best = ConvPlan();
+            best.kind = 4; best.variant = v; best.bm = 1;
+            best_cost = cost;
         }
     }
     const int P = out_dim(d.h, d.r, d.stride, d.pad), Q = out_dim(d.w, d.s, d.stride, d.pad);
@@ -107,9 +122,9 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
     const int ktiles = d.r * d.s * d.cin / kt_el;
     // time of one 128x128 tile over one k-tile on one CU at a realistic rate
     const double us_per_ktile_128 = d.dtype == SGPRS_BF16 ? 0.45 : 1.8;
-    ConvPlan best;
-    double best_cost = 1e30;
-    if (cus < 1) cus = 1;
+    // with two LDS stages a k-tile cannot take less than one trip to the L2 (bf16 14x14x256 -> 256/2
+    // at one image, 18 k-tiles in a row: 10.1 us)
+    const double us_per_ktile_min = 0.45, us_per_block = 2.9;
     for (int v = 0; v < igemm_num_variants(); ++v) {
         Tile t = kTiles[v];
         if (d.cout % t.bn) continue;
@@ -132,7 +147,7 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
             const int kt_per = (ktiles + s - 1) / s;
             if (s > 1 && (long long)(s - 1) * kt_per >= ktiles) continue;  // an empty split
             const double per_block =
-                kt_per * us_per_ktile_128 * (t.bm * t.bn / 16384.0) / t.eff * occ + 2.0;
+                kt_per * std::max(us_per_ktile_min, us_per_ktile_128 * (t.bm * t.bn / 16384.0) / t.eff * occ) + us_per_block;
             const long long rounds = (blocks * s + (long long)cus * occ - 1) / ((long long)cus * occ);
             double cost = rounds * per_block;
             if (s > 1) {
@@ -141,6 +156,7 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
             }
             if (cost < best_cost) {
                 best_cost = cost;
+                best.kind = 0;
                 best.variant = v; best.bm = t.bm; best.bn = t.bn; best.splits = s; best.ktiles = ktiles;
                 best.grid_m = (int)gm; best.grid_n = (int)gn;
             }
@@ -232,9 +248,13 @@ int sgprs_conv2d_workspace(const sgprs_conv_desc_t* d, int partition_cus, size_t
     if (rc) return rc;
     if (!bytes) return fail(SGPRS_ERR_INVALID_ARG, "bytes is NULL");
     if (partition_cus <= 0) return fail(SGPRS_ERR_INVALID_ARG, "partition_cus %d <= 0", partition_cus);
-    // the plan may depend on whether a residual is passed: enough for either
-    *bytes = is_stem(*d) ? 0 : std::max(conv_workspace_bytes(*d, plan_conv(*d, partition_cus, false)),
-                                        conv_workspace_bytes(*d, plan_conv(*d, partition_cus, true)));
+    // The plan may depend on whether a residual is passed, and a tuning override may switch to the
+    // kernels that split K over workgroups after the caller has allocated: enough for all of them.
+    *bytes = 0;
+    if (!is_stem(*d))
+        for (int res = 0; res < 2; ++res)
+            *bytes = std::max({*bytes, conv_workspace_bytes(*d, plan_conv(*d, partition_cus, res != 0)),
+                               conv_workspace_bytes(*d, plan_conv_uncached(*d, partition_cus, res != 0, false))});
     return SGPRS_OK;
 }
 
@@ -250,7 +270,7 @@ int sgprs_conv2d_plan(const sgprs_conv_desc_t* d, int partition_cus, int has_res
     }
     const ConvPlan p = plan_conv(*d, partition_cus, has_residual != 0);
     if (p.bm == 0) return fail(SGPRS_ERR_UNSUPPORTED, "no tile shape fits cout %d", d->cout);
-    *family = p.kind; *detail = p.variant;
+    *family = p.kind == 4 ? 0 : p.kind; *detail = p.kind == 4 ? 8 + p.variant : p.variant;
     return SGPRS_OK;
 }
 

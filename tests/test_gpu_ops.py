@@ -414,3 +414,35 @@ def test_igemm_forced_tiles_and_splits_parity(pools, dtype):
                     assert_close(got, ref, dtype, f"igemm variant {variant} splits {splits} {shape}")
     finally:
         S.sgprs_conv_tuning_override(-1, 0, 1)
+
+
+# ---- implicit GEMM with K split over the wavefronts of a workgroup -----------------------
+KSPLIT_SHAPES = [
+    # n, h, w, cin, cout, k, stride, pad: ragged pixel tiles; fewer k-tiles than wavefronts (1x1); shares of 2..9
+    # k-tiles, i.e. inside and beyond the ring; channel tiles per die (512) and pixel ranges per die (64, 192)
+    (1, 5, 5, 64, 64, 1, 1, 0),
+    (3, 9, 13, 64, 192, 3, 1, 1),
+    (2, 11, 7, 128, 64, 3, 2, 1),
+    (1, 7, 7, 512, 512, 3, 1, 1),
+    (1, 14, 14, 256, 512, 1, 2, 0),
+]
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
+@pytest.mark.parametrize("variant", range(10))
+def test_conv_ksplit_tiles_parity(pools, dtype, variant):
+    pool = pools["full"]
+    try:
+        S.sgprs_conv_tuning_override(2, 8 + variant, 0)
+        for shape in KSPLIT_SHAPES:
+            n, h, w, cin, cout, k, stride, pad = shape
+            d = S.ConvDesc(n, h, w, cin, cout, k, k, stride, pad, dtype, 1)
+            assert S.sgprs_conv2d_plan(d, pool.partition_cus(0)) == (0, 8 + variant)
+            for with_res in (True, False):
+                got, ref = conv_case(dtype, *shape, relu=with_res, with_res=with_res, seed=140 + variant, pool=pool,
+                                     cus=pool.partition_cus(0))
+                e = assert_close(got, ref, dtype, f"ksplit tile {variant} {shape}")
+                if dtype == S.SGPRS_F32:
+                    assert e < 2e-5, e  # fp32 accumulation over K <= 4608: about sqrt(K) * 2^-24
+    finally:
+        S.sgprs_conv_tuning_override(-1, 0, 1)
