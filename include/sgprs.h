@@ -428,10 +428,11 @@ int sgprs_sched_run_periodic(sgprs_sched_t *sched, sgprs_pool_t *pool, sgprs_tas
  * one partition: the comparison shape of "Simulation Results"): task i runs
  * `rounds` inferences of `batch` images on partition partition_of_task[i]
  * (HOST int[n_tasks]) through sgprs_task_run; inputs[i] / logits[i] DEVICE as
- * there.  The calling thread hands out one inference at a time per task,
- * round-robin, keeps at most max_busy partitions busy at once (0: no limit; see
- * sgprs_sched_set_max_busy for why 4 is the useful value on MI355X), and polls
- * one event per task.  Blocking; *elapsed_s (may be NULL) receives the wall time
+ * there.  The calling thread keeps at most max_busy partitions busy at once (0:
+ * no limit; see sgprs_sched_set_max_busy for why 4 is the useful value on
+ * MI355X), up to two inferences queued on each; partitions take turns of up to
+ * eight inferences, the tasks of a partition in round-robin order, and the
+ * thread polls one event per inference.  Blocking; *elapsed_s (may be NULL) receives the wall time
  * from the first launch to the last completion.  Tasks sharing a partition run
  * one after the other. */
 int sgprs_pool_run_static(sgprs_pool_t *pool, sgprs_task_t *const *tasks, int n_tasks,

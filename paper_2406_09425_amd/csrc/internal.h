@@ -30,10 +30,13 @@ int fail(int status, const char* fmt, ...) __attribute__((format(printf, 2, 3)))
                                  hipGetErrorString(e_), __FILE__, __LINE__);              \
     } while (0)
 
-// CU-masked streams that may be busy at once without the throughput of all of them collapsing
-// (measured on MI355X: eight batch-1 tasks reach 20 k images/s over 4 busy partitions of a pool of 8,
-// 8-9 k over 5, 6 or 8, whatever the partition size; idle partitions cost nothing).
-constexpr int kMaxBusyQueues = 4;
+// CU-masked streams are hardware queues, and the queues of a process take turns on four dispatch
+// pipes, queue after queue.  Two queues of one pipe that are busy together slow each other down four
+// times (measured on MI355X, batch-1 tasks on 32-CU partitions of a pool of eight: 290 us per
+// inference on partitions (p, p + 4) for every p, 74 us on all 24 other pairs; 39.5 us on any four
+// partitions that differ modulo 4, 145-156 us on four that do not).  Idle queues cost nothing.
+constexpr int kDispatchPipes = 4;
+constexpr int kMaxBusyQueues = kDispatchPipes;
 
 // ---- pool ------------------------------------------------------------------
 struct Partition {
