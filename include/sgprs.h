@@ -203,7 +203,7 @@ int sgprs_conv2d(const sgprs_conv_desc_t *d, const void *x, const void *w_packed
  * given tile variant (0..4) and split factor where the shape allows it; 2:
  * automatic, but implicit-GEMM launches use tile variant `variant` (0..3)
  * wherever it divides cout, with split-K factor `splits` (0: planner's choice),
- * and with `variant` 8..17 every 3x3 and 1x1 layer uses that tile of the kernel
+ * and with `variant` 8..15 every 3x3 and 1x1 layer uses that tile of the kernel
  * that splits K over a workgroup's wavefronts;
  * 3: automatic, plus the stride-2 LDS-patch kernel (not chosen otherwise) with
  * tile variant `variant` (0: 256 rows, 1: 128 rows) wherever the shape allows

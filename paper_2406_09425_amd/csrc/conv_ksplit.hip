@@ -18,8 +18,9 @@
 //     reproducible), then scale/shift, residual and ReLU in fp32.
 // Measured in a chain of launches (us each, launch included; before: implicit GEMM with split-K
 // over workgroups, or the LDS-patch kernel), bf16, one image on 256 CUs: 56x56x64 3.6 (5.8),
-// 28x28x128 3.5 (7.4), 14x14x256 4.2 (9.9), 7x7x512 5.5 (11.3), 28x28x128 -> 256/2 3.2 (10.1); fp32
-// 6.0 / 5.8 / 5.9 / 8.7 (10.2 / 11.4 / 13.1 / 14.8).  An empty kernel in such a chain takes 1.8.
+// 28x28x128 3.7 (7.4), 14x14x256 3.8 (9.9), 7x7x512 5.0 (11.3), 28x28x128 -> 256/2 3.4 (10.1); fp32
+// 5.7 / 5.4 / 5.7 / 8.7 (10.2 / 11.4 / 13.1 / 14.8), and at 16 images 37 / 36 / 34 for the last three
+// (50 with split-K; 27 at the fp32 matrix rate with the 12 % idle CUs of their tile counts).  An empty kernel in such a chain takes 1.8.
 //
 // Small tiles trade traffic for parallelism, so this kernel is for launches
 // that cannot fill the partition with big tiles; see plan_ksplit for the line.
@@ -34,6 +35,20 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+
+// Pixel and channel tiles (of 16), ring stages.  The set covers the best of sixteen shapes (four and
+// eight wavefronts among them) within 1 % over 171 measured launches (nine layers, 1..16 images,
+// 8..256 CUs, both types): 16x16 and 16x32 for launches that leave CUs idle, 7-row tiles for fp32
+// maps whose pixel count is a multiple of 7 * 16.
+#define SGPRS_KSPLIT_VARIANTS(X) \
+    X(0, 1, 1, 4) X(1, 1, 2, 3) X(2, 2, 2, 2) X(3, 4, 2, 2) X(4, 2, 4, 3) X(5, 4, 4, 2) X(6, 7, 1, 2) X(7, 7, 2, 2)
+constexpr int kKsplitWaves = 4;
+constexpr int kKsplitShape[][3] = {
+#define X(v, tm, tn, ns) {tm, tn, ns},
+    SGPRS_KSPLIT_VARIANTS(X)
+#undef X
+};
+constexpr int kKsplitVariants = sizeof(kKsplitShape) / sizeof(kKsplitShape[0]);
 
 // One convolution.  Divisions m / d of 0 <= m < 2^31 are umulhi(2 m, mul) >> sh (see div_constants).
 struct KsplitArgs {
@@ -74,15 +89,18 @@ template <class F, int... I> __device__ __forceinline__ void for_each_stage(F f,
 }
 
 // One tile of 16*TM pixels x 16*TN channels: pixel tile mt, channel tile nt.
-template <int DT, int TM, int TN, int NW, int NS>
+template <int DT, int TM, int TN, int NS>
 __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
 {
+    constexpr int NW = kKsplitWaves;
     constexpr int ES = DT == SGPRS_BF16 ? 2 : 4;
-    constexpr int KT = 128 / ES, CH = 16 / ES;
     constexpr int BM = 16 * TM, BN = 16 * TN;
     constexpr int A_IT = BM / 8, B_IT = BN / 8, LPS = A_IT + B_IT;
     constexpr int STAGE = (BM + BN) * 128;
     constexpr int SROW = BN + 4;  // padded scratch row, floats
+    // fp32 MFMAs take eight times the cycles of bf16 ones: their k-loop is worth a software pipeline
+    // in every tile shape, the bf16 one only where a k-tile has 16 or more MFMAs
+    constexpr bool PIPELINED = DT == SGPRS_F32 || TM * TN >= 8;
     constexpr int ITEMS = BM * BN / 4, PER = (ITEMS + NW * 64 - 1) / (NW * 64);
     static_assert((NS - 1) * LPS <= 63, "vmcnt range");
     static_assert(BM * SROW * 4 <= NS * STAGE, "a wavefront's partial tile fits its ring");
@@ -99,22 +117,25 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
     // chunk (lane & 7) ^ (row & 7), which makes the fragment reads bank-conflict free.
     const int lrow = lane >> 3, chunk_off = ((lane & 7) ^ lrow) * 16;
     const unsigned b_off = (unsigned)((n0 + lrow) * a.w_row_bytes + chunk_off);
-    // k-tile number j of this wavefront's share, weights; past the share the descriptor has size 0:
-    // nothing is fetched, the count of outstanding requests stays the same for every wavefront
-    auto request_w = [&](int j, int slot) {
+    // Requests of k-tile number j of this wavefront's share, one instruction (8 rows) each; past the
+    // share the descriptor has size 0: nothing is fetched, the count of outstanding requests stays
+    // the same for every wavefront.
+    auto request_w = [&](int j, int slot, int i) {
 #if __HIP_DEVICE_COMPILE__  // the buffer-resource builtins exist in the device pass only
         typedef __attribute__((address_space(3))) void* lds_ptr_t;
-        const bool live = j < nkt;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, live ? (int)a.w_bytes : 0, 0x00020000);
-#pragma unroll
-        for (int i = 0; i < B_IT; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(ring + slot * STAGE + (BM + i * 8) * 128), 16, b_off + i * 8 * a.w_row_bytes,
-                                                     (kt0 + j) * 128, 0, 0);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, j < nkt ? (int)a.w_bytes : 0, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(ring + slot * STAGE + (BM + i * 8) * 128), 16, b_off + i * 8 * a.w_row_bytes,
+                                                 (kt0 + j) * 128, 0, 0);
 #endif
     };
-    // The weights of the first NS k-tiles are requested before the pixel arithmetic.
+    // A share that fits the ring is requested at once, the weights before the pixel arithmetic.
+    const bool at_once = share < NS;
+    if (at_once) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) request_w(s, s);
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int i = 0; i < B_IT; ++i) request_w(s, s, i);
+    }
     // The epilogue's operands come next, so that they are there long before it runs.
     u32x4_t rres[PER];
     f32x4_t sc[PER], sh[PER];
@@ -160,23 +181,30 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
         for (int i = 0; i < A_IT; ++i) a_voff[i] = (a_in[i] & need) == need ? (unsigned)(a_base[i] + tap_off) : 0x80000000u;
     };
     enter_tap();
-    auto request_x = [&](int j, int slot) {
+    auto request_x = [&](int j, int slot, int i) {
 #if __HIP_DEVICE_COMPILE__
         typedef __attribute__((address_space(3))) void* lds_ptr_t;
-        const bool live = j < nkt;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, live ? (int)a.x_bytes : 0, 0x00020000);
-#pragma unroll
-        for (int i = 0; i < A_IT; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(ring + slot * STAGE + i * 8 * 128), 16, a_voff[i], ic * 128, 0, 0);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, j < nkt ? (int)a.x_bytes : 0, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(ring + slot * STAGE + i * 8 * 128), 16, a_voff[i], ic * 128, 0, 0);
+#endif
+    };
+    auto next_channel_tile = [&]() {
         if (++ic == a.cin_tiles) {
             ic = 0;
             if (++is == a.taps) { is = 0; ++ir; }
             enter_tap();
         }
-#endif
     };
 #pragma unroll
-    for (int s = 0; s < NS; ++s) request_x(s, s);
+    for (int s = 0; s < NS; ++s) {
+        if (!at_once) {
+#pragma unroll
+            for (int i = 0; i < B_IT; ++i) request_w(s, s, i);
+        }
+#pragma unroll
+        for (int i = 0; i < A_IT; ++i) request_x(s, s, i);
+        next_channel_tile();
+    }
 
     f32x4_t acc[TM][TN];
 #pragma unroll
@@ -186,61 +214,141 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
 
     const int frow = lane & 15, fgrp = lane >> 4;
     const unsigned f_off = (unsigned)(frow * 128 + ((fgrp ^ (frow & 7)) << 4));  // second half of the k-tile: chunk + 4, i.e. bit 6 flipped
-    auto k_tile = [&](int st) {
-        const unsigned char* S = ring + st * STAGE;
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            u32x4_t pf[TM], wf[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) pf[i] = *(const u32x4_t*)(S + i * 16 * 128 + (f_off ^ (ks << 6)));
-#pragma unroll
-            for (int j = 0; j < TN; ++j) wf[j] = *(const u32x4_t*)(S + (BM + j * 16) * 128 + (f_off ^ (ks << 6)));
-            if constexpr (DT == SGPRS_BF16) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[j]),
-                                                                            __builtin_bit_cast(bf16x8_t, pf[i]), acc[i][j], 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wf[j][u]), __uint_as_float(pf[i][u]),
-                                                                             acc[i][j], 0, 0, 0);
-            }
-        }
+    struct Fragments { u32x4_t px[TM], w[TN]; };
+    auto read_px = [&](Fragments& f, int slot, int ks, int i) {
+        f.px[i] = *(const u32x4_t*)(ring + slot * STAGE + i * 16 * 128 + (f_off ^ (ks << 6)));
     };
-    auto refill = [&](int j, int slot) {
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // the fragments are in registers: the stage may be overwritten
-        __builtin_amdgcn_sched_barrier(0);
-        request_w(j, slot);
-        request_x(j, slot);
+    auto read_w = [&](Fragments& f, int slot, int ks, int j) {
+        f.w[j] = *(const u32x4_t*)(ring + slot * STAGE + (BM + j * 16) * 128 + (f_off ^ (ks << 6)));
     };
-    if (share < NS) {
-        // The whole share is in the ring: k-tile st has landed once only the pixel rows of the later ones are outstanding.
+    constexpr int HALF = TM * TN * (DT == SGPRS_BF16 ? 1 : 4);  // MFMAs of half a k-tile
+    auto mfma = [&](const Fragments& f, int m) {
+        const int u = m / (TM * TN), i = m % (TM * TN) / TN, j = m % TN;
+        if constexpr (DT == SGPRS_BF16)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f.w[j]), __builtin_bit_cast(bf16x8_t, f.px[i]),
+                                                                acc[i][j], 0, 0, 0);
+        else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(f.w[j][u]), __uint_as_float(f.px[i][u]), acc[i][j], 0, 0, 0);
+    };
+    if (at_once) {
+        // k-tile st has landed once only the pixel rows of the later ones are outstanding
         for_each_stage([&](auto st) {
             if (st < nkt) {
                 wait_vmcnt<(NS - 1 - st) * A_IT>();
-                k_tile(st);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    Fragments f;
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) read_px(f, st, ks, i);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) read_w(f, st, ks, j);
+#pragma unroll
+                    for (int m = 0; m < HALF; ++m) mfma(f, m);
+                }
             }
         }, std::make_integer_sequence<int, NS>());
-    } else {
-        for_each_stage([&](auto st) {
-            wait_vmcnt<(NS - 1 - st) * A_IT + st * LPS>();
-            k_tile(st);
-            refill(NS + st, st);
-        }, std::make_integer_sequence<int, NS>());
+    } else if constexpr (!PIPELINED) {
         int st = 0;
-        for (int i = NS; i < nkt; ++i) {
+        for (int t = 0; t < nkt; ++t) {
             wait_vmcnt<(NS - 1) * LPS>();
-            k_tile(st);
-            refill(i + NS, st);
+            Fragments f[2];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) read_px(f[ks], st, ks, i);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) read_w(f[ks], st, ks, j);
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the stage may be overwritten
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < B_IT; ++i) request_w(t + NS, st, i);
+#pragma unroll
+            for (int i = 0; i < A_IT; ++i) request_x(t + NS, st, i);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int m = 0; m < HALF; ++m) mfma(f[ks], m);
+            next_channel_tile();
             if (++st == NS) st = 0;
         }
+    } else {
+        // Software pipeline: while k-tile t is multiplied, its stage (whose fragments are in registers)
+        // is requested anew, and the fragments of k-tile t + 1 are read.  One request or read goes
+        // behind every few MFMAs: in a burst they would hold up the wavefront's MFMAs.
+        Fragments f[2][2];
+        int st = 0;
+        wait_vmcnt<(NS - 1) * LPS>();
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) read_px(f[0][ks], 0, ks, i);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) read_w(f[0][ks], 0, ks, j);
+        }
+        // Tied accumulators: written through the builtin, the compiler renames them within the loop and
+        // copies them back (30-50 moves per k-tile, each waiting for its MFMA: 36 instead of 31 us for
+        // fp32 14x14x256 at 16 images).  The hazard recogniser does not see into the assembly: the
+        // operands come from LDS reads, the first accumulators and the epilogue are fenced by s_nop.
+        auto mfma_tied = [&](const Fragments& f, int m) {
+#if __HIP_DEVICE_COMPILE__
+            const int u = m / (TM * TN), i = m % (TM * TN) / TN, j = m % TN;
+            if constexpr (DT == SGPRS_BF16)
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(f.w[j]), "v"(f.px[i]));
+            else
+                asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(f.w[j][u]), "v"(f.px[i][u]));
+#endif
+        };
+        auto pin_accumulators = [&]() {  // writes above and reads below stay there
+#if __HIP_DEVICE_COMPILE__
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+#endif
+        };
+        auto step = [&](int t, Fragments (&cur)[2], Fragments (&nxt)[2]) {
+            constexpr int READS = 2 * (TM + TN);
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the stage may be overwritten
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < HALF; ++m) {
+                mfma_tied(cur[0], m);
+#pragma unroll
+                for (int k = m * LPS / HALF; k < (m + 1) * LPS / HALF; ++k) {
+                    if (k < B_IT) request_w(t + NS, st, k);
+                    else request_x(t + NS, st, k - B_IT);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            next_channel_tile();
+            if (++st == NS) st = 0;
+            wait_vmcnt<(NS - 1) * LPS>();
+#pragma unroll
+            for (int m = 0; m < HALF; ++m) {
+                mfma_tied(cur[1], m);
+#pragma unroll
+                for (int k = m * READS / HALF; k < (m + 1) * READS / HALF; ++k) {
+                    const int ks = k / (TM + TN), q = k % (TM + TN);
+                    if (q < TM) read_px(nxt[ks], st, ks, q);
+                    else read_w(nxt[ks], st, ks, q - TM);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        pin_accumulators();
+#if __HIP_DEVICE_COMPILE__
+        asm volatile("s_nop 7");
+#endif
+        for (int t = 0; t < nkt; t += 2) {
+            step(t, f[0], f[1]);
+            if (t + 1 < nkt) step(t + 1, f[1], f[0]);
+        }
+#if __HIP_DEVICE_COMPILE__
+        asm volatile("s_nop 15\n\ts_nop 15");
+#endif
+        pin_accumulators();
     }
     __builtin_amdgcn_s_waitcnt(0);  // the (empty) requests still in flight write LDS too
     __builtin_amdgcn_sched_barrier(0);
@@ -296,8 +404,8 @@ __device__ __forceinline__ bool ks_place(const KsplitArgs& a, int b, int* mt, in
 // the same input and have the same output shape, share a launch.  The arguments are read as one
 // batch of scalar loads from the kernel-argument segment: left to itself the compiler loads them
 // piecemeal where they are used, a chain of scalar-cache misses before the first request.
-template <int DT, int TM, int TN, int NW, int NS>
-__global__ __launch_bounds__(NW * 64) void conv_ksplit_kernel(const KsplitLaunch launch)
+template <int DT, int TM, int TN, int NS>
+__global__ __launch_bounds__(kKsplitWaves * 64) void conv_ksplit_kernel(const KsplitLaunch launch)
 {
     KsplitArgs a;
 #if __HIP_DEVICE_COMPILE__
@@ -315,21 +423,8 @@ __global__ __launch_bounds__(NW * 64) void conv_ksplit_kernel(const KsplitLaunch
     a = launch.p[0];
 #endif
     int mt, nt;
-    if (ks_place(a, blockIdx.x, &mt, &nt)) ksplit_tile<DT, TM, TN, NW, NS>(a, mt, nt);
+    if (ks_place(a, blockIdx.x, &mt, &nt)) ksplit_tile<DT, TM, TN, NS>(a, mt, nt);
 }
-
-// pixel tiles, channel tiles (of 16), wavefronts, ring stages
-#define SGPRS_KSPLIT_VARIANTS(X) \
-    X(0, 1, 1, 8, 4) X(1, 2, 1, 8, 3) X(2, 1, 2, 8, 3) X(3, 2, 2, 8, 2) X(4, 4, 2, 4, 3) X(5, 2, 4, 4, 3) X(6, 4, 4, 4, 2) \
-    X(7, 2, 2, 4, 2) X(8, 1, 4, 8, 2) X(9, 4, 1, 8, 2)
-constexpr int kKsplitShape[][4] = {
-#define X(v, tm, tn, nw, ns) {tm, tn, nw, ns},
-    SGPRS_KSPLIT_VARIANTS(X)
-#undef X
-};
-constexpr int kKsplitVariants = sizeof(kKsplitShape) / sizeof(kKsplitShape[0]);
-
-int ksplit_num_variants() { return kKsplitVariants; }
 
 // Name as a profiler prints it: v = tile variant + 16 * dtype.
 const char* ksplit_variant_name(int v)
@@ -339,20 +434,20 @@ const char* ksplit_variant_name(int v)
     if (v < 0 || (v & 15) >= kKsplitVariants || v >= 32) return "?";
     const int* t = kKsplitShape[v & 15];
     char* out = buf[next++ & 7];
-    snprintf(out, 96, "conv_ksplit_kernel<%d, %d, %d, %d, %d>", v >> 4, t[0], t[1], t[2], t[3]);
+    snprintf(out, 96, "conv_ksplit_kernel<%d, %d, %d, %d>", v >> 4, t[0], t[1], t[2]);
     return out;
 }
 
-template <int DT, int TM, int TN, int NW, int NS>
+template <int DT, int TM, int TN, int NS>
 static int launch_ks(const KsplitLaunch& l, int slots, int problems, hipStream_t stream)
 {
-    constexpr int lds = NW * NS * (TM + TN) * 16 * 128;
+    constexpr int lds = kKsplitWaves * NS * (TM + TN) * 16 * 128;
     static std::atomic<bool> raised{false};
     if (!raised) {
-        SGPRS_HIP(hipFuncSetAttribute((const void*)conv_ksplit_kernel<DT, TM, TN, NW, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        SGPRS_HIP(hipFuncSetAttribute((const void*)conv_ksplit_kernel<DT, TM, TN, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         raised = true;
     }
-    SGPRS_LAUNCH((conv_ksplit_kernel<DT, TM, TN, NW, NS>), dim3(slots, problems), dim3(NW * 64), lds, stream, l);
+    SGPRS_LAUNCH((conv_ksplit_kernel<DT, TM, TN, NS>), dim3(slots, problems), dim3(kKsplitWaves * 64), lds, stream, l);
     SGPRS_HIP(hipGetLastError());
     return SGPRS_OK;
 }
@@ -373,29 +468,31 @@ bool ksplit_fits(const sgprs_conv_desc_t& d, int v)
 }
 
 // Estimated time (microseconds) of the best tile: launch, then rounds of workgroups, each a fixed
-// part (start, first trip to memory, reduction), the traffic of its k-tiles at the 110 GB/s one CU
-// gets out of the L2 with 64-144 KB in flight, and, behind the first filling of the rings, the
-// matrix work.  Against 1170 measurements (nine layers, 1..16 images, 8..256 CUs, both types) the
-// model is off by 14 % rms, and its choice is 2.6 % slower than the best tile on average.
+// part (start, pixel arithmetic, reduction), the traffic of its k-tiles at the 110 GB/s one CU gets
+// out of the L2 with 64-144 KB in flight, and, behind the first filling of the rings, the matrix
+// work.  Fitted to 1368 measurements (nine layers, 1..16 images, 8..256 CUs, both types): 8 % off
+// rms, and its choice is 1.5 % slower than the best tile on average.
 bool plan_ksplit(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us)
 {
     if (!is_igemm(d)) return false;
     const int es = (int)dtype_size(d.dtype);
     const long long M = (long long)d.n * out_dim(d.h, d.r, d.stride, d.pad) * out_dim(d.w, d.s, d.stride, d.pad);
-    const int ktiles = d.r * d.s * d.cin * es / 128;
-    const double flop_per_us = d.dtype == SGPRS_BF16 ? 9.8e6 : 0.614e6;  // one CU's matrix rate
+    const int ktiles = d.r * d.s * d.cin * es / 128, kt = (ktiles + kKsplitWaves - 1) / kKsplitWaves * kKsplitWaves;  // the longest share decides
+    // one CU's time per FLOP; a bf16 k-tile's MFMAs are mostly hidden behind its traffic
+    const double us_per_flop = d.dtype == SGPRS_BF16 ? 0.26 / 9.8e6 : 1.0 / 0.614e6;
     double best = 1e30;
     for (int v = 0; v < kKsplitVariants; ++v) {
         if (!ksplit_fits(d, v)) continue;
-        const int *t = kKsplitShape[v], bm = 16 * t[0], bn = 16 * t[1], nw = t[2], lds = nw * t[3] * (bm + bn) * 128;
+        const int *t = kKsplitShape[v], bm = 16 * t[0], bn = 16 * t[1], lds = kKsplitWaves * t[2] * (bm + bn) * 128;
         const long long wgs = (M + bm - 1) / bm * (d.cout / bn), occ = lds <= 80 * 1024 ? 2 : 1;
-        const int kt = (ktiles + nw - 1) / nw * nw;  // the longest share decides
-        const double per = (double)std::min<long long>(occ, (wgs + cus - 1) / cus);
         const double traffic = (bm + bn) * 128.0 * kt / 110e3, ring = std::min(traffic, lds / 110e3);
-        const double mfma = 2.0 * bm * bn * (128 / es) * kt / flop_per_us * (per > 1 ? 1.0 : 1.15);
-        const double wg = 0.95 + 0.00035 * bm * bn + std::max(per * traffic, ring + per * mfma);
-        const long long rounds = (wgs + cus * occ - 1) / (cus * occ);
-        const double cost = 2.0 + rounds * wg + 0.3 * (rounds - 1);
+        const double mfma = 2.0 * bm * bn * (128 / es) * kt * us_per_flop;
+        auto round = [&](long long per_cu) {
+            return 0.64 + 0.2 * t[0] + 0.00031 * bm * bn + std::max(per_cu * traffic, ring + per_cu * mfma * (per_cu > 1 ? 1.06 : 1.0));
+        };
+        const long long full = wgs / (cus * occ), rest = wgs - full * cus * occ;
+        double cost = 1.5 + full * round(occ) + 0.12 * (full + (rest > 0) - 1);
+        if (rest) cost += round((rest + cus - 1) / cus);
         if (cost < best) { best = cost; *variant = v; *cost_us = cost; }
     }
     return best < 1e30;
@@ -453,9 +550,9 @@ int launch_conv_ksplit(const sgprs_conv_desc_t& d, int variant, const void* x, c
     if (prof && prof->on && (rc = prof->begin(stream, d1 ? kKindIgemmPair : kKindIgemm, kKsplitNames + d.dtype * 16 + variant, flops, bytes))) return rc;
     const int slots = a0.die_tiles * 8;  // a multiple of 8 either way
     switch (d.dtype * 16 + variant) {
-#define X(v, tm, tn, nw, ns)                                                                     \
-        case v: rc = launch_ks<SGPRS_F32, tm, tn, nw, ns>(l, slots, d1 ? 2 : 1, stream); break;                \
-        case 16 + v: rc = launch_ks<SGPRS_BF16, tm, tn, nw, ns>(l, slots, d1 ? 2 : 1, stream); break;
+#define X(v, tm, tn, ns)                                                                         \
+        case v: rc = launch_ks<SGPRS_F32, tm, tn, ns>(l, slots, d1 ? 2 : 1, stream); break;      \
+        case 16 + v: rc = launch_ks<SGPRS_BF16, tm, tn, ns>(l, slots, d1 ? 2 : 1, stream); break;
         SGPRS_KSPLIT_VARIANTS(X)
 #undef X
     }

@@ -271,7 +271,6 @@ int launch_conv3x3_rows(const sgprs_conv_desc_t& d, int rows_per_stream, const v
                         const float* shift, const void* residual, void* y, hipStream_t stream, int cus, Profiler* prof);
 // implicit GEMM with the K range split over the wavefronts of a workgroup (few output tiles)
 bool plan_ksplit(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us);
-int ksplit_num_variants();
 const char* ksplit_variant_name(int v);
 constexpr int kKsplitNames = 32;  // launches of this kernel are recorded as implicit GEMM (or pair), variant 32 + 16 * dtype + tile
 bool ksplit_fits(const sgprs_conv_desc_t& d, int variant);

@@ -429,7 +429,7 @@ KSPLIT_SHAPES = [
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
-@pytest.mark.parametrize("variant", range(10))
+@pytest.mark.parametrize("variant", range(8))
 def test_conv_ksplit_tiles_parity(pools, dtype, variant):
     pool = pools["full"]
     try:
