@@ -75,6 +75,7 @@ ConvPlan plan_conv(const sgprs_conv_desc_t& d, int cus, bool has_residual)
 
 static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit)
 {
+    cus = planning_cus(cus);
     const int force_kind = g_conv_force_kind.load(), force_variant = g_igemm_force_variant.load(),
               force_splits = g_igemm_force_splits.load();
     if (force_variant >= 8 && ksplit_fits(d, force_variant - 8)) {
@@ -84,14 +85,13 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
     }
     if (force_kind == -1) {
         int rows = 0;
-        if (plan_rows(d, cus < 1 ? 1 : cus, &rows)) {
+        if (plan_rows(d, cus, &rows)) {
             ConvPlan p;
             p.kind = 3; p.variant = rows; p.splits = 1;
             p.bm = 1;  // marks a valid plan
             return p;
         }
     }
-    if (cus < 1) cus = 1;
     ConvPlan best;
     double best_cost = 1e30;
     if (force_kind != 0) {

@@ -27,7 +27,7 @@ int resolve(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* cus)
         return fail(SGPRS_ERR_INVALID_ARG, "partition %d outside [0,%d)", partition,
                     (int)pool->parts.size());
     *stream = pool->parts[partition].stream;
-    *cus = pool->parts[partition].cus;
+    *cus = planning_cus(pool->parts[partition].cus);
     return SGPRS_OK;
 }
 
