@@ -1,4 +1,5 @@
-"""ctypes binding of libsgprs.so (see include/sgprs.h for the contract).
+"""Binding of libsgprs.so (see include/sgprs.h for the contract): ctypes, and for the entry points
+called once per kernel or inference a CPython extension (csrc/pycalls.cpp).
 
 Argument marshalling only.  Functions keep the C names; `Pool` and `Task` are
 small owners of the opaque handles.  Device tensors are passed as integer
@@ -52,6 +53,7 @@ def lib_path() -> str:
 
 
 _lib = None
+_native = None
 
 
 class Dispatch(ctypes.Structure):
@@ -142,6 +144,21 @@ def lib():
         f.restype, f.argtypes = res, args
     _lib = L
     return L
+
+
+def _calls():
+    """The CPython extension around the entry points called once per kernel or inference; they take
+    integer addresses and return None for arguments that only ctypes can convert."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _calls as ext
+        except ImportError as e:
+            raise ImportError(f"the call extension of {_PKG} is missing or broken ({e}): build it with "
+                              "`python -m paper_2406_09425_amd.build`") from e
+        _native = ext
+    return _native
 
 
 def _check(rc: int) -> int:
@@ -239,7 +256,7 @@ class Pool:
                                                  ctypes.byref(h)))
         else:
             _check(lib().sgprs_pool_create(device, n_p, cus_per_partition, flags, ctypes.byref(h)))
-        self.handle = h
+        self.handle, self.address = h, h.value
 
     def info(self):
         a, b, c, d = c_int(), c_int(), c_int(), c_int()
@@ -290,7 +307,7 @@ class Pool:
 
     def destroy(self) -> None:
         if self.handle:
-            h, self.handle = self.handle, None
+            h, self.handle, self.address = self.handle, None, None
             _check(lib().sgprs_pool_destroy(h))
 
     def __del__(self):
@@ -304,10 +321,19 @@ def _h(pool):
     return pool.handle if isinstance(pool, Pool) else pool
 
 
+def _address(handle):
+    return handle.value if isinstance(handle, c_void_p) else handle
+
+
 def sgprs_conv2d(desc: ConvDesc, x: int, w_packed: int, scale: int, shift: int, residual: int | None, y: int,
                  workspace: int | None, workspace_bytes: int, pool, partition: int) -> None:
-    _check(lib().sgprs_conv2d(ctypes.byref(desc), x, w_packed, scale, shift, residual, y, workspace,
-                              workspace_bytes, _h(pool), partition))
+    rc = (_native or _calls()).conv2d(ctypes.addressof(desc), x, w_packed, scale, shift, residual, y, workspace, workspace_bytes,
+                                      pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+    if rc is None:
+        rc = lib().sgprs_conv2d(ctypes.byref(desc), x, w_packed, scale, shift, residual, y, workspace, workspace_bytes,
+                                _h(pool), partition)
+    if rc:
+        _check(rc)
 
 
 def sgprs_conv_tuning_override(kind: int, variant: int = 0, splits: int = 1) -> None:
@@ -315,30 +341,54 @@ def sgprs_conv_tuning_override(kind: int, variant: int = 0, splits: int = 1) -> 
 
 
 def sgprs_maxpool2d(dtype: int, n: int, h: int, w: int, c: int, x: int, y: int, pool, partition: int) -> None:
-    _check(lib().sgprs_maxpool2d(dtype, n, h, w, c, x, y, _h(pool), partition))
+    rc = (_native or _calls()).maxpool2d(dtype, n, h, w, c, x, y, pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+    if rc is None:
+        rc = lib().sgprs_maxpool2d(dtype, n, h, w, c, x, y, _h(pool), partition)
+    if rc:
+        _check(rc)
 
 
 def sgprs_bn_relu(dtype: int, pixels: int, c: int, x: int, scale: int, shift: int, y: int, pool,
                   partition: int) -> None:
-    _check(lib().sgprs_bn_relu(dtype, pixels, c, x, scale, shift, y, _h(pool), partition))
+    rc = (_native or _calls()).bn_relu(dtype, pixels, c, x, scale, shift, y, pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+    if rc is None:
+        rc = lib().sgprs_bn_relu(dtype, pixels, c, x, scale, shift, y, _h(pool), partition)
+    if rc:
+        _check(rc)
 
 
 def sgprs_add_relu(dtype: int, count: int, a: int, b: int, y: int, relu: bool, pool, partition: int) -> None:
-    _check(lib().sgprs_add_relu(dtype, count, a, b, y, int(relu), _h(pool), partition))
+    rc = (_native or _calls()).add_relu(dtype, count, a, b, y, relu, pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+    if rc is None:
+        rc = lib().sgprs_add_relu(dtype, count, a, b, y, int(relu), _h(pool), partition)
+    if rc:
+        _check(rc)
 
 
 def sgprs_avgpool_fc(dtype: int, n: int, hw: int, cin: int, cout: int, x: int, w: int, bias: int | None,
                      logits: int, workspace: int, pool, partition: int) -> None:
-    _check(lib().sgprs_avgpool_fc(dtype, n, hw, cin, cout, x, w, bias, logits, workspace, _h(pool), partition))
+    rc = (_native or _calls()).avgpool_fc(dtype, n, hw, cin, cout, x, w, bias, logits, workspace, pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+    if rc is None:
+        rc = lib().sgprs_avgpool_fc(dtype, n, hw, cin, cout, x, w, bias, logits, workspace, _h(pool), partition)
+    if rc:
+        _check(rc)
 
 
 def sgprs_global_avgpool(dtype: int, n: int, hw: int, c: int, x: int, pooled: int, pool, partition: int) -> None:
-    _check(lib().sgprs_global_avgpool(dtype, n, hw, c, x, pooled, _h(pool), partition))
+    rc = (_native or _calls()).global_avgpool(dtype, n, hw, c, x, pooled, pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+    if rc is None:
+        rc = lib().sgprs_global_avgpool(dtype, n, hw, c, x, pooled, _h(pool), partition)
+    if rc:
+        _check(rc)
 
 
 def sgprs_avgpool_fc_static(dtype: int, n: int, hw: int, cin: int, cout: int, x: int, w: int, bias: int | None,
                             logits: int, pool, partition: int) -> None:
-    _check(lib().sgprs_avgpool_fc_static(dtype, n, hw, cin, cout, x, w, bias, logits, _h(pool), partition))
+    rc = (_native or _calls()).avgpool_fc_static(dtype, n, hw, cin, cout, x, w, bias, logits, pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+    if rc is None:
+        rc = lib().sgprs_avgpool_fc_static(dtype, n, hw, cin, cout, x, w, bias, logits, _h(pool), partition)
+    if rc:
+        _check(rc)
 
 
 class Task:
@@ -365,7 +415,7 @@ class Task:
         P.bn_eps = eps
         h = c_void_p()
         _check(lib().sgprs_task_create_resnet18(device, dtype, max_batch, ctypes.byref(P), ctypes.byref(h)))
-        self.handle, self.dtype, self.max_batch = h, dtype, max_batch
+        self.handle, self.address, self.dtype, self.max_batch = h, h.value, dtype, max_batch
 
     def num_stages(self) -> int:
         return _check(lib().sgprs_task_num_stages(self.handle))
@@ -377,11 +427,21 @@ class Task:
         return dict(in_bytes=a.value, out_bytes=b.value, in_nchw=tuple(i4), out_nchw=tuple(o4))
 
     def stage_run(self, stage: int, batch: int, inp: int, out: int, pool, partition: int) -> None:
-        _check(lib().sgprs_stage_run(self.handle, stage, batch, inp, out, _h(pool), partition))
+        rc = (_native or _calls()).stage_run(self.address, stage, batch, inp, out, pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+        if rc is None:
+            rc = lib().sgprs_stage_run(self.handle, stage, batch, inp, out, _h(pool), partition)
+        if rc:
+            _check(rc)
 
     def run(self, batch: int, inp: int, logits: int, pool, partition: int, partition_per_stage=None) -> None:
-        pps = (c_int * 6)(*partition_per_stage) if partition_per_stage is not None else None
-        _check(lib().sgprs_task_run(self.handle, batch, inp, logits, _h(pool), partition, pps))
+        rc = None
+        if partition_per_stage is None:
+            rc = (_native or _calls()).task_run(self.address, batch, inp, logits, pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+        if rc is None:
+            pps = (c_int * 6)(*partition_per_stage) if partition_per_stage is not None else None
+            rc = lib().sgprs_task_run(self.handle, batch, inp, logits, _h(pool), partition, pps)
+        if rc:
+            _check(rc)
 
     def stage_output(self, stage: int) -> int:
         p = lib().sgprs_task_stage_output(self.handle, stage)
@@ -408,7 +468,7 @@ class Task:
 
     def destroy(self) -> None:
         if self.handle:
-            h, self.handle = self.handle, None
+            h, self.handle, self.address = self.handle, None, None
             _check(lib().sgprs_task_destroy(h))
 
     def __del__(self):

@@ -1,15 +1,17 @@
-"""Builds libsgprs.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libsgprs.so (HIP kernels + C ABI) for gfx950 with hipcc, and the call extension, in-tree."""
 from __future__ import annotations
 
 import concurrent.futures as cf
 import os
 import shutil
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsgprs.so")
+CALLS = os.path.join(PKG, "_calls.so")  # CPython extension around the entry points called once per kernel
 OBJ_DIR = os.path.join(PKG, "_build")
 
 SOURCES = ["pool.cpp", "pack.cpp", "ops.cpp", "task.cpp", "sched.cpp", "conv_igemm.hip", "conv_ksplit.hip", "conv_stem.hip", "conv3x3_patch.hip", "conv3x3_rows.hip", "stem_pool.hip",
@@ -38,7 +40,7 @@ def _compile(src: str) -> str:
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compiles every source and links libsgprs.so; always rebuilds."""
+    """Compiles every source and links libsgprs.so and _calls.so; always rebuilds."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
@@ -46,6 +48,12 @@ def build_library(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pycalls.cpp"), "-o", CALLS, "-L", PKG, "-lsgprs",
+           "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"building the call extension failed:\n{r.stdout}\n{r.stderr}")
     if verbose:
         print("built", LIB)
     return LIB
