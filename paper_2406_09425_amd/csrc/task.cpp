@@ -11,8 +11,10 @@
 
 namespace {
 
-// Replaying costs about 5 us of GPU time per launch and saves 50-90 us of host time: it pays when
-// one host thread feeds several partitions with short inferences, not for one long batch.
+// Replaying costs about 5 us of GPU time per launch and saves 30 us of host time (20 against 50): it
+// pays when one host thread feeds several partitions with short inferences, not for one long batch,
+// and not on a pool of one partition, where the launches of the next inference hide behind the
+// running one (batch 1 on 256 CUs 82.5 us replayed, 78.0 launched one by one; batch 8 143.2, 138.3).
 constexpr int kReplayMaxBatch = 8;
 
 using namespace sgprs;
@@ -70,7 +72,7 @@ struct sgprs_task {
         hipGraphExec_t exec = nullptr;
     };
     std::vector<Replay> replays;
-    int graph_mode = -1;     // -1: replay batches up to kReplayMaxBatch, 0: never, 1: always
+    int graph_mode = -1;     // -1: replay batches up to kReplayMaxBatch on pools of several partitions, 0: never, 1: always
     bool use_graphs = true;  // cleared when a capture fails
 };
 
@@ -387,7 +389,7 @@ int sgprs_task_run(sgprs_task_t* t, int batch, const void* in, float* logits, sg
     for (int j = 1; j < SGPRS_RESNET18_STAGES; ++j) one_stream = one_stream && s[j] == s[0];
     sgprs_task::Replay* rp = nullptr;
     if (t->use_graphs && one_stream && !t->profiling &&
-        (t->graph_mode == 1 || (t->graph_mode < 0 && batch <= kReplayMaxBatch))) {
+        (t->graph_mode == 1 || (t->graph_mode < 0 && batch <= kReplayMaxBatch && pool->parts.size() > 1))) {
         // the split-K scratch must neither grow while capturing nor move under a captured graph
         for (int j = 1; j <= 4; ++j) {
             const int first = j == 1 ? 1 : 5 + 5 * (j - 2), last = j == 1 ? 4 : first + 4;
@@ -517,7 +519,7 @@ const char* sgprs_kernel_name(int kind, int variant)
         case kKindReduce: return "splitk_reduce_kernel";
         case kKindMaxpool: return "maxpool3x3s2_kernel";
         case kKindAvgpool: return "avgpool_kernel";
-        case kKindFc: return variant >= 4 ? "fc_mfma_kernel" : variant >= 2 ? "avgpool_fc_kernel" : "fc_kernel";
+        case kKindFc: return variant >= 4 ? "fc_gemm_kernel" : variant >= 2 ? "avgpool_fc_kernel" : "fc_kernel";
         case kKindBnRelu: return "bn_relu_kernel";
         case kKindAdd: return "add_relu_kernel";
         default: return "?";
