@@ -179,8 +179,9 @@ struct ConvPlan {
 };
 // Chooses tile shape and split-K factor from the GEMM shape and the CU count of
 // the partition the launch will run on.
-// (has_residual: kernels without a residual input are left out).
-ConvPlan plan_conv(const sgprs_conv_desc_t& d, int partition_cus, bool has_residual = false);
+// (has_residual: kernels without a residual input are left out; ksplit false: so is the kernel that
+// splits K over a workgroup's wavefronts).
+ConvPlan plan_conv(const sgprs_conv_desc_t& d, int partition_cus, bool has_residual = false, bool ksplit = true);
 size_t conv_workspace_bytes(const sgprs_conv_desc_t& d, const ConvPlan& p);
 
 struct KernelRecord {
@@ -236,6 +237,9 @@ int launch_avgpool(int dtype, int n, int hw, int cin, const void* x, float* pool
 int launch_avgpool_fc(int dtype, int n, int hw, int cin, int cout, const void* x, const void* w,
                       const float* bias, float* logits, float* ws, hipStream_t stream, int cus,
                       Profiler* prof);
+// FC of a batch on the matrix cores: v fp32 [n][cin], w [cout][cin] in dtype
+bool fc_gemm_applicable(int n, int cin, int cout);
+int launch_fc_gemm(int dtype, const float* v, const void* w, const float* bias, float* y, int n, int cin, int cout, hipStream_t stream, int cus);
 // Device address of this GPU's static pooled-vector scratch (kStaticScratchFloats fp32), looked up
 // on first use; nothing is allocated.
 constexpr size_t kStaticScratchFloats = 64 * 2048;

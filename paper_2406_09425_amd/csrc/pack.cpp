@@ -62,20 +62,20 @@ std::atomic<int> g_plan_generation{0};
 
 static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit);
 
-ConvPlan plan_conv(const sgprs_conv_desc_t& d, int cus, bool has_residual)
+ConvPlan plan_conv(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit)
 {
-    struct Key { sgprs_conv_desc_t d; int cus, res, gen; };
+    struct Key { sgprs_conv_desc_t d; int cus, res, ksplit, gen; };
     static thread_local PlanMemo<Key, ConvPlan> local;
     static SharedPlanMemo<Key, ConvPlan> memo;
+    cus = planning_cus(cus);
     Key k;
     memset(&k, 0, sizeof(k));
-    k.d = d; k.cus = cus; k.res = has_residual; k.gen = g_plan_generation.load();
-    return memo.get(local, k, [&]() { return plan_conv_uncached(d, cus, has_residual, true); });
+    k.d = d; k.cus = cus; k.res = has_residual; k.ksplit = ksplit; k.gen = g_plan_generation.load();
+    return memo.get(local, k, [&]() { return plan_conv_uncached(d, cus, has_residual, ksplit); });
 }
 
 static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit)
 {
-    cus = planning_cus(cus);
     const int force_kind = g_conv_force_kind.load(), force_variant = g_igemm_force_variant.load(),
               force_splits = g_igemm_force_splits.load();
     if (force_variant >= 8 && ksplit_fits(d, force_variant - 8)) {
@@ -254,7 +254,7 @@ int sgprs_conv2d_workspace(const sgprs_conv_desc_t* d, int partition_cus, size_t
     if (!is_stem(*d))
         for (int res = 0; res < 2; ++res)
             *bytes = std::max({*bytes, conv_workspace_bytes(*d, plan_conv(*d, partition_cus, res != 0)),
-                               conv_workspace_bytes(*d, plan_conv_uncached(*d, partition_cus, res != 0, false))});
+                               conv_workspace_bytes(*d, plan_conv(*d, partition_cus, res != 0, false))});
     return SGPRS_OK;
 }
 

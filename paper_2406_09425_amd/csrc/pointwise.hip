@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void avgpool_kernel(const void* __restrict__ x
     for (int i = 0; i < N; ++i) s[i] = 0.f;
     if (c < cv) {
         int j = wave;
-        for (; j + 12 < HW; j += 16) {  // four positions per round trip
+        for (; j + 12 < HW; j += 16) {  // four positions per round trip (13, a whole share of a 7x7 map, was no faster)
             Vec<DT> t[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) t[u].load(x, (n * HW + j + 4 * u) * cv + c);
@@ -423,66 +423,6 @@ __global__ __launch_bounds__(256) void fc_kernel(const float* __restrict__ v, co
     }
 }
 
-// ---- FC on the matrix cores, for batches of 32 images and more (bf16 weights) ------------
-// logits[n][o] = sum_c w[o][c] v[n][c] + b[o] as 32 x 32 tiles of MFMA 32x32x16: rows = outputs
-// (weights straight from memory, 16 bytes per lane), columns = images.  The pooled vectors stay
-// fp32: each value goes in as a bf16 head plus a bf16 remainder (two MFMAs; products of two bf16
-// are exact in fp32, so what is lost is below 2^-17 of a value).  The four wavefronts of a
-// workgroup split the inputs of one tile and add their partial tiles through LDS in wavefront
-// order, so the result does not depend on timing.
-typedef __bf16 fc_bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float fc_f32x16_t __attribute__((ext_vector_type(16)));
-__global__ __launch_bounds__(256) void fc_mfma_kernel(const float* __restrict__ v, const void* __restrict__ w,
-                                                      const float* __restrict__ bias, float* __restrict__ y, int Nimg,
-                                                      int Cin, int Cout)
-{
-    __shared__ f32x4_t part[4][4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int frow = lane & 31, half = lane >> 5;
-    const int o0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
-    const int o = min(o0 + frow, Cout - 1), n = min(n0 + frow, Nimg - 1);   // rows and columns past the end repeat the last one
-    const int kq = Cin / 4, k0 = wave * kq + half * 8;
-    const unsigned short* wp = (const unsigned short*)w + (size_t)o * Cin + k0;
-    const float* vp = v + (size_t)n * Cin + k0;
-    fc_f32x16_t acc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    for (int kb = 0; kb < kq; kb += 128) {   // eight k-steps per round trip
-        u32x4_t a[8];
-        f32x4_t b0[8], b1[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            a[s] = *(const u32x4_t*)(wp + kb + s * 16);
-            b0[s] = *(const f32x4_t*)(vp + kb + s * 16);
-            b1[s] = *(const f32x4_t*)(vp + kb + s * 16 + 4);
-        }
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            fc_bf16x8_t hi, lo;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float f = i < 4 ? b0[s][i] : b1[s][i - 4];
-                hi[i] = (__bf16)f;
-                lo[i] = (__bf16)(f - (float)hi[i]);
-            }
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(fc_bf16x8_t, a[s]), hi, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(fc_bf16x8_t, a[s]), lo, acc, 0, 0, 0);
-        }
-    }
-    // accumulator register 4q + u: output o0 + 8q + 4 * half + u of image n0 + frow
-#pragma unroll
-    for (int q = 0; q < 4; ++q) part[wave][q][lane] = f32x4_t{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-    __syncthreads();
-    {
-        const int q = wave, ob = o0 + 8 * q + 4 * half;
-        f32x4_t r = ((part[0][q][lane] + part[1][q][lane]) + part[2][q][lane]) + part[3][q][lane];
-        if (n0 + frow < Nimg && ob < Cout) {   // (Cout is a multiple of 4: a group of four is inside or outside as a whole)
-            if (bias) r += *(const f32x4_t*)(bias + ob);
-            *(f32x4_t*)(y + (size_t)(n0 + frow) * Cout + ob) = r;
-        }
-    }
-}
-
 // ---- placement probe --------------------------------------------------------
 __global__ __launch_bounds__(64) void probe_kernel(uint32_t* out, int spin)
 {
@@ -588,7 +528,7 @@ int launch_avgpool(int dtype, int n, int hw, int cin, const void* x, float* ws, 
 }
 
 int launch_avgpool_fc(int dtype, int n, int hw, int cin, int cout, const void* x, const void* w,
-                      const float* bias, float* logits, float* ws, hipStream_t stream, int, Profiler* prof)
+                      const float* bias, float* logits, float* ws, hipStream_t stream, int cus, Profiler* prof)
 {
     const int vec = dtype == SGPRS_BF16 ? 8 : 4;
     const size_t es = dtype_size(dtype);
@@ -610,10 +550,9 @@ int launch_avgpool_fc(int dtype, int n, int hw, int cin, int cout, const void* x
     int rc = launch_avgpool(dtype, n, hw, cin, x, ws, stream, prof);
     if (rc) return rc;
 
-    if (dtype == SGPRS_BF16 && n >= 32 && cout % 4 == 0 && cin % 512 == 0) {   // enough images for 32 x 32 tiles on the matrix cores
-        PROF_BEGIN(kKindFc, 4, 2.0 * n * cin * cout, (double)cin * cout * es + (double)n * (cin + cout) * 4);
-        SGPRS_LAUNCH(fc_mfma_kernel, dim3((cout + 31) / 32, (n + 31) / 32), dim3(256), 0, stream, (const float*)ws, w, bias, logits, n, cin, cout);
-        SGPRS_HIP(hipGetLastError());
+    if (fc_gemm_applicable(n, cin, cout)) {
+        PROF_BEGIN(kKindFc, 4 + dtype, 2.0 * n * cin * cout, (double)cin * cout * es + (double)n * (cin + cout) * 4);
+        if ((rc = launch_fc_gemm(dtype, ws, w, bias, logits, n, cin, cout, stream, cus))) return rc;
         PROF_END();
         return SGPRS_OK;
     }

@@ -446,3 +446,28 @@ def test_conv_ksplit_tiles_parity(pools, dtype, variant):
                     assert e < 2e-5, e  # fp32 accumulation over K <= 4608: about sqrt(K) * 2^-24
     finally:
         S.sgprs_conv_tuning_override(-1, 0, 1)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
+@pytest.mark.parametrize("n,cin,cout,cus", [(32, 512, 36, 8), (70, 1024, 100, 8), (129, 2048, 36, "full"), (65, 512, 1000, 64)], ids=str)
+def test_fc_gemm_tiles_parity(pools, dtype, n, cin, cout, cus):
+    """The FC of 32 images and more: both tile sizes (64x64 where they fill the partition), ragged in images and
+    outputs, ring shares of 4, 8 and 16 k-tiles, without a bias and with one.  fp32: sums of up to 2048 products,
+    about sqrt(2048) * 2^-24; bf16: exact weights, pooled values to 2^-17."""
+    bf = dtype == S.SGPRS_BF16
+    x = make_input(97, n, (n, cin, 2, 1), bf16=bf)
+    w = make_conv_weight(97, n, 1, cout, cin, 1, bf16=bf)[:, :, 0, 0]
+    bias = make_input(97, n, (cout,), tensor_id=2).astype(np.float32) if n % 2 else np.zeros(cout, np.float32)
+    ref = oracle.fc(oracle.global_avgpool(x), w, bias)
+    xd = dev_nhwc(x, dtype)
+    wd = torch.from_numpy(np.ascontiguousarray(w)).to(xd.dtype).cuda()
+    bd = dev_f32(bias) if n % 2 else None
+    ws = torch.empty(n * cin, dtype=torch.float32, device="cuda")
+    lg = torch.full((n + 1, cout), float("nan"), dtype=torch.float32, device="cuda")
+    pool = pools[cus]
+    S.sgprs_avgpool_fc(dtype, n, 2, cin, cout, xd.data_ptr(), wd.data_ptr(), bd.data_ptr() if n % 2 else None, lg.data_ptr(),
+                       ws.data_ptr(), pool, 0)
+    pool.sync()
+    got = lg.cpu().numpy().astype(np.float64)
+    assert np.all(np.isnan(got[n]))    # nothing is written past the last image
+    assert rel_err(got[:n], ref) <= (2e-5 if bf else 4e-6)
