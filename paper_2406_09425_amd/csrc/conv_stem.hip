@@ -196,8 +196,11 @@ int launch_stem(const sgprs_conv_desc_t& d, const void* x, const void* w, const 
     const double flops = 2.0 * d.n * a.P * a.Q * 64.0 * 147.0;
     const double bytes = ((double)d.n * d.h * d.w * 3 + 64.0 * 147 + (double)d.n * a.P * a.Q * 64) * dtype_size(d.dtype);
     int rc;
-    if (prof && prof->on && (rc = prof->begin(stream, kKindStem, d.dtype * 2 + (tp == 8 ? 0 : 1), flops, bytes))) return rc;
-    if (d.dtype == SGPRS_BF16)
+    const bool packed = d.dtype == SGPRS_F32 && stem_f32_applicable(d.n, d.h, d.w);
+    if (prof && prof->on && (rc = prof->begin(stream, kKindStem, packed ? 4 : d.dtype * 2 + (tp == 8 ? 0 : 1), flops, bytes))) return rc;
+    if (packed)
+        rc = launch_stem_f32(d.n, d.h, d.w, x, w, scale, shift, y, d.relu, false, stream, cus);
+    else if (d.dtype == SGPRS_BF16)
         rc = tp == 8 ? launch_stem_variant<SGPRS_BF16, 8>(a, grid, stream) : launch_stem_variant<SGPRS_BF16, 4>(a, grid, stream);
     else
         rc = tp == 8 ? launch_stem_variant<SGPRS_F32, 8>(a, grid, stream) : launch_stem_variant<SGPRS_F32, 4>(a, grid, stream);

@@ -248,6 +248,10 @@ int static_scratch(int device, float** out);
 int launch_probe(int n_blocks, int spin_cycles, uint32_t* out, hipStream_t stream);
 int launch_mfma_probe(int cus, int steps, int random_data, unsigned long long* out, hipStream_t stream);
 int launch_load_probe(int cus, const void* buf, size_t buf_bytes, unsigned region, int iters, unsigned* out, hipStream_t stream);
+// fp32 stem on packed input rows, alone (pool false) or with the max-pool; no profiling record of its own
+bool stem_f32_applicable(int n, int h, int w);
+int launch_stem_f32(int n, int h, int w, const void* x, const void* wts, const float* scale, const float* shift, void* y,
+                    int relu, bool pool, hipStream_t stream, int cus);
 // stage 0 fused: conv7x7/2 + BN + ReLU + max-pool 3x3/2
 bool stem_pool_applicable(int dtype, int n, int h, int w, int cus);
 // wts: the stem layout of sgprs_pack_conv_weights; wts_rows: the bf16 [64][176] tap-row layout of

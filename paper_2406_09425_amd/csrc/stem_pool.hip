@@ -1,4 +1,4 @@
-// Stage 0 in one kernel: conv 7x7/2 (3 -> 64) + folded BN + ReLU + max-pool 3x3/2.
+// Stage 0 in one kernel, bf16 (fp32: stem_f32.hip): conv 7x7/2 (3 -> 64) + folded BN + ReLU + max-pool 3x3/2.
 //
 // The stem's 64 x 112 x 112 output is the largest tensor of the network; written
 // out and read back by a separate pooling kernel it costs more HBM traffic than
@@ -12,10 +12,9 @@
 // in LDS in the matching 7 x 32 tap-row layout.  The MFMA operands are swapped
 // (weights as the row operand, pixels as the column operand) so that a lane's
 // accumulator registers hold 4 consecutive channels of one pixel, which go to
-// the LDS staging area as one 8-byte (bf16) or 16-byte (fp32) write.
-// Positions outside the conv output hold -inf (fp32) or 0 (bf16, where the
-// post-ReLU values are pooled as unsigned bit patterns) in the staging area, so
-// padding never wins the maximum.
+// the LDS staging area as one 8-byte write.
+// Positions outside the conv output hold 0 in the staging area (the post-ReLU
+// values are pooled as unsigned bit patterns), so padding never wins the maximum.
 #include "internal.h"
 
 namespace sgprs {
@@ -51,7 +50,8 @@ constexpr int kInC = 2 * kConvC + 6;              // 40 input columns (one spare
 template <int DT>
 __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
 {
-    constexpr int ES = DT == SGPRS_BF16 ? 2 : 4;
+    static_assert(DT == SGPRS_BF16, "fp32 has stem_f32_kernel");
+    constexpr int ES = 2;
     constexpr int PIX = 4 * ES;                      // staged input pixel: 4 channel slots
     constexpr int WROW = kStemK * ES + 16;           // padded weight row
     constexpr int W_BYTES = 64 * WROW;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
     // The next tile's input patch is fetched into registers while the current
     // tile computes: PF_IT pixels per thread, 3 channels each.
     constexpr int PF_IT = (kInR * kInC + 255) / 256;
-    unsigned pf_lo[PF_IT], pf_hi[PF_IT], pf_x[DT == SGPRS_BF16 ? 1 : PF_IT];
+    unsigned pf_lo[PF_IT], pf_hi[PF_IT];
     auto fetch_patch = [&](int tile) {
         const int n = tile / (a.tiles_p * a.tiles_q), t2 = tile - n * (a.tiles_p * a.tiles_q);
         const int pp0 = (t2 / a.tiles_q) * kPoolTP, pq0 = (t2 % a.tiles_q) * kPoolTQ;
@@ -87,18 +87,12 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
             const int ih = h_base + pr, iw = w_base + pc;
             const bool ok = i < kInR * kInC && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
             const size_t g = ((size_t)(n * a.H + (ok ? ih : 0)) * a.W + (ok ? iw : 0)) * 3;
-            if constexpr (DT == SGPRS_BF16) {
-                const unsigned short* xp = (const unsigned short*)a.x + g;
-                // unconditional loads from a clamped (always valid) pixel, zeroed afterwards:
-                // nothing waits on a branch, all loads of the patch are in flight together
-                const unsigned v0 = xp[0], v1 = xp[1], v2 = xp[2];
-                pf_lo[it] = ok ? v0 | (v1 << 16) : 0u;
-                pf_hi[it] = ok ? v2 : 0u;
-            } else {
-                const unsigned* xp = (const unsigned*)a.x + g;
-                const unsigned v0 = xp[0], v1 = xp[1], v2 = xp[2];
-                pf_lo[it] = ok ? v0 : 0u; pf_hi[it] = ok ? v1 : 0u; pf_x[it] = ok ? v2 : 0u;
-            }
+            const unsigned short* xp = (const unsigned short*)a.x + g;
+            // unconditional loads from a clamped (always valid) pixel, zeroed afterwards:
+            // nothing waits on a branch, all loads of the patch are in flight together
+            const unsigned v0 = xp[0], v1 = xp[1], v2 = xp[2];
+            pf_lo[it] = ok ? v0 | (v1 << 16) : 0u;
+            pf_hi[it] = ok ? v2 : 0u;
         }
     };
     auto store_patch = [&]() {
@@ -106,13 +100,8 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
         for (int it = 0; it < PF_IT; ++it) {
             const int i = it * 256 + tid;
             if (i >= kInR * kInC) continue;
-            if constexpr (DT == SGPRS_BF16) {
-                u32x2_t o = {pf_lo[it], pf_hi[it]};
-                *(u32x2_t*)(Ps + i * PIX) = o;
-            } else {
-                u32x4_t o = {pf_lo[it], pf_hi[it], pf_x[it], 0u};
-                *(u32x4_t*)(Ps + i * PIX) = o;
-            }
+            u32x2_t o = {pf_lo[it], pf_hi[it]};
+            *(u32x2_t*)(Ps + i * PIX) = o;
         }
     };
 
@@ -159,9 +148,8 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
 
 #pragma unroll
         for (int r = 0; r < 7; ++r) {
-            constexpr int KSTEPS = DT == SGPRS_BF16 ? 2 : 4;
 #pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) {
+            for (int ks = 0; ks < 2; ++ks) {
                 const int chunk = 2 * ks + fhalf;
                 u32x4_t pf[2], wf[2];
 #pragma unroll
@@ -171,17 +159,9 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        if constexpr (DT == SGPRS_BF16) {
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wf[i]),
-                                                                              __builtin_bit_cast(bf16x8_t, pf[j]), acc[i][j], 0, 0, 0);
-                        } else {
-#pragma unroll
-                            for (int u = 0; u < 3; ++u)  // slot 3 is the zero channel
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wf[i][u]), __uint_as_float(pf[j][u]),
-                                                                                acc[i][j], 0, 0, 0);
-                        }
-                    }
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wf[i]),
+                                                                          __builtin_bit_cast(bf16x8_t, pf[j]), acc[i][j], 0, 0, 0);
             }
         }
 
@@ -202,20 +182,15 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
                     float v[4];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) v[u] = fmaxf(acc[i][j][4 * g + u] * sc[i][g][u] + sh[i][g][u], 0.f);
-                    if constexpr (DT == SGPRS_BF16) {
-                        // After the ReLU every value is >= 0, so pooling can compare bf16 bit
-                        // patterns as unsigned integers and positions outside the conv output
-                        // hold 0: each pooling window has a real pixel, so 0 never wins wrongly.
-                        // The sign bit is cleared so that a -0 cannot compare as large.
-                        const f32x2_t p0 = {v[0], v[1]}, p1 = {v[2], v[3]};
-                        const unsigned keep = ok ? 0x7fff7fffu : 0u;
-                        u32x2_t o = {__builtin_bit_cast(unsigned, __builtin_convertvector(p0, bf16x2_t)) & keep,
-                                     __builtin_bit_cast(unsigned, __builtin_convertvector(p1, bf16x2_t)) & keep};
-                        *(u32x2_t*)(Ps + t * SROWB + c * 2) = o;
-                    } else {
-                        f32x4_t o = {ok ? v[0] : -INFINITY, ok ? v[1] : -INFINITY, ok ? v[2] : -INFINITY, ok ? v[3] : -INFINITY};
-                        *(f32x4_t*)(Ps + t * SROWB + c * 4) = o;
-                    }
+                    // After the ReLU every value is >= 0, so pooling can compare bf16 bit
+                    // patterns as unsigned integers and positions outside the conv output
+                    // hold 0: each pooling window has a real pixel, so 0 never wins wrongly.
+                    // The sign bit is cleared so that a -0 cannot compare as large.
+                    const f32x2_t p0 = {v[0], v[1]}, p1 = {v[2], v[3]};
+                    const unsigned keep = ok ? 0x7fff7fffu : 0u;
+                    u32x2_t o = {__builtin_bit_cast(unsigned, __builtin_convertvector(p0, bf16x2_t)) & keep,
+                                 __builtin_bit_cast(unsigned, __builtin_convertvector(p1, bf16x2_t)) & keep};
+                    *(u32x2_t*)(Ps + t * SROWB + c * 2) = o;
                 }
         }
         __syncthreads();
@@ -232,14 +207,9 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
 #pragma unroll
             for (int rs = 1; rs < 9; ++rs) {
                 const u32x4_t t = *(const u32x4_t*)(base + ((rs / 3) * kConvC + rs % 3) * SROWB);
-                if constexpr (DT == SGPRS_BF16) {
-                    // whole-vector form: eight unsigned 16-bit maxima per tap
-                    m = __builtin_bit_cast(u32x4_t, __builtin_elementwise_max(__builtin_bit_cast(u16x8_t, m),
-                                                                              __builtin_bit_cast(u16x8_t, t)));
-                } else {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) m[u] = __float_as_uint(fmaxf(__uint_as_float(m[u]), __uint_as_float(t[u])));
-                }
+                // whole-vector form: eight unsigned 16-bit maxima per tap
+                m = __builtin_bit_cast(u32x4_t, __builtin_elementwise_max(__builtin_bit_cast(u16x8_t, m),
+                                                                          __builtin_bit_cast(u16x8_t, t)));
             }
             *(u32x4_t*)(a.y + (((size_t)(n * a.PP + gp) * a.PQ + gq) * 64) * ES + grp * 16) = m;
         }
@@ -513,8 +483,10 @@ bool stem_pool_applicable(int dtype, int n, int h, int w, int cus)
     const int PP = (P - 1) / 2 + 1, PQ = (Q - 1) / 2 + 1;
     const long long tiles = (long long)n * ((PP + kPoolTP - 1) / kPoolTP) * ((PQ + kPoolTQ - 1) / kPoolTQ);
     // smaller launches keep the finer-grained two-kernel path; in bf16 the fused kernel wins down
-    // to one image (9.4 us against 8.5 + 4.9 us at batch 1), in fp32 it does not (17.9 against 16.3)
-    return dtype == SGPRS_BF16 ? tiles >= 32 : tiles >= 2ll * cus;
+    // to one image (9.4 us against 8.5 + 4.9 us at batch 1); in fp32 it
+    // does where every CU gets work (us, two kernels and the gap between them against one, 256 CUs: 3 images
+    // 20 / 21, 5 images 24 / 21, 9 images 38 / 34)
+    return dtype == SGPRS_BF16 ? tiles >= 32 : tiles >= cus && stem_f32_applicable(n, h, w);
 }
 
 std::atomic<int> g_stem_pool_force{-1};
@@ -552,7 +524,7 @@ int launch_stem_pool(int dtype, int n, int h, int w, const void* x, const void* 
     const double flops = 2.0 * n * a.P * a.Q * 64.0 * 147.0;
     const double bytes = ((double)n * h * w * 3 + 64.0 * 147 + (double)n * a.PP * a.PQ * 64) * es;
     int rc;
-    static std::atomic<bool> raised[3] = {{false}, {false}, {false}};
+    static std::atomic<bool> raised[2] = {{false}, {false}};
     const long long x_bytes = (long long)n * h * w * 6;
     const bool packed = dtype == SGPRS_BF16 && wts_rows && w % 8 == 0 && ((uintptr_t)x & 15) == 0 && x_bytes < (1ll << 31) &&
                         g_stem_pool_force.load() != 1;
@@ -560,27 +532,22 @@ int launch_stem_pool(int dtype, int n, int h, int w, const void* x, const void* 
     if (packed) {
         a.w = (const unsigned char*)wts_rows;
         constexpr int lds_rows = 2 * kPatchPitch + 256 * (64 * 2 + 16) + 512;
-        if (!raised[2]) {
+        if (!raised[1]) {
             SGPRS_HIP(hipFuncSetAttribute((const void*)stem_pool_packed_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                           lds_rows));
-            raised[2] = true;
+            raised[1] = true;
         }
         SGPRS_LAUNCH(stem_pool_packed_kernel, dim3((int)std::min<long long>(nt, 2ll * cus)), dim3(256), lds_rows, stream, a,
                      (unsigned)x_bytes);
     } else if (dtype == SGPRS_BF16) {
-        if (!raised[1]) {
-            SGPRS_HIP(hipFuncSetAttribute((const void*)stem_pool_kernel<SGPRS_BF16>,
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            raised[1] = true;
-        }
-        SGPRS_LAUNCH(stem_pool_kernel<SGPRS_BF16>, dim3(grid), dim3(256), lds, stream, a);
-    } else {
         if (!raised[0]) {
-            SGPRS_HIP(hipFuncSetAttribute((const void*)stem_pool_kernel<SGPRS_F32>,
+            SGPRS_HIP(hipFuncSetAttribute((const void*)stem_pool_kernel<SGPRS_BF16>,
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
             raised[0] = true;
         }
-        SGPRS_LAUNCH(stem_pool_kernel<SGPRS_F32>, dim3(grid), dim3(256), lds, stream, a);
+        SGPRS_LAUNCH(stem_pool_kernel<SGPRS_BF16>, dim3(grid), dim3(256), lds, stream, a);
+    } else if ((rc = launch_stem_f32(n, h, w, x, wts, scale, shift, y, 1, true, stream, cus))) {
+        return rc;
     }
     SGPRS_HIP(hipGetLastError());
     if (prof && prof->on && (rc = prof->end(stream))) return rc;

@@ -513,9 +513,9 @@ const char* sgprs_kernel_name(int kind, int variant)
         case kKindPatch: return patch_variant_name(variant);
         case kKindS2Patch: return s2patch_variant_name(variant);
         case kKindRows: return "conv3x3_rows_kernel";
-        case kKindStem: return "conv_stem_kernel";
+        case kKindStem: return variant == 4 ? "stem_f32_kernel" : "conv_stem_kernel";
         case kKindStemPool:
-            return variant == 2 ? "stem_pool_packed_kernel" : variant == SGPRS_BF16 ? "stem_pool_kernel<1>" : "stem_pool_kernel<0>";
+            return variant == 2 ? "stem_pool_packed_kernel" : variant == SGPRS_BF16 ? "stem_pool_kernel<1>" : "stem_f32_kernel";
         case kKindReduce: return "splitk_reduce_kernel";
         case kKindMaxpool: return "maxpool3x3s2_kernel";
         case kKindAvgpool: return "avgpool_kernel";

@@ -104,6 +104,36 @@ def test_conv_stem_parity(pools, dtype, shape):
         assert_close(got, ref, dtype, f"stem {shape}")
 
 
+@pytest.mark.parametrize("shape,relu", [((1, 1, 4), True), ((2, 31, 28), False), ((1, 33, 64), True), ((3, 130, 132), True),
+                                        ((2, 224, 224), False)], ids=str)
+def test_stem_f32_packed_rows(pools, shape, relu):
+    """The fp32 stem on packed input rows (widths that are a multiple of four): one output pixel, tails
+    in both directions, tiles of 4 and of 8 rows, one workgroup walking many tiles.  148 products and
+    sums of |w x| per output: below 148 * 2^-24 = 9e-6 of the largest.  An infinite input pixel reaches
+    the outputs whose window holds it and no other."""
+    n, h, w = shape
+    for cus in (8, "full"):
+        pool = pools[cus]
+        got, ref = conv_case(S.SGPRS_F32, n, h, w, 3, 64, 7, 2, 3, relu=relu, with_res=False, seed=33, pool=pool,
+                             cus=pool.partition_cus(0))
+        assert got.shape == ref.shape and rel_err(got, ref) <= 9e-6, shape
+        x = make_input(90, 34, (n, 3, h, w))
+        wt = make_conv_weight(90, 34, 1, 64, 3, 7)
+        dc = DevConv(S.ConvDesc(n, h, w, 3, 64, 7, 7, 2, 3, S.SGPRS_F32, int(relu)), wt, *make_bn(90, 34, 2, 64), BN_EPS)
+        ih, iw, outs = h // 2, w // 2, []
+        for v in (0.0, np.inf):
+            x[-1, 1, ih, iw] = v
+            yd = dev_empty((n,) + ref.shape[2:] + (64,), S.SGPRS_F32)
+            keep = dc.run(dev_nhwc(x, S.SGPRS_F32), yd, None, pool, 0, pool.partition_cus(0))
+            pool.sync()
+            outs.append(host_nchw(yd))
+        p, q = np.meshgrid(np.arange(ref.shape[2]), np.arange(ref.shape[3]), indexing="ij")
+        hit = (np.abs(2 * p - ih) <= 3) & (np.abs(2 * q - iw) <= 3)
+        same = np.array_equal
+        assert same(outs[0][:-1], outs[1][:-1]) and same(outs[0][-1][:, ~hit], outs[1][-1][:, ~hit])
+        assert not np.isfinite(outs[1][-1][:, hit]).all()
+
+
 @pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
 def test_conv_is_deterministic_and_mask_independent(pools, dtype):
     shape = (1, 14, 14, 256, 256, 3, 1, 1)
