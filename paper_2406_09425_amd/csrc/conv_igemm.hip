@@ -562,12 +562,12 @@ int launch_conv_pair(const sgprs_conv_desc_t& d0, const void* w0, const float* s
 {
     *done = false;
     if (d0.dtype != d1.dtype || d0.n != d1.n || d0.h != d1.h || d0.w != d1.w || d0.cin != d1.cin) return SGPRS_OK;
-    const ConvPlan p0 = plan_conv(d0, cus);
+    const ConvPlan p0 = plan_conv_pair(d0, d1, cus);
     if (p0.bm != 0 && p0.kind == 4 && ksplit_fits(d1, p0.variant) && d1.cout == d0.cout && d1.stride == d0.stride && d1.pad == d1.r / 2 && d0.pad == d0.r / 2) {
         *done = true;
         return launch_conv_ksplit(d0, p0.variant, x, w0, scale0, shift0, nullptr, y0, &d1, w1, scale1, shift1, y1, stream, prof);
     }
-    ConvPlan p1 = plan_conv(d1, cus);
+    ConvPlan p1 = plan_conv(d1, cus, false, false);
     if (p0.bm == 0 || p0.kind != 0 || p0.splits != 1 || p1.bm == 0 || p1.kind != 0) return SGPRS_OK;
     // the second problem takes the first one's tile shape
     const int es = (int)dtype_size(d1.dtype);

@@ -467,32 +467,47 @@ bool ksplit_fits(const sgprs_conv_desc_t& d, int v)
     return is_igemm(d) && v >= 0 && v < kKsplitVariants && d.cout % (16 * kKsplitShape[v][1]) == 0;
 }
 
-// Estimated time (microseconds) of the best tile: launch, then rounds of workgroups, each a fixed
+// Estimated time (microseconds) of a tile shape: launch, then rounds of workgroups, each a fixed
 // part (start, pixel arithmetic, reduction), the traffic of its k-tiles at the 110 GB/s one CU gets
 // out of the L2 with 64-144 KB in flight, and, behind the first filling of the rings, the matrix
 // work.  Fitted to 1368 measurements (nine layers, 1..16 images, 8..256 CUs, both types): 8 % off
-// rms, and its choice is 1.5 % slower than the best tile on average.
-bool plan_ksplit(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us)
+// rms, and its choice is 1.5 % slower than the best tile on average.  With the block's shortcut d1 in
+// the same launch, the shortcut's workgroups first fill what the last round leaves idle (324 paired
+// launches: 10 % off rms without refitting).
+double ksplit_cost(const sgprs_conv_desc_t& d, int v, int cus, const sgprs_conv_desc_t* d1)
 {
-    if (!is_igemm(d)) return false;
     const int es = (int)dtype_size(d.dtype);
+    const int *t = kKsplitShape[v], bm = 16 * t[0], bn = 16 * t[1], lds = kKsplitWaves * t[2] * (bm + bn) * 128;
     const long long M = (long long)d.n * out_dim(d.h, d.r, d.stride, d.pad) * out_dim(d.w, d.s, d.stride, d.pad);
-    const int ktiles = d.r * d.s * d.cin * es / 128, kt = (ktiles + kKsplitWaves - 1) / kKsplitWaves * kKsplitWaves;  // the longest share decides
+    const long long wgs = (M + bm - 1) / bm * (d.cout / bn), occ = lds <= 80 * 1024 ? 2 : 1, room = cus * occ;
     // one CU's time per FLOP; a bf16 k-tile's MFMAs are mostly hidden behind its traffic
     const double us_per_flop = d.dtype == SGPRS_BF16 ? 0.26 / 9.8e6 : 1.0 / 0.614e6;
-    double best = 1e30;
-    for (int v = 0; v < kKsplitVariants; ++v) {
-        if (!ksplit_fits(d, v)) continue;
-        const int *t = kKsplitShape[v], bm = 16 * t[0], bn = 16 * t[1], lds = kKsplitWaves * t[2] * (bm + bn) * 128;
-        const long long wgs = (M + bm - 1) / bm * (d.cout / bn), occ = lds <= 80 * 1024 ? 2 : 1;
+    auto rounds = [&](const sgprs_conv_desc_t& p, long long n) {
+        const int ktiles = p.r * p.s * p.cin * es / 128, kt = (ktiles + kKsplitWaves - 1) / kKsplitWaves * kKsplitWaves;  // the longest share decides
         const double traffic = (bm + bn) * 128.0 * kt / 110e3, ring = std::min(traffic, lds / 110e3);
         const double mfma = 2.0 * bm * bn * (128 / es) * kt * us_per_flop;
         auto round = [&](long long per_cu) {
             return 0.64 + 0.2 * t[0] + 0.00031 * bm * bn + std::max(per_cu * traffic, ring + per_cu * mfma * (per_cu > 1 ? 1.06 : 1.0));
         };
-        const long long full = wgs / (cus * occ), rest = wgs - full * cus * occ;
-        double cost = 1.5 + full * round(occ) + 0.12 * (full + (rest > 0) - 1);
-        if (rest) cost += round((rest + cus - 1) / cus);
+        const long long full = n / room, rest = n - full * room;
+        return full * round(occ) + 0.12 * (full + (rest > 0) - 1) + (rest ? round((rest + cus - 1) / cus) : 0.0);
+    };
+    double cost = 1.5 + rounds(d, wgs);
+    if (d1) {
+        const long long left = wgs - (room - wgs % room) % room;
+        if (left > 0) cost += rounds(*d1, left);
+    }
+    return cost;
+}
+
+int ksplit_num_variants() { return kKsplitVariants; }
+
+bool plan_ksplit(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us)
+{
+    double best = 1e30;
+    for (int v = 0; v < kKsplitVariants; ++v) {
+        if (!ksplit_fits(d, v)) continue;
+        const double cost = ksplit_cost(d, v, cus, nullptr);
         if (cost < best) { best = cost; *variant = v; *cost_us = cost; }
     }
     return best < 1e30;

@@ -182,6 +182,8 @@ struct ConvPlan {
 // (has_residual: kernels without a residual input are left out; ksplit false: so is the kernel that
 // splits K over a workgroup's wavefronts).
 ConvPlan plan_conv(const sgprs_conv_desc_t& d, int partition_cus, bool has_residual = false, bool ksplit = true);
+// The plan of d0 for a launch that also runs the block's shortcut d1 on the same input (same output shape).
+ConvPlan plan_conv_pair(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int partition_cus);
 size_t conv_workspace_bytes(const sgprs_conv_desc_t& d, const ConvPlan& p);
 
 struct KernelRecord {
@@ -286,6 +288,8 @@ int launch_conv3x3_rows(const sgprs_conv_desc_t& d, int rows_per_stream, const v
                         const float* shift, const void* residual, void* y, hipStream_t stream, int cus, Profiler* prof);
 // implicit GEMM with the K range split over the wavefronts of a workgroup (few output tiles)
 bool plan_ksplit(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us);
+int ksplit_num_variants();
+double ksplit_cost(const sgprs_conv_desc_t& d, int variant, int cus, const sgprs_conv_desc_t* d1);
 const char* ksplit_variant_name(int v);
 constexpr int kKsplitNames = 32;  // launches of this kernel are recorded as implicit GEMM (or pair), variant 32 + 16 * dtype + tile
 bool ksplit_fits(const sgprs_conv_desc_t& d, int variant);

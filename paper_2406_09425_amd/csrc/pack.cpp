@@ -165,6 +165,69 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
     return best;
 }
 
+// A down-sampling block's first 3x3 convolution and its 1x1 shortcut in one launch: the tile that is
+// best for the two together.  The single-convolution estimates do not rank these launches: the
+// implicit-GEMM workgroups of the shortcut run beside the main problem's (three to five fit a CU)
+// where the K-split kernel, one or two to a CU, needs further rounds.  Implicit GEMM: launch and
+// epilogue, the k-tiles of one workgroup or, if that is longer, of the busiest CU, and a part per
+// workgroup and CU; fitted per tile to 324 launches (the network's three blocks, 1..128 images,
+// 32..256 CUs, both types; 5-12 % off rms).  The choice is 2 % slower than the best tile on average,
+// that of the single-convolution plan was 7 %; 64 images on 256 CUs, 14x14x256 -> 512: 19.2 us with
+// 64x64 implicit-GEMM tiles, 23.4 with the K-split kernel.  Near a tie the K-split kernel is the one
+// that keeps its time inside the network (4 images on 96 CUs, whole inference: 156.0 us with it in
+// the second block, 159.4 with implicit GEMM, whose launch alone is as fast): 5 % in its favour.
+static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int cus)
+{
+    const ConvPlan single = plan_conv(d0, cus);
+    const int P = out_dim(d0.h, d0.r, d0.stride, d0.pad), Q = out_dim(d0.w, d0.s, d0.stride, d0.pad);
+    if (g_conv_force_kind.load() != -1 || g_igemm_force_variant.load() >= 0 || single.bm == 0 || (single.kind != 0 && single.kind != 4) ||
+        !is_igemm(d1) || d1.cout != d0.cout || P != out_dim(d1.h, d1.r, d1.stride, d1.pad) || Q != out_dim(d1.w, d1.s, d1.stride, d1.pad))
+        return single;
+    static const double kCost[2][4][4] = {  // fp32, bf16: {fixed, per k-tile of a workgroup, per k-tile of the busiest CU, per workgroup and CU}
+        {{0.0, 1.86, 1.86, 9.5}, {3.9, 0.98, 0.860, 3.4}, {6.1, 0.51, 0.478, 0.44}, {4.9, 0.54, 0.490, 0.50}},
+        {{4.2, 0.50, 0.316, 2.6}, {4.1, 0.40, 0.235, 1.07}, {2.4, 0.38, 0.145, 0.75}, {2.0, 0.45, 0.189, 0.61}}};
+    const int kt_el = d0.dtype == SGPRS_BF16 ? 64 : 32;
+    const long long M = (long long)d0.n * P * Q;
+    const int kt0 = d0.r * d0.s * d0.cin / kt_el, kt1 = d1.r * d1.s * d1.cin / kt_el;
+    ConvPlan best;
+    double best_cost = 1e30;
+    for (int v = 0; v < igemm_num_variants(); ++v) {
+        const Tile& t = kTiles[v];
+        if (d0.cout % t.bn) continue;
+        const long long gm = (M + t.bm - 1) / t.bm, gn = d0.cout / t.bn, blocks = gm * gn;
+        const double* c = kCost[d0.dtype == SGPRS_BF16][v];
+        const double busiest = std::max((double)((blocks + cus - 1) / cus * kt0), (double)blocks * (kt0 + kt1) / cus);
+        const double cost = 1.05 * (c[0] + std::max(c[1] * kt0, c[2] * busiest) + c[3] * std::max(1.0, 2.0 * blocks / cus));
+        if (cost < best_cost) {
+            best_cost = cost;
+            best.variant = v; best.bm = t.bm; best.bn = t.bn; best.splits = 1; best.ktiles = kt0;
+            best.grid_m = (int)gm; best.grid_n = (int)gn;
+        }
+    }
+    for (int v = 0; v < ksplit_num_variants(); ++v) {
+        if (!ksplit_fits(d0, v) || !ksplit_fits(d1, v)) continue;
+        const double cost = ksplit_cost(d0, v, cus, &d1);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = ConvPlan();
+            best.kind = 4; best.variant = v; best.bm = 1;
+        }
+    }
+    return best.bm ? best : single;
+}
+
+ConvPlan plan_conv_pair(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int cus)
+{
+    struct Key { sgprs_conv_desc_t d0, d1; int cus, gen; };
+    static thread_local PlanMemo<Key, ConvPlan> local;
+    static SharedPlanMemo<Key, ConvPlan> memo;
+    cus = planning_cus(cus);
+    Key k;
+    memset(&k, 0, sizeof(k));
+    k.d0 = d0; k.d1 = d1; k.cus = cus; k.gen = g_plan_generation.load();
+    return memo.get(local, k, [&]() { return plan_conv_pair_uncached(d0, d1, cus); });
+}
+
 size_t conv_workspace_bytes(const sgprs_conv_desc_t& d, const ConvPlan& p)
 {
     if (p.splits <= 1) return 0;

@@ -176,6 +176,40 @@ def test_downsample_block_runs_as_one_paired_launch(cfg1):
         pool.destroy()
 
 
+@pytest.mark.parametrize("n", [1, 5, 20])
+@pytest.mark.parametrize("dtype", [S.SGPRS_F32, S.SGPRS_BF16], ids=DT_ID.get)
+def test_paired_launch_families_parity(cfg1, dtype, n):
+    """The down-sampling blocks with the pair's own plan (small, middle and large partition: both kernel
+    families are chosen over these) and with every tile of both families forced, against the oracle."""
+    params = cfg1[0]
+    total = S.Pool(1, 8).info()["total_cus"]
+    task = S.Task(params, dtype, n, BN_EPS)
+    task.set_profiling(True)
+    seen = set()
+    try:
+        for j in (2, 3, 4):
+            x = np.maximum(make_input(n, 40 + j, stage_shape(j, n, out=False)[:1] + STAGE_IO[j][0]), 0.0)
+            ref = oracle.resnet18_stage(j, params, BN_EPS, x)
+            xd = dev_nhwc(x, dtype)
+            runs = [(c, (-1, 0, 1)) for c in (32, 96, total)] + [(total, (2, v, 1)) for v in (0, 1, 2, 3, 8, 9, 10, 11, 12, 13, 14, 15)]
+            for cus, override in runs:
+                S.sgprs_conv_tuning_override(*override)
+                pool = S.Pool(1, cus)
+                o = dev_empty(stage_shape(j, n), dtype)
+                task.stage_run(j, n, xd.data_ptr(), o.data_ptr(), pool, 0)
+                pool.sync()
+                assert_close(host_nchw(o), ref, dtype, f"stage {j} n={n} cus={cus} override {override}")
+                if override[0] < 0:
+                    pair = [k for k in task.kernel_times(j) if k["kind"] == 10]
+                    assert len(pair) == 1
+                    seen.add("ksplit" in pair[0]["name"])
+                pool.destroy()
+        assert n != 5 or seen == {True, False}
+    finally:
+        S.sgprs_conv_tuning_override(-1, 0, 1)
+        task.destroy()
+
+
 def test_stage0_fp32_fused_stem_pool_elementwise(cfg1):
     """fp32 launches of at least two tiles per CU take the fused conv7x7 + max-pool kernel
     (kind 9): its stage-0 output, element by element against the oracle, on 8 and 64 CUs, with a
