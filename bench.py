@@ -342,7 +342,7 @@ def leg_batch1(S, hip, pool, stream, nhwc, torch, total_cus, runs=100):
 
 def leg_batch_sweep(S, hip, torch, pool, stream, nhwc, batches=(1, 2, 4, 8, 16, 32), runs=200):
     """bf16 whole-network throughput at batch sizes below the headline's, on the whole chip, through
-    sgprs_task_run (graph replay), back to back on one stream."""
+    sgprs_task_run, back to back on one stream."""
     from workloads import BN_EPS, make_input, make_resnet18_params
     params = make_resnet18_params(4, 0, bf16=True)
     res = {}
@@ -694,8 +694,8 @@ def leg_periodic(S, hip, torch, total_cus, nhwc, n_list=(128, 256, 320, 384, 448
 def leg_pool_scaling(S, torch, total_cus, nhwc, instances=8, rounds=150, partitions=(1, 2, 3, 4, 8)):
     """Eight bf16 batch-1 instances spread round-robin over pools of 1, 2, 3, 4 and 8 equal
     partitions (the paper's question: how does throughput grow with the number of contexts?).
-    Every instance is issued with sgprs_task_run from one host thread, i.e. replayed as a HIP
-    graph after its second run: one host call per inference."""
+    Every instance is issued with sgprs_task_run from one host thread: on pools of several
+    partitions replayed as a HIP graph after its second run."""
     from workloads import BN_EPS, make_input, make_resnet18_params
     tasks, xs, lgs = [], [], []
     for i in range(instances):
