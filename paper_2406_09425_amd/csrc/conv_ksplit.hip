@@ -28,6 +28,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "tap_mask.h"
 
 namespace sgprs {
 
@@ -168,8 +169,7 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
         const int p = ks_div(rem, a.q_mul, a.q_sh), q = rem - p * a.Q;
         const int h0 = p * a.stride - a.pad, w0 = q * a.stride - a.pad;
         a_base[i] = (n * a.H + h0) * a.row_bytes + w0 * a.pixel_bytes + chunk_off;
-        const int hl = max(-h0, 0), hn = min(a.H - h0, a.taps), wl = max(-w0, 0), wn = min(a.W - w0, a.taps);
-        a_in[i] = (((1u << hn) - (1u << hl)) | (((1u << wn) - (1u << wl)) << 16)) & (unsigned)((m - a.M) >> 31);
+        a_in[i] = (tap_mask(h0, a.H, a.taps) | (tap_mask(w0, a.W, a.taps) << 16)) & (unsigned)((m - a.M) >> 31);
     }
     const int tap0 = ks_div(kt0, a.ct_mul, a.ct_sh);
     int ic = kt0 - tap0 * a.cin_tiles, ir = a.taps == 3 ? tap0 / 3 : tap0, is = a.taps == 3 ? tap0 - ir * 3 : 0;

@@ -455,6 +455,12 @@ KSPLIT_SHAPES = [
     (2, 11, 7, 128, 64, 3, 2, 1),
     (1, 7, 7, 512, 512, 3, 1, 1),
     (1, 14, 14, 256, 512, 1, 2, 0),
+    # padding wider than the filter: whole windows before and past the image, in rows and columns, beyond
+    # what a 32-bit shift holds (pad 33), strided, two images so that the neighbour's pixels are there to be read
+    (2, 5, 7, 64, 64, 3, 1, 4),
+    (2, 4, 3, 64, 64, 1, 1, 2),
+    (1, 3, 2, 64, 64, 3, 2, 33),
+    (2, 6, 5, 128, 64, 1, 2, 3),
 ]
 
 
