@@ -64,8 +64,10 @@ namespace sgprs {
 // batch 1 on 32 / 48 / 56 / 64: 135 / 135 / 160 / 108).
 inline int planning_cus(int cus) { return cus < 1 ? 1 : cus < 32 ? cus : cus / 32 * 32; }
 
-// validates pool/partition, returns the stream and the CU count to plan for
+// validates pool/partition, returns the stream and the number of CUs in the mask
 int resolve(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* cus);
+// the same for calls that launch planned work: the CU count is the one to plan for
+int resolve_launch(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* plan_cus);
 
 inline size_t dtype_size(int dtype) { return dtype == SGPRS_BF16 ? 2 : 4; }
 inline bool dtype_ok(int dtype) { return dtype == SGPRS_F32 || dtype == SGPRS_BF16; }

@@ -58,7 +58,7 @@ int sgprs_conv2d(const sgprs_conv_desc_t* d, const void* x, const void* w_packed
     if (rc) return rc;
     hipStream_t stream;
     int cus = 0;
-    if ((rc = resolve(pool, partition, &stream, &cus))) return rc;
+    if ((rc = resolve_launch(pool, partition, &stream, &cus))) return rc;
     if (!x || !w_packed || !scale || !shift || !y) return fail(SGPRS_ERR_INVALID_ARG, "NULL tensor pointer");
     if (!aligned16(x) || !aligned16(w_packed) || !aligned16(y) || !aligned16(residual) || !aligned16(scale) ||
         !aligned16(shift) || !aligned16(workspace))
@@ -92,7 +92,7 @@ int sgprs_maxpool2d(int dtype, int n, int h, int w, int c, const void* x, void* 
 {
     hipStream_t stream;
     int cus = 0, rc;
-    if ((rc = resolve(pool, partition, &stream, &cus))) return rc;
+    if ((rc = resolve_launch(pool, partition, &stream, &cus))) return rc;
     if (!dtype_ok(dtype)) return fail(SGPRS_ERR_UNSUPPORTED, "dtype %d", dtype);
     if (n <= 0 || h <= 0 || w <= 0 || c <= 0) return fail(SGPRS_ERR_INVALID_ARG, "non-positive dimension");
     if (c % (dtype == SGPRS_BF16 ? 8 : 4)) return fail(SGPRS_ERR_UNSUPPORTED, "c %d not a multiple of the vector width", c);
@@ -107,7 +107,7 @@ int sgprs_bn_relu(int dtype, size_t pixels, int c, const void* x, const float* s
 {
     hipStream_t stream;
     int cus = 0, rc;
-    if ((rc = resolve(pool, partition, &stream, &cus))) return rc;
+    if ((rc = resolve_launch(pool, partition, &stream, &cus))) return rc;
     if (!dtype_ok(dtype)) return fail(SGPRS_ERR_UNSUPPORTED, "dtype %d", dtype);
     if (pixels == 0 || c <= 0) return fail(SGPRS_ERR_INVALID_ARG, "empty tensor");
     if (c % (dtype == SGPRS_BF16 ? 8 : 4)) return fail(SGPRS_ERR_UNSUPPORTED, "c %d not a multiple of the vector width", c);
@@ -123,7 +123,7 @@ int sgprs_add_relu(int dtype, size_t count, const void* a, const void* b, void* 
 {
     hipStream_t stream;
     int cus = 0, rc;
-    if ((rc = resolve(pool, partition, &stream, &cus))) return rc;
+    if ((rc = resolve_launch(pool, partition, &stream, &cus))) return rc;
     if (!dtype_ok(dtype)) return fail(SGPRS_ERR_UNSUPPORTED, "dtype %d", dtype);
     if (count == 0 || count % 8) return fail(SGPRS_ERR_INVALID_ARG, "count %zu must be a positive multiple of 8", count);
     if (count >= (1ull << 31)) return fail(SGPRS_ERR_UNSUPPORTED, "tensor with 2^31 or more elements");
@@ -137,7 +137,7 @@ int sgprs_avgpool_fc(int dtype, int n, int hw, int cin, int cout, const void* x,
 {
     hipStream_t stream;
     int cus = 0, rc;
-    if ((rc = resolve(pool, partition, &stream, &cus))) return rc;
+    if ((rc = resolve_launch(pool, partition, &stream, &cus))) return rc;
     if (!dtype_ok(dtype)) return fail(SGPRS_ERR_UNSUPPORTED, "dtype %d", dtype);
     if (n <= 0 || hw <= 0 || cout <= 0) return fail(SGPRS_ERR_INVALID_ARG, "non-positive dimension");
     if (n > 65535 || cout > (1 << 20) || (long long)n * hw * cin >= (1ll << 31))
@@ -153,7 +153,7 @@ int sgprs_global_avgpool(int dtype, int n, int hw, int c, const void* x, float* 
 {
     hipStream_t stream;
     int cus = 0, rc;
-    if ((rc = resolve(pool, partition, &stream, &cus))) return rc;
+    if ((rc = resolve_launch(pool, partition, &stream, &cus))) return rc;
     if (!dtype_ok(dtype)) return fail(SGPRS_ERR_UNSUPPORTED, "dtype %d", dtype);
     if (n <= 0 || hw <= 0) return fail(SGPRS_ERR_INVALID_ARG, "non-positive dimension");
     if (n > 65535 || (long long)n * hw * c >= (1ll << 31))
@@ -169,7 +169,7 @@ int sgprs_avgpool_fc_static(int dtype, int n, int hw, int cin, int cout, const v
 {
     hipStream_t stream;
     int cus = 0, rc;
-    if ((rc = resolve(pool, partition, &stream, &cus))) return rc;
+    if ((rc = resolve_launch(pool, partition, &stream, &cus))) return rc;
     if (!dtype_ok(dtype)) return fail(SGPRS_ERR_UNSUPPORTED, "dtype %d", dtype);
     if (n <= 0 || hw <= 0 || cout <= 0) return fail(SGPRS_ERR_INVALID_ARG, "non-positive dimension");
     if (n > 65535 || cout > (1 << 20) || (long long)n * hw * cin >= (1ll << 31))

@@ -27,8 +27,15 @@ int resolve(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* cus)
         return fail(SGPRS_ERR_INVALID_ARG, "partition %d outside [0,%d)", partition,
                     (int)pool->parts.size());
     *stream = pool->parts[partition].stream;
-    *cus = planning_cus(pool->parts[partition].cus);
+    *cus = pool->parts[partition].cus;
     return SGPRS_OK;
+}
+
+int resolve_launch(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* plan_cus)
+{
+    const int rc = resolve(pool, partition, stream, plan_cus);
+    if (!rc) *plan_cus = planning_cus(*plan_cus);
+    return rc;
 }
 
 static int popcount_mask(const std::vector<uint32_t>& m)

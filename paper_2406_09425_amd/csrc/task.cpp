@@ -364,7 +364,7 @@ int sgprs_stage_run(sgprs_task_t* t, int stage, int batch, const void* in, void*
     if (rc) return rc;
     hipStream_t s;
     int cus = 0;
-    if ((rc = resolve(pool, partition, &s, &cus))) return rc;
+    if ((rc = resolve_launch(pool, partition, &s, &cus))) return rc;
     if (!in || !out || ((uintptr_t)in & 15) || ((uintptr_t)out & 15) || in == out)
         return fail(SGPRS_ERR_INVALID_ARG, "in and out must be distinct, non-NULL and 16-byte aligned");
     if (pool->device != t->device) return fail(SGPRS_ERR_INVALID_ARG, "pool and task live on different devices");
@@ -381,7 +381,7 @@ int sgprs_task_run(sgprs_task_t* t, int batch, const void* in, float* logits, sg
     hipStream_t s[SGPRS_RESNET18_STAGES];
     int cus[SGPRS_RESNET18_STAGES];
     for (int j = 0; j < SGPRS_RESNET18_STAGES; ++j)
-        if ((rc = resolve(pool, pps ? pps[j] : partition, &s[j], &cus[j]))) return rc;
+        if ((rc = resolve_launch(pool, pps ? pps[j] : partition, &s[j], &cus[j]))) return rc;
     if (pool->device != t->device) return fail(SGPRS_ERR_INVALID_ARG, "pool and task live on different devices");
 
     // ---- graph replay: one partition, no per-kernel timing ----

@@ -38,6 +38,21 @@ def test_pool_info_and_masks():
     pool.destroy()
 
 
+@pytest.mark.parametrize("cus", [8, 40, 56, 200, 248])
+def test_partition_cus_is_the_mask_and_every_cu_is_probed(cus):
+    """The reported CU count is the mask's, also where launches are planned for fewer CUs, and the
+    load probe runs one workgroup per CU of the mask (a word each; none behind the last)."""
+    pool = S.Pool(1, cus)
+    assert pool.partition_cus(0) == cus == sum(bin(int(w)).count("1") for w in pool.mask(0))
+    buf = torch.ones(1 << 20, dtype=torch.int32, device="cuda")
+    out = torch.zeros(cus + 8, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    pool.load_probe(0, buf.data_ptr(), buf.numel() * 4, 64 << 10, 2, out.data_ptr())
+    pool.sync()
+    assert out.cpu().tolist() == [16384] * cus + [0] * 8
+    pool.destroy()
+
+
 def test_oversubscription_needs_flag():
     total = S.Pool(1, 8).info()["total_cus"]
     with pytest.raises(S.SgprsError) as e:
