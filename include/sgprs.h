@@ -92,7 +92,10 @@ int sgprs_build_cu_mask(int total_cus, int n_xcd, int cus, int partition, int bl
 
 /* Creates n_p partitions of cus_per_partition CUs on `device`.  cus must be a
  * multiple of the die count.  NO_DEVICE if there is no usable GPU,
- * OVERSUBSCRIBED if n_p*cus exceeds the device without the flag. */
+ * OVERSUBSCRIBED if n_p*cus exceeds the device without the flag.
+ * Beyond 32 CUs, launches on these partitions are planned for a multiple of 32
+ * CUs; with the blocked layout and with caller-chosen masks they are planned for
+ * every CU of the mask. */
 int sgprs_pool_create(int device, int n_p, int cus_per_partition, unsigned flags,
                       sgprs_pool_t **out);
 /* Same with caller-chosen masks: masks[p*words_per_mask .. +words_per_mask) HOST.
@@ -182,7 +185,7 @@ int sgprs_unpack_conv_weights(const sgprs_conv_desc_t *d, const void *w_packed, 
 int sgprs_conv2d_workspace(const sgprs_conv_desc_t *d, int partition_cus, size_t *bytes);
 /* Which kernel sgprs_conv2d would launch for this shape on a partition of
  * partition_cus CUs, with or without a residual (host logic only, nothing is
- * enqueued).  family: 0 implicit GEMM, 1 LDS-patch 3x3, 2 stride-2 LDS-patch
+ * enqueued; the partition is one of sgprs_pool_create's default layout).  family: 0 implicit GEMM, 1 LDS-patch 3x3, 2 stride-2 LDS-patch
  * 3x3, 3 row-streaming 3x3 (64 -> 64 channels, 56-pixel rows), 4 the 7x7 stem;
  * detail: the tile variant (family 0: from 8 on, those that split K over the
  * wavefronts of a workgroup), or the output rows per stream and job of family 3. */

@@ -42,7 +42,8 @@ constexpr int kMaxBusyQueues = kDispatchPipes;
 struct Partition {
     hipStream_t stream = nullptr;
     std::vector<uint32_t> mask;
-    int cus = 0;
+    int cus = 0;       // in the mask
+    int plan_cus = 0;  // that launches are planned for
 };
 
 }  // namespace sgprs
@@ -57,7 +58,8 @@ struct sgprs_pool {
 
 namespace sgprs {
 
-// CUs that launches are planned for.  Workgroups are dealt to the 8 dies in turn and, within a die,
+// CUs that launches are planned for on a partition with an interleaved mask (sgprs_build_cu_mask; other
+// masks are planned for all their CUs).  Workgroups are dealt to the 8 dies in turn and, within a die,
 // to its 4 shader engines in turn, and a workgroup waits for room in the engine whose turn it is:
 // the engine with the fewest CUs sets the pace, so beyond 32 CUs a partition is worth a multiple of
 // 32 (batch-8 inference on 192 / 200 / 216 / 224 CUs, planned for all of them: 167 / 207 / 195 / 146 us;

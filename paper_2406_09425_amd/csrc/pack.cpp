@@ -67,7 +67,6 @@ ConvPlan plan_conv(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool 
     struct Key { sgprs_conv_desc_t d; int cus, res, ksplit, gen; };
     static thread_local PlanMemo<Key, ConvPlan> local;
     static SharedPlanMemo<Key, ConvPlan> memo;
-    cus = planning_cus(cus);
     Key k;
     memset(&k, 0, sizeof(k));
     k.d = d; k.cus = cus; k.res = has_residual; k.ksplit = ksplit; k.gen = g_plan_generation.load();
@@ -221,7 +220,6 @@ ConvPlan plan_conv_pair(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1
     struct Key { sgprs_conv_desc_t d0, d1; int cus, gen; };
     static thread_local PlanMemo<Key, ConvPlan> local;
     static SharedPlanMemo<Key, ConvPlan> memo;
-    cus = planning_cus(cus);
     Key k;
     memset(&k, 0, sizeof(k));
     k.d0 = d0; k.d1 = d1; k.cus = cus; k.gen = g_plan_generation.load();
@@ -311,13 +309,15 @@ int sgprs_conv2d_workspace(const sgprs_conv_desc_t* d, int partition_cus, size_t
     if (rc) return rc;
     if (!bytes) return fail(SGPRS_ERR_INVALID_ARG, "bytes is NULL");
     if (partition_cus <= 0) return fail(SGPRS_ERR_INVALID_ARG, "partition_cus %d <= 0", partition_cus);
-    // The plan may depend on whether a residual is passed, and a tuning override may switch to the
-    // kernels that split K over workgroups after the caller has allocated: enough for all of them.
+    // The plan may depend on whether a residual is passed and on the kind of the partition's mask
+    // (planning_cus), and a tuning override may switch to the kernels that split K over workgroups
+    // after the caller has allocated: enough for all of them.
     *bytes = 0;
     if (!is_stem(*d))
-        for (int res = 0; res < 2; ++res)
-            *bytes = std::max({*bytes, conv_workspace_bytes(*d, plan_conv(*d, partition_cus, res != 0)),
-                               conv_workspace_bytes(*d, plan_conv(*d, partition_cus, res != 0, false))});
+        for (int cus : {partition_cus, planning_cus(partition_cus)})
+            for (int res = 0; res < 2; ++res)
+                *bytes = std::max({*bytes, conv_workspace_bytes(*d, plan_conv(*d, cus, res != 0)),
+                                   conv_workspace_bytes(*d, plan_conv(*d, cus, res != 0, false))});
     return SGPRS_OK;
 }
 
@@ -331,7 +331,7 @@ int sgprs_conv2d_plan(const sgprs_conv_desc_t* d, int partition_cus, int has_res
         *family = 4; *detail = 0;
         return SGPRS_OK;
     }
-    const ConvPlan p = plan_conv(*d, partition_cus, has_residual != 0);
+    const ConvPlan p = plan_conv(*d, planning_cus(partition_cus), has_residual != 0);
     if (p.bm == 0) return fail(SGPRS_ERR_UNSUPPORTED, "no tile shape fits cout %d", d->cout);
     *family = p.kind == 4 ? 0 : p.kind; *detail = p.kind == 4 ? 8 + p.variant : p.variant;
     return SGPRS_OK;

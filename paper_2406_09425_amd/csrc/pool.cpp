@@ -34,7 +34,7 @@ int resolve(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* cus)
 int resolve_launch(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* plan_cus)
 {
     const int rc = resolve(pool, partition, stream, plan_cus);
-    if (!rc) *plan_cus = planning_cus(*plan_cus);
+    if (!rc) *plan_cus = pool->parts[partition].plan_cus;
     return rc;
 }
 
@@ -68,8 +68,9 @@ static int device_cus(int device, int* total)
     return SGPRS_OK;
 }
 
+// dealt: the masks are the interleaved ones of sgprs_build_cu_mask, for which planning_cus() was measured
 static int make_pool(int device, int total, const std::vector<std::vector<uint32_t>>& masks,
-                     int cus_per_partition, sgprs_pool_t** out)
+                     int cus_per_partition, bool dealt, sgprs_pool_t** out)
 {
     sgprs_pool* p = new (std::nothrow) sgprs_pool;
     if (!p) return fail(SGPRS_ERR_OOM, "out of host memory");
@@ -84,6 +85,7 @@ static int make_pool(int device, int total, const std::vector<std::vector<uint32
         Partition part;
         part.mask = masks[i];
         part.cus = popcount_mask(part.mask);
+        part.plan_cus = dealt ? planning_cus(part.cus) : part.cus;
         e = hipExtStreamCreateWithCUMask(&part.stream, (uint32_t)part.mask.size(), part.mask.data());
         if (e == hipSuccess) p->parts.push_back(part);
     }
@@ -168,7 +170,7 @@ int sgprs_pool_create(int device, int n_p, int cus, unsigned flags, sgprs_pool_t
                                  masks[p].data(), n_words);
         if (rc) return rc;
     }
-    return make_pool(device, total, masks, cus, out);
+    return make_pool(device, total, masks, cus, !(flags & SGPRS_POOL_BLOCKED_LAYOUT), out);
 }
 
 int sgprs_pool_create_masks(int device, int n_p, const uint32_t* masks, int words_per_mask,
@@ -207,7 +209,7 @@ int sgprs_pool_create_masks(int device, int n_p, const uint32_t* masks, int word
                             p, x, x, x + n_xcd, n_xcd);
         }
     }
-    return make_pool(device, total, m, 0, out);
+    return make_pool(device, total, m, 0, false, out);
 }
 
 int sgprs_pool_destroy(sgprs_pool_t* pool)

@@ -185,3 +185,14 @@ def test_conv_plan_query_and_row_streaming_eligibility():
     assert plan(64, 256) == (3, 7)
     with pytest.raises(S.SgprsError):
         S.sgprs_conv2d_plan(S.ConvDesc(1, 56, 56, 64, 64, 3, 3, 1, 1, S.SGPRS_BF16, 1), 0, False)
+
+
+def test_workspace_covers_both_cu_counts_a_launch_may_be_planned_for():
+    """Launches are planned for a multiple of 32 CUs on default partitions and for all CUs on others:
+    the workspace of an odd size is at least that of the multiple of 32 below it."""
+    for n, h, c in [(1, 14, 256), (3, 7, 512), (2, 28, 128), (16, 14, 256)]:
+        for dtype in (S.SGPRS_F32, S.SGPRS_BF16):
+            d = S.ConvDesc(n, h, h, c, c, 3, 3, 1, 1, dtype, 1)
+            for cus in (40, 56, 104, 200, 248):
+                assert S.sgprs_conv2d_workspace(d, cus) >= S.sgprs_conv2d_workspace(d, cus // 32 * 32)
+            assert S.sgprs_conv2d_plan(d, 56) == S.sgprs_conv2d_plan(d, 32)

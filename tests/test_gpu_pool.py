@@ -53,6 +53,28 @@ def test_partition_cus_is_the_mask_and_every_cu_is_probed(cus):
     pool.destroy()
 
 
+@pytest.mark.parametrize("kind,fused", [("default", True), ("blocked", False), ("masks", False)])
+def test_only_the_default_layout_is_planned_for_a_multiple_of_32(kind, fused):
+    """Four fp32 images are 224 tiles of stage 0, which runs as one fused kernel (kind 9) where every CU
+    it is planned for gets one: 224 on a default partition of 248 CUs, all 248 with other masks."""
+    from workloads import BN_EPS, make_resnet18_params
+    cus = 248
+    base = S.Pool(1, cus)
+    pool = dict(default=lambda: base, blocked=lambda: S.Pool(1, cus, S.SGPRS_POOL_BLOCKED_LAYOUT),
+                masks=lambda: S.Pool(1, 0, masks=base.mask(0)[None, :]))[kind]()
+    task = S.Task(make_resnet18_params(1, 0), S.SGPRS_F32, 4, BN_EPS)
+    x = torch.zeros((4, 224, 224, 3), device="cuda")
+    o = torch.empty((4, 56, 56, 64), device="cuda")
+    torch.cuda.synchronize()
+    task.set_profiling(True)
+    task.stage_run(0, 4, x.data_ptr(), o.data_ptr(), pool, 0)
+    pool.sync()
+    assert ([r["kind"] for r in task.kernel_times(0)] == [9]) == fused
+    task.destroy()
+    for p in {pool, base}:
+        p.destroy()
+
+
 def test_oversubscription_needs_flag():
     total = S.Pool(1, 8).info()["total_cus"]
     with pytest.raises(S.SgprsError) as e:
