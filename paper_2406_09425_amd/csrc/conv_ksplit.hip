@@ -19,7 +19,7 @@
 // Measured in a chain of launches (us each, launch included; before: implicit GEMM with split-K
 // over workgroups, or the LDS-patch kernel), bf16, one image on 256 CUs: 56x56x64 3.6 (5.8),
 // 28x28x128 3.7 (7.4), 14x14x256 3.8 (9.9), 7x7x512 5.0 (11.3), 28x28x128 -> 256/2 3.4 (10.1); fp32
-// 5.7 / 5.4 / 5.7 / 8.7 (10.2 / 11.4 / 13.1 / 14.8), and at 16 images 37 / 36 / 34 for the last three
+// with a residual 6.3 / 5.7 / 6.1 / 9.0 (10.2 / 11.4 / 13.1 / 14.8), and at 16 images 40 / 38 / 40 for the last three
 // (50 with split-K; 27 at the fp32 matrix rate with the 12 % idle CUs of their tile counts).  An empty kernel in such a chain takes 1.8.
 //
 // Small tiles trade traffic for parallelism, so this kernel is for launches
@@ -90,7 +90,12 @@ template <class F, int... I> __device__ __forceinline__ void for_each_stage(F f,
 }
 
 // One tile of 16*TM pixels x 16*TN channels: pixel tile mt, channel tile nt.
-template <int DT, int TM, int TN, int NS>
+// SETS accumulator sets: the error of a sum grows with the square root of the length of its chains
+// (each product is added and rounded in turn), so fp32 keeps the halves of a k-tile apart, and with
+// SETS = 4 even and odd k-tiles too; the sets are added at the end (relative to 64 bits, one image,
+// 14x14x256 and 7x7x512: 3.0e-7 each with 2 and 4 sets, 4.2e-7 and 5.8e-7 with one, 3.0e-7 and 3.1e-7
+// for the implicit GEMM with K split over workgroups).
+template <int DT, int TM, int TN, int NS, int SETS>
 __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
 {
     constexpr int NW = kKsplitWaves;
@@ -206,11 +211,13 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
         next_channel_tile();
     }
 
-    f32x4_t acc[TM][TN];
+    f32x4_t acc[SETS][TM][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int s = 0; s < SETS; ++s)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[s][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     const int frow = lane & 15, fgrp = lane >> 4;
     const unsigned f_off = (unsigned)(frow * 128 + ((fgrp ^ (frow & 7)) << 4));  // second half of the k-tile: chunk + 4, i.e. bit 6 flipped
@@ -222,13 +229,13 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
         f.w[j] = *(const u32x4_t*)(ring + slot * STAGE + (BM + j * 16) * 128 + (f_off ^ (ks << 6)));
     };
     constexpr int HALF = TM * TN * (DT == SGPRS_BF16 ? 1 : 4);  // MFMAs of half a k-tile
-    auto mfma = [&](const Fragments& f, int m) {
+    auto mfma = [&](const Fragments& f, int m, int set) {
         const int u = m / (TM * TN), i = m % (TM * TN) / TN, j = m % TN;
+        f32x4_t& c = acc[set % SETS][i][j];
         if constexpr (DT == SGPRS_BF16)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f.w[j]), __builtin_bit_cast(bf16x8_t, f.px[i]),
-                                                                acc[i][j], 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f.w[j]), __builtin_bit_cast(bf16x8_t, f.px[i]), c, 0, 0, 0);
         else
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(f.w[j][u]), __uint_as_float(f.px[i][u]), acc[i][j], 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(f.w[j][u]), __uint_as_float(f.px[i][u]), c, 0, 0, 0);
     };
     if (at_once) {
         // k-tile st has landed once only the pixel rows of the later ones are outstanding
@@ -243,7 +250,7 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
 #pragma unroll
                     for (int j = 0; j < TN; ++j) read_w(f, st, ks, j);
 #pragma unroll
-                    for (int m = 0; m < HALF; ++m) mfma(f, m);
+                    for (int m = 0; m < HALF; ++m) mfma(f, m, 2 * (st & 1) + ks);
                 }
             }
         }, std::make_integer_sequence<int, NS>());
@@ -269,7 +276,7 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                for (int m = 0; m < HALF; ++m) mfma(f[ks], m);
+                for (int m = 0; m < HALF; ++m) mfma(f[ks], m, 0);
             next_channel_tile();
             if (++st == NS) st = 0;
         }
@@ -291,30 +298,33 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
         // copies them back (30-50 moves per k-tile, each waiting for its MFMA: 36 instead of 31 us for
         // fp32 14x14x256 at 16 images).  The hazard recogniser does not see into the assembly: the
         // operands come from LDS reads, the first accumulators and the epilogue are fenced by s_nop.
-        auto mfma_tied = [&](const Fragments& f, int m) {
+        auto mfma_tied = [&](const Fragments& f, int m, int set) {
 #if __HIP_DEVICE_COMPILE__
             const int u = m / (TM * TN), i = m % (TM * TN) / TN, j = m % TN;
+            f32x4_t& c = acc[set % SETS][i][j];
             if constexpr (DT == SGPRS_BF16)
-                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(f.w[j]), "v"(f.px[i]));
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(f.w[j]), "v"(f.px[i]));
             else
-                asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(f.w[j][u]), "v"(f.px[i][u]));
+                asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(c) : "v"(f.w[j][u]), "v"(f.px[i][u]));
 #endif
         };
         auto pin_accumulators = [&]() {  // writes above and reads below stay there
 #if __HIP_DEVICE_COMPILE__
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int s = 0; s < SETS; ++s)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[s][i][j]));
 #endif
         };
-        auto step = [&](int t, Fragments (&cur)[2], Fragments (&nxt)[2]) {
+        auto step = [&](int t, auto odd, Fragments (&cur)[2], Fragments (&nxt)[2]) {
             constexpr int READS = 2 * (TM + TN);
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the stage may be overwritten
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int m = 0; m < HALF; ++m) {
-                mfma_tied(cur[0], m);
+                mfma_tied(cur[0], m, 2 * odd);
 #pragma unroll
                 for (int k = m * LPS / HALF; k < (m + 1) * LPS / HALF; ++k) {
                     if (k < B_IT) request_w(t + NS, st, k);
@@ -327,7 +337,7 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
             wait_vmcnt<(NS - 1) * LPS>();
 #pragma unroll
             for (int m = 0; m < HALF; ++m) {
-                mfma_tied(cur[1], m);
+                mfma_tied(cur[1], m, 2 * odd + 1);
 #pragma unroll
                 for (int k = m * READS / HALF; k < (m + 1) * READS / HALF; ++k) {
                     const int ks = k / (TM + TN), q = k % (TM + TN);
@@ -342,8 +352,8 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
         asm volatile("s_nop 7");
 #endif
         for (int t = 0; t < nkt; t += 2) {
-            step(t, f[0], f[1]);
-            if (t + 1 < nkt) step(t + 1, f[1], f[0]);
+            step(t, std::integral_constant<int, 0>(), f[0], f[1]);
+            if (t + 1 < nkt) step(t + 1, std::integral_constant<int, 1>(), f[1], f[0]);
         }
 #if __HIP_DEVICE_COMPILE__
         asm volatile("s_nop 15\n\ts_nop 15");
@@ -358,7 +368,12 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
 #pragma unroll
     for (int ti = 0; ti < TM; ++ti)
 #pragma unroll
-        for (int tj = 0; tj < TN; ++tj) *(f32x4_t*)(part + (ti * 16 + frow) * SROW + tj * 16 + fgrp * 4) = acc[ti][tj];
+        for (int tj = 0; tj < TN; ++tj) {
+            f32x4_t c = acc[0][ti][tj];
+            if constexpr (SETS == 2) c += acc[1][ti][tj];
+            if constexpr (SETS == 4) c = (c + acc[1][ti][tj]) + (acc[2][ti][tj] + acc[3][ti][tj]);
+            *(f32x4_t*)(part + (ti * 16 + frow) * SROW + tj * 16 + fgrp * 4) = c;
+        }
     __syncthreads();
     const unsigned relu_floor = a.relu ? kReluFloor : kNoReluFloor;
 #pragma unroll
@@ -404,7 +419,7 @@ __device__ __forceinline__ bool ks_place(const KsplitArgs& a, int b, int* mt, in
 // the same input and have the same output shape, share a launch.  The arguments are read as one
 // batch of scalar loads from the kernel-argument segment: left to itself the compiler loads them
 // piecemeal where they are used, a chain of scalar-cache misses before the first request.
-template <int DT, int TM, int TN, int NS>
+template <int DT, int TM, int TN, int NS, int SETS>
 __global__ __launch_bounds__(kKsplitWaves * 64) void conv_ksplit_kernel(const KsplitLaunch launch)
 {
     KsplitArgs a;
@@ -423,31 +438,32 @@ __global__ __launch_bounds__(kKsplitWaves * 64) void conv_ksplit_kernel(const Ks
     a = launch.p[0];
 #endif
     int mt, nt;
-    if (ks_place(a, blockIdx.x, &mt, &nt)) ksplit_tile<DT, TM, TN, NS>(a, mt, nt);
+    if (ks_place(a, blockIdx.x, &mt, &nt)) ksplit_tile<DT, TM, TN, NS, SETS>(a, mt, nt);
 }
 
-// Name as a profiler prints it: v = tile variant + 16 * dtype.
+// Name as a profiler prints it: v = tile variant + 16 * dtype, + 32 for four accumulator sets.
 const char* ksplit_variant_name(int v)
 {
     static char buf[8][96];
     static int next = 0;
-    if (v < 0 || (v & 15) >= kKsplitVariants || v >= 32) return "?";
+    if (v < 0 || (v & 15) >= kKsplitVariants || v >= 64) return "?";
     const int* t = kKsplitShape[v & 15];
     char* out = buf[next++ & 7];
-    snprintf(out, 96, "conv_ksplit_kernel<%d, %d, %d, %d>", v >> 4, t[0], t[1], t[2]);
+    const int dtype = v >> 4 & 1;
+    snprintf(out, 96, "conv_ksplit_kernel<%d, %d, %d, %d, %d>", dtype, t[0], t[1], t[2], v >= 32 ? 4 : dtype == SGPRS_BF16 ? 1 : 2);
     return out;
 }
 
-template <int DT, int TM, int TN, int NS>
+template <int DT, int TM, int TN, int NS, int SETS>
 static int launch_ks(const KsplitLaunch& l, int slots, int problems, hipStream_t stream)
 {
     constexpr int lds = kKsplitWaves * NS * (TM + TN) * 16 * 128;
     static std::atomic<bool> raised{false};
     if (!raised) {
-        SGPRS_HIP(hipFuncSetAttribute((const void*)conv_ksplit_kernel<DT, TM, TN, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        SGPRS_HIP(hipFuncSetAttribute((const void*)conv_ksplit_kernel<DT, TM, TN, NS, SETS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         raised = true;
     }
-    SGPRS_LAUNCH((conv_ksplit_kernel<DT, TM, TN, NS>), dim3(slots, problems), dim3(kKsplitWaves * 64), lds, stream, l);
+    SGPRS_LAUNCH((conv_ksplit_kernel<DT, TM, TN, NS, SETS>), dim3(slots, problems), dim3(kKsplitWaves * 64), lds, stream, l);
     SGPRS_HIP(hipGetLastError());
     return SGPRS_OK;
 }
@@ -462,9 +478,12 @@ static void div_constants(int d, unsigned* mul, int* sh)
     *sh = L;
 }
 
+// fp32 up to 768 input channels: beyond, even four accumulator sets leave chains whose error is larger
+// than split-K's over workgroups (relative to 64 bits, 7x7 3x3 convolution: 768 channels 3.5e-7 against
+// 3.7e-7, 1024 channels 4.1e-7 against 3.2e-7).
 bool ksplit_fits(const sgprs_conv_desc_t& d, int v)
 {
-    return is_igemm(d) && v >= 0 && v < kKsplitVariants && d.cout % (16 * kKsplitShape[v][1]) == 0;
+    return is_igemm(d) && (d.dtype == SGPRS_BF16 || d.cin <= 768) && v >= 0 && v < kKsplitVariants && d.cout % (16 * kKsplitShape[v][1]) == 0;
 }
 
 // Estimated time (microseconds) of a tile shape: launch, then rounds of workgroups, each a fixed
@@ -562,12 +581,16 @@ int launch_conv_ksplit(const sgprs_conv_desc_t& d, int variant, const void* x, c
         flops += 2.0 * a1.M * d1->cout * (double)d1->r * d1->s * d1->cin;
         bytes += ((double)d1->cout * d1->r * d1->s * d1->cin + (double)a1.M * d1->cout) * es;
     }
-    if (prof && prof->on && (rc = prof->begin(stream, d1 ? kKindIgemmPair : kKindIgemm, kKsplitNames + d.dtype * 16 + variant, flops, bytes))) return rc;
+    // two sets hold a chain to 288 products up to K = 2304, four up to 4608; split-K gave deep 1x1
+    // convolutions shorter chains still (768 channels: 1.85e-7, with two sets here 1.86e-7)
+    const int key = d.dtype * 16 + variant + (d.dtype == SGPRS_F32 && (a0.ktiles > 72 || (d.r == 1 && d.cin > 512)) ? 32 : 0);
+    if (prof && prof->on && (rc = prof->begin(stream, d1 ? kKindIgemmPair : kKindIgemm, kKsplitNames + key, flops, bytes))) return rc;
     const int slots = a0.die_tiles * 8;  // a multiple of 8 either way
-    switch (d.dtype * 16 + variant) {
-#define X(v, tm, tn, ns)                                                                         \
-        case v: rc = launch_ks<SGPRS_F32, tm, tn, ns>(l, slots, d1 ? 2 : 1, stream); break;      \
-        case 16 + v: rc = launch_ks<SGPRS_BF16, tm, tn, ns>(l, slots, d1 ? 2 : 1, stream); break;
+    switch (key) {
+#define X(v, tm, tn, ns)                                                                          \
+        case v: rc = launch_ks<SGPRS_F32, tm, tn, ns, 2>(l, slots, d1 ? 2 : 1, stream); break;      \
+        case 32 + v: rc = launch_ks<SGPRS_F32, tm, tn, ns, 4>(l, slots, d1 ? 2 : 1, stream); break; \
+        case 16 + v: rc = launch_ks<SGPRS_BF16, tm, tn, ns, 1>(l, slots, d1 ? 2 : 1, stream); break;
         SGPRS_KSPLIT_VARIANTS(X)
 #undef X
     }

@@ -295,7 +295,7 @@ bool plan_ksplit(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost
 int ksplit_num_variants();
 double ksplit_cost(const sgprs_conv_desc_t& d, int variant, int cus, const sgprs_conv_desc_t* d1);
 const char* ksplit_variant_name(int v);
-constexpr int kKsplitNames = 32;  // launches of this kernel are recorded as implicit GEMM (or pair), variant 32 + 16 * dtype + tile
+constexpr int kKsplitNames = 32;  // launches of this kernel are recorded as implicit GEMM (or pair), variant 32 + 16 * dtype + tile (+ 32: four accumulator sets)
 bool ksplit_fits(const sgprs_conv_desc_t& d, int variant);
 int launch_conv_ksplit(const sgprs_conv_desc_t& d, int variant, const void* x, const void* w, const float* scale, const float* shift,
                        const void* res, void* y, const sgprs_conv_desc_t* d1, const void* w1, const float* scale1,

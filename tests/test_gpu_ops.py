@@ -484,6 +484,23 @@ def test_conv_ksplit_tiles_parity(pools, dtype, variant):
         S.sgprs_conv_tuning_override(-1, 0, 1)
 
 
+@pytest.mark.parametrize("variant", range(8))
+@pytest.mark.parametrize("shape", [(1, 7, 7, 512, 512, 3, 1, 1), (1, 14, 14, 256, 256, 3, 1, 1), (1, 14, 14, 768, 64, 1, 1, 0)], ids=str)
+def test_conv_ksplit_f32_keeps_its_chains_short(pools, variant, shape):
+    """fp32 sums are kept in chains of at most 288 products (64 for the 1x1): each step adds a rounding error
+    of about 2^-24 / sqrt(6) of the running sum, sqrt(288 / 2) of them in the root mean square, plus the partial
+    sums' and the epilogue's roundings.  A single chain per wavefront (1152, 576 or 192 products) is past the line."""
+    n, h, w, cin, cout, k, stride, pad = shape
+    pool, chain = pools["full"], 64 if k == 1 else 288
+    try:
+        S.sgprs_conv_tuning_override(2, 8 + variant, 0)
+        got, ref = conv_case(S.SGPRS_F32, *shape, relu=False, with_res=False, seed=160, pool=pool, cus=pool.partition_cus(0))
+    finally:
+        S.sgprs_conv_tuning_override(-1, 0, 1)
+    e = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert e <= 2.0 ** -24 / 6.0 ** 0.5 * (chain / 2 + 20) ** 0.5, e
+
+
 @pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
 @pytest.mark.parametrize("n,cin,cout,cus", [(32, 512, 36, 8), (70, 1024, 100, 8), (129, 2048, 36, "full"), (65, 512, 1000, 64)], ids=str)
 def test_fc_gemm_tiles_parity(pools, dtype, n, cin, cout, cus):
