@@ -327,8 +327,10 @@ def _address(handle):
 
 def sgprs_conv2d(desc: ConvDesc, x: int, w_packed: int, scale: int, shift: int, residual: int | None, y: int,
                  workspace: int | None, workspace_bytes: int, pool, partition: int) -> None:
-    rc = (_native or _calls()).conv2d(ctypes.addressof(desc), x, w_packed, scale, shift, residual, y, workspace, workspace_bytes,
-                                      pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
+    rc = None
+    if desc.__class__ is ConvDesc:  # an address carries no type: whatever else it is, ctypes checks it
+        rc = (_native or _calls()).conv2d(ctypes.addressof(desc), x, w_packed, scale, shift, residual, y, workspace, workspace_bytes,
+                                          pool.address if pool.__class__ is Pool else _address(_h(pool)), partition)
     if rc is None:
         rc = lib().sgprs_conv2d(ctypes.byref(desc), x, w_packed, scale, shift, residual, y, workspace, workspace_bytes,
                                 _h(pool), partition)
