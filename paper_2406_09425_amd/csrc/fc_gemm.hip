@@ -37,11 +37,11 @@ __device__ __forceinline__ void split_bf16(const u32x4_t a, const u32x4_t b, u32
 
 // 16*TM images x 16*TN outputs per workgroup; k-tiles of 32 inputs, ring of NS stages per wavefront.
 // cin is a multiple of 512 and cout of 4 (checked by the launcher); images and outputs past the end
-// read zeros (buffer bounds) and are not stored.
+// read zeros (the buffers are the tile's own rows, so operands of any size are addressed with 32-bit
+// offsets) and are not stored.
 template <int DT, int TM, int TN, int NS>
 __global__ __launch_bounds__(256) void fc_gemm_kernel(const float* __restrict__ v, const unsigned char* __restrict__ w,
-                                                      const float* __restrict__ bias, float* __restrict__ y, int nimg, int cin, int cout,
-                                                      unsigned v_bytes, unsigned w_bytes)
+                                                      const float* __restrict__ bias, float* __restrict__ y, int nimg, int cin, int cout)
 {
     constexpr int BM = 16 * TM, BN = 16 * TN, WROW = DT == SGPRS_BF16 ? 64 : 128;
     constexpr int A_IT = BM / 8, B_IT = BN * WROW / 1024, LPS = A_IT + B_IT;
@@ -57,15 +57,18 @@ __global__ __launch_bounds__(256) void fc_gemm_kernel(const float* __restrict__ 
 
     // LDS slots hold swizzled 16-byte chunks, so that a fragment read meets no bank twice: slot s of a
     // 128-byte row holds chunk s ^ (row & 7), of a 64-byte row chunk s ^ ((row >> 1) & 3).
-    const unsigned v_off = (unsigned)((n0 + (lane >> 3)) * cin * 4 + (((lane & 7) ^ (lane >> 3)) << 4));
-    const unsigned w_off = DT == SGPRS_BF16 ? (unsigned)((o0 + (lane >> 2)) * cin * 2 + (((lane & 3) ^ ((lane >> 3) & 3)) << 4))
-                                            : (unsigned)((o0 + (lane >> 3)) * cin * 4 + (((lane & 7) ^ (lane >> 3)) << 4));
+    const unsigned v_off = (unsigned)((lane >> 3) * cin * 4 + (((lane & 7) ^ (lane >> 3)) << 4));
+    const unsigned w_off = DT == SGPRS_BF16 ? (unsigned)((lane >> 2) * cin * 2 + (((lane & 3) ^ ((lane >> 3) & 3)) << 4))
+                                            : (unsigned)((lane >> 3) * cin * 4 + (((lane & 7) ^ (lane >> 3)) << 4));
+    const float* v_rows = v + (size_t)n0 * cin;
+    const unsigned char* w_rows = w + (size_t)o0 * cin * (WROW / 32);
+    const int v_bytes = min(BM, nimg - n0) * cin * 4, w_bytes = min(BN, cout - o0) * cin * (WROW / 32);
     auto request = [&](int t, int slot) {
 #if __HIP_DEVICE_COMPILE__  // the buffer-resource builtins exist in the device pass only
         typedef __attribute__((address_space(3))) void* lds_ptr_t;
         const bool live = t < nkt;  // past the share: descriptors of size 0, the count of requests stays
-        const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc((void*)w, 0, live ? (int)w_bytes : 0, 0x00020000);
-        const __amdgpu_buffer_rsrc_t v_rs = __builtin_amdgcn_make_buffer_rsrc((void*)v, 0, live ? (int)v_bytes : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc((void*)w_rows, 0, live ? w_bytes : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t v_rs = __builtin_amdgcn_make_buffer_rsrc((void*)v_rows, 0, live ? v_bytes : 0, 0x00020000);
         unsigned char* st = ring + slot * STAGE;
 #pragma unroll
         for (int i = 0; i < B_IT; ++i)
@@ -173,8 +176,7 @@ static int launch_tile(const float* v, const void* w, const float* bias, float* 
         raised = true;
     }
     const dim3 grid((cout + 16 * TN - 1) / (16 * TN), (n + 16 * TM - 1) / (16 * TM));
-    SGPRS_LAUNCH((fc_gemm_kernel<DT, TM, TN, NS>), grid, dim3(256), lds, stream, v, (const unsigned char*)w, bias, y, n, cin, cout,
-                 (unsigned)((size_t)n * cin * 4), (unsigned)((size_t)cout * cin * dtype_size(DT)));
+    SGPRS_LAUNCH((fc_gemm_kernel<DT, TM, TN, NS>), grid, dim3(256), lds, stream, v, (const unsigned char*)w, bias, y, n, cin, cout);
     SGPRS_HIP(hipGetLastError());
     return SGPRS_OK;
 }
@@ -182,7 +184,7 @@ static int launch_tile(const float* v, const void* w, const float* bias, float* 
 bool fc_gemm_applicable(int n, int cin, int cout)
 {
     // fewer images leave most of a tile's columns empty, and their logits match the one-launch kernel's bit for bit
-    return n >= 32 && cin % 512 == 0 && cout % 4 == 0 && (long long)n * cin * 4 < (1ll << 31) && (long long)cout * cin * 4 < (1ll << 31);
+    return n >= 32 && cin % 512 == 0 && cout % 4 == 0;
 }
 
 // 64x64 tiles halve the traffic of 32x32 ones; they need enough images to occupy the partition.

@@ -33,6 +33,11 @@ def pools():
         p.destroy()
 
 
+def fc_gemm_applicable(n, cin, cout):
+    """Whether the FC of n images takes the tiled kernel: the library's own rule."""
+    return bool(getattr(S.lib(), "_ZN5sgprs18fc_gemm_applicableEiii")(n, cin, cout) & 1)
+
+
 def conv_case(dtype, n, h, w, cin, cout, k, stride, pad, relu, with_res, seed, pool, cus, absx=False):
     bf = dtype == S.SGPRS_BF16
     x = make_input(90, seed, (n, cin, h, w), "absnormal" if absx else "normal", bf16=bf)
@@ -524,3 +529,28 @@ def test_fc_gemm_tiles_parity(pools, dtype, n, cin, cout, cus):
     got = lg.cpu().numpy().astype(np.float64)
     assert np.all(np.isnan(got[n]))    # nothing is written past the last image
     assert rel_err(got[:n], ref) <= (2e-5 if bf else 4e-6)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
+def test_fc_gemm_weights_beyond_two_gib(pools, dtype):
+    """More than 2^31 bytes of weights: the first and last outputs and those around byte 2^31, against fp64
+    (bf16: pooled values to 2^-17; fp32: sums of 2048 products)."""
+    n, cin = 33, 2048
+    es = 2 if dtype == S.SGPRS_BF16 else 4
+    mid = (1 << 31) // (cin * es)
+    cout = mid + 132
+    assert fc_gemm_applicable(n, cin, cout)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = torch.randn((n, 1, cin), generator=g, device="cuda").to(torch.bfloat16 if es == 2 else torch.float32)
+    w = torch.empty((cout, cin), device="cuda", dtype=x.dtype).normal_(generator=g)
+    ws = torch.empty(n * cin, device="cuda")
+    lg = torch.full((n, cout), float("nan"), device="cuda")
+    pool = pools["full"]
+    torch.cuda.synchronize()
+    S.sgprs_avgpool_fc(dtype, n, 1, cin, cout, x.data_ptr(), w.data_ptr(), None, lg.data_ptr(), ws.data_ptr(), pool, 0)
+    pool.sync()
+    assert bool(torch.isfinite(lg).all())
+    rows = [0, 1, 65, mid - 1, mid, mid + 1, cout - 2, cout - 1]
+    ref = x[:, 0].double().cpu().numpy() @ w[rows].double().cpu().numpy().T
+    assert rel_err(lg[:, rows].double().cpu().numpy(), ref) <= (2e-5 if es == 2 else 4e-6)
