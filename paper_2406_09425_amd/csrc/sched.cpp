@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "static_turns.h"
 
 namespace {
 
@@ -460,7 +461,7 @@ int sgprs_sched_run_periodic(sgprs_sched_t* s, sgprs_pool_t* pool, sgprs_task_t*
 }
 
 // Static (purely spatial) execution: every task keeps the partition it is given; the calling thread
-// hands out whole inferences and polls one event per task, with the same gate on busy partitions.
+// hands out whole inferences and polls one event per inference, with the same gate on busy partitions.
 int sgprs_pool_run_static(sgprs_pool_t* pool, sgprs_task_t* const* tasks, int n_tasks, const void* const* inputs,
                           float* const* logits, int batch, const int* partition_of_task, int rounds, int max_busy,
                           double* elapsed_s)
@@ -473,26 +474,17 @@ int sgprs_pool_run_static(sgprs_pool_t* pool, sgprs_task_t* const* tasks, int n_
         if (!tasks[i] || !inputs[i] || !logits[i]) return fail(SGPRS_ERR_INVALID_ARG, "task %d: NULL handle or buffer", i);
         if (partition_of_task[i] < 0 || partition_of_task[i] >= n_p) return fail(SGPRS_ERR_INVALID_ARG, "task %d: partition %d outside the pool", i, partition_of_task[i]);
     }
-    // Partitions p and p + 4 of a pool share a dispatch pipe (kDispatchPipes): with a gate of up to
-    // that many, no two busy partitions may share one.
-    const bool per_pipe = max_busy > 0 && max_busy <= kDispatchPipes;
-    // A partition's turn: while it is active, up to kStaticDepth inferences are queued on its stream, so
-    // the next one starts without a host round trip behind the one before (with one at a time, the
-    // event poll and the launch lay between them: eight tasks on 8 x 32 CUs, four busy, 68 us per
-    // inference against 37).  After kStaticTurn inferences it makes room if others are waiting.
-    constexpr int kStaticDepth = 2, kStaticTurn = 8;
     struct Part {
-        std::vector<int> tasks;              // tasks pinned here, served in turn
+        std::vector<int> tasks;  // tasks pinned here, served in turn
         size_t next = 0;
-        long long left = 0;                  // inferences not yet launched
-        int queued = 0, head = 0, turn = 0;  // in flight, oldest slot, launches left in this turn
+        int head = 0;            // oldest event in flight
         hipEvent_t ev[kStaticDepth] = {};
-        bool active = false;
     };
     std::vector<Part> parts(n_p);
+    std::vector<long long> left(n_p, 0);
     for (int i = 0; i < n_tasks; ++i) {
         parts[partition_of_task[i]].tasks.push_back(i);
-        parts[partition_of_task[i]].left += rounds;
+        left[partition_of_task[i]] += rounds;
     }
     auto cleanup = [&]() {
         for (Part& q : parts)
@@ -506,59 +498,35 @@ int sgprs_pool_run_static(sgprs_pool_t* pool, sgprs_task_t* const* tasks, int n_
                 cleanup();
                 return fail(SGPRS_ERR_HIP, "hipEventCreateWithFlags failed");
             }
-    std::vector<int> active;
-    std::vector<int> pipe_busy(kDispatchPipes, 0), pipe_waiting(kDispatchPipes, 0);
-    int waiting = 0, status = SGPRS_OK, next = 0;
-    for (int p = 0; p < n_p; ++p)
-        if (!parts[p].tasks.empty()) ++waiting, ++pipe_waiting[p % kDispatchPipes];
+    StaticTurns turns(left, max_busy, kDispatchPipes);
+    int status = SGPRS_OK;
     const auto t0 = std::chrono::steady_clock::now();
-    while ((waiting || !active.empty()) && !status) {
-        // partitions take their turns round-robin
-        for (int k = 0; k < n_p && waiting && (max_busy == 0 || (int)active.size() < max_busy); ++k) {
-            const int p = (next + k) % n_p, pipe = p % kDispatchPipes;
+    while (!turns.finished() && !status) {
+        turns.admit();
+        for (size_t a = 0; a < turns.active().size() && !status;) {
+            const int p = turns.active()[a];
             Part& q = parts[p];
-            if (q.active || !q.left || (per_pipe && pipe_busy[pipe])) continue;
-            q.active = true;
-            q.turn = kStaticTurn;
-            active.push_back(p);
-            ++pipe_busy[pipe];
-            --waiting, --pipe_waiting[pipe];
-            next = (p + 1) % n_p;
-            k = -1;
-        }
-        for (size_t a = 0; a < active.size() && !status;) {
-            const int p = active[a], pipe = p % kDispatchPipes;
-            Part& q = parts[p];
-            if (!(per_pipe ? pipe_waiting[pipe] : waiting)) q.turn = kStaticTurn;  // nobody to make room for
             // one launch per visit: the partitions start together, then each gets its second
-            if (q.queued < kStaticDepth && q.left && q.turn) {
+            if (turns.may_launch(p)) {
                 const int i = q.tasks[q.next];
                 if ((status = sgprs_task_run(tasks[i], batch, inputs[i], logits[i], pool, p, nullptr))) break;
-                if (hipEventRecord(q.ev[(q.head + q.queued) % kStaticDepth], (hipStream_t)sgprs_pool_stream(pool, p)) != hipSuccess)
+                if (hipEventRecord(q.ev[(q.head + turns.queued(p)) % kStaticDepth], (hipStream_t)sgprs_pool_stream(pool, p)) != hipSuccess) {
                     status = fail(SGPRS_ERR_HIP, "hipEventRecord failed");
+                    break;
+                }
                 q.next = (q.next + 1) % q.tasks.size();
-                ++q.queued;
-                --q.left;
-                --q.turn;
+                turns.launched(p);
             }
-            if (status) break;
-            if (q.queued) {
+            if (turns.queued(p)) {
                 const hipError_t e = hipEventQuery(q.ev[q.head]);
                 if (e == hipSuccess) {
                     q.head = (q.head + 1) % kStaticDepth;
-                    --q.queued;
+                    turns.completed(p);
                 } else if (e != hipErrorNotReady) {
                     status = fail(SGPRS_ERR_HIP, "hipEventQuery: %s", hipGetErrorString(e));
                 }
             }
-            if (!q.queued && (!q.left || !q.turn)) {
-                q.active = false;
-                --pipe_busy[pipe];
-                if (q.left) ++waiting, ++pipe_waiting[pipe];
-                active.erase(active.begin() + a);
-            } else {
-                ++a;
-            }
+            if (!turns.release(p)) ++a;
         }
     }
     cleanup();   // (waits for whatever is still queued)

@@ -194,3 +194,33 @@ def test_static_execution_on_eight_partitions_with_the_gate():
         for t in tasks:
             t.destroy()
         pool.destroy()
+
+
+@pytest.mark.parametrize("pinning,gate,rounds", [
+    ([0, 1, 2, 3], 1, 9), ([0, 1, 2, 3], 2, 20), ([0, 1, 2, 3], 3, 20), ([0, 4], 2, 20), ([0, 0, 4, 1, 1], 3, 11),
+], ids=["gate1", "gate2", "gate3", "one-pipe", "shared-partitions"])
+def test_static_execution_hands_places_over(pinning, gate, rounds):
+    """More inferences than one turn and fewer places than partitions: turns end and begin again, partitions
+    0 and 4 of a pool (one dispatch pipe) relieve each other, tasks that share a partition alternate.  Every
+    task's logits are those of its own inference alone (the order of turns is checked without a GPU)."""
+    pool = S.Pool(5, 32)
+    params = [make_resnet18_params(3, i % 2, bf16=True) for i in range(len(pinning))]
+    tasks = [S.Task(p, S.SGPRS_BF16, 1, BN_EPS) for p in params]
+    xs = [dev_nhwc(make_input(3, i, (1, 3, 224, 224), bf16=True), S.SGPRS_BF16) for i in range(len(pinning))]
+    try:
+        want = []
+        for t, x, p in zip(tasks, xs, pinning):
+            o = torch.full((1, 1000), float("nan"), dtype=torch.float32, device="cuda")
+            torch.cuda.synchronize()
+            t.run(1, x.data_ptr(), o.data_ptr(), pool, p)
+            pool.sync()
+            want.append(o.clone())
+        for _ in range(2):
+            lgs = [torch.full((1, 1000), float("nan"), dtype=torch.float32, device="cuda") for _ in pinning]
+            torch.cuda.synchronize()
+            pool.run_static(tasks, [x.data_ptr() for x in xs], [l.data_ptr() for l in lgs], 1, pinning, rounds, gate)
+            assert all(torch.equal(a, b) for a, b in zip(lgs, want))
+    finally:
+        for t in tasks:
+            t.destroy()
+        pool.destroy()
