@@ -2,6 +2,8 @@
 benchmark configurations: the single layer1 block (fp32), the full ResNet18 at
 batch 1 (fp32, six stages), eight concurrent bf16 instances on an 8 x 32-CU
 pool, and the batch-64 bf16 forward."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -365,6 +367,7 @@ def test_whole_network_at_other_batch_sizes(full_pool, dtype, n, cus):
     task = S.Task(params, dtype, n, BN_EPS)
     xd = dev_nhwc(x, dtype)
     lg = torch.full((n, 1000), float("nan"), dtype=torch.float32, device="cuda")
+    task.set_graph_replay(1)    # whatever the pool and the batch
     for _ in range(3):      # eager, capture, replay
         task.run(n, xd.data_ptr(), lg.data_ptr(), pool, part)
     pool.sync()
@@ -387,6 +390,7 @@ def test_task_run_graph_replay_matches_eager(full_pool, cfg1):
     params, x, _, _ = cfg1
     for dtype in (S.SGPRS_F32, S.SGPRS_BF16):
         task = S.Task(params, dtype, 1, BN_EPS)
+        task.set_graph_replay(1)    # on a pool of one partition the automatic mode launches kernel by kernel
         xd = dev_nhwc(x, dtype)
         x2 = dev_nhwc(make_input(1, 9, (1, 3, 224, 224)), dtype)
         xin = torch.empty_like(xd)
@@ -409,7 +413,25 @@ def test_task_run_graph_replay_matches_eager(full_pool, cfg1):
             task.run(1, xin.data_ptr(), lg.data_ptr(), full_pool, 0)   # call 1 eager, call 2 captures, then replays
             full_pool.sync()
             assert torch.equal(lg, ref), (dtype, it)
+        # these were replays: one host call, against a launch per kernel (18 and more)
+        replayed = host_us(task, xin, lg, full_pool, 0)
+        task.set_graph_replay(0)
+        assert replayed < host_us(task, xin, lg, full_pool, 0)
         task.destroy()
+
+
+def host_us(task, x, logits, pool, part, others=()):
+    """Least host time of a one-image call out of 30; before each, the calls in `others` are made."""
+    best = 1e9
+    for _ in range(30):
+        for call in others:
+            call()
+        pool.sync()
+        t0 = time.perf_counter()
+        task.run(1, x.data_ptr(), logits.data_ptr(), pool, part)
+        best = min(best, time.perf_counter() - t0)
+        pool.sync()
+    return best * 1e6
 
 
 def test_graph_replay_survives_other_batches_and_partitions(cfg1):
