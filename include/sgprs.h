@@ -321,9 +321,11 @@ const void *sgprs_task_stage_output(const sgprs_task_t *task, int stage);
 int sgprs_task_set_profiling(sgprs_task_t *task, int on);
 /* Graph replay of sgprs_task_run (see there): mode 1 always, 0 never (every
  * call enqueues its kernels one by one), -1 automatic (default): batches of up
- * to 8 images on pools of several partitions.  A replay costs about 5 us of GPU
- * time and saves 30 us of host time: it pays when one host thread feeds several
- * partitions with short inferences.  Graphs already captured are kept. */
+ * to 8 images on pools of several partitions, and on pools of one partition if
+ * one of the calling thread's last 8 task or stage runs used another partition.
+ * A replay costs about 5 us of GPU time and saves 30 us of host time: it pays
+ * when one host thread feeds several partitions with short inferences.  Graphs
+ * already captured are kept. */
 int sgprs_task_set_graph_replay(sgprs_task_t *task, int mode);
 int sgprs_task_kernel_times(sgprs_task_t *task, int stage, int *count, int *kind, int *variant,
                             float *ms, double *flops, double *bytes);

@@ -7,17 +7,22 @@
 #include <cstring>
 #include <new>
 
+#include "fed_streams.h"
 #include "internal.h"
 
 namespace {
 
-// Replaying costs about 5 us of GPU time per launch and saves 30 us of host time (20 against 50): it
-// pays when one host thread feeds several partitions with short inferences, not for one long batch,
-// and not on a pool of one partition, where the launches of the next inference hide behind the
-// running one (batch 1 on 256 CUs 82.5 us replayed, 78.0 launched one by one; batch 8 143.2, 138.3).
+// Replaying costs about 5 us of GPU time per launch and saves 30 us of host time (20 against 50).  It
+// pays for short inferences when the calling thread feeds several partitions, of one pool or of several
+// pools (one image, us per inference: 4 pools of one 64-CU partition 30 replayed, 66 launched kernel by
+// kernel, 2 of 128 CUs 46, 69, two that both span the device 50, 65), and not when it feeds one, where
+// the launches of the next inference hide behind the running one (256 CUs 84 replayed, 80 launched one by
+// one, 32 CUs 133, 128; a thread for each of 4 pools of 64 CUs 30, 29).  A pool of several partitions counts as several.
 constexpr int kReplayMaxBatch = 8;
 
 using namespace sgprs;
+
+thread_local FedStreams t_fed;
 
 // cin, cout, kernel, stride, pad, input height -- forward order
 struct ConvSpec { int cin, cout, k, stride, pad, h; };
@@ -59,7 +64,7 @@ struct sgprs_task {
     bool profiling = false;
     hipEvent_t chain[SGPRS_RESNET18_STAGES] = {};
     // Whole-task launches with the same arguments are captured into a HIP graph the second time
-    // they are seen and replayed from then on (one host call instead of 20-33 kernel launches).
+    // they are seen and replayed from then on (one host call instead of 18-20 kernel launches).
     struct Replay {
         int batch = 0, partition = 0;
         const void* in = nullptr;
@@ -72,7 +77,7 @@ struct sgprs_task {
         hipGraphExec_t exec = nullptr;
     };
     std::vector<Replay> replays;
-    int graph_mode = -1;     // -1: replay batches up to kReplayMaxBatch on pools of several partitions, 0: never, 1: always
+    int graph_mode = -1;     // -1: replay batches up to kReplayMaxBatch where the thread feeds several partitions, 0: never, 1: always
     bool use_graphs = true;  // cleared when a capture fails
 };
 
@@ -368,6 +373,7 @@ int sgprs_stage_run(sgprs_task_t* t, int stage, int batch, const void* in, void*
     if (!in || !out || ((uintptr_t)in & 15) || ((uintptr_t)out & 15) || in == out)
         return fail(SGPRS_ERR_INVALID_ARG, "in and out must be distinct, non-NULL and 16-byte aligned");
     if (pool->device != t->device) return fail(SGPRS_ERR_INVALID_ARG, "pool and task live on different devices");
+    t_fed.only(s);
     return run_stage(t, stage, batch, in, out, s, cus);
 }
 
@@ -387,9 +393,10 @@ int sgprs_task_run(sgprs_task_t* t, int batch, const void* in, float* logits, sg
     // ---- graph replay: one partition, no per-kernel timing ----
     bool one_stream = true;
     for (int j = 1; j < SGPRS_RESNET18_STAGES; ++j) one_stream = one_stream && s[j] == s[0];
+    const bool several = !t_fed.only(one_stream ? s[0] : nullptr) || pool->parts.size() > 1;
     sgprs_task::Replay* rp = nullptr;
     if (t->use_graphs && one_stream && !t->profiling &&
-        (t->graph_mode == 1 || (t->graph_mode < 0 && batch <= kReplayMaxBatch && pool->parts.size() > 1))) {
+        (t->graph_mode == 1 || (t->graph_mode < 0 && batch <= kReplayMaxBatch && several))) {
         // the split-K scratch must neither grow while capturing nor move under a captured graph
         for (int j = 1; j <= 4; ++j) {
             const int first = j == 1 ? 1 : 5 + 5 * (j - 2), last = j == 1 ? 4 : first + 4;

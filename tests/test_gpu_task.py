@@ -390,7 +390,7 @@ def test_task_run_graph_replay_matches_eager(full_pool, cfg1):
     params, x, _, _ = cfg1
     for dtype in (S.SGPRS_F32, S.SGPRS_BF16):
         task = S.Task(params, dtype, 1, BN_EPS)
-        task.set_graph_replay(1)    # on a pool of one partition the automatic mode launches kernel by kernel
+        task.set_graph_replay(1)    # the automatic mode does not replay for a thread that feeds one partition
         xd = dev_nhwc(x, dtype)
         x2 = dev_nhwc(make_input(1, 9, (1, 3, 224, 224)), dtype)
         xin = torch.empty_like(xd)
@@ -432,6 +432,40 @@ def host_us(task, x, logits, pool, part, others=()):
         best = min(best, time.perf_counter() - t0)
         pool.sync()
     return best * 1e6
+
+
+def test_automatic_replay_where_the_thread_feeds_several_partitions(cfg1):
+    """The automatic mode: eager launches while a thread feeds one pool of one partition, replays on a
+    pool of two and on two pools of one that take turns (told apart by the call's host time, against the
+    forced modes); the logits are the same every time."""
+    params, x, _, _ = cfg1
+    dtype = S.SGPRS_BF16
+    a, b, two = S.Pool(1, 64), S.Pool(1, 64), S.Pool(2, 64)
+    xd = dev_nhwc(x, dtype)
+    tasks = [S.Task(params, dtype, 1, BN_EPS) for _ in range(4)]
+    lgs = [torch.full((1, 1000), float("nan"), dtype=torch.float32, device="cuda") for _ in range(4)]
+    torch.cuda.synchronize()
+    try:
+        auto, other, forced, eager = tasks
+        forced.set_graph_replay(1)
+        eager.set_graph_replay(0)
+        t_replay, t_eager = host_us(forced, xd, lgs[2], a, 0), host_us(eager, xd, lgs[3], a, 0)
+        line = (t_replay + t_eager) / 2
+        assert t_replay < t_eager
+        for _ in range(9):                         # from here on the thread feeds one partition
+            eager.run(1, xd.data_ptr(), lgs[3].data_ptr(), a, 0)
+        assert host_us(auto, xd, lgs[0], a, 0) > line
+        turn = [lambda: other.run(1, xd.data_ptr(), lgs[1].data_ptr(), b, 0)]
+        assert host_us(auto, xd, lgs[0], a, 0, turn) < line
+        assert host_us(auto, xd, lgs[0], two, 1) < line
+        for p in (a, b, two):
+            p.sync()
+        assert bool(torch.isfinite(lgs[3]).all()) and all(torch.equal(l, lgs[3]) for l in lgs)
+    finally:
+        for t in tasks:
+            t.destroy()
+        for p in (a, b, two):
+            p.destroy()
 
 
 def test_graph_replay_survives_other_batches_and_partitions(cfg1):
