@@ -166,7 +166,7 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
     }
 
     int a_base[A_IT];
-    unsigned a_in[A_IT];  // filter rows (bits 0..) and columns (bits 16..) inside the image
+    unsigned a_in[A_IT];  // filter rows (bits 0..) and columns (bits kTapMaskBits..) inside the image
 #pragma unroll
     for (int i = 0; i < A_IT; ++i) {
         const int m = m0 + lrow + 8 * i;
@@ -174,14 +174,14 @@ __device__ __forceinline__ void ksplit_tile(const KsplitArgs& a, int mt, int nt)
         const int p = ks_div(rem, a.q_mul, a.q_sh), q = rem - p * a.Q;
         const int h0 = p * a.stride - a.pad, w0 = q * a.stride - a.pad;
         a_base[i] = (n * a.H + h0) * a.row_bytes + w0 * a.pixel_bytes + chunk_off;
-        a_in[i] = (tap_mask(h0, a.H, a.taps) | (tap_mask(w0, a.W, a.taps) << 16)) & (unsigned)((m - a.M) >> 31);
+        a_in[i] = (tap_mask(h0, a.H) | (tap_mask(w0, a.W) << kTapMaskBits)) & (unsigned)((m - a.M) >> 31);
     }
     const int tap0 = ks_div(kt0, a.ct_mul, a.ct_sh);
     int ic = kt0 - tap0 * a.cin_tiles, ir = a.taps == 3 ? tap0 / 3 : tap0, is = a.taps == 3 ? tap0 - ir * 3 : 0;
     unsigned a_voff[A_IT];
     auto enter_tap = [&]() {
         const int tap_off = ir * a.row_bytes + is * a.pixel_bytes;
-        const unsigned need = (1u << ir) | (0x10000u << is);
+        const unsigned need = (1u << ir) | (1u << kTapMaskBits << is);
 #pragma unroll
         for (int i = 0; i < A_IT; ++i) a_voff[i] = (a_in[i] & need) == need ? (unsigned)(a_base[i] + tap_off) : 0x80000000u;
     };

@@ -10,15 +10,18 @@
 
 namespace sgprs {
 
-// Bit t (t < taps) is set when input row first + t lies in [0, size).  Both ends are clamped: with
-// wide padding a window may lie wholly before or past the image, where -first exceeds taps and
-// size - first is negative.
-SGPRS_HD unsigned tap_mask(int first, int size, int taps)
+constexpr int kTapMaskBits = 16;
+
+// Bit t (t < kTapMaskBits - 1) is set when input row first + t lies in [0, size); no bit from kTapMaskBits on.
+// Both ends are clamped: with wide padding a window may lie wholly before or past the image, where -first
+// exceeds any shift and size - first is negative.  The clamps are constants, one instruction each, and need
+// no filter size: whoever reads the mask asks for the bits of the filter's taps only.
+SGPRS_HD unsigned tap_mask(int first, int size)
 {
     const int before = -first, left = size - first;
-    const int lo = before < 0 ? 0 : before < taps ? before : taps;
-    const int hi = left < lo ? lo : left < taps ? left : taps;
-    return (1u << hi) - (1u << lo);
+    const int lo = before < 0 ? 0 : before > kTapMaskBits - 1 ? kTapMaskBits - 1 : before;
+    const int hi = left < 0 ? 0 : left > kTapMaskBits - 1 ? kTapMaskBits - 1 : left;
+    return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
 }
 
 }  // namespace sgprs

@@ -12,4 +12,4 @@ def test_tap_masks_match_their_definition(tmp_path):
                     os.path.join(ROOT, "tests", "cpp", "tap_mask_check.cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
-    assert int(r.stdout.split()[1]) > 50000
+    assert int(r.stdout.split()[1]) > 25000
