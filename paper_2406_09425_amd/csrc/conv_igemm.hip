@@ -518,15 +518,12 @@ int launch_splitk_reduce(int dtype, const float* partial, int splits, size_t tot
 
 // Kernel arguments for plan p; false if the plan does not match the shape
 // (the host-side checks the kernel relies on).
-// Constants for fast_div: with L = ceil(log2 d) and mul = ceil(2^(31+L) / d) < 2^32,
-// floor(m / d) = (m * mul) >> (31 + L) for every 0 <= m < 2^31.
+// Constants for fast_div: those of div_constants(), with the doubling of m taken out of the shift.
 static void fast_div_constants(int d, unsigned* mul, int* sh)
 {
     if (d <= 1) { *mul = 0; *sh = -1; return; }
-    int L = 1;
-    while ((1ll << L) < d) ++L;
-    *mul = (unsigned)(((1ull << (31 + L)) + (unsigned)d - 1) / (unsigned)d);
-    *sh = L - 1;
+    div_constants(d, mul, sh);
+    --*sh;
 }
 
 static bool fill_igemm_args(const sgprs_conv_desc_t& d, const ConvPlan& p, const void* x, const void* w,

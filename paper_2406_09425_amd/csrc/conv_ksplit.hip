@@ -468,16 +468,6 @@ static int launch_ks(const KsplitLaunch& l, int slots, int problems, hipStream_t
     return SGPRS_OK;
 }
 
-// With L = ceil(log2 d) and mul = ceil(2^(31+L) / d) < 2^32, floor(m / d) = (m * mul) >> (31 + L) for
-// every 0 <= m < 2^31: the upper half of 2 m * mul, shifted by L.
-static void div_constants(int d, unsigned* mul, int* sh)
-{
-    int L = 0;
-    while ((1ll << L) < d) ++L;
-    *mul = (unsigned)(((1ull << (31 + L)) + (unsigned)d - 1) / (unsigned)d);
-    *sh = L;
-}
-
 // fp32 up to 768 input channels: beyond, even four accumulator sets leave chains whose error is larger
 // than split-K's over workgroups (relative to 64 bits, 7x7 3x3 convolution: 768 channels 3.5e-7 against
 // 3.7e-7, 1024 channels 4.1e-7 against 3.2e-7).

@@ -71,6 +71,16 @@ int resolve(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* cus);
 // the same for calls that launch planned work: the CU count is the one to plan for
 int resolve_launch(sgprs_pool_t* pool, int partition, hipStream_t* stream, int* plan_cus);
 
+// With L = ceil(log2 d) and mul = ceil(2^(31+L) / d) < 2^32, floor(m / d) = (m * mul) >> (31 + L) for
+// every 0 <= m < 2^31: the upper half of 2 m * mul, shifted by L.
+inline void div_constants(int d, unsigned* mul, int* sh)
+{
+    int L = 0;
+    while ((1ll << L) < d) ++L;
+    *mul = (unsigned)(((1ull << (31 + L)) + (unsigned)d - 1) / (unsigned)d);
+    *sh = L;
+}
+
 inline size_t dtype_size(int dtype) { return dtype == SGPRS_BF16 ? 2 : 4; }
 inline bool dtype_ok(int dtype) { return dtype == SGPRS_F32 || dtype == SGPRS_BF16; }
 
