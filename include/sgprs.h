@@ -27,9 +27,10 @@
  *  - Activation layout is NHWC (channels fastest) in the call's dtype.
  *    SGPRS_BF16 means bf16 storage with fp32 accumulation and an fp32
  *    epilogue; results are rounded to bf16 (nearest, ties to even) on store.
- *  - A CU mask never changes results, only speed: for a given tensor shape the
- *    arithmetic order depends on the partition's CU count only through the
- *    split-K factor, whose second pass sums in a fixed order.
+ *  - A CU mask changes results only by rounding: the kernel, tile and split of K
+ *    that a launch is planned with, and with them the order of its sums, depend on
+ *    the tensor shape and the number of CUs it is planned for.  Each order is fixed:
+ *    the same call on a partition planned for as many CUs gives the same bits.
  */
 #ifndef SGPRS_H
 #define SGPRS_H
@@ -310,8 +311,10 @@ const void *sgprs_task_stage_output(const sgprs_task_t *task, int stage);
  * latency; keep it off when timing throughput).  After synchronising,
  * sgprs_task_kernel_times returns, for the last run of each stage, one record
  * per launch: HOST arrays of length *count (in: capacity).  kind: 0 conv
- * implicit GEMM, 1 stem conv, 2 split-K reduce, 3 max-pool, 4 avg-pool, 5 FC
- * (variant 2, 3: avg-pool and FC in one launch; 4: the FC on the matrix cores),
+ * implicit GEMM (variant 32 and more: K split over the wavefronts of a
+ * workgroup; kind 10 likewise), 1 stem conv (variant 4: the fp32 kernel with
+ * packed input rows), 2 split-K reduce, 3 max-pool, 4 avg-pool, 5 FC (variant 2,
+ * 3: avg-pool and FC in one launch; 4, 5: the FC on the matrix cores, fp32, bf16),
  * 6 BN+ReLU, 7 add+ReLU, 8 LDS-patch 3x3 conv, 9 fused stem conv + max-pool
  * (variant 2: the bf16 kernel with packed input rows),
  * 10 two implicit-GEMM convolutions of one input in a single launch, 11 the
@@ -392,9 +395,10 @@ int sgprs_sched_complete(sgprs_sched_t *sched, int task, int job, int stage, dou
 int sgprs_sched_get_stats(const sgprs_sched_t *sched, sgprs_sched_stats_t *out);
 /* Run loop only (sgprs_sched_run_periodic): at most max_busy lanes have a stage
  * in flight at once; further stages wait in the scheduler's queues even if their
- * lane is free.  Default 4: on MI355X more than four CU-masked streams busy at
- * once cut the throughput of all of them by more than half, whatever their
- * size (idle ones cost nothing).  0: no limit.  The scheduler's decisions
+ * lane is free.  Default 4: on MI355X the CU-masked streams of a process share
+ * four dispatch pipes (of a pool's partitions, p and p + 4 the same one), and two
+ * busy streams on one pipe slow each other down four times, whatever their size
+ * (idle ones cost nothing).  0: no limit.  The scheduler's decisions
  * (sgprs_sched_next) are not affected. */
 int sgprs_sched_set_max_busy(sgprs_sched_t *sched, int max_busy);
 

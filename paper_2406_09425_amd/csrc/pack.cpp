@@ -169,12 +169,16 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
 // implicit-GEMM workgroups of the shortcut run beside the main problem's (three to five fit a CU)
 // where the K-split kernel, one or two to a CU, needs further rounds.  Implicit GEMM: launch and
 // epilogue, the k-tiles of one workgroup or, if that is longer, of the busiest CU, and a part per
-// workgroup and CU; fitted per tile to 324 launches (the network's three blocks, 1..128 images,
-// 32..256 CUs, both types; 5-12 % off rms).  The choice is 2 % slower than the best tile on average,
-// that of the single-convolution plan was 7 %; 64 images on 256 CUs, 14x14x256 -> 512: 19.2 us with
-// 64x64 implicit-GEMM tiles, 23.4 with the K-split kernel.  Near a tie the K-split kernel is the one
-// that keeps its time inside the network (4 images on 96 CUs, whole inference: 156.0 us with it in
-// the second block, 159.4 with implicit GEMM, whose launch alone is as fast): 5 % in its favour.
+// workgroup and CU; fitted per tile to 324 launches in loops over one input (the network's three
+// blocks, 1..128 images, 32..256 CUs, both types; 5-12 % off rms).  Whole inferences with inputs that
+// change from pass to pass, plan of the single convolution against this one, us: bf16 one image on 32
+// CUs 130.2 / 126.6, on 64 CUs stage by stage 104.5 / 103.5, on 256 CUs 78.2 / 78.3; fp32 on 256 CUs one
+// image 117.6 / 116.2, 16 images 652.6 / 641.1; bf16 13 images on 96 CUs and 128 on 256 the same; 64
+// images on 256 CUs 397.0 / 399.4, the one that loses: in a loop its 14x14x256 -> 512 pair takes 19.2 us
+// with the 64x64 implicit-GEMM tiles chosen here and 23.4 with the K-split kernel, in the network it is
+// the other way round by 2 us.  Near a tie the K-split kernel is the one that keeps its time inside the
+// network (4 images on 96 CUs, whole inference: 156.0 us with it in the second block, 159.4 with implicit
+// GEMM, whose launch alone is as fast): 5 % in its favour.
 static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int cus)
 {
     const ConvPlan single = plan_conv(d0, cus);

@@ -483,9 +483,9 @@ bool stem_pool_applicable(int dtype, int n, int h, int w, int cus)
     const int PP = (P - 1) / 2 + 1, PQ = (Q - 1) / 2 + 1;
     const long long tiles = (long long)n * ((PP + kPoolTP - 1) / kPoolTP) * ((PQ + kPoolTQ - 1) / kPoolTQ);
     // smaller launches keep the finer-grained two-kernel path; in bf16 the fused kernel wins down
-    // to one image (9.4 us against 8.5 + 4.9 us at batch 1); in fp32 it
-    // does where every CU gets work (us, two kernels and the gap between them against one, 256 CUs: 3 images
-    // 20 / 21, 5 images 24 / 21, 9 images 38 / 34)
+    // to one image (9.4 us against 8.5 + 4.9 us at batch 1); the line for fp32 is where its times cross
+    // (us, two kernels and the gap between them against one, 256 CUs: 3 images 20 / 21, 5 images 24 / 21,
+    // 9 images 38 / 34), expressed in the 7x8 tiles counted here, not the 4x8 ones of its own kernel
     return dtype == SGPRS_BF16 ? tiles >= 32 : tiles >= cus && stem_f32_applicable(n, h, w);
 }
 
@@ -517,10 +517,6 @@ int launch_stem_pool(int dtype, int n, int h, int w, const void* x, const void* 
     if (nt >= (1ll << 31)) return fail(SGPRS_ERR_UNSUPPORTED, "too many stem tiles");
     a.ntiles = (int)nt;
     const int es = (int)dtype_size(dtype);
-    const int patch = kInR * kInC * 4 * es, stg = 256 * (64 * es + 16);
-    const size_t lds = 64 * (kStemK * es + 16) + (patch > stg ? patch : stg);
-    const int occ = lds <= 80 * 1024 ? 2 : 1;
-    const int grid = (int)std::min<long long>(nt, (long long)cus * occ);
     const double flops = 2.0 * n * a.P * a.Q * 64.0 * 147.0;
     const double bytes = ((double)n * h * w * 3 + 64.0 * 147 + (double)n * a.PP * a.PQ * 64) * es;
     int rc;
@@ -540,9 +536,12 @@ int launch_stem_pool(int dtype, int n, int h, int w, const void* x, const void* 
         SGPRS_LAUNCH(stem_pool_packed_kernel, dim3((int)std::min<long long>(nt, 2ll * cus)), dim3(256), lds_rows, stream, a,
                      (unsigned)x_bytes);
     } else if (dtype == SGPRS_BF16) {
+        constexpr int patch = kInR * kInC * 4 * 2, stg = 256 * (64 * 2 + 16);
+        constexpr int lds = 64 * (kStemK * 2 + 16) + (patch > stg ? patch : stg), occ = lds <= 80 * 1024 ? 2 : 1;
+        const int grid = (int)std::min<long long>(nt, (long long)cus * occ);
         if (!raised[0]) {
             SGPRS_HIP(hipFuncSetAttribute((const void*)stem_pool_kernel<SGPRS_BF16>,
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds));
             raised[0] = true;
         }
         SGPRS_LAUNCH(stem_pool_kernel<SGPRS_BF16>, dim3(grid), dim3(256), lds, stream, a);

@@ -213,8 +213,8 @@ def test_paired_launch_families_parity(cfg1, dtype, n):
 
 
 def test_stage0_fp32_fused_stem_pool_elementwise(cfg1):
-    """fp32 launches of at least two tiles per CU take the fused conv7x7 + max-pool kernel
-    (kind 9): its stage-0 output, element by element against the oracle, on 8 and 64 CUs, with a
+    """fp32 launches of at least one 7x8 tile of pooled pixels per CU take the fused conv7x7 + max-pool
+    kernel (kind 9): its stage-0 output, element by element against the oracle, on 8 and 64 CUs, with a
     ragged batch; the same images on the whole chip take the two-kernel path and agree."""
     params = cfg1[0]
     dtype = S.SGPRS_F32
