@@ -5,13 +5,15 @@
 // operands get to the matrix cores.  Fragment-shaped loads (a row per lane) reach a quarter of the
 // load path's rate and left a 4096-image layer at 55 us (bf16); one wavefront per output with
 // register weights re-reads the pooled vectors for every four outputs (fp32: 60 us at 433 images).
-// Here (avg-pool + FC: 433 images fp32 on 128 CUs 72 -> 21 us, 4096 images fp32 359 -> 114, 1820 images
-// bf16 on 48 CUs 220 -> 145), as in the convolution that splits K over wavefronts, every wavefront moves its own quarter of
-// the inputs into an LDS ring of its own with loads that write LDS directly, multiplies them without a
-// barrier, and the four partial tiles meet in LDS at the end, added in wavefront order.
-// fp32 weights: MFMA 16x16x4.  bf16 weights: the fp32 pooled values go in as a bf16 head plus a bf16
-// remainder (two MFMA 16x16x32; products of two bf16 are exact in fp32, so what is lost is below
-// 2^-17 of a value), split when the fragment is read.
+// Here (avg-pool + FC on 256 CUs: 433 images fp32 46.7 -> 16.7 us, 4096 images fp32 364 -> 128; 1820 images
+// bf16 on 48 CUs 220 -> 145), as in the convolution that splits K over wavefronts, every wavefront moves its
+// own share of the inputs into an LDS ring of its own with loads that write LDS directly, multiplies them
+// without a barrier, and the partial tiles meet in LDS at the end, added in a fixed order.
+// fp32 weights: MFMA 16x16x4, in chains of eight products that are added as trees: the error against 64
+// bits is that of a register FC with shuffle sums (512 inputs 8.6e-8 relative, 2048 inputs 9.9e-8 against
+// 1.23e-7), where one chain per wavefront had 2.1e-7 and 4.1e-7 and took 10 to 20 % less time.  bf16
+// weights: the fp32 pooled values go in as a bf16 head plus a bf16 remainder (two MFMA 16x16x32; products
+// of two bf16 are exact in fp32, so what is lost is below 2^-17 of a value), split when the fragment is read.
 #include "internal.h"
 
 namespace sgprs {
@@ -38,21 +40,23 @@ __device__ __forceinline__ void split_bf16(const u32x4_t a, const u32x4_t b, u32
 // 16*TM images x 16*TN outputs per workgroup; k-tiles of 32 inputs, ring of NS stages per wavefront.
 // cin is a multiple of 512 and cout of 4 (checked by the launcher); images and outputs past the end
 // read zeros (the buffers are the tile's own rows, so operands of any size are addressed with 32-bit
-// offsets) and are not stored.
-template <int DT, int TM, int TN, int NS>
-__global__ __launch_bounds__(256) void fc_gemm_kernel(const float* __restrict__ v, const unsigned char* __restrict__ w,
-                                                      const float* __restrict__ bias, float* __restrict__ y, int nimg, int cin, int cout)
+// offsets) and are not stored.  (fp32: at most 256 registers, so that the MFMAs write plain vector registers
+// and their sums need no copies.)
+template <int DT, int TM, int TN, int NS, int NW>
+__global__ __launch_bounds__(NW * 64, DT == SGPRS_F32 ? 2 : 1) void fc_gemm_kernel(const float* __restrict__ v, const unsigned char* __restrict__ w,
+                                                                                   const float* __restrict__ bias, float* __restrict__ y,
+                                                                                   int nimg, int cin, int cout)
 {
     constexpr int BM = 16 * TM, BN = 16 * TN, WROW = DT == SGPRS_BF16 ? 64 : 128;
     constexpr int A_IT = BM / 8, B_IT = BN * WROW / 1024, LPS = A_IT + B_IT;
-    constexpr int STAGE = BM * 128 + BN * WROW, SROW = BN + 4;
+    constexpr int STAGE = BM * 128 + BN * WROW, SROW = BN + 4, SETS = DT == SGPRS_BF16 ? 1 : 2;
     static_assert((NS - 1) * LPS <= 63, "vmcnt range");
     static_assert(BM * SROW * 4 <= NS * STAGE, "a wavefront's partial tile fits its ring");
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = blockIdx.y * BM, o0 = blockIdx.x * BN;
-    const int nkt = cin >> 7, kt0 = wave * nkt;
+    const int nkt = cin / (32 * NW), kt0 = wave * nkt;  // an even number of k-tiles
     unsigned char* ring = smem + wave * (NS * STAGE);
 
     // LDS slots hold swizzled 16-byte chunks, so that a fragment read meets no bank twice: slot s of a
@@ -82,15 +86,31 @@ __global__ __launch_bounds__(256) void fc_gemm_kernel(const float* __restrict__ 
 #pragma unroll
     for (int s = 0; s < NS; ++s) request(s, s);
 
-    f32x4_t acc[TM][TN];
+    f32x4_t acc[SETS][TM][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int s = 0; s < SETS; ++s)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[s][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int frow = lane & 15, fgrp = lane >> 4;
     auto v_chunk = [&](const unsigned char* st, int i, int c) { return *(const u32x4_t*)(st + (i * 16 + frow) * 128 + ((c ^ (frow & 7)) << 4)); };
+    // fp32: the 32 products of a k-tile are four
+    // chains of two MFMAs from zero, added as a tree, even and odd k-tiles apart.  The tree of output tile
+    // ij runs between the MFMAs of the next tile, the last tile's in the next k-tile (at first it adds zeros).
+    static_assert(DT == SGPRS_BF16 || TM * TN % 2 == 0, "the two sets of chains alternate");
+    f32x4_t chain[2][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) chain[1][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto add_chains = [&](int ij, int set, int step) {
+        f32x4_t(&c)[4] = chain[ij & 1];
+        if (step == 0) c[0] += c[1];
+        else if (step == 1) c[2] += c[3];
+        else if (step == 2) c[0] += c[2];
+        else acc[set % SETS][ij / TN][ij % TN] += c[0];
+    };
     int slot = 0;
-    for (int t = 0; t < nkt; ++t) {
+    auto k_tile = [&](int t, auto odd) {
         __builtin_amdgcn_s_waitcnt(((NS - 1) * LPS & 15) | (((NS - 1) * LPS >> 4) << 14) | 0x0F70);
         __builtin_amdgcn_sched_barrier(0);
         const unsigned char* st = ring + slot * STAGE;
@@ -123,22 +143,31 @@ __global__ __launch_bounds__(256) void fc_gemm_kernel(const float* __restrict__ 
                 for (int p = 0; p < 2; ++p)
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[j][0]),
-                                                                            __builtin_bit_cast(bf16x8_t, part[p]), acc[i][j], 0, 0, 0);
+                        acc[0][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[j][0]),
+                                                                            __builtin_bit_cast(bf16x8_t, part[p]), acc[0][i][j], 0, 0, 0);
             }
         } else {
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int ij = 0; ij < TM * TN; ++ij)
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(b[j][h][u]), __uint_as_float(a[i][h][u]),
-                                                                             acc[i][j], 0, 0, 0);
+                for (int k = 0; k < 8; ++k) {
+                    const int i = ij / TN, j = ij % TN;
+                    f32x4_t& c = chain[ij & 1][k / 2];
+                    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+                    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(b[j][k >> 2][k & 3]), __uint_as_float(a[i][k >> 2][k & 3]),
+                                                             k % 2 ? c : zero, 0, 0, 0);
+                    if (k % 2) add_chains(ij ? ij - 1 : TM * TN - 1, ij ? odd : odd + 1, k / 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
         }
+    };
+    for (int t = 0; t < nkt; t += 2) {
+        k_tile(t, std::integral_constant<int, 0>());
+        k_tile(t + 1, std::integral_constant<int, 1>());
     }
+    if constexpr (DT == SGPRS_F32)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) add_chains(TM * TN - 1, 1, k);
     __builtin_amdgcn_s_waitcnt(0);  // the (empty) requests still in flight write LDS too
     __builtin_amdgcn_sched_barrier(0);
 
@@ -147,14 +176,24 @@ __global__ __launch_bounds__(256) void fc_gemm_kernel(const float* __restrict__ 
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) *(f32x4_t*)(part + (i * 16 + frow) * SROW + j * 16 + fgrp * 4) = acc[i][j];
+        for (int j = 0; j < TN; ++j)
+            *(f32x4_t*)(part + (i * 16 + frow) * SROW + j * 16 + fgrp * 4) = SETS == 1 ? acc[0][i][j] : acc[0][i][j] + acc[SETS - 1][i][j];
     __syncthreads();
-    for (int item = tid; item < BM * BN / 4; item += 256) {
+    for (int item = tid; item < BM * BN / 4; item += NW * 64) {
         const int img = item / (BN / 4), c = (item % (BN / 4)) * 4, o = o0 + c;
         const float* src = (const float*)smem + img * SROW + c;
-        f32x4_t s = *(const f32x4_t*)src;
+        f32x4_t p[NW], s;
 #pragma unroll
-        for (int q = 1; q < 4; ++q) s += *(const f32x4_t*)(src + q * (NS * STAGE / 4));
+        for (int q = 0; q < NW; ++q) p[q] = *(const f32x4_t*)(src + q * (NS * STAGE / 4));
+        if constexpr (DT == SGPRS_BF16) {
+            s = ((p[0] + p[1]) + p[2]) + p[3];
+        } else {
+#pragma unroll
+            for (int d = 1; d < NW; d *= 2)
+#pragma unroll
+                for (int q = 0; q < NW; q += 2 * d) p[q] += p[q + d];
+            s = p[0];
+        }
         if (n0 + img >= nimg || o >= cout) continue;
         if (bias) {
 #pragma unroll
@@ -166,17 +205,17 @@ __global__ __launch_bounds__(256) void fc_gemm_kernel(const float* __restrict__ 
     }
 }
 
-template <int DT, int TM, int TN, int NS>
+template <int DT, int TM, int TN, int NS, int NW = 4>
 static int launch_tile(const float* v, const void* w, const float* bias, float* y, int n, int cin, int cout, hipStream_t stream)
 {
-    constexpr int lds = 4 * NS * (16 * TM * 128 + 16 * TN * (DT == SGPRS_BF16 ? 64 : 128));
+    constexpr int lds = NW * NS * (16 * TM * 128 + 16 * TN * (DT == SGPRS_BF16 ? 64 : 128));
     static std::atomic<bool> raised{false};
     if (!raised) {
-        SGPRS_HIP(hipFuncSetAttribute((const void*)fc_gemm_kernel<DT, TM, TN, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        SGPRS_HIP(hipFuncSetAttribute((const void*)fc_gemm_kernel<DT, TM, TN, NS, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         raised = true;
     }
     const dim3 grid((cout + 16 * TN - 1) / (16 * TN), (n + 16 * TM - 1) / (16 * TM));
-    SGPRS_LAUNCH((fc_gemm_kernel<DT, TM, TN, NS>), grid, dim3(256), lds, stream, v, (const unsigned char*)w, bias, y, n, cin, cout);
+    SGPRS_LAUNCH((fc_gemm_kernel<DT, TM, TN, NS, NW>), grid, dim3(NW * 64), lds, stream, v, (const unsigned char*)w, bias, y, n, cin, cout);
     SGPRS_HIP(hipGetLastError());
     return SGPRS_OK;
 }
@@ -187,13 +226,19 @@ bool fc_gemm_applicable(int n, int cin, int cout)
     return n >= 32 && cin % 512 == 0 && cout % 4 == 0;
 }
 
-// 64x64 tiles halve the traffic of 32x32 ones; they need enough images to occupy the partition.
+// 64x64 tiles halve the traffic of 32x32 ones; they need enough images to occupy the partition, and in
+// fp32, where they cost matrix time, more than half a tile of them (32 images of 2048 inputs on 8 CUs:
+// 48 us with 32x32 tiles, 93 with 64x64).  Small fp32 tiles: eight wavefronts halve the chain of k-tiles
+// where a CU gets one tile, beyond that two workgroups of four (64 images of 512 inputs on 256 CUs 7.8 and
+// 8.4 us, 433 images 17.7 with four and 19.1 with eight).
 int launch_fc_gemm(int dtype, const float* v, const void* w, const float* bias, float* y, int n, int cin, int cout, hipStream_t stream, int cus)
 {
-    const bool big = (long long)((cout + 63) / 64) * ((n + 63) / 64) >= cus;
+    const bool big = (long long)((cout + 63) / 64) * ((n + 63) / 64) >= cus && (dtype == SGPRS_BF16 || n > 32);
     if (dtype == SGPRS_BF16)
         return big ? launch_tile<SGPRS_BF16, 4, 4, 2>(v, w, bias, y, n, cin, cout, stream) : launch_tile<SGPRS_BF16, 2, 2, 3>(v, w, bias, y, n, cin, cout, stream);
-    return big ? launch_tile<SGPRS_F32, 4, 4, 2>(v, w, bias, y, n, cin, cout, stream) : launch_tile<SGPRS_F32, 2, 2, 2>(v, w, bias, y, n, cin, cout, stream);
+    if (big) return launch_tile<SGPRS_F32, 4, 4, 2>(v, w, bias, y, n, cin, cout, stream);
+    return (long long)((cout + 31) / 32) * ((n + 31) / 32) > cus ? launch_tile<SGPRS_F32, 2, 2, 2>(v, w, bias, y, n, cin, cout, stream)
+                                                                : launch_tile<SGPRS_F32, 2, 2, 2, 8>(v, w, bias, y, n, cin, cout, stream);
 }
 
 }  // namespace sgprs

@@ -509,8 +509,8 @@ def test_conv_ksplit_f32_keeps_its_chains_short(pools, variant, shape):
 @pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
 @pytest.mark.parametrize("n,cin,cout,cus", [(32, 512, 36, 8), (70, 1024, 100, 8), (129, 2048, 36, "full"), (65, 512, 1000, 64)], ids=str)
 def test_fc_gemm_tiles_parity(pools, dtype, n, cin, cout, cus):
-    """The FC of 32 images and more: both tile sizes (64x64 where they fill the partition), ragged in images and
-    outputs, ring shares of 4, 8 and 16 k-tiles, without a bias and with one.  fp32: sums of up to 2048 products,
+    """The FC of 32 images and more: small tiles (the large ones: the tests below), ragged in images and
+    outputs, ring shares of 2 to 16 k-tiles, without a bias and with one.  fp32: sums of up to 2048 products,
     about sqrt(2048) * 2^-24; bf16: exact weights, pooled values to 2^-17."""
     bf = dtype == S.SGPRS_BF16
     x = make_input(97, n, (n, cin, 2, 1), bf16=bf)
@@ -529,6 +529,26 @@ def test_fc_gemm_tiles_parity(pools, dtype, n, cin, cout, cus):
     got = lg.cpu().numpy().astype(np.float64)
     assert np.all(np.isnan(got[n]))    # nothing is written past the last image
     assert rel_err(got[:n], ref) <= (2e-5 if bf else 4e-6)
+
+
+@pytest.mark.parametrize("n,cin,cus", [(64, 512, "full"), (40, 1024, "full"), (65, 512, 64), (200, 512, 8), (130, 2048, 8), (64, 2048, "full")], ids=str)
+def test_fc_f32_keeps_its_chains_short(pools, n, cin, cus):
+    """fp32 FC of 32 images and more, in each of its tile shapes: products are summed in chains of eight, the
+    rest is trees (16 roundings cover their levels).  Each rounding is about 2^-24 / sqrt(6) of its sum; a
+    chain of eight adds 8 / 2 of them in the mean square, the quarter of the inputs that one wavefront
+    multiplies (128 products and more) would be past the line.  One position per image: pooling is exact."""
+    assert fc_gemm_applicable(n, cin, 1000)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    x = torch.randn((n, 1, cin), generator=g, device="cuda")
+    w = torch.randn((1000, cin), generator=g, device="cuda")
+    ws, lg = torch.empty(n * cin, device="cuda"), torch.empty((n, 1000), device="cuda")
+    torch.cuda.synchronize()
+    S.sgprs_avgpool_fc(S.SGPRS_F32, n, 1, cin, 1000, x.data_ptr(), w.data_ptr(), None, lg.data_ptr(), ws.data_ptr(), pools[cus], 0)
+    pools[cus].sync()
+    ref = x[:, 0].double().cpu().numpy() @ w.double().cpu().numpy().T
+    e = np.linalg.norm(lg.double().cpu().numpy() - ref) / np.linalg.norm(ref)
+    assert e <= 2.0 ** -24 / 6.0 ** 0.5 * (8 / 2 + 16) ** 0.5, e
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
