@@ -531,9 +531,10 @@ def test_fc_gemm_tiles_parity(pools, dtype, n, cin, cout, cus):
     assert rel_err(got[:n], ref) <= (2e-5 if bf else 4e-6)
 
 
-@pytest.mark.parametrize("n,cin,cus", [(64, 512, "full"), (40, 1024, "full"), (65, 512, 64), (200, 512, 8), (130, 2048, 8), (64, 2048, "full")], ids=str)
+@pytest.mark.parametrize("n,cin,cus", [(64, 512, "full"), (39, 512, "full"), (40, 1024, "full"), (65, 512, 64), (200, 512, 8), (130, 2048, 8), (64, 2048, "full")], ids=str)
 def test_fc_f32_keeps_its_chains_short(pools, n, cin, cus):
-    """fp32 FC of 32 images and more, in each of its tile shapes: products are summed in chains of eight, the
+    """fp32 FC of 32 images and more, in each of its tile shapes and with the register kernel that fewer than
+    40 images on most of the chip keep: products are summed in chains of eight, the
     rest is trees (16 roundings cover their levels).  Each rounding is about 2^-24 / sqrt(6) of its sum; a
     chain of eight adds 8 / 2 of them in the mean square, the quarter of the inputs that one wavefront
     multiplies (128 products and more) would be past the line.  One position per image: pooling is exact."""
