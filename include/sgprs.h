@@ -319,7 +319,8 @@ const void *sgprs_task_stage_output(const sgprs_task_t *task, int stage);
  * (variant 2: the bf16 kernel with packed input rows),
  * 10 two implicit-GEMM convolutions of one input in a single launch, 11 the
  * stride-2 LDS-patch 3x3 conv (variant + 4: together with the 1x1 shortcut),
- * 12 the row-streaming 3x3 conv of the 64 -> 64 layers.
+ * 12 the row-streaming 3x3 conv of the 64 -> 64 layers, 13 the 3x3 conv whose
+ * weights go from the L2 to registers (variant: wavefronts that share a tile).
  * flops/bytes are the algorithmic work of the launch. */
 int sgprs_task_set_profiling(sgprs_task_t *task, int on);
 /* Graph replay of sgprs_task_run (see there): mode 1 always, 0 never (every

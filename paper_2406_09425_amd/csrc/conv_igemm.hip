@@ -592,15 +592,16 @@ int launch_conv_pair(const sgprs_conv_desc_t& d0, const void* w0, const float* s
 
 int launch_conv(const sgprs_conv_desc_t& d, const void* x, const void* w, const float* scale,
                 const float* shift, const void* residual, void* y, void* ws, size_t ws_bytes,
-                hipStream_t stream, int cus, Profiler* prof)
+                hipStream_t stream, int cus, Profiler* prof, const void* w_fragments)
 {
-    const ConvPlan p = plan_conv(d, cus, residual != nullptr);
+    const ConvPlan p = plan_conv(d, cus, residual != nullptr, true, w_fragments != nullptr);
     if (p.bm == 0) return fail(SGPRS_ERR_UNSUPPORTED, "no tile shape fits cout %d", d.cout);
     if (p.kind == 1)
         return launch_conv3x3_patch(d, p.variant, p.splits, x, w, scale, shift, residual, y, ws, ws_bytes, stream, cus,
                                     prof);
     if (p.kind == 4)
         return launch_conv_ksplit(d, p.variant, x, w, scale, shift, residual, y, nullptr, nullptr, nullptr, nullptr, nullptr, stream, prof);
+    if (p.kind == 5) return launch_conv3x3_wtile(d, p.variant, x, w_fragments, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 3) return launch_conv3x3_rows(d, p.variant, x, w, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 2) {
         return launch_conv3x3s2_patch(d, p.variant, x, w, scale, shift, y, nullptr, nullptr, nullptr, nullptr, nullptr, stream, cus,

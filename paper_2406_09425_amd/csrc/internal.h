@@ -184,7 +184,8 @@ extern std::atomic<int> g_plan_generation;  // bumped whenever a tuning override
 // Tile configuration of one implicit-GEMM launch.
 struct ConvPlan {
     int kind = 0;      // 0: implicit GEMM, 1: LDS-patch 3x3 kernel, 2: its stride-2 variant, 3: row streaming,
-                       // 4: implicit GEMM with K split over a workgroup's wavefronts
+                       // 4: implicit GEMM with K split over a workgroup's wavefronts,
+                       // 5: weights from the L2 to registers (variant: wavefronts that share a tile)
     int variant = 0;   // index into the kernel's tile table (row streaming: output rows per stream and job)
     int bm = 0, bn = 0;
     int splits = 1;    // split-K factor (grid.z)
@@ -194,8 +195,8 @@ struct ConvPlan {
 // Chooses tile shape and split-K factor from the GEMM shape and the CU count of
 // the partition the launch will run on.
 // (has_residual: kernels without a residual input are left out; ksplit false: so is the kernel that
-// splits K over a workgroup's wavefronts).
-ConvPlan plan_conv(const sgprs_conv_desc_t& d, int partition_cus, bool has_residual = false, bool ksplit = true);
+// splits K over a workgroup's wavefronts; fragments: the weights are there in fragment order too).
+ConvPlan plan_conv(const sgprs_conv_desc_t& d, int partition_cus, bool has_residual = false, bool ksplit = true, bool fragments = false);
 // The plan of d0 for a launch that also runs the block's shortcut d1 on the same input (same output shape).
 ConvPlan plan_conv_pair(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int partition_cus);
 size_t conv_workspace_bytes(const sgprs_conv_desc_t& d, const ConvPlan& p);
@@ -235,12 +236,12 @@ struct Profiler {
 
 enum KernelKind { kKindIgemm = 0, kKindStem = 1, kKindReduce = 2, kKindMaxpool = 3, kKindAvgpool = 4,
                   kKindFc = 5, kKindBnRelu = 6, kKindAdd = 7, kKindPatch = 8, kKindStemPool = 9,
-                  kKindIgemmPair = 10, kKindS2Patch = 11, kKindRows = 12 };
+                  kKindIgemmPair = 10, kKindS2Patch = 11, kKindRows = 12, kKindWtile = 13 };
 
 // launchers (device pointers; validated by callers)
 int launch_conv(const sgprs_conv_desc_t& d, const void* x, const void* w, const float* scale,
                 const float* shift, const void* residual, void* y, void* ws, size_t ws_bytes,
-                hipStream_t stream, int cus, Profiler* prof);
+                hipStream_t stream, int cus, Profiler* prof, const void* w_fragments = nullptr);
 int launch_stem(const sgprs_conv_desc_t& d, const void* x, const void* w, const float* scale,
                 const float* shift, void* y, hipStream_t stream, int cus, Profiler* prof);
 int launch_maxpool(int dtype, int n, int h, int w, int c, const void* x, void* y, hipStream_t stream,
@@ -310,6 +311,13 @@ bool ksplit_fits(const sgprs_conv_desc_t& d, int variant);
 int launch_conv_ksplit(const sgprs_conv_desc_t& d, int variant, const void* x, const void* w, const float* scale, const float* shift,
                        const void* res, void* y, const sgprs_conv_desc_t* d1, const void* w1, const float* scale1,
                        const float* shift1, void* y1, hipStream_t stream, Profiler* prof);
+// 3x3 stride-1 kernel with private patches and weights from the L2 to registers (bf16); its weights come in fragment order
+bool fragments_applicable(const sgprs_conv_desc_t& d);
+int repack_fragments(const sgprs_conv_desc_t& d, const void* src, void* dst, hipStream_t stream);
+bool wtile_applicable(const sgprs_conv_desc_t& d);
+bool plan_wtile(const sgprs_conv_desc_t& d, int cus, int* ks, double* cost_us);
+int launch_conv3x3_wtile(const sgprs_conv_desc_t& d, int ks, const void* x, const void* w_fragments, const float* scale, const float* shift,
+                         const void* res, void* y, hipStream_t stream, int cus, Profiler* prof);
 // tuning override: kind -1 automatic, 0 implicit GEMM only, 1 force patch (variant, splits)
 extern std::atomic<int> g_conv_force_kind;
 extern std::atomic<int> g_igemm_force_variant, g_igemm_force_splits;

@@ -60,20 +60,20 @@ std::atomic<int> g_igemm_force_splits{0};
 
 std::atomic<int> g_plan_generation{0};
 
-static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit);
+static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit, bool fragments);
 
-ConvPlan plan_conv(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit)
+ConvPlan plan_conv(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit, bool fragments)
 {
-    struct Key { sgprs_conv_desc_t d; int cus, res, ksplit, gen; };
+    struct Key { sgprs_conv_desc_t d; int cus, res, ksplit, fragments, gen; };
     static thread_local PlanMemo<Key, ConvPlan> local;
     static SharedPlanMemo<Key, ConvPlan> memo;
     Key k;
     memset(&k, 0, sizeof(k));
-    k.d = d; k.cus = cus; k.res = has_residual; k.ksplit = ksplit; k.gen = g_plan_generation.load();
-    return memo.get(local, k, [&]() { return plan_conv_uncached(d, cus, has_residual, ksplit); });
+    k.d = d; k.cus = cus; k.res = has_residual; k.ksplit = ksplit; k.fragments = fragments; k.gen = g_plan_generation.load();
+    return memo.get(local, k, [&]() { return plan_conv_uncached(d, cus, has_residual, ksplit, fragments); });
 }
 
-static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit)
+static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has_residual, bool ksplit, bool fragments)
 {
     const int force_kind = g_conv_force_kind.load(), force_variant = g_igemm_force_variant.load(),
               force_splits = g_igemm_force_splits.load();
@@ -113,6 +113,17 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
             best = ConvPlan();
             best.kind = 4; best.variant = v; best.bm = 1;
             best_cost = cost;
+        }
+        if (fragments && force_kind == -1 && force_variant < 0 && plan_wtile(d, cus, &v, &cost)) {
+            // Its estimate holds for the clock that the launch leaves the chip; those of the other two were
+            // fitted where few CUs ran, and fall short of what launches on most of the chip take (LDS
+            // patches: 12.5 estimated, 12.4 us on 32 CUs, 14.0 on 256; K split: 14.9, 13.2 and 16.9).
+            const double chip = std::min(cus, 256) / 256.0, scaled = cost * (1.0 - 0.18 * chip);
+            if ((best.kind == 4 ? cost * (1.02 - 0.15 * chip) : scaled) < best_cost) {
+                best = ConvPlan();
+                best.kind = 5; best.variant = v; best.bm = 1;
+                best_cost = scaled;
+            }
         }
     }
     const int P = out_dim(d.h, d.r, d.stride, d.pad), Q = out_dim(d.w, d.s, d.stride, d.pad);

@@ -41,6 +41,7 @@ constexpr int kFcIn = 512, kFcOut = 1000;
 struct ConvLayer {
     sgprs_conv_desc_t d;
     void* w = nullptr;
+    void* w_fragments = nullptr;  // bf16 3x3 stride-1 layers: the same in fragment order
     float* scale = nullptr;
     float* shift = nullptr;
 };
@@ -169,7 +170,7 @@ int run_conv(sgprs_task* t, int i, int batch, const void* x, const void* res, vo
     d.relu = relu;
     if (is_stem(d)) return launch_stem(d, x, t->conv[i].w, t->conv[i].scale, t->conv[i].shift, y, s, cus, prof);
     return launch_conv(d, x, t->conv[i].w, t->conv[i].scale, t->conv[i].shift, res, y, t->splitk, t->splitk_bytes, s,
-                       cus, prof);
+                       cus, prof, t->conv[i].w_fragments);
 }
 
 // BasicBlock: out = ReLU(BN2(conv2(ReLU(BN1(conv1(x))))) + shortcut(x)); the
@@ -279,6 +280,7 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
     int rc = SGPRS_OK;
     std::vector<unsigned char> packed;
     std::vector<float> scale, shift;
+    size_t fragment_bytes = 0;
     for (int i = 0; i < SGPRS_RESNET18_CONVS && !rc; ++i) {
         const ConvSpec& cs = kConvs[i];
         sgprs_conv_desc_t& d = t->conv[i].d;
@@ -295,6 +297,7 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
         if ((rc = upload(t, packed.data(), bytes, &t->conv[i].w))) break;
         if ((rc = upload(t, scale.data(), cs.cout * sizeof(float), (void**)&t->conv[i].scale))) break;
         if ((rc = upload(t, shift.data(), cs.cout * sizeof(float), (void**)&t->conv[i].shift))) break;
+        if (wtile_applicable(d)) fragment_bytes += bytes;
         if (i == 0 && dtype == SGPRS_BF16) {
             std::vector<uint16_t> rows((size_t)64 * kStemRowsK);
             pack_stem_rows(hp->conv_w[0], rows.data());
@@ -312,6 +315,20 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
         }
     }
     if (!rc && hp->fc_b) rc = upload(t, hp->fc_b, kFcOut * sizeof(float), (void**)&t->fc_b);
+    if (!rc && fragment_bytes) {
+        void* to = nullptr;
+        rc = dev_alloc(t, fragment_bytes, &to);
+        for (int i = 0; i < SGPRS_RESNET18_CONVS && !rc; ++i) {
+            ConvLayer& l = t->conv[i];
+            if (!wtile_applicable(l.d)) continue;
+            size_t bytes = 0;
+            if ((rc = sgprs_conv_packed_weight_bytes(&l.d, &bytes)) || (rc = repack_fragments(l.d, l.w, to, nullptr))) break;
+            l.w_fragments = to;
+            to = (unsigned char*)to + bytes;
+        }
+    }
+    // partition streams are not ordered after the null stream
+    if (!rc && hipStreamSynchronize(nullptr) != hipSuccess) rc = fail(SGPRS_ERR_HIP, "packing the weights failed");
     const size_t es = dtype_size(dtype);
     if (!rc) rc = dev_alloc(t, (size_t)max_batch * 112 * 112 * 64 * es, &t->stem_out);
     for (int i = 0; i < 3 && !rc; ++i) rc = dev_alloc(t, (size_t)max_batch * 56 * 56 * 64 * es, &t->tmp[i]);
@@ -520,6 +537,7 @@ const char* sgprs_kernel_name(int kind, int variant)
         case kKindPatch: return patch_variant_name(variant);
         case kKindS2Patch: return s2patch_variant_name(variant);
         case kKindRows: return "conv3x3_rows_kernel";
+        case kKindWtile: return variant == 1 ? "conv3x3_wtile_kernel<1>" : variant == 2 ? "conv3x3_wtile_kernel<2>" : "conv3x3_wtile_kernel<4>";
         case kKindStem: return variant == 4 ? "stem_f32_kernel" : "conv_stem_kernel";
         case kKindStemPool:
             return variant == 2 ? "stem_pool_packed_kernel" : variant == SGPRS_BF16 ? "stem_pool_kernel<1>" : "stem_f32_kernel";

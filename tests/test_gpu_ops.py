@@ -5,6 +5,8 @@ inputs and compares element by element with the oracle:
 max|gpu - ref| <= 1e-4 * max|ref| for fp32 and <= 2e-2 * max|ref| for
 bf16-storage / fp32-accumulate (the oracle is fed the bf16-rounded values).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -575,3 +577,46 @@ def test_fc_gemm_weights_beyond_two_gib(pools, dtype):
     rows = [0, 1, 65, mid - 1, mid, mid + 1, cout - 2, cout - 1]
     ref = x[:, 0].double().cpu().numpy() @ w[rows].double().cpu().numpy().T
     assert rel_err(lg[:, rows].double().cpu().numpy(), ref) <= (2e-5 if es == 2 else 4e-6)
+
+
+WTILE_SHAPES = [
+    # n, h, w, cin, cout, cus: the network's layers, several rounds of tiles on few CUs ...
+    (2, 56, 56, 64, 64, 8), (3, 28, 28, 128, 128, 8), (5, 14, 14, 256, 256, "full"), (9, 7, 7, 512, 512, 64),
+    # ... tiles of one or several images, cut in rows and in columns, with remainders, and single rows and columns
+    (1, 60, 41, 192, 64, 64), (9, 5, 5, 128, 64, 8), (3, 9, 13, 256, 128, "full"), (1, 2, 130, 64, 192, 8), (3, 1, 6, 128, 64, 8),
+    (2, 17, 1, 64, 64, 64), (1, 1, 1, 256, 64, "full")]
+
+
+@pytest.mark.parametrize("ks,shape", [(ks, s) for ks in (1, 2, 4) for s in WTILE_SHAPES if s[3] // 64 % ks == 0], ids=str)
+def test_conv3x3_wtile_parity(pools, ks, shape):
+    """The kernel whose weights come in fragment order (tasks keep such a copy), by its launcher: `ks` wavefronts
+    share a tile.  Weights in fragment order are those of the packed layout, 16 bytes at a time."""
+    n, h, w, cin, cout, cus = shape
+    pool, lib = pools[cus], S.lib()
+    for relu, with_res in ((1, True), (0, False)):
+        x = make_input(98, ks, (n, cin, h, w), bf16=True)
+        wt = make_conv_weight(98, ks, 1, cout, cin, 3, bf16=True)
+        g, b, m, v = make_bn(98, ks, 2, cout)
+        ref = oracle.bn(oracle.conv2d(x, wt, 1, 1), g, b, m, v, BN_EPS)
+        res = make_input(98, ks, ref.shape, bf16=True, tensor_id=7) if with_res else None
+        if with_res:
+            ref = oracle.add(ref, res)
+        if relu:
+            ref = oracle.relu(ref)
+        d = S.ConvDesc(n, h, w, cin, cout, 3, 3, 1, 1, S.SGPRS_BF16, relu)
+        dc = DevConv(d, wt, g, b, m, v, BN_EPS)
+        wf = torch.zeros_like(dc.w)
+        xd = dev_nhwc(x, S.SGPRS_BF16)
+        rd = dev_nhwc(res, S.SGPRS_BF16) if with_res else None
+        yd = dev_empty((n + 1, h, w, cout), S.SGPRS_BF16)
+        torch.cuda.synchronize()
+        ptr = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else None)
+        stream = ctypes.c_void_p(pool.stream(0))
+        assert getattr(lib, "_ZN5sgprs16repack_fragmentsERK17sgprs_conv_desc_tPKvPvP12ihipStream_t")(ctypes.byref(d), ptr(dc.w), ptr(wf), stream) == 0
+        assert getattr(lib, "_ZN5sgprs20launch_conv3x3_wtileERK17sgprs_conv_desc_tiPKvS4_PKfS6_S4_PvP12ihipStream_tiPNS_8ProfilerE")(
+            ctypes.byref(d), ks, ptr(xd), ptr(wf), ptr(dc.scale), ptr(dc.shift), ptr(rd), ptr(yd), stream, pool.partition_cus(0), None) == 0
+        pool.sync()
+        packed = dc.w.cpu().numpy().reshape(cout // 64, 4, 16, 9, cin // 64, 2, 4, 16)  # block, tile, channel, tap, chunk, half, group
+        assert np.array_equal(wf.cpu().numpy().reshape(-1), packed.transpose(0, 4, 3, 5, 1, 6, 2, 7).reshape(-1))
+        assert bool(torch.isnan(yd[n].float()).all())  # nothing is written past the last image
+        assert_close(host_nchw(yd[:n]), ref, S.SGPRS_BF16, f"wtile {ks} {shape}")
