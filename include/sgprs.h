@@ -189,7 +189,7 @@ int sgprs_conv2d_workspace(const sgprs_conv_desc_t *d, int partition_cus, size_t
  * enqueued; the partition is one of sgprs_pool_create's default layout).  family: 0 implicit GEMM, 1 LDS-patch 3x3, 2 stride-2 LDS-patch
  * 3x3, 3 row-streaming 3x3 (64 -> 64 channels, 56-pixel rows), 4 the 7x7 stem;
  * detail: the tile variant (family 0: from 8 on, those that split K over the
- * wavefronts of a workgroup), or the output rows per stream and job of family 3. */
+ * wavefronts of a workgroup, from 16 on with the tile's input pixels in LDS), or the output rows per stream and job of family 3. */
 int sgprs_conv2d_plan(const sgprs_conv_desc_t *d, int partition_cus, int has_residual, int *family,
                       int *detail);
 /* y = act( scale[k] * conv(x, w)[.,k] + shift[k] (+ residual) ).
@@ -208,7 +208,8 @@ int sgprs_conv2d(const sgprs_conv_desc_t *d, const void *x, const void *w_packed
  * automatic, but implicit-GEMM launches use tile variant `variant` (0..3)
  * wherever it divides cout, with split-K factor `splits` (0: planner's choice),
  * and with `variant` 8..15 every 3x3 and 1x1 layer uses that tile of the kernel
- * that splits K over a workgroup's wavefronts;
+ * that splits K over a workgroup's wavefronts, with 16..20 every stride-1 3x3
+ * bf16 layer that tile of the kernel that does so with its pixels in LDS;
  * 3: automatic, plus the stride-2 LDS-patch kernel (not chosen otherwise) with
  * tile variant `variant` (0: 256 rows, 1: 128 rows) wherever the shape allows
  * it; variant 2 switches it off again; 4: automatic, but stage 0 of a bf16
@@ -312,7 +313,8 @@ const void *sgprs_task_stage_output(const sgprs_task_t *task, int stage);
  * sgprs_task_kernel_times returns, for the last run of each stage, one record
  * per launch: HOST arrays of length *count (in: capacity).  kind: 0 conv
  * implicit GEMM (variant 32 and more: K split over the wavefronts of a
- * workgroup; kind 10 likewise), 1 stem conv (variant 4: the fp32 kernel with
+ * workgroup, 96 and more: with the tile's input pixels in LDS; kind 10 up to 95
+ * likewise), 1 stem conv (variant 4: the fp32 kernel with
  * packed input rows), 2 split-K reduce, 3 max-pool, 4 avg-pool, 5 FC (variant 2,
  * 3: avg-pool and FC in one launch; 4, 5: the FC on the matrix cores, fp32, bf16),
  * 6 BN+ReLU, 7 add+ReLU, 8 LDS-patch 3x3 conv, 9 fused stem conv + max-pool

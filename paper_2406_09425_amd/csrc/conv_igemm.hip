@@ -493,6 +493,7 @@ const char* igemm_variant_name(int v)
 {
     static char buf[8][96];
     static int next = 0;
+    if (v >= kKpatchNames) return kpatch_variant_name(v - kKpatchNames);
     if (v >= kKsplitNames) return ksplit_variant_name(v - kKsplitNames);
     if (v < 0 || v >= 32 || (v & 7) >= 4) return "?";
     const int* t = kIgemmShape[v & 7];
@@ -601,6 +602,7 @@ int launch_conv(const sgprs_conv_desc_t& d, const void* x, const void* w, const 
                                     prof);
     if (p.kind == 4)
         return launch_conv_ksplit(d, p.variant, x, w, scale, shift, residual, y, nullptr, nullptr, nullptr, nullptr, nullptr, stream, prof);
+    if (p.kind == 6) return launch_conv3x3_kpatch(d, p.variant, x, w, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 5) return launch_conv3x3_wtile(d, p.variant, x, w_fragments, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 3) return launch_conv3x3_rows(d, p.variant, x, w, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 2) {

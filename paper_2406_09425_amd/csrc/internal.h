@@ -185,7 +185,8 @@ extern std::atomic<int> g_plan_generation;  // bumped whenever a tuning override
 struct ConvPlan {
     int kind = 0;      // 0: implicit GEMM, 1: LDS-patch 3x3 kernel, 2: its stride-2 variant, 3: row streaming,
                        // 4: implicit GEMM with K split over a workgroup's wavefronts,
-                       // 5: weights from the L2 to registers (variant: wavefronts that share a tile)
+                       // 5: weights from the L2 to registers (variant: wavefronts that share a tile),
+                       // 6: K split over a workgroup's wavefronts, input patch in LDS
     int variant = 0;   // index into the kernel's tile table (row streaming: output rows per stream and job)
     int bm = 0, bn = 0;
     int splits = 1;    // split-K factor (grid.z)
@@ -318,6 +319,13 @@ bool wtile_applicable(const sgprs_conv_desc_t& d);
 bool plan_wtile(const sgprs_conv_desc_t& d, int cus, int* ks, double* cost_us);
 int launch_conv3x3_wtile(const sgprs_conv_desc_t& d, int ks, const void* x, const void* w_fragments, const float* scale, const float* shift,
                          const void* res, void* y, hipStream_t stream, int cus, Profiler* prof);
+// 3x3 stride-1 kernel with K split over a workgroup's wavefronts and the tile's input pixels in LDS once (bf16, at most one tile per CU)
+bool kpatch_fits(const sgprs_conv_desc_t& d, int variant);
+bool plan_kpatch(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us);
+constexpr int kKpatchNames = 96;  // recorded as implicit GEMM, variant 96 + tile
+const char* kpatch_variant_name(int variant);
+int launch_conv3x3_kpatch(const sgprs_conv_desc_t& d, int variant, const void* x, const void* w, const float* scale, const float* shift,
+                          const void* res, void* y, hipStream_t stream, int cus, Profiler* prof);
 // tuning override: kind -1 automatic, 0 implicit GEMM only, 1 force patch (variant, splits)
 extern std::atomic<int> g_conv_force_kind;
 extern std::atomic<int> g_igemm_force_variant, g_igemm_force_splits;

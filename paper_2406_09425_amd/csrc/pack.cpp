@@ -77,6 +77,11 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
 {
     const int force_kind = g_conv_force_kind.load(), force_variant = g_igemm_force_variant.load(),
               force_splits = g_igemm_force_splits.load();
+    if (force_variant >= 16 && kpatch_fits(d, force_variant - 16)) {
+        ConvPlan p;
+        p.kind = 6; p.variant = force_variant - 16; p.bm = 1;
+        return p;
+    }
     if (force_variant >= 8 && ksplit_fits(d, force_variant - 8)) {
         ConvPlan p;
         p.kind = 4; p.variant = force_variant - 8; p.bm = 1;
@@ -114,12 +119,17 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
             best.kind = 4; best.variant = v; best.bm = 1;
             best_cost = cost;
         }
+        if (ksplit && force_variant < 0 && force_kind != 1 && plan_kpatch(d, cus, &v, &cost) && cost < best_cost) {
+            best = ConvPlan();
+            best.kind = 6; best.variant = v; best.bm = 1;
+            best_cost = cost;
+        }
         if (fragments && force_kind == -1 && force_variant < 0 && plan_wtile(d, cus, &v, &cost)) {
             // Its estimate holds for the clock that the launch leaves the chip; those of the other two were
             // fitted where few CUs ran, and fall short of what launches on most of the chip take (LDS
             // patches: 12.5 estimated, 12.4 us on 32 CUs, 14.0 on 256; K split: 14.9, 13.2 and 16.9).
             const double chip = std::min(cus, 256) / 256.0, scaled = cost * (1.0 - 0.18 * chip);
-            if ((best.kind == 4 ? cost * (1.02 - 0.15 * chip) : scaled) < best_cost) {
+            if ((best.kind >= 4 ? cost * (1.02 - 0.15 * chip) : scaled) < best_cost) {
                 best = ConvPlan();
                 best.kind = 5; best.variant = v; best.bm = 1;
                 best_cost = scaled;
@@ -348,7 +358,7 @@ int sgprs_conv2d_plan(const sgprs_conv_desc_t* d, int partition_cus, int has_res
     }
     const ConvPlan p = plan_conv(*d, planning_cus(partition_cus), has_residual != 0);
     if (p.bm == 0) return fail(SGPRS_ERR_UNSUPPORTED, "no tile shape fits cout %d", d->cout);
-    *family = p.kind == 4 ? 0 : p.kind; *detail = p.kind == 4 ? 8 + p.variant : p.variant;
+    *family = p.kind == 4 || p.kind == 6 ? 0 : p.kind; *detail = p.kind == 4 ? 8 + p.variant : p.kind == 6 ? 16 + p.variant : p.variant;
     return SGPRS_OK;
 }
 

@@ -620,3 +620,32 @@ def test_conv3x3_wtile_parity(pools, ks, shape):
         assert np.array_equal(wf.cpu().numpy().reshape(-1), packed.transpose(0, 4, 3, 5, 1, 6, 2, 7).reshape(-1))
         assert bool(torch.isnan(yd[n].float()).all())  # nothing is written past the last image
         assert_close(host_nchw(yd[:n]), ref, S.SGPRS_BF16, f"wtile {ks} {shape}")
+
+
+KPATCH_SHAPES = [
+    # the network's layers, several images to a tile, odd maps and channel counts (pixels of an odd number of 128 bytes) ...
+    (1, 56, 56, 64, 64, 3, 1, 1), (1, 14, 14, 256, 256, 3, 1, 1), (3, 7, 7, 512, 512, 3, 1, 1), (5, 3, 2, 64, 64, 3, 1, 1), (2, 9, 13, 192, 128, 3, 1, 1),
+    (1, 1, 1, 320, 64, 3, 1, 1), (1, 2, 90, 64, 192, 3, 1, 1),
+    # ... and windows partly or wholly outside the image
+    (2, 6, 5, 128, 64, 3, 1, 0), (2, 5, 7, 64, 64, 3, 1, 4), (1, 2, 3, 64, 64, 3, 1, 21)]
+
+
+@pytest.mark.parametrize("variant", range(5))
+def test_conv3x3_kpatch_tiles_parity(pools, variant):
+    """Every tile of the kernel that keeps a tile's input pixels in LDS, also where a CU gets more than one of them."""
+    kpatch_fits = getattr(S.lib(), "_ZN5sgprs11kpatch_fitsERK17sgprs_conv_desc_ti")
+    try:
+        S.sgprs_conv_tuning_override(2, 16 + variant, 0)
+        for shape in KPATCH_SHAPES:
+            n, h, w, cin, cout, k, stride, pad = shape
+            pool = pools[8 if cin == 64 else "full"]
+            d = S.ConvDesc(n, h, w, cin, cout, k, k, stride, pad, S.SGPRS_BF16, 1)
+            takes = kpatch_fits(ctypes.byref(d), variant) & 1  # cout, and what the LDS holds beside the weights
+            assert (S.sgprs_conv2d_plan(d, pool.partition_cus(0)) == (0, 16 + variant)) == takes, shape
+            if not takes:
+                continue
+            for with_res in (True, False):
+                got, ref = conv_case(S.SGPRS_BF16, *shape, relu=with_res, with_res=with_res, seed=170 + variant, pool=pool, cus=pool.partition_cus(0))
+                assert_close(got, ref, S.SGPRS_BF16, f"tile {variant} {shape}")
+    finally:
+        S.sgprs_conv_tuning_override(-1, 0, 1)
