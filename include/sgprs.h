@@ -313,8 +313,8 @@ const void *sgprs_task_stage_output(const sgprs_task_t *task, int stage);
  * sgprs_task_kernel_times returns, for the last run of each stage, one record
  * per launch: HOST arrays of length *count (in: capacity).  kind: 0 conv
  * implicit GEMM (variant 32 and more: K split over the wavefronts of a
- * workgroup, 96 and more: with the tile's input pixels in LDS; kind 10 up to 95
- * likewise), 1 stem conv (variant 4: the fp32 kernel with
+ * workgroup, 96 to 103: with the tile's input pixels in LDS, 104 and more: fp32 by
+ * three bf16 planes; kind 10 likewise), 1 stem conv (variant 4: the fp32 kernel with
  * packed input rows), 2 split-K reduce, 3 max-pool, 4 avg-pool, 5 FC (variant 2,
  * 3: avg-pool and FC in one launch; 4, 5: the FC on the matrix cores, fp32, bf16),
  * 6 BN+ReLU, 7 add+ReLU, 8 LDS-patch 3x3 conv, 9 fused stem conv + max-pool

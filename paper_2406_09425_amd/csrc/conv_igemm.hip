@@ -480,6 +480,7 @@ const char* igemm_pair_variant_name(int v)
 {
     static char buf[8][96];
     static int next = 0;
+    if (v >= kSplitNames) return split_variant_name(v - kSplitNames);
     if (v >= kKsplitNames) return ksplit_variant_name(v - kKsplitNames);
     if (v < 0 || v >= 16 || (v & 7) >= 4) return "?";
     const int* t = kIgemmShape[v & 7];
@@ -493,6 +494,7 @@ const char* igemm_variant_name(int v)
 {
     static char buf[8][96];
     static int next = 0;
+    if (v >= kSplitNames) return split_variant_name(v - kSplitNames);
     if (v >= kKpatchNames) return kpatch_variant_name(v - kKpatchNames);
     if (v >= kKsplitNames) return ksplit_variant_name(v - kKsplitNames);
     if (v < 0 || v >= 32 || (v & 7) >= 4) return "?";
@@ -556,14 +558,18 @@ static bool fill_igemm_args(const sgprs_conv_desc_t& d, const ConvPlan& p, const
 // tile without split-K; *done = false (and nothing launched) otherwise.
 int launch_conv_pair(const sgprs_conv_desc_t& d0, const void* w0, const float* scale0, const float* shift0, void* y0,
                      const sgprs_conv_desc_t& d1, const void* w1, const float* scale1, const float* shift1, void* y1,
-                     const void* x, hipStream_t stream, int cus, Profiler* prof, bool* done)
+                     const void* x, hipStream_t stream, int cus, Profiler* prof, bool* done, const void* fragments0, const void* fragments1)
 {
     *done = false;
     if (d0.dtype != d1.dtype || d0.n != d1.n || d0.h != d1.h || d0.w != d1.w || d0.cin != d1.cin) return SGPRS_OK;
-    const ConvPlan p0 = plan_conv_pair(d0, d1, cus);
+    const ConvPlan p0 = plan_conv_pair(d0, d1, cus, fragments0 && fragments1);
     if (p0.bm != 0 && p0.kind == 4 && ksplit_fits(d1, p0.variant) && d1.cout == d0.cout && d1.stride == d0.stride && d1.pad == d1.r / 2 && d0.pad == d0.r / 2) {
         *done = true;
         return launch_conv_ksplit(d0, p0.variant, x, w0, scale0, shift0, nullptr, y0, &d1, w1, scale1, shift1, y1, stream, prof);
+    }
+    if (p0.bm != 0 && p0.kind == 7 && split_fits(d1, p0.variant) && d1.cout == d0.cout && d1.stride == d0.stride && d1.pad == d1.r / 2 && d0.pad == d0.r / 2) {
+        *done = true;
+        return launch_conv_split(d0, p0.variant, x, w0, fragments0, scale0, shift0, nullptr, y0, &d1, w1, fragments1, scale1, shift1, y1, stream, prof);
     }
     ConvPlan p1 = plan_conv(d1, cus, false, false);
     if (p0.bm == 0 || p0.kind != 0 || p0.splits != 1 || p1.bm == 0 || p1.kind != 0) return SGPRS_OK;
@@ -602,6 +608,8 @@ int launch_conv(const sgprs_conv_desc_t& d, const void* x, const void* w, const 
                                     prof);
     if (p.kind == 4)
         return launch_conv_ksplit(d, p.variant, x, w, scale, shift, residual, y, nullptr, nullptr, nullptr, nullptr, nullptr, stream, prof);
+    if (p.kind == 7)
+        return launch_conv_split(d, p.variant, x, w, w_fragments, scale, shift, residual, y, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, stream, prof);
     if (p.kind == 6) return launch_conv3x3_kpatch(d, p.variant, x, w, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 5) return launch_conv3x3_wtile(d, p.variant, x, w_fragments, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 3) return launch_conv3x3_rows(d, p.variant, x, w, scale, shift, residual, y, stream, cus, prof);

@@ -199,7 +199,7 @@ struct ConvPlan {
 // splits K over a workgroup's wavefronts; fragments: the weights are there in fragment order too).
 ConvPlan plan_conv(const sgprs_conv_desc_t& d, int partition_cus, bool has_residual = false, bool ksplit = true, bool fragments = false);
 // The plan of d0 for a launch that also runs the block's shortcut d1 on the same input (same output shape).
-ConvPlan plan_conv_pair(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int partition_cus);
+ConvPlan plan_conv_pair(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int partition_cus, bool fragments);
 size_t conv_workspace_bytes(const sgprs_conv_desc_t& d, const ConvPlan& p);
 
 struct KernelRecord {
@@ -326,6 +326,18 @@ constexpr int kKpatchNames = 96;  // recorded as implicit GEMM, variant 96 + til
 const char* kpatch_variant_name(int variant);
 int launch_conv3x3_kpatch(const sgprs_conv_desc_t& d, int variant, const void* x, const void* w, const float* scale, const float* shift,
                           const void* res, void* y, hipStream_t stream, int cus, Profiler* prof);
+// fp32 by three bf16 planes of every operand, K range split like conv_ksplit's
+bool split_fits(const sgprs_conv_desc_t& d, int variant);
+bool plan_split(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us);
+int split_num_variants();
+double split_cost(const sgprs_conv_desc_t& d, int variant, int cus, const sgprs_conv_desc_t* d1);
+constexpr int kSplitNames = 104;  // recorded as implicit GEMM (or pair), variant 104 + tile
+const char* split_variant_name(int variant);
+size_t split_weight_bytes(const sgprs_conv_desc_t& d);  // of the planes; 0: none for this shape
+int split_weights(const sgprs_conv_desc_t& d, const void* src, void* dst, hipStream_t stream);
+int launch_conv_split(const sgprs_conv_desc_t& d, int variant, const void* x, const void* w, const void* planes, const float* scale, const float* shift,
+                      const void* res, void* y, const sgprs_conv_desc_t* d1, const void* w1, const void* planes1, const float* scale1,
+                      const float* shift1, void* y1, hipStream_t stream, Profiler* prof);
 // tuning override: kind -1 automatic, 0 implicit GEMM only, 1 force patch (variant, splits)
 extern std::atomic<int> g_conv_force_kind;
 extern std::atomic<int> g_igemm_force_variant, g_igemm_force_splits;
@@ -334,7 +346,8 @@ const char* igemm_variant_name(int v);
 const char* igemm_pair_variant_name(int v);
 int launch_conv_pair(const sgprs_conv_desc_t& d0, const void* w0, const float* scale0, const float* shift0, void* y0,
                      const sgprs_conv_desc_t& d1, const void* w1, const float* scale1, const float* shift1, void* y1,
-                     const void* x, hipStream_t stream, int cus, Profiler* prof, bool* done);
+                     const void* x, hipStream_t stream, int cus, Profiler* prof, bool* done, const void* fragments0 = nullptr,
+                     const void* fragments1 = nullptr);
 int igemm_num_variants();
 
 }  // namespace sgprs

@@ -77,6 +77,11 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
 {
     const int force_kind = g_conv_force_kind.load(), force_variant = g_igemm_force_variant.load(),
               force_splits = g_igemm_force_splits.load();
+    if (fragments && force_variant >= 24 && split_fits(d, force_variant - 24)) {
+        ConvPlan p;
+        p.kind = 7; p.variant = force_variant - 24; p.bm = 1;
+        return p;
+    }
     if (force_variant >= 16 && kpatch_fits(d, force_variant - 16)) {
         ConvPlan p;
         p.kind = 6; p.variant = force_variant - 16; p.bm = 1;
@@ -122,6 +127,11 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
         if (ksplit && force_variant < 0 && force_kind != 1 && plan_kpatch(d, cus, &v, &cost) && cost < best_cost) {
             best = ConvPlan();
             best.kind = 6; best.variant = v; best.bm = 1;
+            best_cost = cost;
+        }
+        if (fragments && force_kind == -1 && force_variant < 0 && plan_split(d, cus, &v, &cost) && cost < best_cost) {
+            best = ConvPlan();
+            best.kind = 7; best.variant = v; best.bm = 1;
             best_cost = cost;
         }
         if (fragments && force_kind == -1 && force_variant < 0 && plan_wtile(d, cus, &v, &cost)) {
@@ -200,7 +210,7 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
 // the other way round by 2 us.  Near a tie the K-split kernel is the one that keeps its time inside the
 // network (4 images on 96 CUs, whole inference: 156.0 us with it in the second block, 159.4 with implicit
 // GEMM, whose launch alone is as fast): 5 % in its favour.
-static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int cus)
+static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int cus, bool fragments)
 {
     const ConvPlan single = plan_conv(d0, cus);
     const int P = out_dim(d0.h, d0.r, d0.stride, d0.pad), Q = out_dim(d0.w, d0.s, d0.stride, d0.pad);
@@ -237,18 +247,27 @@ static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs
             best.kind = 4; best.variant = v; best.bm = 1;
         }
     }
+    for (int v = 0; v < split_num_variants() && fragments; ++v) {
+        if (!split_fits(d0, v) || !split_fits(d1, v)) continue;
+        const double cost = split_cost(d0, v, cus, &d1);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = ConvPlan();
+            best.kind = 7; best.variant = v; best.bm = 1;
+        }
+    }
     return best.bm ? best : single;
 }
 
-ConvPlan plan_conv_pair(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int cus)
+ConvPlan plan_conv_pair(const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int cus, bool fragments)
 {
-    struct Key { sgprs_conv_desc_t d0, d1; int cus, gen; };
+    struct Key { sgprs_conv_desc_t d0, d1; int cus, fragments, gen; };
     static thread_local PlanMemo<Key, ConvPlan> local;
     static SharedPlanMemo<Key, ConvPlan> memo;
     Key k;
     memset(&k, 0, sizeof(k));
-    k.d0 = d0; k.d1 = d1; k.cus = cus; k.gen = g_plan_generation.load();
-    return memo.get(local, k, [&]() { return plan_conv_pair_uncached(d0, d1, cus); });
+    k.d0 = d0; k.d1 = d1; k.cus = cus; k.fragments = fragments; k.gen = g_plan_generation.load();
+    return memo.get(local, k, [&]() { return plan_conv_pair_uncached(d0, d1, cus, fragments); });
 }
 
 size_t conv_workspace_bytes(const sgprs_conv_desc_t& d, const ConvPlan& p)
@@ -358,7 +377,8 @@ int sgprs_conv2d_plan(const sgprs_conv_desc_t* d, int partition_cus, int has_res
     }
     const ConvPlan p = plan_conv(*d, planning_cus(partition_cus), has_residual != 0);
     if (p.bm == 0) return fail(SGPRS_ERR_UNSUPPORTED, "no tile shape fits cout %d", d->cout);
-    *family = p.kind == 4 || p.kind == 6 ? 0 : p.kind; *detail = p.kind == 4 ? 8 + p.variant : p.kind == 6 ? 16 + p.variant : p.variant;
+    *family = p.kind == 4 || p.kind >= 6 ? 0 : p.kind;
+    *detail = p.variant + (p.kind == 4 ? 8 : p.kind == 6 ? 16 : p.kind == 7 ? 24 : 0);
     return SGPRS_OK;
 }
 

@@ -41,7 +41,7 @@ constexpr int kFcIn = 512, kFcOut = 1000;
 struct ConvLayer {
     sgprs_conv_desc_t d;
     void* w = nullptr;
-    void* w_fragments = nullptr;  // bf16 3x3 stride-1 layers: the same in fragment order
+    void* w_fragments = nullptr;  // bf16 3x3 stride-1 layers: the same in fragment order; fp32: in three bf16 planes
     float* scale = nullptr;
     float* shift = nullptr;
 };
@@ -194,7 +194,7 @@ int run_block(sgprs_task* t, int c1, int c2, int down, int batch, const void* x,
             paired = true;
         } else if ((rc = launch_conv_pair(d0, t->conv[c1].w, t->conv[c1].scale, t->conv[c1].shift, t->tmp[0], d1,
                                    t->conv[down].w, t->conv[down].scale, t->conv[down].shift, t->tmp[1], x, s, cus, prof,
-                                   &paired)))
+                                   &paired, t->conv[c1].w_fragments, t->conv[down].w_fragments)))
             return rc;
         shortcut = t->tmp[1];
     }
@@ -297,7 +297,7 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
         if ((rc = upload(t, packed.data(), bytes, &t->conv[i].w))) break;
         if ((rc = upload(t, scale.data(), cs.cout * sizeof(float), (void**)&t->conv[i].scale))) break;
         if ((rc = upload(t, shift.data(), cs.cout * sizeof(float), (void**)&t->conv[i].shift))) break;
-        if (wtile_applicable(d)) fragment_bytes += bytes;
+        fragment_bytes += wtile_applicable(d) ? bytes : split_weight_bytes(d);
         if (i == 0 && dtype == SGPRS_BF16) {
             std::vector<uint16_t> rows((size_t)64 * kStemRowsK);
             pack_stem_rows(hp->conv_w[0], rows.data());
@@ -320,9 +320,11 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
         rc = dev_alloc(t, fragment_bytes, &to);
         for (int i = 0; i < SGPRS_RESNET18_CONVS && !rc; ++i) {
             ConvLayer& l = t->conv[i];
-            if (!wtile_applicable(l.d)) continue;
-            size_t bytes = 0;
-            if ((rc = sgprs_conv_packed_weight_bytes(&l.d, &bytes)) || (rc = repack_fragments(l.d, l.w, to, nullptr))) break;
+            size_t bytes = split_weight_bytes(l.d);
+            if (!bytes && !wtile_applicable(l.d)) continue;
+            if (bytes) rc = split_weights(l.d, l.w, to, nullptr);
+            else if (!(rc = sgprs_conv_packed_weight_bytes(&l.d, &bytes))) rc = repack_fragments(l.d, l.w, to, nullptr);
+            if (rc) break;
             l.w_fragments = to;
             to = (unsigned char*)to + bytes;
         }

@@ -649,3 +649,72 @@ def test_conv3x3_kpatch_tiles_parity(pools, variant):
                 assert_close(got, ref, S.SGPRS_BF16, f"tile {variant} {shape}")
     finally:
         S.sgprs_conv_tuning_override(-1, 0, 1)
+
+
+SPLIT_SHAPES = [
+    # n, h, w, cin, cout, k, stride, pad: the network's layers, ragged pixel tiles and channel counts ...
+    (1, 56, 56, 64, 64, 3, 1, 1), (2, 14, 14, 256, 256, 3, 1, 1), (3, 7, 7, 512, 512, 3, 1, 1), (3, 9, 13, 96, 192, 3, 2, 1),
+    # ... fewer k-tiles than wavefronts, shares of one and of odd numbers of them, windows outside the image
+    (1, 5, 3, 32, 64, 1, 2, 0), (1, 11, 7, 160, 64, 1, 1, 0), (1, 1, 1, 32, 128, 3, 1, 1), (2, 5, 7, 64, 64, 3, 1, 4), (1, 3, 2, 64, 64, 3, 2, 33)]
+
+
+def split_case(lib, pool, variant, d, dc, x, res, guard=1):
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else None)
+    p, q = (d.h + 2 * d.pad - d.r) // d.stride + 1, (d.w + 2 * d.pad - d.s) // d.stride + 1
+    planes = torch.zeros(6 * d.cout * d.cin * d.r * d.s, dtype=torch.uint8, device="cuda")
+    y = torch.full((d.n + guard, p, q, d.cout), float("nan"), device="cuda")
+    torch.cuda.synchronize()
+    stream = ctypes.c_void_p(pool.stream(0))
+    assert getattr(lib, "_ZN5sgprs13split_weightsERK17sgprs_conv_desc_tPKvPvP12ihipStream_t")(ctypes.byref(d), ptr(dc.w), ptr(planes), stream) == 0
+    assert getattr(lib, "_ZN5sgprs17launch_conv_splitERK17sgprs_conv_desc_tiPKvS4_S4_PKfS6_S4_PvPS1_S4_S4_S6_S6_S7_P12ihipStream_tPNS_8ProfilerE")(
+        ctypes.byref(d), variant, ptr(x), ptr(dc.w), ptr(planes), ptr(dc.scale), ptr(dc.shift), ptr(res), ptr(y), *[None] * 6, stream, None) == 0
+    pool.sync()
+    assert bool(torch.isnan(y[d.n:]).all())  # nothing is written past the last image
+    return y[:d.n]
+
+
+@pytest.mark.parametrize("variant", range(6))
+def test_conv_split_tiles_parity(pools, variant):
+    """fp32 by three bf16 planes of every operand (tasks keep the weights' planes), by its launcher.  The planes are
+    exact, what is left out stays below 2^-26: the error is held to the line of the fp32 kernel's chains of
+    288 products (see above), over K <= 4608."""
+    lib, pool = S.lib(), pools["full"]
+    fits = getattr(lib, "_ZN5sgprs10split_fitsERK17sgprs_conv_desc_ti")
+    for shape in SPLIT_SHAPES:
+        n, h, w, cin, cout, k, stride, pad = shape
+        for relu, with_res in ((1, True), (0, False)):
+            x, wt = make_input(99, variant, (n, cin, h, w)), make_conv_weight(99, variant, 1, cout, cin, k)
+            g, b, m, v = make_bn(99, variant, 2, cout)
+            ref = oracle.bn(oracle.conv2d(x, wt, stride, pad), g, b, m, v, BN_EPS)
+            res = make_input(99, variant, ref.shape, tensor_id=7) if with_res else None
+            ref = oracle.relu(oracle.add(ref, res)) if with_res else ref
+            d = S.ConvDesc(n, h, w, cin, cout, k, k, stride, pad, S.SGPRS_F32, relu)
+            assert fits(ctypes.byref(d), variant) & 1
+            dc = DevConv(d, wt, g, b, m, v, BN_EPS)
+            y = split_case(lib, pool, variant, d, dc, dev_nhwc(x, S.SGPRS_F32), dev_nhwc(res, S.SGPRS_F32) if with_res else None)
+            got = host_nchw(y)
+            assert_close(got, ref, S.SGPRS_F32, f"split tile {variant} {shape}")
+            e = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+            assert e <= 2.0 ** -24 / 6.0 ** 0.5 * (288 / 2 + 20) ** 0.5, (shape, e)
+
+
+@pytest.mark.parametrize("variant", range(6))
+@pytest.mark.parametrize("what", ["infinities", "rounds to infinity", "tiny", "huge", "zeros"])
+def test_conv_split_where_the_planes_end(pools, variant, what):
+    """Values that three bf16 planes do not hold: the tile is multiplied again with the fp32 MFMAs, and each output
+    is infinite, NaN or accurate as in plain fp32."""
+    gen = torch.Generator().manual_seed(5)
+    x, wt = torch.randn((1, 9, 9, 64), generator=gen), (torch.randn((64, 64, 3, 3), generator=gen) / 24).numpy()
+    if what == "infinities":
+        x[0, 3, 3, 5], x[0, 7, 7, 9], x[0, 1, 8, 0] = float("inf"), -float("inf"), float("nan")
+    elif what == "rounds to infinity":
+        x[0, 3, 3, 5] = 3.4e38
+    else:
+        x *= {"tiny": 1e-36, "huge": 1e30, "zeros": 0.0}[what]
+    d = S.ConvDesc(1, 9, 9, 64, 64, 3, 3, 1, 1, S.SGPRS_F32, 0)
+    one, zero = np.ones(64, np.float32), np.zeros(64, np.float32)
+    y = split_case(S.lib(), pools["full"], variant, d, DevConv(d, wt, one, zero, zero, one, 0.0), x.cuda(), None).double().cpu()
+    ref = torch.nn.functional.conv2d(x.double().permute(0, 3, 1, 2), torch.from_numpy(wt).double(), padding=1).permute(0, 2, 3, 1)
+    finite = torch.isfinite(ref)
+    assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(y[torch.isinf(ref)], ref[torch.isinf(ref)])
+    assert float((y - ref)[finite].norm()) <= 3.1e-7 * float(ref[finite].norm())
