@@ -12,8 +12,12 @@
 //     on its SIMD issues an instruction only every 5 to 6 cycles, which would bound this loop; hence tiles of at most 256
 //     registers, two wavefronts a SIMD, as two workgroups of four or, where tiles are few, one of eight.
 //   * Partial tiles meet in LDS and are added in wavefront order.
-// Infinities, NaNs and what rounds to infinity make the planes' products NaN, and planes below 2^-126 count as 0:
-// a tile with such a sum (not finite, or nonzero below 2^-64) is multiplied again with the fp32 MFMAs.
+// What leaves bf16's range of exponents (planes and products below 2^-126 count as 0) costs a product at most 2^-122
+// if weights are at most 2 and nothing of them is lost.  So a channel's weights are scaled by a power of two to a
+// largest one of 1 to 2, exactly, and its scale the other way; layers where a channel's weights other than 0 lie more
+// than 2^50 apart, or are not finite, keep the fp32 kernels.  K <= 4608 products then lose 2^-109 at most, 2^-29 of a
+// sum of 2^-80.  A tile with a sum that is not finite, or nonzero and smaller, is multiplied again with the fp32
+// MFMAs; so is one with a sum of 0 that reads a pixel value other than 0 below 2^-30 (above, no product is below 2^-80).
 // Error relative to 64 bits, fp32 MFMAs in two to four chains / here: 56x56x64 1.6e-7 / 0.8e-7, 28x28x128 2.2e-7 /
 // 1.0e-7, 14x14x256 3.0e-7 / 1.4e-7, 7x7x512 3.0e-7 / 1.9e-7; 40 random layers: half on average, 0.66 at most.
 // 16 images on 256 CUs, us per launch inside the network, before / now: 56x56x64 40.6 / 31.0, 28x28x128 39.8 / 26.2,
@@ -34,6 +38,8 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
+constexpr int kWeightRange = 50;
+
 // Pixel and channel tiles (of 16), wavefronts that share the K range.
 #define SGPRS_SPLIT_VARIANTS(X) X(0, 4, 2, 4) X(1, 2, 4, 4) X(2, 4, 4, 4) X(3, 4, 2, 8) X(4, 2, 4, 8) X(5, 4, 4, 8)
 constexpr int kSplitShape[][3] = {
@@ -52,6 +58,7 @@ struct SplitArgs {
     const float* shift;
     const unsigned char* res;
     const unsigned char* planes;
+    const float* plane_scale;          // scale for the sums of the planes' products
     unsigned x_bytes, w_bytes, planes_bytes;
     int H, W, Q, PQ, M, Cout;
     int taps, stride, pad;             // filter height and width
@@ -60,7 +67,7 @@ struct SplitArgs {
     unsigned pq_mul, q_mul, ct_mul, place_mul;
     int pq_sh, q_sh, ct_sh, place_sh;
     int gm, gn, die_cols, die_tiles;   // pixel tiles, channel tiles; see below
-    int relu;
+    int relu, unused[2];
 };
 struct SplitLaunch { SplitArgs p[2]; };
 
@@ -120,7 +127,7 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, int mt, int nt)
     const int share = (int)((unsigned)a.ktiles / NW), extra = a.ktiles & (NW - 1);
     const int kt0 = wave * share + min(wave, extra), nkt = share + (wave < extra ? 1 : 0);
     unsigned char* ring = smem + wave * PART;
-    int* again = (int*)(smem + NW * PART);
+    int* found = (int*)(smem + NW * PART);  // see below
 
     // Weights of k-tile j of this wavefront's share: TN x 3 fragments, one coalesced KiB each, into set j % 2.
     u32x4_t pw[2][TN][3];
@@ -133,7 +140,7 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, int mt, int nt)
                 pw[set][c][p] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + p * 1024, (((nt * TN + c) * a.ktiles) + kt0 + j) * 3072, 0);
     };
     load_w(0, 0);
-    if (tid == 0) *again = 0;
+    if (tid < 4) found[tid] = 0;
 
     // Pixels: row of instruction i is i*8 + lane/8; this lane's LDS slot (lane & 7) holds the global 16-byte
     // chunk (lane & 7) ^ (row & 7), which makes the fragment reads bank-conflict free.
@@ -251,7 +258,7 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, int mt, int nt)
         __builtin_amdgcn_s_waitcnt(0);  // the (empty) requests still in flight write LDS too
         __builtin_amdgcn_sched_barrier(0);
         // the epilogue's operands arrive while the partial tiles are exchanged
-        const f32x4_t sc = sp_load<f32x4_t>(a.scale + c0), sh = sp_load<f32x4_t>(a.shift + c0);
+        const f32x4_t sc = sp_load<f32x4_t>((exact ? a.scale : a.plane_scale) + c0), sh = sp_load<f32x4_t>(a.shift + c0);
         f32x4_t rres[PER];
 #pragma unroll
         for (int v = 0; v < PER; ++v) {
@@ -266,21 +273,25 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, int mt, int nt)
 #pragma unroll
             for (int tj = 0; tj < TN; ++tj) *(f32x4_t*)(mine + (ti * 16 + frow) * SROW + tj * 16 + fgrp * 4) = SETS > 1 ? acc[0][ti][tj] + acc[SETS - 1][ti][tj] : acc[0][ti][tj];
         __syncthreads();
-        unsigned largest = 0u, smallest = ~0u;  // of the sums' magnitudes as whole numbers, twice; the smallest but for 0
-#pragma unroll
-        for (int v = 0; v < PER; ++v) {
-            const int item = tid + v * NW * 64, px = item / (BN / 4), c = (item % (BN / 4)) * 4;
-            if (ITEMS % (NW * 64) != 0 && item >= ITEMS) break;
+        auto sum = [&](int px, int c) {
             const float* src = (const float*)smem + px * SROW + c;
             f32x4_t s = *(const f32x4_t*)src;
 #pragma unroll
             for (int w = 1; w < NW; ++w) s += *(const f32x4_t*)(src + w * (PART / 4));
+            return s;
+        };
+        unsigned least = ~0u, most = 0u;  // of the sums' magnitudes as whole numbers, twice, less one: 0 is the largest
+#pragma unroll
+        for (int v = 0; v < PER; ++v) {
+            const int item = tid + v * NW * 64, px = item / (BN / 4), c = (item % (BN / 4)) * 4;
+            if (ITEMS % (NW * 64) != 0 && item >= ITEMS) break;
+            f32x4_t s = sum(px, c);
             if (m0 + px >= a.M) continue;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const unsigned bits = __float_as_uint(s[e]) << 1;
-                largest = max(largest, bits);
-                smallest = min(smallest, bits - 1);
+                const unsigned size = (__float_as_uint(s[e]) << 1) - 1;
+                least = min(least, size);
+                most = max(most, size);
             }
             s = s * sc + sh;
             s += rres[v];
@@ -291,12 +302,45 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, int mt, int nt)
             sp_store(a.y + ((size_t)(m0 + px) * a.Cout + n0 + c) * 4, s);
         }
         if (exact) return;
-        // A value beyond what the planes hold (an infinity, a NaN, a number that rounds to infinity) has made its
-        // products NaN, and planes below 2^-126 count as 0, which a sum below 2^-64 may feel: such a tile is
-        // multiplied again, by the fp32 MFMAs.
-        if (largest >= 0x7f800000u << 1 || smallest < 0x1f800000u << 1) *again = 1;
+        constexpr unsigned kInfinity = 0x7f800000u << 1, kSmallSum = 0x17800000u << 1, kSmallPixel = 0x30800000u << 1;
+        if (most >= kInfinity - 1 || least < kSmallSum - 1) found[0] = 1;
         __syncthreads();
-        if (!*again) return;
+        if (!found[0]) return;
+        // Rare: which of the two it is, a sum of 0 (of a channel that has weights) or one that the planes cannot hold.
+#pragma nounroll
+        for (int v = 0; v < PER; ++v) {
+            const int item = tid + v * NW * 64, px = item / (BN / 4), c = (item % (BN / 4)) * 4;
+            if ((ITEMS % (NW * 64) != 0 && item >= ITEMS) || m0 + px >= a.M) break;
+            const f32x4_t s = sum(px, c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const unsigned size = __float_as_uint(s[e]) << 1;
+                if (size == 0 ? sc[e] != 0.f : size >= kInfinity || size < kSmallSum) found[size == 0 ? 2 : 1] = 1;
+            }
+        }
+        __syncthreads();
+        if (!found[1]) {
+            if (!found[2]) return;
+            // Sums of 0 are rare but where all pixels are 0, which this finds out in a part of the products' time.
+            least = ~0u;
+            first_tap();
+            for (int t = 0; t < nkt; t += 2) {  // (past the share: zeros)
+                request(t, 0);
+                request(t + 1, 1);
+                sp_wait_vmcnt<0>();
+#pragma unroll
+                for (int i = 0; i < 2 * TM; ++i) {
+                    const Raw px = read_px(i / TM, i % TM);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) least = min(least, (__float_as_uint(px.v[e / 4][e % 4]) << 1) - 1);
+                }
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the stages may be overwritten
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (least < kSmallPixel) found[3] = 1;
+            __syncthreads();
+            if (!found[3]) return;
+        }
         clear();
         first_tap();
         const unsigned w_row = (unsigned)(n0 + frow) * a.w_row_bytes + fgrp * 16;
@@ -327,15 +371,57 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, int mt, int nt)
 }
 
 // ---- weights in planes --------------------------------------------------------------
+// Exponent of every output channel's largest weight, and the channel's scale with it (0 where all weights are 0);
+// *unfit where the planes do not hold a channel's weights (see above) or that scale leaves the normal range.
+__global__ __launch_bounds__(256) void weight_exponents_kernel(const f32x4_t* src, const float* scale, float* plane_scale, int* exponents, int* unfit, int quads)
+{
+    unsigned largest = 0u, least = ~0u;  // magnitudes as whole numbers; the least one but for 0, less one
+    for (int i = threadIdx.x; i < quads; i += 256) {
+        const f32x4_t v = src[(size_t)blockIdx.x * quads + i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned bits = __float_as_uint(v[e]) & 0x7fffffffu;
+            largest = max(largest, bits);
+            least = min(least, bits - 1);
+        }
+    }
+    __shared__ unsigned of_wave[4][2];
+#pragma unroll
+    for (int o = 32; o > 0; o /= 2) {
+        largest = max(largest, (unsigned)__shfl_xor((int)largest, o));
+        least = min(least, (unsigned)__shfl_xor((int)least, o));
+    }
+    if (threadIdx.x % 64 == 0) { of_wave[threadIdx.x / 64][0] = largest; of_wave[threadIdx.x / 64][1] = least; }
+    __syncthreads();
+    if (threadIdx.x) return;
+    for (int w = 1; w < 4; ++w) { largest = max(largest, of_wave[w][0]); least = min(least, of_wave[w][1]); }
+    int exponent = 0;
+    float scaled = 0.f;
+    if (largest >= 0x7f800000u) {
+        *unfit = 1;
+    } else if (largest) {
+        exponent = ilogbf(__uint_as_float(largest));
+        scaled = scale[blockIdx.x];
+        const int scaled_exponent = scaled == 0.f ? 0 : ilogbf(scaled) + exponent;  // (an infinity's and a NaN's lie outside too)
+        if (ilogbf(__uint_as_float(least + 1)) < exponent - kWeightRange || scaled_exponent < -126 || scaled_exponent > 126) *unfit = 1;
+        scaled = ldexpf(scaled, exponent);
+    }
+    exponents[blockIdx.x] = exponent;
+    plane_scale[blockIdx.x] = scaled;
+}
+
 // From [cout][tap][cin] fp32 to [cout / 16][tap][cin / 32][plane][lane][16 bytes]: lane l of a fragment holds, of
 // channel l % 16, floats 4g .. 4g + 3 and 16 + 4g .. 16 + 4g + 3 of the 32, g = l / 16.
-__global__ void split_weights_kernel(const f32x4_t* src, u32x4_t* dst, int ktiles, int units)
+__global__ void split_weights_kernel(const f32x4_t* src, u32x4_t* dst, const int* exponents, int ktiles, int units)
 {
     const int u = blockIdx.x * 256 + threadIdx.x;
     if (u >= units) return;
     const int lane = u & 63, rest = u >> 6, kt = rest % ktiles, row = rest / ktiles * 16 + (lane & 15);
     const f32x4_t* from = src + ((size_t)row * ktiles + kt) * 8 + (lane >> 4);
     f32x4_t r[2] = {from[0], from[4]};
+    const int exponent = exponents[row];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e / 4][e % 4] = ldexpf(r[e / 4][e % 4], -exponent);
     u32x4_t d[3];
 #pragma unroll
     for (int o = 0; o < kSplitOps; ++o) split_op(d, r, o);
@@ -343,17 +429,24 @@ __global__ void split_weights_kernel(const f32x4_t* src, u32x4_t* dst, int ktile
     for (int p = 0; p < 3; ++p) dst[((size_t)rest * 3 + p) * 64 + lane] = d[p];
 }
 
-size_t split_weight_bytes(const sgprs_conv_desc_t& d)
+static size_t plane_bytes(const sgprs_conv_desc_t& d)
 {
     const long long bytes = 6ll * d.cout * d.r * d.s * d.cin;
     return is_igemm(d) && d.dtype == SGPRS_F32 && d.cout % 16 == 0 && bytes < (1ll << 31) ? (size_t)bytes : 0;
 }
 
-int split_weights(const sgprs_conv_desc_t& d, const void* src, void* dst, hipStream_t stream)
+size_t split_weight_bytes(const sgprs_conv_desc_t& d) { return plane_bytes(d) ? plane_bytes(d) + d.cout * (sizeof(float) + sizeof(int)) : 0; }
+
+int split_weights(const sgprs_conv_desc_t& d, const void* src, const float* scale, void* dst, int* unfit, hipStream_t stream)
 {
     if (!split_weight_bytes(d)) return fail(SGPRS_ERR_INVALID_ARG, "internal: no planes for this shape");
     const int units = d.cout * d.r * d.s * (d.cin / 8);
-    hipLaunchKernelGGL(split_weights_kernel, dim3((units + 255) / 256), dim3(256), 0, stream, (const f32x4_t*)src, (u32x4_t*)dst, d.r * d.s * d.cin / 32, units);
+    float* plane_scale = (float*)((unsigned char*)dst + plane_bytes(d));
+    int* exponents = (int*)(plane_scale + d.cout);
+    hipLaunchKernelGGL(weight_exponents_kernel, dim3(d.cout), dim3(256), 0, stream, (const f32x4_t*)src, scale, plane_scale, exponents, unfit, d.r * d.s * d.cin / 4);
+    SGPRS_HIP(hipGetLastError());
+    hipLaunchKernelGGL(split_weights_kernel, dim3((units + 255) / 256), dim3(256), 0, stream, (const f32x4_t*)src, (u32x4_t*)dst, exponents,
+                       d.r * d.s * d.cin / 32, units);
     SGPRS_HIP(hipGetLastError());
     return SGPRS_OK;
 }
@@ -454,6 +547,7 @@ static int fill(const sgprs_conv_desc_t& d, int variant, const void* x, const vo
     memset(&a, 0, sizeof(a));
     a.x = (const unsigned char*)x; a.w = (const unsigned char*)w; a.y = (unsigned char*)y;
     a.scale = scale; a.shift = shift; a.res = (const unsigned char*)res; a.planes = (const unsigned char*)planes;
+    a.plane_scale = (const float*)(a.planes + plane_bytes(d));
     const int P = out_dim(d.h, d.r, d.stride, d.pad);
     a.H = d.h; a.W = d.w; a.Cout = d.cout; a.Q = out_dim(d.w, d.s, d.stride, d.pad);
     a.taps = d.r; a.stride = d.stride; a.pad = d.pad; a.relu = d.relu;
@@ -466,7 +560,7 @@ static int fill(const sgprs_conv_desc_t& d, int variant, const void* x, const vo
     const long long xb = (long long)d.n * d.h * d.w * d.cin * 4, wb = (long long)d.cout * d.r * d.s * d.cin * 4;
     if (!split_fits(d, variant) || d.r > 3 || d.s != d.r || d.cin % 32 || xb >= (1ll << 31) || wb >= (1ll << 31))
         return fail(SGPRS_ERR_INVALID_ARG, "internal: launch plan does not match the shape");
-    a.x_bytes = (unsigned)xb; a.w_bytes = (unsigned)wb; a.planes_bytes = (unsigned)split_weight_bytes(d);
+    a.x_bytes = (unsigned)xb; a.w_bytes = (unsigned)wb; a.planes_bytes = (unsigned)plane_bytes(d);
     a.gm = (a.M + 16 * t[0] - 1) / (16 * t[0]); a.gn = d.cout / (16 * t[1]);
     a.die_cols = a.gn % 8 == 0 ? a.gn / 8 : 0;
     a.die_tiles = (a.gm * a.gn + 7) / 8;

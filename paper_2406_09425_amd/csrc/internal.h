@@ -333,8 +333,9 @@ int split_num_variants();
 double split_cost(const sgprs_conv_desc_t& d, int variant, int cus, const sgprs_conv_desc_t* d1);
 constexpr int kSplitNames = 104;  // recorded as implicit GEMM (or pair), variant 104 + tile
 const char* split_variant_name(int variant);
-size_t split_weight_bytes(const sgprs_conv_desc_t& d);  // of the planes; 0: none for this shape
-int split_weights(const sgprs_conv_desc_t& d, const void* src, void* dst, hipStream_t stream);
+size_t split_weight_bytes(const sgprs_conv_desc_t& d);  // of the planes and what belongs to them; 0: none for this shape
+// sets *unfit (device memory) where the planes do not hold the weights
+int split_weights(const sgprs_conv_desc_t& d, const void* src, const float* scale, void* dst, int* unfit, hipStream_t stream);
 int launch_conv_split(const sgprs_conv_desc_t& d, int variant, const void* x, const void* w, const void* planes, const float* scale, const float* shift,
                       const void* res, void* y, const sgprs_conv_desc_t* d1, const void* w1, const void* planes1, const float* scale1,
                       const float* shift1, void* y1, hipStream_t stream, Profiler* prof);

@@ -41,7 +41,7 @@ constexpr int kFcIn = 512, kFcOut = 1000;
 struct ConvLayer {
     sgprs_conv_desc_t d;
     void* w = nullptr;
-    void* w_fragments = nullptr;  // bf16 3x3 stride-1 layers: the same in fragment order; fp32: in three bf16 planes
+    void* w_fragments = nullptr;  // bf16 3x3 stride-1 layers: the same in fragment order; fp32: in three bf16 planes, where these hold them
     float* scale = nullptr;
     float* shift = nullptr;
 };
@@ -317,20 +317,25 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
     if (!rc && hp->fc_b) rc = upload(t, hp->fc_b, kFcOut * sizeof(float), (void**)&t->fc_b);
     if (!rc && fragment_bytes) {
         void* to = nullptr;
-        rc = dev_alloc(t, fragment_bytes, &to);
+        int unfit[SGPRS_RESNET18_CONVS] = {};
+        rc = dev_alloc(t, fragment_bytes + sizeof(unfit), &to);
+        int* const dev_unfit = rc ? nullptr : (int*)((unsigned char*)to + fragment_bytes);
+        if (!rc && hipMemcpy(dev_unfit, unfit, sizeof(unfit), hipMemcpyHostToDevice) != hipSuccess) rc = fail(SGPRS_ERR_HIP, "packing the weights failed");
         for (int i = 0; i < SGPRS_RESNET18_CONVS && !rc; ++i) {
             ConvLayer& l = t->conv[i];
             size_t bytes = split_weight_bytes(l.d);
             if (!bytes && !wtile_applicable(l.d)) continue;
-            if (bytes) rc = split_weights(l.d, l.w, to, nullptr);
+            if (bytes) rc = split_weights(l.d, l.w, l.scale, to, dev_unfit + i, nullptr);
             else if (!(rc = sgprs_conv_packed_weight_bytes(&l.d, &bytes))) rc = repack_fragments(l.d, l.w, to, nullptr);
             if (rc) break;
             l.w_fragments = to;
             to = (unsigned char*)to + bytes;
         }
+        // partition streams are not ordered after the null stream: this copy waits for it
+        if (!rc && hipMemcpy(unfit, dev_unfit, sizeof(unfit), hipMemcpyDeviceToHost) != hipSuccess) rc = fail(SGPRS_ERR_HIP, "packing the weights failed");
+        for (int i = 0; i < SGPRS_RESNET18_CONVS && !rc; ++i)
+            if (unfit[i]) t->conv[i].w_fragments = nullptr;
     }
-    // partition streams are not ordered after the null stream
-    if (!rc && hipStreamSynchronize(nullptr) != hipSuccess) rc = fail(SGPRS_ERR_HIP, "packing the weights failed");
     const size_t es = dtype_size(dtype);
     if (!rc) rc = dev_alloc(t, (size_t)max_batch * 112 * 112 * 64 * es, &t->stem_out);
     for (int i = 0; i < 3 && !rc; ++i) rc = dev_alloc(t, (size_t)max_batch * 56 * 56 * 64 * es, &t->tmp[i]);

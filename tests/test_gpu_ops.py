@@ -658,14 +658,25 @@ SPLIT_SHAPES = [
     (1, 5, 3, 32, 64, 1, 2, 0), (1, 11, 7, 160, 64, 1, 1, 0), (1, 1, 1, 32, 128, 3, 1, 1), (2, 5, 7, 64, 64, 3, 1, 4), (1, 3, 2, 64, 64, 3, 2, 33)]
 
 
+def split_planes(lib, pool, d, dc):
+    """The weights' planes with their scales and exponents, and whether the planes do not hold the weights."""
+    planes = torch.zeros(6 * d.cout * d.cin * d.r * d.s + 8 * d.cout, dtype=torch.uint8, device="cuda")
+    unfit = torch.zeros(1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    assert getattr(lib, "_ZN5sgprs13split_weightsERK17sgprs_conv_desc_tPKvPKfPvPiP12ihipStream_t")(
+        ctypes.byref(d), ctypes.c_void_p(dc.w.data_ptr()), ctypes.c_void_p(dc.scale.data_ptr()), ctypes.c_void_p(planes.data_ptr()), ctypes.c_void_p(unfit.data_ptr()), ctypes.c_void_p(pool.stream(0))) == 0
+    pool.sync()
+    return planes, bool(unfit.item())
+
+
 def split_case(lib, pool, variant, d, dc, x, res, guard=1):
     ptr = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else None)
     p, q = (d.h + 2 * d.pad - d.r) // d.stride + 1, (d.w + 2 * d.pad - d.s) // d.stride + 1
-    planes = torch.zeros(6 * d.cout * d.cin * d.r * d.s, dtype=torch.uint8, device="cuda")
+    planes, unfit = split_planes(lib, pool, d, dc)
+    assert not unfit
     y = torch.full((d.n + guard, p, q, d.cout), float("nan"), device="cuda")
     torch.cuda.synchronize()
     stream = ctypes.c_void_p(pool.stream(0))
-    assert getattr(lib, "_ZN5sgprs13split_weightsERK17sgprs_conv_desc_tPKvPvP12ihipStream_t")(ctypes.byref(d), ptr(dc.w), ptr(planes), stream) == 0
     assert getattr(lib, "_ZN5sgprs17launch_conv_splitERK17sgprs_conv_desc_tiPKvS4_S4_PKfS6_S4_PvPS1_S4_S4_S6_S6_S7_P12ihipStream_tPNS_8ProfilerE")(
         ctypes.byref(d), variant, ptr(x), ptr(dc.w), ptr(planes), ptr(dc.scale), ptr(dc.shift), ptr(res), ptr(y), *[None] * 6, stream, None) == 0
     pool.sync()
@@ -698,23 +709,54 @@ def test_conv_split_tiles_parity(pools, variant):
             assert e <= 2.0 ** -24 / 6.0 ** 0.5 * (288 / 2 + 20) ** 0.5, (shape, e)
 
 
+PLANES_END = {  # factors of pixels and weights
+    "infinities": (1.0, 1.0), "rounds to infinity": (1.0, 1.0), "tiny": (1e-36, 1.0), "huge": (1e30, 1.0), "zeros": (0.0, 1.0),
+    # pixels whose lower planes, or all of them, are lost below 2^-126, with weights that make ordinary sums of them ...
+    "tiny, huge weights": (2.0 ** -116, 2.0 ** 60), "subnormal, huge weights": (2.0 ** -128, 2.0 ** 80), "lost, huge weights": (2.0 ** -141, 2.0 ** 60),
+    "few and lost": (2.0 ** -141, 2.0 ** 60), "subnormal": (1e-39, 2.0 ** 20),
+    # ... and the reverse
+    "huge, tiny weights": (1e30, 1e-36), "huge, subnormal weights": (1e30, 1e-39), "large, tiny weights": (1e20, 1e-35), "dead filters": (1.0, 1.0)}
+
+
 @pytest.mark.parametrize("variant", range(6))
-@pytest.mark.parametrize("what", ["infinities", "rounds to infinity", "tiny", "huge", "zeros"])
+@pytest.mark.parametrize("what", PLANES_END)
 def test_conv_split_where_the_planes_end(pools, variant, what):
-    """Values that three bf16 planes do not hold: the tile is multiplied again with the fp32 MFMAs, and each output
-    is infinite, NaN or accurate as in plain fp32."""
+    """Values that three bf16 planes do not hold: a channel's weights are scaled, or the tile is multiplied again with
+    the fp32 MFMAs, and each output is infinite, NaN or accurate as in plain fp32."""
     gen = torch.Generator().manual_seed(5)
-    x, wt = torch.randn((1, 9, 9, 64), generator=gen), (torch.randn((64, 64, 3, 3), generator=gen) / 24).numpy()
+    x, wt = torch.randn((1, 9, 9, 64), generator=gen) * PLANES_END[what][0], (torch.randn((64, 64, 3, 3), generator=gen) / 24 * PLANES_END[what][1]).numpy()
     if what == "infinities":
         x[0, 3, 3, 5], x[0, 7, 7, 9], x[0, 1, 8, 0] = float("inf"), -float("inf"), float("nan")
     elif what == "rounds to infinity":
         x[0, 3, 3, 5] = 3.4e38
-    else:
-        x *= {"tiny": 1e-36, "huge": 1e30, "zeros": 0.0}[what]
+    elif what == "few and lost":
+        x[0, :, :, 1:], x[0, 4:] = 0.0, 0.0
+    elif what == "dead filters":
+        wt[[7, 40]] *= np.float32(1e-30)
+        wt[[9, 63]] = 0.0
     d = S.ConvDesc(1, 9, 9, 64, 64, 3, 3, 1, 1, S.SGPRS_F32, 0)
     one, zero = np.ones(64, np.float32), np.zeros(64, np.float32)
-    y = split_case(S.lib(), pools["full"], variant, d, DevConv(d, wt, one, zero, zero, one, 0.0), x.cuda(), None).double().cpu()
+    scale = np.float32(2.0 ** 60) * one if what == "huge, subnormal weights" else one
+    y = split_case(S.lib(), pools["full"], variant, d, DevConv(d, wt, scale, zero, zero, one, 0.0), x.cuda(), None).double().cpu() / float(scale[0])
     ref = torch.nn.functional.conv2d(x.double().permute(0, 3, 1, 2), torch.from_numpy(wt).double(), padding=1).permute(0, 2, 3, 1)
     finite = torch.isfinite(ref)
     assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(y[torch.isinf(ref)], ref[torch.isinf(ref)])
-    assert float((y - ref)[finite].norm()) <= 3.1e-7 * float(ref[finite].norm())
+    for c in ([7, 40], [9, 63], slice(None)):
+        assert float((y - ref)[..., c][finite[..., c]].norm()) <= 3.1e-7 * float(ref[..., c][finite[..., c]].norm())
+
+
+def test_weights_that_the_planes_do_not_hold(pools):
+    """Told when the planes are made: a channel's weights more than 2^50 apart, or not finite, or a scale that
+    the weights' exponent takes out of the normal range."""
+    d = S.ConvDesc(1, 9, 9, 64, 64, 3, 3, 1, 1, S.SGPRS_F32, 0)
+    one, zero = np.ones(64, np.float32), np.zeros(64, np.float32)
+    base = np.random.default_rng(3).uniform(0.5, 1.0, (64, 64, 3, 3)).astype(np.float32)
+    for value, want in ((0.0, False), (2.0 ** -50, False), (-2.0 ** -50, False), (2.0 ** -52, True), (2.0 ** 51, True), (2.0 ** 127, True),
+                        (1e-45, True), (np.inf, True), (np.nan, True)):
+        for where in ((0, 0, 0, 0), (63, 63, 2, 2), (31, 17, 1, 0)):
+            wt = base.copy()
+            wt[where] = value
+            assert split_planes(S.lib(), pools["full"], d, DevConv(d, wt, one, zero, zero, one, 0.0))[1] == want, (value, where)
+    for scale, factor, want in ((1.0, 1e-30, False), (1.0, 1e-42, True), (1e38, 1e-42, False), (1.0, 0.0, False), (1e-45, 0.0, False),
+                                (0.0, 1e30, False), (2.0 ** 90, 2.0 ** 9, False), (2.0 ** 90, 2.0 ** 38, True), (-1e-38, 1.0, True)):
+        assert split_planes(S.lib(), pools["full"], d, DevConv(d, base * np.float32(factor), one * np.float32(scale), zero, zero, one, 0.0))[1] == want, (scale, factor)

@@ -212,6 +212,41 @@ def test_paired_launch_families_parity(cfg1, dtype, n):
         task.destroy()
 
 
+@pytest.mark.parametrize("what", ["tiny pixels, huge weights", "huge pixels, tiny weights", "one weight far below the others"])
+def test_fp32_layers_of_extreme_weights(cfg1, what):
+    """A layer whose weights and pixels are far from 1, in both directions, with a BN that brings its sums back: as
+    accurate as any other.  Where a channel's weights lie so far apart that three bf16 planes do not hold
+    them, the layer keeps the fp32 kernels (kernel name recorded by the task)."""
+    n, cus = 4, 64
+    params = {k: [a.copy() for a in v] if isinstance(v, list) else v for k, v in cfg1[0].items()}
+    x = np.maximum(make_input(n, 50, (n, 64, 56, 56)), 0.0)
+    xf, wf = {"tiny pixels, huge weights": (2.0 ** -128, 2.0 ** 80), "huge pixels, tiny weights": (2.0 ** 90, 2.0 ** -116)}.get(what, (1.0, 1.0))
+    x *= np.float32(xf)
+    params["conv_w"][1] *= np.float32(wf)
+    params["mean"][1] *= np.float32(xf * wf)
+    params["gamma"][1] *= np.float32(1 / (xf * wf))
+    if xf > 1:  # the block's residual too
+        for key in ("gamma", "beta"):
+            params[key][2] *= np.float32(xf)
+    if what.startswith("one"):
+        params["conv_w"][1][5, 6, 1, 1] = 1e-30
+    task = S.Task(params, S.SGPRS_F32, n, BN_EPS)
+    task.set_profiling(True)
+    pool = S.Pool(1, cus)
+    try:
+        o = dev_empty(stage_shape(1, n), S.SGPRS_F32)
+        xd = dev_nhwc(x, S.SGPRS_F32)
+        task.stage_run(1, n, xd.data_ptr(), o.data_ptr(), pool, 0)
+        pool.sync()
+        split = ["conv_split" in r["name"] for r in task.kernel_times(1)]
+        assert split == [not what.startswith("one"), True, True, True]
+        got, ref = host_nchw(o), oracle.resnet18_stage(1, params, BN_EPS, x)
+        assert np.linalg.norm(got - ref) <= 1e-6 * np.linalg.norm(ref)
+    finally:
+        task.destroy()
+        pool.destroy()
+
+
 def test_stage0_fp32_fused_stem_pool_elementwise(cfg1):
     """fp32 launches of at least one 7x8 tile of pooled pixels per CU take the fused conv7x7 + max-pool
     kernel (kind 9): its stage-0 output, element by element against the oracle, on 8 and 64 CUs, with a
