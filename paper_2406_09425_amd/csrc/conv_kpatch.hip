@@ -355,12 +355,15 @@ static bool kpatch_tile_shape(const sgprs_conv_desc_t& d, int v, int tw, KpatchT
 
 // Estimated time (us) where every CU gets at most one tile: launch, a tile's chain, its k-tiles per wavefront,
 // and its bytes at the 120 GB/s that a CU gets out of the L2.  Fitted to 27 launches of the network's layers (1 to
-// 8 images, 32 to 256 CUs): 3 % off rms.
+// 8 images, 32 to 256 CUs): 3 % off rms.  The 32x16 tile takes 0.55 us more where the longest share ends inside a
+// half of the ring: 22 drawn layers of 384 channels, 7 k-tiles a share, were estimated 9 % faster than
+// conv_ksplit_kernel and took 0.97 to 1.07 of its time (3 images of 24x15 on 248 CUs 5.57 us against 5.22).
 static double kpatch_cost(const sgprs_conv_desc_t& d, int v, const KpatchTile& t)
 {
     static const double kChain[kKpatchVariants] = {3.35, 3.6, 3.25, 3.6, 4.1}, kPerKtile[kKpatchVariants] = {0.0, 0.04, 0.08, 0.18, 0.3};
     const double kt = 9.0 * d.cin / 64, bytes = kt * 128 * 16 * kKpatchShape[v].tn + (double)t.rows * t.pw * d.cin * 2;
-    return kChain[v] + kPerKtile[v] * kt / kKpatchWaves + bytes / 120e3;
+    const int share = (9 * d.cin / 64 + kKpatchWaves - 1) / kKpatchWaves;
+    return kChain[v] + kPerKtile[v] * kt / kKpatchWaves + bytes / 120e3 + (v == 1 && share % kKpatchShape[v].h ? 0.55 : 0.0);
 }
 
 // Variant v's best tile: fewest tiles where a CU would get more than one (tests force such launches), least time otherwise.

@@ -54,3 +54,9 @@ def test_planner_takes_it_for_one_tile_per_cu(n, h, c):
             assert family != 0 or detail < 16
     if (n, h) == (1, 7):  # 49 pixels, 2 x 32 tiles
         assert S.sgprs_conv2d_plan(S.ConvDesc(1, 7, 7, 512, 512, 3, 3, 1, 1, S.SGPRS_BF16, 1), 64) == (0, 17)
+
+
+@pytest.mark.parametrize("n,h,w,cout,cus", [(3, 24, 15, 64, 248), (2, 12, 14, 192, 224), (8, 5, 6, 64, 32)])
+def test_planner_leaves_it_where_a_share_ends_inside_a_half(n, h, w, cout, cus):
+    """384 channels are 54 k-tiles, 7 in a wavefront's share, 3 in half a ring."""
+    assert S.sgprs_conv2d_plan(S.ConvDesc(n, h, w, 384, cout, 3, 3, 1, 1, S.SGPRS_BF16, 1), cus, True) != (0, 17)
