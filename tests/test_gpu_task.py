@@ -181,8 +181,9 @@ def test_downsample_block_runs_as_one_paired_launch(cfg1):
 @pytest.mark.parametrize("n", [1, 5, 20])
 @pytest.mark.parametrize("dtype", [S.SGPRS_F32, S.SGPRS_BF16], ids=DT_ID.get)
 def test_paired_launch_families_parity(cfg1, dtype, n):
-    """The down-sampling blocks with the pair's own plan (small, middle and large partition: both kernel
-    families are chosen over these) and with every tile of both families forced, against the oracle."""
+    """The down-sampling blocks with the pair's own plan (small, middle and large partition: two kernel families are
+    chosen over these, over the batches all three for fp32) and with every tile of the two families that can be
+    forced, against the oracle."""
     params = cfg1[0]
     total = S.Pool(1, 8).info()["total_cus"]
     task = S.Task(params, dtype, n, BN_EPS)
@@ -204,9 +205,10 @@ def test_paired_launch_families_parity(cfg1, dtype, n):
                 if override[0] < 0:
                     pair = [k for k in task.kernel_times(j) if k["kind"] == 10]
                     assert len(pair) == 1
-                    seen.add("ksplit" in pair[0]["name"])
+                    seen.add(pair[0]["name"].split("<")[0])
                 pool.destroy()
-        assert n != 5 or seen == {True, False}
+        third = "conv_ksplit_kernel" if n < 20 else "conv_igemm_pair_kernel"
+        assert seen == ({"conv_split_kernel", third} if dtype == S.SGPRS_F32 else {"conv_igemm_pair_kernel", "conv_ksplit_kernel"})
     finally:
         S.sgprs_conv_tuning_override(-1, 0, 1)
         task.destroy()
