@@ -40,8 +40,8 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWeightRange = 50;
 
-// Pixel and channel tiles (of 16), wavefronts that share the K range.
-#define SGPRS_SPLIT_VARIANTS(X) X(0, 4, 2, 4) X(1, 2, 4, 4) X(2, 4, 4, 4) X(3, 4, 2, 8) X(4, 2, 4, 8) X(5, 4, 4, 8)
+// Pixel and channel tiles (of 16), wavefronts that share the K range (tiles of 32 channels were never the best of a layer).
+#define SGPRS_SPLIT_VARIANTS(X) X(0, 2, 4, 4) X(1, 4, 4, 4) X(2, 2, 4, 8) X(3, 4, 4, 8)
 constexpr int kSplitShape[][3] = {
 #define X(v, tm, tn, nw) {tm, tn, nw},
     SGPRS_SPLIT_VARIANTS(X)
@@ -510,7 +510,7 @@ bool split_fits(const sgprs_conv_desc_t& d, int v)
 // the network's layers, 2 to 16 images, 64 to 256 CUs (within 10 % but for a few at 15 %).
 double split_cost(const sgprs_conv_desc_t& d, int v, int cus, const sgprs_conv_desc_t* d1)
 {
-    static const double kFixed[kSplitVariants] = {4.6, 4.3, 5.4, 6.0, 4.3, 6.4}, kPerKtile[kSplitVariants] = {0.79, 0.72, 0.985, 1.19, 1.155, 1.64};
+    static const double kFixed[kSplitVariants] = {4.3, 5.4, 4.3, 6.4}, kPerKtile[kSplitVariants] = {0.72, 0.985, 1.155, 1.64};
     const int tm = kSplitShape[v][0], tn = kSplitShape[v][1], nw = kSplitShape[v][2];
     const long long M = (long long)d.n * out_dim(d.h, d.r, d.stride, d.pad) * out_dim(d.w, d.s, d.stride, d.pad);
     const long long wgs = (M + 16 * tm - 1) / (16 * tm) * (d.cout / (16 * tn)), rounds = (wgs + cus - 1) / cus;

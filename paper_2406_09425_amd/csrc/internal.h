@@ -186,7 +186,8 @@ struct ConvPlan {
     int kind = 0;      // 0: implicit GEMM, 1: LDS-patch 3x3 kernel, 2: its stride-2 variant, 3: row streaming,
                        // 4: implicit GEMM with K split over a workgroup's wavefronts,
                        // 5: weights from the L2 to registers (variant: wavefronts that share a tile),
-                       // 6: K split over a workgroup's wavefronts, input patch in LDS
+                       // 6: K split over a workgroup's wavefronts, input patch in LDS,
+                       // 7: fp32 by three bf16 planes of every operand (5 and 7 only where the weights are there in fragment order)
     int variant = 0;   // index into the kernel's tile table (row streaming: output rows per stream and job)
     int bm = 0, bn = 0;
     int splits = 1;    // split-K factor (grid.z)

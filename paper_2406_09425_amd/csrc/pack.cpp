@@ -77,11 +77,6 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
 {
     const int force_kind = g_conv_force_kind.load(), force_variant = g_igemm_force_variant.load(),
               force_splits = g_igemm_force_splits.load();
-    if (fragments && force_variant >= 24 && split_fits(d, force_variant - 24)) {
-        ConvPlan p;
-        p.kind = 7; p.variant = force_variant - 24; p.bm = 1;
-        return p;
-    }
     if (force_variant >= 16 && kpatch_fits(d, force_variant - 16)) {
         ConvPlan p;
         p.kind = 6; p.variant = force_variant - 16; p.bm = 1;
@@ -381,8 +376,8 @@ int sgprs_conv2d_plan(const sgprs_conv_desc_t* d, int partition_cus, int has_res
     }
     const ConvPlan p = plan_conv(*d, planning_cus(partition_cus), has_residual != 0);
     if (p.bm == 0) return fail(SGPRS_ERR_UNSUPPORTED, "no tile shape fits cout %d", d->cout);
-    *family = p.kind == 4 || p.kind >= 6 ? 0 : p.kind;
-    *detail = p.variant + (p.kind == 4 ? 8 : p.kind == 6 ? 16 : p.kind == 7 ? 24 : 0);
+    *family = p.kind == 4 || p.kind == 6 ? 0 : p.kind;
+    *detail = p.variant + (p.kind == 4 ? 8 : p.kind == 6 ? 16 : 0);
     return SGPRS_OK;
 }
 

@@ -669,22 +669,33 @@ def split_planes(lib, pool, d, dc):
     return planes, bool(unfit.item())
 
 
-def split_case(lib, pool, variant, d, dc, x, res, guard=1):
+def split_case(lib, pool, variant, d, dc, x, res, guard=1, second=None):
+    """`second`: descriptor and operands of the shortcut that goes along; its output is returned too."""
     ptr = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else None)
     p, q = (d.h + 2 * d.pad - d.r) // d.stride + 1, (d.w + 2 * d.pad - d.s) // d.stride + 1
     planes, unfit = split_planes(lib, pool, d, dc)
     assert not unfit
     y = torch.full((d.n + guard, p, q, d.cout), float("nan"), device="cuda")
+    along = [None] * 6
+    if second:
+        d1, dc1 = second
+        planes1, unfit = split_planes(lib, pool, d1, dc1)
+        assert not unfit
+        y1 = torch.full_like(y, float("nan"))
+        along = [ctypes.byref(d1), ptr(dc1.w), ptr(planes1), ptr(dc1.scale), ptr(dc1.shift), ptr(y1)]
     torch.cuda.synchronize()
     stream = ctypes.c_void_p(pool.stream(0))
     assert getattr(lib, "_ZN5sgprs17launch_conv_splitERK17sgprs_conv_desc_tiPKvS4_S4_PKfS6_S4_PvPS1_S4_S4_S6_S6_S7_P12ihipStream_tPNS_8ProfilerE")(
-        ctypes.byref(d), variant, ptr(x), ptr(dc.w), ptr(planes), ptr(dc.scale), ptr(dc.shift), ptr(res), ptr(y), *[None] * 6, stream, None) == 0
+        ctypes.byref(d), variant, ptr(x), ptr(dc.w), ptr(planes), ptr(dc.scale), ptr(dc.shift), ptr(res), ptr(y), *along, stream, None) == 0
     pool.sync()
     assert bool(torch.isnan(y[d.n:]).all())  # nothing is written past the last image
+    if second:
+        assert bool(torch.isnan(y1[d.n:]).all())
+        return y[:d.n], y1[:d.n]
     return y[:d.n]
 
 
-@pytest.mark.parametrize("variant", range(6))
+@pytest.mark.parametrize("variant", range(4))
 def test_conv_split_tiles_parity(pools, variant):
     """fp32 by three bf16 planes of every operand (tasks keep the weights' planes), by its launcher.  The planes are
     exact, what is left out stays below 2^-26: the error is held to the line of the fp32 kernel's chains of
@@ -709,6 +720,30 @@ def test_conv_split_tiles_parity(pools, variant):
             assert e <= 2.0 ** -24 / 6.0 ** 0.5 * (288 / 2 + 20) ** 0.5, (shape, e)
 
 
+@pytest.mark.parametrize("variant", range(4))
+@pytest.mark.parametrize("lost", [False, True])
+def test_conv_split_with_its_shortcut(pools, variant, lost):
+    """A down-sampling block's first convolution and its 1x1 shortcut in one launch, every tile; `lost`: the shortcut's
+    sums are too small for the planes where an image is, and only there, so that one of the two is multiplied again."""
+    for n, h, w, cin, cout in ((2, 56, 56, 64, 128), (3, 14, 14, 256, 512), (1, 9, 13, 96, 192), (1, 2, 1, 32, 64)):
+        x = make_input(97, variant, (n, cin, h, w))
+        if lost:
+            x[:, :, ::2, ::2] *= np.float32(2.0 ** -110)  # what the shortcut reads
+        convs, refs = [], []
+        for k, relu in ((3, 1), (1, 0)):
+            wt = make_conv_weight(97, variant, k, cout, cin, k)
+            g, b, m, v = make_bn(97, variant, k, cout)
+            if lost and k == 1:
+                g, m, b = g * np.float32(2.0 ** 110), m * np.float32(2.0 ** -110), b
+            ref = oracle.bn(oracle.conv2d(x, wt, 2, k // 2), g, b, m, v, BN_EPS)
+            d = S.ConvDesc(n, h, w, cin, cout, k, k, 2, k // 2, S.SGPRS_F32, relu)
+            convs.append((d, DevConv(d, wt, g, b, m, v, BN_EPS)))
+            refs.append(oracle.relu(ref) if relu else ref)
+        got = split_case(S.lib(), pools["full"], variant, *convs[0], dev_nhwc(x, S.SGPRS_F32), None, second=convs[1])
+        for y, ref in zip(got, refs):
+            assert np.linalg.norm(host_nchw(y) - ref) <= 2.0 ** -24 / 6.0 ** 0.5 * (288 / 2 + 20) ** 0.5 * np.linalg.norm(ref)
+
+
 PLANES_END = {  # factors of pixels and weights
     "infinities": (1.0, 1.0), "rounds to infinity": (1.0, 1.0), "tiny": (1e-36, 1.0), "huge": (1e30, 1.0), "zeros": (0.0, 1.0),
     # pixels whose lower planes, or all of them, are lost below 2^-126, with weights that make ordinary sums of them ...
@@ -718,7 +753,7 @@ PLANES_END = {  # factors of pixels and weights
     "huge, tiny weights": (1e30, 1e-36), "huge, subnormal weights": (1e30, 1e-39), "large, tiny weights": (1e20, 1e-35), "dead filters": (1.0, 1.0)}
 
 
-@pytest.mark.parametrize("variant", range(6))
+@pytest.mark.parametrize("variant", range(4))
 @pytest.mark.parametrize("what", PLANES_END)
 def test_conv_split_where_the_planes_end(pools, variant, what):
     """Values that three bf16 planes do not hold: a channel's weights are scaled, or the tile is multiplied again with

@@ -16,7 +16,7 @@ def test_weights_that_the_pixel_wait_counts(tmp_path):
                    os.path.join(build.CSRC, "conv_split.hip"), "-o", out], check=True, capture_output=True)
     with open(out) as f:
         kernels = {tuple(map(int, m.groups())): m.group(0) for m in KERNEL.finditer(f.read())}
-    assert len(kernels) == 6
+    assert len(kernels) == 4
     for (tm, tn, nw), text in kernels.items():
         assert "scratch_" not in text
         tiles = 0
