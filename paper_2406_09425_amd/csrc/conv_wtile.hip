@@ -49,7 +49,7 @@ struct WtileArgs {
     const float* shift;
     const unsigned char* res;
     unsigned x_bytes, w_bytes, y_bytes;
-    int H, W, Cout;
+    int H, W;
     int x_pitch, y_pitch;        // bytes of a pixel
     int chunks, chunks_per_wave; // of 64 input channels
     int TH, TW, PW, patch, images, image_rows;  // patch pixels; images of a tile; patch rows of one of them
@@ -370,30 +370,22 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wtile_kernel(const WtileArgs a
 
 // ---- weights in fragment order -----------------------------------------------------
 // From [cout][tap][cin] to [cout / 64][cin / 64][tap][half][16 channels of 64][lane][16 bytes]: lane l of a
-// fragment holds channel l % 16 and the 16-byte group l / 16 of the half.  Counted in bytes, so the same for
-// fp32 with 32 input channels in the place of 64.
-__global__ void repack_fragments_kernel(const u32x4_t* src, u32x4_t* dst, int taps, int chunks, int units)
+// fragment holds channel l % 16 and the 16-byte group l / 16 of the half.
+__global__ void repack_fragments_kernel(const u32x4_t* src, u32x4_t* dst, int chunks, int units)
 {
     const int u = blockIdx.x * 256 + threadIdx.x;
     if (u >= units) return;
     const int lane = u & 63, j = (u >> 6) & 3, ks = (u >> 8) & 1, rest = u >> 9;
-    const int tap = rest % taps, chunk = rest / taps % chunks, nb = rest / taps / chunks;
+    const int tap = rest % 9, chunk = rest / 9 % chunks, nb = rest / 9 / chunks;
     const int row = nb * 64 + j * 16 + (lane & 15);
-    dst[u] = src[((size_t)row * taps + tap) * (chunks * 8) + chunk * 8 + ks * 4 + (lane >> 4)];
-}
-
-bool fragments_applicable(const sgprs_conv_desc_t& d)
-{
-    const int pitch = d.cin * (int)dtype_size(d.dtype);
-    return is_igemm(d) && pitch % 128 == 0 && d.cout % 64 == 0 && (long long)d.cout * d.r * d.s * pitch < (1ll << 31);
+    dst[u] = src[((size_t)row * 9 + tap) * (chunks * 8) + chunk * 8 + ks * 4 + (lane >> 4)];
 }
 
 int repack_fragments(const sgprs_conv_desc_t& d, const void* src, void* dst, hipStream_t stream)
 {
-    if (!fragments_applicable(d)) return fail(SGPRS_ERR_INVALID_ARG, "internal: no fragment order for this shape");
-    const int pitch = d.cin * (int)dtype_size(d.dtype), units = d.cout * d.r * d.s * (pitch / 16);
-    hipLaunchKernelGGL(repack_fragments_kernel, dim3((units + 255) / 256), dim3(256), 0, stream, (const u32x4_t*)src, (u32x4_t*)dst, d.r * d.s,
-                       pitch / 128, units);
+    if (!wtile_applicable(d)) return fail(SGPRS_ERR_INVALID_ARG, "internal: no fragment order for this shape");
+    const int units = d.cout * 9 * (d.cin / 8);
+    hipLaunchKernelGGL(repack_fragments_kernel, dim3((units + 255) / 256), dim3(256), 0, stream, (const u32x4_t*)src, (u32x4_t*)dst, d.cin / 64, units);
     SGPRS_HIP(hipGetLastError());
     return SGPRS_OK;
 }
@@ -429,7 +421,7 @@ bool wtile_applicable(const sgprs_conv_desc_t& d)
 {
     const long long xb = (long long)d.n * d.h * d.w * d.cin * 2, yb = (long long)d.n * d.h * d.w * d.cout * 2;
     return d.dtype == SGPRS_BF16 && d.r == 3 && d.s == 3 && d.stride == 1 && d.pad == 1 && d.cin % 64 == 0 && d.cout % 64 == 0 &&
-           fragments_applicable(d) && xb < (1ll << 31) && yb < (1ll << 31) && d.h < (1 << 15) && d.w < (1 << 15);
+           (long long)d.cout * 9 * d.cin * 2 < (1ll << 31) && xb < (1ll << 31) && yb < (1ll << 31) && d.h < (1 << 15) && d.w < (1 << 15);
 }
 
 // Best split of the input channels over KS wavefronts, and its time: launch, prologue and epilogue, 18 steps
@@ -477,7 +469,7 @@ int launch_conv3x3_wtile(const sgprs_conv_desc_t& d, int ks, const void* x, cons
     a.x_bytes = (unsigned)((long long)d.n * d.h * d.w * d.cin * 2);
     a.y_bytes = (unsigned)((long long)d.n * d.h * d.w * d.cout * 2);
     a.w_bytes = (unsigned)((long long)d.cout * 9 * d.cin * 2);
-    a.H = d.h; a.W = d.w; a.Cout = d.cout;
+    a.H = d.h; a.W = d.w;
     a.x_pitch = d.cin * 2; a.y_pitch = d.cout * 2;
     a.chunks = chunks; a.chunks_per_wave = chunks / ks;
     a.TH = t.th; a.TW = t.tw; a.PW = t.pw; a.patch = t.patch; a.images = t.images;

@@ -314,7 +314,6 @@ int launch_conv_ksplit(const sgprs_conv_desc_t& d, int variant, const void* x, c
                        const void* res, void* y, const sgprs_conv_desc_t* d1, const void* w1, const float* scale1,
                        const float* shift1, void* y1, hipStream_t stream, Profiler* prof);
 // 3x3 stride-1 kernel with private patches and weights from the L2 to registers (bf16); its weights come in fragment order
-bool fragments_applicable(const sgprs_conv_desc_t& d);
 int repack_fragments(const sgprs_conv_desc_t& d, const void* src, void* dst, hipStream_t stream);
 bool wtile_applicable(const sgprs_conv_desc_t& d);
 bool plan_wtile(const sgprs_conv_desc_t& d, int cus, int* ks, double* cost_us);
