@@ -124,14 +124,16 @@ void destroy_task(sgprs_task* t)
     delete t;
 }
 
+// Only stride-1 layers take a residual here, and their plan is the same with and without; creating a task asks
+// for 64 batches and partition sizes, so a layer like the one before it is not planned again.
 size_t splitk_need(const sgprs_task* t, int first, int last, int batch, int cus)
 {
     size_t need = 0;
     for (int i = first; i <= last; ++i) {
-        if (is_stem(t->conv[i].d)) continue;
         sgprs_conv_desc_t d = t->conv[i].d;
+        if (is_stem(d) || (i > first && !memcmp(&d, &t->conv[i - 1].d, sizeof(d)))) continue;
         d.n = batch;
-        need = std::max(need, std::max(conv_workspace_bytes(d, plan_conv(d, cus, false)), conv_workspace_bytes(d, plan_conv(d, cus, true))));
+        need = std::max(need, conv_workspace_bytes(d, plan_conv(d, cus)));
     }
     return need;
 }

@@ -196,3 +196,18 @@ def test_workspace_covers_both_cu_counts_a_launch_may_be_planned_for():
             for cus in (40, 56, 104, 200, 248):
                 assert S.sgprs_conv2d_workspace(d, cus) >= S.sgprs_conv2d_workspace(d, cus // 32 * 32)
             assert S.sgprs_conv2d_plan(d, 56) == S.sgprs_conv2d_plan(d, 32)
+
+
+@pytest.mark.parametrize("override", [(-1, 0, 1), (0, 0, 1), (1, 0, 1), (1, 3, 2), (2, 2, 4), (2, 9, 0), (2, 18, 0), (3, 0, 1), (5, 0, 1)])
+def test_plan_of_stride_1_layers_is_the_same_with_a_residual(override):
+    """Tasks size their split-K scratch by the plan without: the scratch and the kernel of both."""
+    try:
+        S.sgprs_conv_tuning_override(*override)
+        for dtype in (S.SGPRS_F32, S.SGPRS_BF16):
+            for h, c in ((56, 64), (28, 128), (14, 256), (7, 512)):
+                for n in (1, 3, 16, 64):
+                    for cus in (8, 32, 96, 256):
+                        d = S.ConvDesc(n, h, h, c, c, 3, 3, 1, 1, dtype, 1)
+                        assert S.sgprs_conv2d_plan(d, cus, False) == S.sgprs_conv2d_plan(d, cus, True)
+    finally:
+        S.sgprs_conv_tuning_override(-1, 0, 1)
