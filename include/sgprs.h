@@ -209,7 +209,9 @@ int sgprs_conv2d(const sgprs_conv_desc_t *d, const void *x, const void *w_packed
  * wherever it divides cout, with split-K factor `splits` (0: planner's choice),
  * and with `variant` 8..15 every 3x3 and 1x1 layer uses that tile of the kernel
  * that splits K over a workgroup's wavefronts, with 16..20 every stride-1 3x3
- * bf16 layer that tile of the kernel that does so with its pixels in LDS;
+ * bf16 layer that tile of the kernel that does so with its pixels in LDS, with
+ * 24..27 every down-sampling block of a bf16 task that tile of the paired
+ * kernel whose weights go from the L2 to registers;
  * 3: automatic, plus the stride-2 LDS-patch kernel (not chosen otherwise) with
  * tile variant `variant` (0: 256 rows, 1: 128 rows) wherever the shape allows
  * it; variant 2 switches it off again; 4: automatic, but stage 0 of a bf16

@@ -14,7 +14,7 @@ LIB = os.path.join(PKG, "libsgprs.so")
 CALLS = os.path.join(PKG, "_calls.so")  # CPython extension around the entry points called once per kernel
 OBJ_DIR = os.path.join(PKG, "_build")
 
-SOURCES = ["pool.cpp", "pack.cpp", "ops.cpp", "task.cpp", "sched.cpp", "conv_igemm.hip", "conv_ksplit.hip", "conv_wtile.hip", "conv_kpatch.hip", "conv_split.hip", "conv_stem.hip", "conv3x3_patch.hip", "conv3x3_rows.hip", "stem_pool.hip", "stem_f32.hip",
+SOURCES = ["pool.cpp", "pack.cpp", "ops.cpp", "task.cpp", "sched.cpp", "conv_igemm.hip", "conv_ksplit.hip", "conv_wtile.hip", "conv_kpatch.hip", "conv_split.hip", "conv_s2tile.hip", "conv_stem.hip", "conv3x3_patch.hip", "conv3x3_rows.hip", "stem_pool.hip", "stem_f32.hip",
            "pointwise.hip", "fc_gemm.hip", "mfma_probe.hip", "load_probe.hip"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-variable", "-I", os.path.join(ROOT, "include"),

@@ -482,6 +482,7 @@ const char* igemm_pair_variant_name(int v)
     static int next = 0;
     if (v >= kSplitNames) return split_variant_name(v - kSplitNames);
     if (v >= kKsplitNames) return ksplit_variant_name(v - kKsplitNames);
+    if (v >= kS2tileNames) return s2tile_variant_name(v - kS2tileNames);
     if (v < 0 || v >= 16 || (v & 7) >= 4) return "?";
     const int* t = kIgemmShape[v & 7];
     char* out = buf[next++ & 7];
@@ -570,6 +571,10 @@ int launch_conv_pair(const sgprs_conv_desc_t& d0, const void* w0, const float* s
     if (p0.bm != 0 && p0.kind == 7 && split_fits(d1, p0.variant) && d1.cout == d0.cout && d1.stride == d0.stride && d1.pad == d1.r / 2 && d0.pad == d0.r / 2) {
         *done = true;
         return launch_conv_split(d0, p0.variant, x, w0, fragments0, scale0, shift0, nullptr, y0, &d1, w1, fragments1, scale1, shift1, y1, stream, prof);
+    }
+    if (p0.bm != 0 && p0.kind == 8 && fragments0 && fragments1) {
+        *done = true;
+        return launch_conv_s2tile(d0, p0.variant, x, fragments0, scale0, shift0, y0, d1, fragments1, scale1, shift1, y1, stream, cus, prof);
     }
     ConvPlan p1 = plan_conv(d1, cus, false, false);
     if (p0.bm == 0 || p0.kind != 0 || p0.splits != 1 || p1.bm == 0 || p1.kind != 0) return SGPRS_OK;

@@ -371,21 +371,26 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wtile_kernel(const WtileArgs a
 // ---- weights in fragment order -----------------------------------------------------
 // From [cout][tap][cin] to [cout / 64][cin / 64][tap][half][16 channels of 64][lane][16 bytes]: lane l of a
 // fragment holds channel l % 16 and the 16-byte group l / 16 of the half.
-__global__ void repack_fragments_kernel(const u32x4_t* src, u32x4_t* dst, int chunks, int units)
+__global__ void repack_fragments_kernel(const u32x4_t* src, u32x4_t* dst, int taps, int chunks, int units)
 {
     const int u = blockIdx.x * 256 + threadIdx.x;
     if (u >= units) return;
     const int lane = u & 63, j = (u >> 6) & 3, ks = (u >> 8) & 1, rest = u >> 9;
-    const int tap = rest % 9, chunk = rest / 9 % chunks, nb = rest / 9 / chunks;
+    const int tap = rest % taps, chunk = rest / taps % chunks, nb = rest / taps / chunks;
     const int row = nb * 64 + j * 16 + (lane & 15);
-    dst[u] = src[((size_t)row * 9 + tap) * (chunks * 8) + chunk * 8 + ks * 4 + (lane >> 4)];
+    dst[u] = src[((size_t)row * taps + tap) * (chunks * 8) + chunk * 8 + ks * 4 + (lane >> 4)];
+}
+
+bool fragment_order(const sgprs_conv_desc_t& d)
+{
+    return is_igemm(d) && d.dtype == SGPRS_BF16 && d.cin % 64 == 0 && d.cout % 64 == 0 && (long long)d.cout * d.r * d.s * d.cin * 2 < (1ll << 31);
 }
 
 int repack_fragments(const sgprs_conv_desc_t& d, const void* src, void* dst, hipStream_t stream)
 {
-    if (!wtile_applicable(d)) return fail(SGPRS_ERR_INVALID_ARG, "internal: no fragment order for this shape");
-    const int units = d.cout * 9 * (d.cin / 8);
-    hipLaunchKernelGGL(repack_fragments_kernel, dim3((units + 255) / 256), dim3(256), 0, stream, (const u32x4_t*)src, (u32x4_t*)dst, d.cin / 64, units);
+    if (!fragment_order(d)) return fail(SGPRS_ERR_INVALID_ARG, "internal: no fragment order for this shape");
+    const int taps = d.r * d.s, units = d.cout * taps * (d.cin / 8);
+    hipLaunchKernelGGL(repack_fragments_kernel, dim3((units + 255) / 256), dim3(256), 0, stream, (const u32x4_t*)src, (u32x4_t*)dst, taps, d.cin / 64, units);
     SGPRS_HIP(hipGetLastError());
     return SGPRS_OK;
 }

@@ -187,7 +187,8 @@ struct ConvPlan {
                        // 4: implicit GEMM with K split over a workgroup's wavefronts,
                        // 5: weights from the L2 to registers (variant: wavefronts that share a tile),
                        // 6: K split over a workgroup's wavefronts, input patch in LDS,
-                       // 7: fp32 by three bf16 planes of every operand (5 and 7 only where the weights are there in fragment order)
+                       // 7: fp32 by three bf16 planes of every operand,
+                       // 8: stride-2 pair, weights from the L2 to registers (5, 7 and 8 only where the weights are there in fragment order)
     int variant = 0;   // index into the kernel's tile table (row streaming: output rows per stream and job)
     int bm = 0, bn = 0;
     int splits = 1;    // split-K factor (grid.z)
@@ -314,6 +315,7 @@ int launch_conv_ksplit(const sgprs_conv_desc_t& d, int variant, const void* x, c
                        const void* res, void* y, const sgprs_conv_desc_t* d1, const void* w1, const float* scale1,
                        const float* shift1, void* y1, hipStream_t stream, Profiler* prof);
 // 3x3 stride-1 kernel with private patches and weights from the L2 to registers (bf16); its weights come in fragment order
+bool fragment_order(const sgprs_conv_desc_t& d);
 int repack_fragments(const sgprs_conv_desc_t& d, const void* src, void* dst, hipStream_t stream);
 bool wtile_applicable(const sgprs_conv_desc_t& d);
 bool plan_wtile(const sgprs_conv_desc_t& d, int cus, int* ks, double* cost_us);
@@ -326,6 +328,14 @@ constexpr int kKpatchNames = 96;  // recorded as implicit GEMM, variant 96 + til
 const char* kpatch_variant_name(int variant);
 int launch_conv3x3_kpatch(const sgprs_conv_desc_t& d, int variant, const void* x, const void* w, const float* scale, const float* shift,
                           const void* res, void* y, hipStream_t stream, int cus, Profiler* prof);
+// a block's 3x3 stride-2 convolution with its shortcut, weights from the L2 to registers (bf16); its weights come in fragment order
+bool plan_s2tile(const sgprs_conv_desc_t& d, const sgprs_conv_desc_t& d1, int cus, int* variant, double* cost_us);
+bool s2tile_fits(const sgprs_conv_desc_t& d, const sgprs_conv_desc_t& d1, int variant);
+constexpr int kS2tileNames = 24;  // recorded as implicit-GEMM pair, variant 24 + tile
+const char* s2tile_variant_name(int variant);
+int launch_conv_s2tile(const sgprs_conv_desc_t& d, int variant, const void* x, const void* fragments0, const float* scale0, const float* shift0, void* y0,
+                       const sgprs_conv_desc_t& d1, const void* fragments1, const float* scale1, const float* shift1, void* y1, hipStream_t stream,
+                       int cus, Profiler* prof);
 // fp32 by three bf16 planes of every operand, K range split like conv_ksplit's
 bool split_fits(const sgprs_conv_desc_t& d, int variant);
 bool plan_split(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us);

@@ -213,6 +213,12 @@ static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs
 {
     const ConvPlan single = plan_conv(d0, cus);
     const int P = out_dim(d0.h, d0.r, d0.stride, d0.pad), Q = out_dim(d0.w, d0.s, d0.stride, d0.pad);
+    const int forced = g_igemm_force_variant.load() - kS2tileNames;
+    if (fragments && s2tile_fits(d0, d1, forced)) {
+        ConvPlan p;
+        p.kind = 8; p.variant = forced; p.bm = 1;
+        return p;
+    }
     if (g_conv_force_kind.load() != -1 || g_igemm_force_variant.load() >= 0 || single.bm == 0 || (single.kind != 0 && single.kind != 4) ||
         !is_igemm(d1) || d1.cout != d0.cout || P != out_dim(d1.h, d1.r, d1.stride, d1.pad) || Q != out_dim(d1.w, d1.s, d1.stride, d1.pad))
         return single;
@@ -254,6 +260,15 @@ static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs
             best = ConvPlan();
             best.kind = 7; best.variant = v; best.bm = 1;
         }
+    }
+    // The estimates above are of launches in a loop, whose weights stay in the L2: inside a network these take 0.8 to 1.0 times
+    // that on 64 to 96 CUs and 1.05 to 1.4 times on 128 to 256 (64 images on 256 CUs, the three blocks: 18.7 / 16.6 / 19.3
+    // estimated, 21.8 / 19.9 / 27.2 measured with inputs that change; with the kernel chosen here 19.0 / 17.2 / 18.0).
+    int variant;
+    double cost;
+    if (fragments && plan_s2tile(d0, d1, cus, &variant, &cost) && cost < best_cost * (0.9 + 0.3 * std::min(cus, 256) / 256)) {
+        best = ConvPlan();
+        best.kind = 8; best.variant = variant; best.bm = 1;
     }
     return best.bm ? best : single;
 }

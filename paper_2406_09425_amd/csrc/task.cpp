@@ -41,7 +41,7 @@ constexpr int kFcIn = 512, kFcOut = 1000;
 struct ConvLayer {
     sgprs_conv_desc_t d;
     void* w = nullptr;
-    void* w_fragments = nullptr;  // bf16 3x3 stride-1 layers: the same in fragment order; fp32: in three bf16 planes, where these hold them
+    void* w_fragments = nullptr;  // bf16: the same in fragment order (all layers but the stem); fp32: in three bf16 planes, where these hold them
     float* scale = nullptr;
     float* shift = nullptr;
 };
@@ -299,7 +299,7 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
         if ((rc = upload(t, packed.data(), bytes, &t->conv[i].w))) break;
         if ((rc = upload(t, scale.data(), cs.cout * sizeof(float), (void**)&t->conv[i].scale))) break;
         if ((rc = upload(t, shift.data(), cs.cout * sizeof(float), (void**)&t->conv[i].shift))) break;
-        fragment_bytes += wtile_applicable(d) ? bytes : split_weight_bytes(d);
+        fragment_bytes += fragment_order(d) ? bytes : split_weight_bytes(d);
         if (i == 0 && dtype == SGPRS_BF16) {
             std::vector<uint16_t> rows((size_t)64 * kStemRowsK);
             pack_stem_rows(hp->conv_w[0], rows.data());
@@ -326,7 +326,7 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
         for (int i = 0; i < SGPRS_RESNET18_CONVS && !rc; ++i) {
             ConvLayer& l = t->conv[i];
             size_t bytes = split_weight_bytes(l.d);
-            if (!bytes && !wtile_applicable(l.d)) continue;
+            if (!bytes && !fragment_order(l.d)) continue;
             if (bytes) rc = split_weights(l.d, l.w, l.scale, to, dev_unfit + i, nullptr);
             else if (!(rc = sgprs_conv_packed_weight_bytes(&l.d, &bytes))) rc = repack_fragments(l.d, l.w, to, nullptr);
             if (rc) break;

@@ -214,6 +214,36 @@ def test_paired_launch_families_parity(cfg1, dtype, n):
         task.destroy()
 
 
+@pytest.mark.parametrize("n,cus", [(1, 8), (2, 32), (5, 8), (5, 64), (11, 16)])
+def test_stride2_pair_tiles_parity(cfg1, n, cus):
+    """The down-sampling blocks by every tile of the kernel whose weights go from the L2 to registers: one item and
+    several per workgroup, a last tile of one image instead of two, an odd number of tiles, input channels in one
+    part and in two.  Each against the oracle, and the blocks' first convolutions by name."""
+    params = cfg1[0]
+    task = S.Task(params, S.SGPRS_BF16, n, BN_EPS)
+    task.set_profiling(True)
+    pool = S.Pool(1, cus)
+    try:
+        for j in (2, 3, 4):
+            x = np.maximum(make_input(n, 60 + j, stage_shape(j, n, out=False)[:1] + STAGE_IO[j][0]), 0.0)
+            ref = oracle.resnet18_stage(j, params, BN_EPS, x)
+            xd = dev_nhwc(x, S.SGPRS_BF16)
+            for v, (tm, ks) in enumerate(((7, 1), (7, 2), (4, 1), (4, 2))):
+                S.sgprs_conv_tuning_override(2, 24 + v, 1)
+                o = dev_empty(stage_shape(j, n), S.SGPRS_BF16)
+                o.fill_(float("nan"))
+                task.stage_run(j, n, xd.data_ptr(), o.data_ptr(), pool, 0)
+                pool.sync()
+                pair = [k["name"] for k in task.kernel_times(j) if k["kind"] == 10]
+                if STAGE_IO[j][0][0] // 64 % ks == 0:
+                    assert pair == [f"conv_igemm_pair_kernel<{tm}, {ks}>"], (j, v)
+                assert_close(host_nchw(o), ref, S.SGPRS_BF16, f"stage {j} n={n} cus={cus} tile {tm}, {ks}")
+    finally:
+        S.sgprs_conv_tuning_override(-1, 0, 1)
+        task.destroy()
+        pool.destroy()
+
+
 @pytest.mark.parametrize("what", ["tiny pixels, huge weights", "huge pixels, tiny weights", "one weight far below the others"])
 def test_fp32_layers_of_extreme_weights(cfg1, what):
     """A layer whose weights and pixels are far from 1, in both directions, with a BN that brings its sums back: as
