@@ -274,10 +274,10 @@ int launch_stem_f32(int n, int h, int w, const void* x, const void* wts, const f
                     int relu, bool pool, hipStream_t stream, int cus);
 // stage 0 fused: conv7x7/2 + BN + ReLU + max-pool 3x3/2
 bool stem_pool_applicable(int dtype, int n, int h, int w, int cus);
-// wts: the stem layout of sgprs_pack_conv_weights; wts_rows: the bf16 [64][176] tap-row layout of
-// pack_stem_rows (may be NULL: then the kernel that reads wts runs)
-constexpr int kStemRowsK = 176;
-void pack_stem_rows(const float* oihw, uint16_t* out);
+// wts: the stem layout of sgprs_pack_conv_weights; wts_rows: bf16 fragments of pack_stem_rows, negated
+// where scale is negative, and both tables (may be NULL: then the kernel that reads wts runs)
+constexpr int kStemRowsElems = 44 * 512 + 256;
+void pack_stem_rows(const float* oihw, const float* scale, const float* shift, uint16_t* out);
 void stem_pool_force(int v);  // -1 automatic, 1: never the packed-row kernel
 int launch_stem_pool(int dtype, int n, int h, int w, const void* x, const void* wts, const void* wts_rows,
                      const float* scale, const float* shift, void* y, hipStream_t stream, int cus, Profiler* prof);

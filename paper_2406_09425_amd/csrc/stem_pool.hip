@@ -15,6 +15,10 @@
 // the LDS staging area as one 8-byte write.
 // Positions outside the conv output hold 0 in the staging area (the post-ReLU
 // values are pooled as unsigned bit patterns), so padding never wins the maximum.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
 #include "internal.h"
 
 namespace sgprs {
@@ -219,262 +223,311 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
 // ---------------------------------------------------------------------------------------------
 // bf16 variant with packed input rows.
 //
-// In the kernel above every wavefront re-reads all weights from LDS for each tile, the 4-slot pixel
-// layout pads K from 147 to 224, and the patch goes through registers and LDS stores.  Here
-//  * the weights are stationary in registers (88 VGPRs: 2 channel tiles x 11 K-steps), loaded once
-//    per workgroup from a [64][176] layout prepared at task creation;
-//  * the input patch keeps the image's own 3-channel packing: 35 rows of 17 16-byte pieces are
-//    copied global -> LDS by the load unit itself (zero fill outside the image comes from the
-//    buffer bounds check), double buffered so that the next tile's patch lands during this
-//    tile's arithmetic;
-//  * a pixel's K-run for tap row r is the 24 consecutive bf16 that start one element before its
-//    first tap (elements 0, 22, 23 meet zero weights), so K = 7 x 24 = 168 (+8 zero) = 176 and
-//    the run starts on a 4-byte boundary;
-//  * BN scale / shift live in LDS, and there are two barriers per tile instead of four.
-// Element 0 / 22 / 23 of a run are real neighbouring inputs multiplied by zero weights: the
-// result equals the plain definition for finite inputs (a non-finite input pixel would also
+//  * The input keeps the image's own 3-channel packing: rows are copied global -> LDS by the load unit itself
+//    (zero fill outside the image comes from the buffer bounds check).  A pixel's K-run for tap row r is the 24
+//    consecutive bf16 that start one element before its first tap (elements 0, 22, 23 meet zero weights), so
+//    K = 7 x 24 = 168 (+8 zero) = 176.
+//  * A wavefront goes its own way, one per SIMD: a strip of `rows` pooled rows x up to 30 pooled columns.  It computes the
+//    strip's conv rows one by one, even and odd columns as two MFMA tiles of 32 pixels, so that lane l has the conv
+//    columns 2q and 2q + 1 of pooled column q = q0 - 1 + l and gets 2q - 1 from the lane before: the maximum over
+//    the window never leaves the registers.  No patch staging, no pooling reads, no barriers; one conv row per strip and
+//    one column in 29 are computed twice.
+//  * The maximum is taken of the sums; scale, shift and ReLU follow it, a quarter of the work (they are monotone: the weights of
+//    channels with a negative scale are negated, which is exact, and rounding keeps the order).
+//  * The weights of both tiles (176 registers) and the input fragments (44) are accumulation registers, read from LDS right into
+//    them; sums, maxima, scale and shift are the other 256.  Two thirds of a K-run's groups are the same for an
+//    odd column and the even one before it: 15 reads per conv row, not 22 (8-aligned reads give 73 bytes a cycle and CU, and with
+//    scale and shift read from there as well they were the bound).
+//  * A SIMD starts an MFMA every 32 cycles and up to six other instructions of the same wavefront are free behind it (measured;
+//    eight: 43 cycles).  A conv row has 44 MFMAs and about 230 others, laid behind them five at a time.
+//  * Groups of four input rows are loaded as far ahead as their latency asks for, not as soon as there is room: a wavefront
+//    that requests more than the memory takes waits at the request (all 27 loads of a strip first: 5 us instead of 2 before the
+//    first MFMA at batch 64).
+// Bound: the MFMAs (22 GFLOP with padding and what is computed twice at batch 64) at the clock they leave: 2816 cycles of MFMAs in
+// 3660 per row pair, at 1.7 GHz.  Measured (us per launch inside the network, this kernel / the one of 8x7 patches with two
+// workgroups per CU before it): batch 64 22.6 / 35.6, batch 128 40.4 / 66.4, 13 images on 96 CUs 11.5 / 18.9, 16 images 9.1 / 15.9,
+// one image 6.0 / 9.3, one on 32 CUs 5.9 / 11.2.
+// The elements of a run beside its taps (0 / 22 / 23, of even columns the three before and none behind) are real neighbouring inputs
+// multiplied by zero weights: the result equals the plain definition for finite inputs (a non-finite input pixel would also
 // reach the output columns next to its window).
-constexpr int kRowPitch = 272;                       // 17 pieces of 16 bytes per staged input row
-constexpr int kRowUnits = kInR * 17;                 // 595 pieces per patch
-constexpr int kPatchPitch = 640 * 16;                // 3 rounds of 256 lanes, the tail lands as zeros (row 35, 36)
-constexpr int kPackedK = 176;
+constexpr int kStripCols = 30, kStripRows = 7;       // pooled columns and rows of a strip, at most
+constexpr int kRowPitch = 24 * kStripCols + 48;      // bytes of an input row in LDS: 48 pieces of 16
+constexpr int kGroupBytes = 4 * kRowPitch;           // rows are loaded by fours: three instructions
+constexpr int kStripLds = (kStripRows + 2) * kGroupBytes;
+constexpr int kAhead = 5;                            // groups of rows loaded before the first is used: two row pairs, 3.5 us
+constexpr int kFragments = 44;                       // [odd, even][K-step 0 .. 10][channel tile], 1024 bytes each; then scale and shift
+constexpr int kFragmentLds = 48 * 1024;              // (what the wavefronts load of them, twelve instructions each)
+constexpr int kOutPitch = 144;                       // a pixel of a finished row, where the fragments were
+static_assert(kFragments * 512 + 256 == kStemRowsElems, "");
+static_assert(4 * 32 * kOutPitch <= kFragmentLds, "");
+constexpr int kPackedLds = kFragmentLds + 4 * kStripLds + 64;  // (the idle lanes of the last row read a little past it)
 
-typedef unsigned int u32x4a4_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int u32x4a8_t __attribute__((ext_vector_type(4), aligned(8)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-__global__ __launch_bounds__(256, 2) void stem_pool_packed_kernel(const StemPoolArgs a, const unsigned x_bytes)
+struct StemRowsArgs {
+    const unsigned char* x;
+    const unsigned char* w;
+    unsigned char* y;
+    int H, W, P, PP, PQ;              // input, rows of the conv output, pooled output
+    int rows, cols;                   // of a strip
+    int ahead;                        // groups of rows loaded ahead: kAhead, or fewer where a strip has no more
+    int strips_q, strips, per_die;    // strips of a pooled row, all, of a die (each walks a contiguous eighth: workgroup b runs on die b % 8)
+    unsigned q_mul, p_mul;
+    int q_sh, p_sh, strips_p;
+};
+
+template <int N> __device__ __forceinline__ void stem_wait_vmcnt()
 {
-    constexpr int SROWB = 64 * 2 + 16;
-    constexpr int STG_BASE = 2 * kPatchPitch;
-    constexpr int SC_BASE = STG_BASE + 256 * SROWB;
+    static_assert(N <= 63, "vmcnt range");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+}
 
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__global__ __launch_bounds__(256, 1) void stem_pool_packed_kernel(const StemRowsArgs a)
+{
+#if __HIP_DEVICE_COMPILE__
+    // LDS by address (0: the start of the workgroup's): what reads it is not held up for the rows still on their way.
+    typedef const __attribute__((address_space(3))) u32x4a8_t* lds_a8_t;
+    typedef const __attribute__((address_space(3))) u32x4_t* lds_a16_t;
+    typedef __attribute__((address_space(3))) u32x4_t* lds_w16_t;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int frow = lane & 31, fhalf = lane >> 5;
-
-    const __amdgpu_buffer_rsrc_t x_rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, (int)x_bytes, 0x00020000);
+    constexpr unsigned kOutside = 0x80000000u;
+    const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, kStemRowsElems * 2, 0x00020000);
+    const unsigned staged = wave * 32 * kOutPitch, mine = kFragmentLds + wave * kStripLds;
     const int row_bytes = a.W * 6;
-    // Workgroup b runs on die b % 8 (whole chip; on a masked partition the dies of the mask take
-    // turns the same way).  Each die walks its own contiguous eighth of the tiles, so neighbouring
-    // tiles, whose input patches overlap by a quarter, meet in one L2 and the overlap is fetched
-    // from HBM once.
-    int first_tile = blockIdx.x, tile_step = gridDim.x, tile_end = a.ntiles;
-    if (gridDim.x % 8 == 0) {
-        const int per_die = (a.ntiles + 7) / 8, die = blockIdx.x & 7;
-        first_tile = die * per_die + ((int)blockIdx.x >> 3);
-        tile_step = (int)gridDim.x >> 3;
-        tile_end = min((die + 1) * per_die, a.ntiles);
-    }
-    // A tile is (image n, tile row tp, tile column tq).  The walk tile += tile_step is kept in
-    // that form with carries, so that no tile costs an integer division.
-    struct TilePos { int n, tp, tq; };
-    const int per_image = a.tiles_p * a.tiles_q;
-    const int step_n = tile_step / per_image, step_r = tile_step - step_n * per_image;
-    const int step_p = step_r / a.tiles_q, step_q = step_r - step_p * a.tiles_q;
-    auto advance = [&](TilePos t) {
-        t.tq += step_q;
-        if (t.tq >= a.tiles_q) { t.tq -= a.tiles_q; ++t.tp; }
-        t.tp += step_p;
-        if (t.tp >= a.tiles_p) { t.tp -= a.tiles_p; ++t.n; }
-        t.n += step_n;
-        return t;
+
+    struct Strip { int n, p0, q0; bool valid; };
+    const int die = (int)blockIdx.x & 7, block = (int)blockIdx.x >> 3, step = (int)gridDim.x >> 3;
+    const int end = min(a.strips, (die + 1) * a.per_die);
+    auto div = [](int m, unsigned mul, int sh) { return (int)(__umulhi(2u * (unsigned)m, mul) >> sh); };
+    auto decode = [&](int t) {
+        Strip s;
+        s.valid = t < end;
+        const int u = min(t, a.strips - 1), rest = div(u, a.q_mul, a.q_sh);
+        s.n = div(rest, a.p_mul, a.p_sh);
+        s.p0 = (rest - s.n * a.strips_p) * a.rows;
+        s.q0 = (u - rest * a.strips_q) * a.cols;
+        return s;
     };
-    // The patch of a tile: 16-byte piece u = it * 256 + tid is piece u % 17 of input row u / 17.  Offsets
-    // first (vector arithmetic), then one load instruction per round, so that the loads can be
-    // placed between the MFMAs of the tile before (issued back to back they stall on the address queue).
-    auto patch_offsets = [&](const TilePos t, unsigned (&off)[3]) {
-        const int n = t.n, pp0 = t.tp * kPoolTP, pq0 = t.tq * kPoolTQ;
-        const int h_base = 4 * pp0 - 5, b_base = 24 * pq0 - 32;  // first input row; byte of the first piece in its row
+    // Row k of a strip is input row 4 p0 - 5 + k, from byte 24 q0 - 32 on, 48 pieces of 16 bytes.  Instruction i of a group of four
+    // rows has pieces 64 i .. 64 i + 63.  The descriptor is the image's: rows above and below it are beyond the size (as are all
+    // where there is no strip: the waits count every instruction), pieces beside it are given such an offset.
+    struct Pieces { unsigned at[3]; };
+    auto pieces = [&](const Strip& s) {
+        Pieces p;
 #pragma unroll
-        for (int it = 0; it < 3; ++it) {
-            const int u = it * 256 + tid;
-            const int row = u / 17, seg = u - row * 17;
-            const int ih = h_base + row, b = b_base + 16 * seg;
-            const bool ok = u < kRowUnits && seg < 16 && (unsigned)ih < (unsigned)a.H && (unsigned)b < (unsigned)row_bytes;
-            off[it] = ok ? (unsigned)((n * a.H + ih) * row_bytes + b) : 0x80000000u;
+        for (int i = 0; i < 3; ++i) {
+            const int u = lane + i * 64, row = (int)(__umul24((unsigned)u, 1366u) >> 16), b = 24 * s.q0 + (u - row * 48) * 16 - 32;
+            p.at[i] = (unsigned)b < (unsigned)row_bytes ? (unsigned)((4 * s.p0 - 5 + row) * row_bytes + b) : kOutside;
+        }
+        return p;
+    };
+    auto load_group = [&](const Strip& s, const Pieces& p, int group) {
+        const __amdgpu_buffer_rsrc_t x_rs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.x + (long long)s.n * a.H * row_bytes), 0,
+                                                                              s.valid ? a.H * row_bytes : 0, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rs, (lds_ptr_t)(unsigned long)(mine + group * kGroupBytes + i * 1024), 16,
+                                                     p.at[i] + (unsigned)(4 * group * row_bytes), 0, 0, 0);
+    };
+#pragma unroll
+    for (int k = 0; k < kFragmentLds / 4096; ++k) {
+        int f = k * 4 + wave + block % 16 * 3;  // (not all in the same order: a die's CUs would meet at one channel of its L2)
+        f -= f >= 48 ? 48 : 0;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr_t)(unsigned long)(f * 1024), 16, f * 1024 + lane * 16, 0, 0, 0);
+    }
+    int t = die * a.per_die + block + wave * step;  // (few strips: one or two on a CU, whose loads are what they wait for)
+    Strip cur = decode(t);
+    Pieces cur_at = pieces(cur);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) load_group(cur, cur_at, k);
+    __builtin_amdgcn_sched_barrier(0);
+    stem_wait_vmcnt<9>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    u32x4_t w[2][11][2];              // of the odd and of the even columns
+    f32x4_t sc[8], sh[8];             // of channels 8 q + 4 fhalf + 0 .. 3
+#pragma unroll
+    for (int f = 0; f < kFragments; ++f) w[f / 22][f % 22 / 2][f % 2] = *(lds_a16_t)(unsigned long)(f * 1024 + lane * 16);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        sc[q] = __builtin_bit_cast(f32x4_t, *(lds_a16_t)(unsigned long)(kFragments * 1024 + q * 32 + fhalf * 16));
+        sh[q] = __builtin_bit_cast(f32x4_t, *(lds_a16_t)(unsigned long)(kFragments * 1024 + 256 + q * 32 + fhalf * 16));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    for (int k = 3; k < a.ahead; ++k) load_group(cur, cur_at, k);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int f = 0; f < kFragments; ++f) asm volatile("" : "+a"(w[f / 22][f % 22 / 2][f % 2]));
+#pragma unroll
+    for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(sc[q]), "+v"(sh[q]));
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();     // finished rows go where the fragments were
+    asm volatile("" ::: "memory");
+
+    // Groups are loaded `ahead` of the first one of a conv row, one every two rows (more at once only wait in the wavefront's way):
+    // the three that a row reads have landed when all but the last ahead - 3 have.
+    auto wait_for_rows = [&] {
+        __builtin_amdgcn_sched_barrier(0);
+        if (a.ahead >= kAhead) stem_wait_vmcnt<3 * (kAhead - 3)>();
+        else stem_wait_vmcnt<0>();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // A conv row is two multiplications of 22 MFMAs; behind each, up to six other instructions are free.  What is done with the sums of
+    // the multiplication before is cut into N steps and spread over them.
+    f32x16_t acc[2][2];               // of the odd and of the even columns
+    float odd[2][16], m[2][16];       // maxima: over the odd columns of a window, over the rows of a window so far
+    u32x4_t both[7], own[4];          // the row's K groups that odd and even columns share, those that they do not
+    auto read = [&](unsigned base, int off) { return (u32x4_t) * ((lds_a8_t)(unsigned long)base + off / 16); };
+    struct Bases { unsigned s0, s3, s6, h0, h4, l6; };  // of tap rows: 0, 3, 6 of the shared groups; 0, 4 (upper half-wave: the next one) and 6 of the others
+    auto multiply = [&](auto even, const Bases& row, unsigned next, auto steps, auto work) {
+        constexpr int E = decltype(even)::value, N = decltype(steps)::value, OWN = E ? 0 : 48;
+#pragma unroll
+        for (int ks = 0; ks < 11; ++ks) {
+            if (!E && ks < 3) both[ks + 3] = read(row.s3, ks * kRowPitch);
+            if (!E && ks == 3) both[6] = read(row.s6, 0);
+            // the last step's upper group has zero weights: it re-reads the lower one
+            if (ks >= 4 && ks < 8) own[ks - 4] = read(ks == 7 ? row.l6 : ks == 6 ? row.h4 : row.h0, OWN + (ks == 5 ? 2 * kRowPitch : 0));
+            if (E && ks >= 8) both[ks - 8] = read(next, (ks - 8) * kRowPitch);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const u32x4_t b = ks < 7 ? both[ks] : own[ks - 7];
+                // (as assembly: the builtin would put the sums where vector instructions cannot read them)
+                if (ks == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc[E][i]) : "a"(w[E][ks][i]), "a"(b));
+                else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc[E][i]) : "a"(w[E][ks][i]), "a"(b));
+                const int s = 2 * ks + i - 1;    // sums are read from the second MFMA on
+                __builtin_amdgcn_sched_barrier(0);
+                if (s >= 0) {
+#pragma unroll
+                    for (int k = s * N / 21; k < (s + 1) * N / 21; ++k) work(k);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     };
-    auto patch_load = [&](int it, const unsigned (&off)[3], int buf) {
-        if (it == 2 && wave >= 2) return;            // 640 piece slots: the third round is half a round
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rs, (lds_ptr_t)(smem + buf * kPatchPitch + (it * 256 + wave * 64) * 16), 16,
-                                                 off[it], 0, 0, 0);
-    };
-    TilePos cur;
-    cur.n = first_tile / per_image;
-    cur.tp = (first_tile - cur.n * per_image) / a.tiles_q;
-    cur.tq = first_tile - cur.n * per_image - cur.tp * a.tiles_q;
-    unsigned poffs[3];
-    if (first_tile < tile_end) {
-        patch_offsets(cur, poffs);
-#pragma unroll
-        for (int it = 0; it < 3; ++it) patch_load(it, poffs, 0);
-    }
-
-    if (tid < 32) {
-        const int c4 = (tid & 15) * 4;
-        const float* src = tid < 16 ? a.scale : a.shift;
-        *(f32x4_t*)(smem + SC_BASE + (tid < 16 ? 0 : 256) + c4 * 4) = *(const f32x4_t*)(src + c4);
-    }
-
-    // stationary weights: A fragment of channel tile i, K-step ks = 16 bytes at [32i + frow][(2ks + fhalf) * 8]
-    u32x4_t wreg[2][11];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int ks = 0; ks < 11; ++ks)
-            wreg[i][ks] = *(const u32x4_t*)(a.w + (size_t)(32 * i + frow) * (kPackedK * 2) + (2 * ks + fhalf) * 16);
-
-    // this lane's two conv pixels: byte offset of their K-run for tap row 0 inside a patch
-    int poff[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        int t = wave * 64 + j * 32 + frow;
-        if (t >= kConvR * kConvC) t = 0;             // the one padding row of the 256-row tile: computed, never used
-        const int cr = t / kConvC, cc = t - cr * kConvC;
-        poff[j] = (2 * cr) * kRowPitch + 12 * cc;
-    }
-
-    int buf = 0;
-    for (int tile = first_tile; tile < tile_end; tile += tile_step, buf ^= 1) {
-        const int n = cur.n, pp0 = cur.tp * kPoolTP, pq0 = cur.tq * kPoolTQ;
-        cur = advance(cur);
-        const int cr0 = 2 * pp0 - 1, cc0 = 2 * pq0 - 1;
-
-        __builtin_amdgcn_s_waitcnt(0);               // this tile's patch has landed (and the last tile's stores have left)
-        __syncthreads();                             // ... for every wavefront; the last tile's pooling reads are done
-        const bool has_next = tile + tile_step < tile_end;
-        if (has_next) patch_offsets(cur, poffs);
-
-        f32x16_t acc[2][2];
+    for (; cur.valid; t += 4 * step) {
+        const Strip nxt = decode(t + 4 * step);
+        const Pieces nxt_at = pieces(nxt);
+        // Of the first strip of a row, lane 0 has the column left of the image: it takes the first one instead, which changes no maximum.
+        const unsigned run = mine + 24 * (cur.q0 == 0 && frow == 0 ? 1 : frow);
+        unsigned shared = run + fhalf * 16, upper = run - 16 + fhalf * kRowPitch, lower = run - 16;
+        asm volatile("" : "+v"(shared), "+v"(upper), "+v"(lower));
+        // Likewise the conv rows above and below the image: the first and the last one.
+        auto conv_row = [&](int r) { return (unsigned)(max(min(r, a.P - 2 * cur.p0), cur.p0 == 0 ? 1 : 0) * (2 * kRowPitch)); };
+        auto bases = [&](unsigned r) {
+            return Bases{shared + r, shared + (r + 3 * kRowPitch), shared + (r + 6 * kRowPitch), upper + r, upper + (r + 4 * kRowPitch), lower + (r + 6 * kRowPitch)};
+        };
+        // Accumulator register e: column lane%32 = pixel, row 8*(e/4) + 4*(lane/32) + e%4 = channel.  Registers of both channel tiles
+        // one after the other: x = 16 i + e.
+        auto neighbour = [](float v) {
+            return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x138 /* wave_shr:1 */, 0xf, 0xf, true));
+        };
+        float before[2];
+        // Odd rows of the conv output are the last of a pooled row and the first of the next one.
+        auto last_odd = [&](int k) {      // 64
+            const int x = (k >> 2) * 2 + (k & 1), i = x >> 4, e = x & 15;
+            if (!(k & 2)) before[k & 1] = neighbour(acc[0][i][e]);
+            else odd[i][e] = __builtin_elementwise_maximum(before[k & 1], acc[0][i][e]);
+        };
+        auto last_even = [&](int k) {     // 96: m becomes the result
+            const int x = k / 3, i = x >> 4, e = x & 15;
+            if (k % 3 == 0) odd[i][e] = __builtin_elementwise_maximum(odd[i][e], acc[1][i][e]);
+            if (k % 3 == 1) m[i][e] = __builtin_elementwise_maximum(m[i][e], odd[i][e]);
+            if (k % 3 == 2) m[i][e] = m[i][e] * sc[x >> 2][e & 3] + sh[x >> 2][e & 3];
+        };
+        // A finished row goes to LDS, pixel by pixel, and from there eight pixels a store (straight from the lanes that have them, 16 bytes of a
+        // pixel each, a store took four times as long).
+        unsigned o[4];
+        auto pack = [&](int x) {
+            o[(x >> 1) & 3] = pack_bf16x2_relu(m[x >> 4][x & 15], m[x >> 4][(x & 15) + 1], kReluFloor);
+        };
+        auto stage = [&](int x) {         // lanes 0 .. 31 take all eight channels of the first group of four registers, lanes 32 .. 63 those of the second
+            const auto s0 = __builtin_amdgcn_permlane32_swap(o[0], o[2], false, false);
+            const auto s1 = __builtin_amdgcn_permlane32_swap(o[1], o[3], false, false);
+            *(lds_w16_t)(unsigned long)(staged + frow * kOutPitch + fhalf * 16 + x * 4) = u32x4_t{s0[0], s1[0], s0[1], s1[1]};
+        };
+        auto middle_odd = [&](int k) {    // 96: packs the result, then m is the maximum of the next pooled row
+            const int x = k / 6 * 2, i = x >> 4, e = (x & 15) + (k & 1);
+            if (k % 6 == 0) pack(x);
+            if (k % 6 == 1 && x % 8 == 6) stage(x - 6);
+            if (k % 6 == 2 || k % 6 == 3) before[k & 1] = neighbour(acc[0][i][e]);
+            if (k % 6 >= 4) m[i][e] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(before[k & 1], acc[0][i][e]), odd[i][e]);
+        };
+        u32x4_t line[4];
+        auto fetch = [&](int s) {         // lane l has 16 bytes of the pixels 8 s + l / 8; the first one of the strip is pixel 1
+            line[s] = *(lds_a16_t)(unsigned long)(staged + ((lane >> 3) + 8 * s) * kOutPitch + (lane & 7) * 16);
+        };
+        const int row_out = a.PQ * 128, records = min(a.cols, a.PQ - cur.q0) * 128, live_rows = min(a.rows, a.PP - cur.p0);
+        const unsigned char* out = a.y + (((long long)cur.n * a.PP + cur.p0) * a.PQ + cur.q0) * 128;
+        auto store = [&](int s, const unsigned char* out, bool live) {
+            const __amdgpu_buffer_rsrc_t y_rs = __builtin_amdgcn_make_buffer_rsrc((void*)out, 0, live ? records : 0, 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b128(line[s], y_rs, s ? lane * 16 + 896 + (s - 1) * 1024 : lane * 16 - 128, 0, 0);
+        };
+        const auto nothing = [](int) {};
+        constexpr std::integral_constant<int, 0> odds, n0;
+        constexpr std::integral_constant<int, 1> evens;
+        constexpr std::integral_constant<int, 40> n40;
+        constexpr std::integral_constant<int, 64> n64;
+        constexpr std::integral_constant<int, 96> n96;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-        // K group kg = 2ks + fhalf covers tap row kg / 3, 16-byte part kg % 3.  The upper half-wave
-        // is one group ahead: 16 bytes further, or 240 (next tap row, part 0) when kg % 3 == 2.
-        const unsigned char* P = smem + buf * kPatchPitch;
-        const unsigned char *b0[2], *bA[2], *bB[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            b0[j] = P + poff[j];
-            bA[j] = b0[j] + fhalf * 16;
-            bB[j] = b0[j] + fhalf * (kRowPitch - 32);
-        }
-        // B fragments are read one K-step ahead of the MFMAs that use them
-        auto read_b = [&](int ks, u32x4_t (&pf)[2]) {
-            const int kg = 2 * ks, off = (kg / 3) * kRowPitch + (kg % 3) * 16;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                // the last step's upper group (21) has zero weights: it re-reads group 20
-                const unsigned char* src = ks == 10 ? b0[j] : kg % 3 == 2 ? bB[j] : bA[j];
-                pf[j] = *(const u32x4a4_t*)(src + off);
-            }
+            for (int e = 0; e < 16; ++e) m[i][e] = 0.f;  // (of a row that is not there)
+        // Conv row r reads input rows 2r .. 2r + 6: new groups of four are needed by rows 0 (three, where row 1 stands in for it), 3, 5, ...
+        // (not by what is read ahead for them); those that rows 0 .. 2j + 2 have read make room for the next strip's.
+        auto load_next = [&](int k) {     // the strip's groups and then the next one's
+            const int g = k - (a.rows + 2);
+            Strip s = cur;
+            Pieces p = cur_at;
+            if (g >= 0) { s = nxt; p = nxt_at; }
+            load_group(s, p, g >= 0 ? g : k);
         };
-        constexpr int STEM_DEPTH = 1;   // deeper prefetch measured no faster
-        u32x4_t pf[STEM_DEPTH + 1][2];
+        wait_for_rows();
+        unsigned r1 = conv_row(1);
+        const Bases b0 = bases(conv_row(0));
 #pragma unroll
-        for (int d = 0; d < STEM_DEPTH; ++d) read_b(d, pf[d]);
-#pragma unroll
-        for (int ks = 0; ks < 11; ++ks) {
-            if (ks + STEM_DEPTH < 11) read_b(ks + STEM_DEPTH, pf[(ks + STEM_DEPTH) % (STEM_DEPTH + 1)]);
-            if (has_next && ks % 3 == 1 && ks < 9) patch_load(ks / 3, poffs, buf ^ 1);   // the next tile's patch: K-steps 1, 4, 7
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wreg[i][ks]),
-                                                                      __builtin_bit_cast(bf16x8_t, pf[ks % (STEM_DEPTH + 1)][j]),
-                                                                      acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int k = 0; k < 3; ++k) both[k] = read(b0.s0, k * kRowPitch);
+        multiply(odds, b0, 0, n0, nothing);
+        multiply(evens, b0, shared + r1, n64, last_odd);
+        for (int j = 0; j < a.rows; ++j) {
+            wait_for_rows();
+            const Bases b1 = bases(r1), b2 = bases(conv_row(2 * j + 2));
+            r1 = conv_row(2 * j + 3);
+            multiply(odds, b1, 0, n96, last_even);
+            multiply(evens, b1, b2.s0, n96, middle_odd);
+            multiply(odds, b2, 0, n40, [&](int k) {
+                if (k < 32) m[k >> 4][k & 15] = __builtin_elementwise_maximum(m[k >> 4][k & 15], acc[1][k >> 4][k & 15]);
+                if (k % 8 == 1 && k < 32) fetch(k / 8);
+                if (k >= 32 && k % 2) store((k - 32) / 2, out - row_out, j > 0 && j <= live_rows);
+            });
+            multiply(evens, b2, shared + r1, n64, last_odd);
+            load_next(j + a.ahead);
+            out += row_out;
         }
-
-        // Accumulator register e: column lane%32 = pixel, row 8*(e/4) + 4*(lane/32) + e%4 = channel.
-        // Scale and shift of the next channel group are read from LDS while this one is computed.
-        // ReLU is taken after the rounding, on the bf16 pair as signed 16-bit integers (rounding
-        // is monotone and keeps 0, so the order does not matter); the staged values are then
-        // non-negative bit patterns, which the pooling compares as unsigned integers.  Positions
-        // outside the conv output are cleared to 0 afterwards: each pooling window has a real pixel,
-        // so 0 never wins wrongly.
-        int tpix[2];
-        bool keep[2];
+        load_next(a.rows + a.ahead);
+        load_next(a.rows + 1 + a.ahead);
+        // The hazard recogniser does not see into the assembly: what reads the last sums keeps its distance (elsewhere MFMAs lie between).
+        asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[1][0]), "+v"(acc[1][1]));
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int t = wave * 64 + j * 32 + frow;
-            const int cr = t / kConvC, cc = t - cr * kConvC;
-            const int crow = cr0 + cr, ccol = cc0 + cc;
-            const bool ok = t < kConvR * kConvC && (unsigned)crow < (unsigned)a.P && (unsigned)ccol < (unsigned)a.Q;
-            keep[j] = ok;
-            tpix[j] = t;
+        for (int k = 0; k < 96; ++k) last_even(k);
+#pragma unroll
+        for (int x = 0; x < 32; x += 2) {
+            pack(x);
+            if (x % 8 == 6) stage(x - 6);
         }
-        const unsigned char* scp = smem + SC_BASE + 16 * fhalf;
-        f32x4_t sc_n = *(const f32x4_t*)scp, sh_n = *(const f32x4_t*)(scp + 256);
 #pragma unroll
-        for (int ig = 0; ig < 8; ++ig) {
-            const int i = ig >> 2, g = ig & 3;
-            const f32x4_t sc = sc_n, sh = sh_n;
-            if (ig + 1 < 8) {
-                sc_n = *(const f32x4_t*)(scp + (ig + 1) * 32);
-                sh_n = *(const f32x4_t*)(scp + 256 + (ig + 1) * 32);
-            }
+        for (int s = 0; s < 4; ++s) fetch(s);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                float v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = acc[i][j][4 * g + u] * sc[u] + sh[u];
-                const f32x2_t p0 = {v[0], v[1]}, p1 = {v[2], v[3]};
-                const i16x2_t zero = {0, 0};
-                const i16x2_t r0 = __builtin_elementwise_max(__builtin_bit_cast(i16x2_t, __builtin_convertvector(p0, bf16x2_t)), zero);
-                const i16x2_t r1 = __builtin_elementwise_max(__builtin_bit_cast(i16x2_t, __builtin_convertvector(p1, bf16x2_t)), zero);
-                u32x2_t o = {__builtin_bit_cast(unsigned, r0), __builtin_bit_cast(unsigned, r1)};
-                *(u32x2_t*)(smem + STG_BASE + tpix[j] * SROWB + (32 * i + 8 * g + 4 * fhalf) * 2) = o;
-            }
-        }
-        // border tiles only: a lane whose pixel lies outside the conv output clears what it staged
-        // (both half-waves of a pixel take the branch together and write the same zeros)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            if (!keep[j]) {
-                const u32x4_t z = {0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int q = 0; q < 8; ++q) *(u32x4_t*)(smem + STG_BASE + tpix[j] * SROWB + q * 16) = z;
-            }
-        __syncthreads();
-
-        // pooling: one item = (pooled pixel, 16-byte channel group); 448 items, two per thread (the
-        // second only for threads 0..191), the 18 LDS reads of both in flight together
-        {
-            constexpr int ITEMS = kPoolTP * kPoolTQ * 8;
-            u32x4_t m[2];
-            const unsigned char* base[2];
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int it = tid + 256 * k < ITEMS ? tid + 256 * k : tid;
-                const int px = it >> 3, lp = px / kPoolTQ, lq = px - lp * kPoolTQ;
-                base[k] = smem + STG_BASE + ((2 * lp) * kConvC + 2 * lq) * SROWB + (it & 7) * 16;
-                m[k] = *(const u32x4_t*)base[k];
-            }
-#pragma unroll
-            for (int rs = 1; rs < 9; ++rs)
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const u32x4_t t = *(const u32x4_t*)(base[k] + ((rs / 3) * kConvC + rs % 3) * SROWB);
-                    m[k] = __builtin_bit_cast(u32x4_t, __builtin_elementwise_max(__builtin_bit_cast(u16x8_t, m[k]), __builtin_bit_cast(u16x8_t, t)));
-                }
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int it = tid + 256 * k;
-                const int px = it >> 3, lp = px / kPoolTQ, lq = px - lp * kPoolTQ;
-                const int gp = pp0 + lp, gq = pq0 + lq;
-                if (it < ITEMS && gp < a.PP && gq < a.PQ)
-                    *(u32x4_t*)(a.y + (((size_t)(n * a.PP + gp) * a.PQ + gq) * 64) * 2 + (it & 7) * 16) = m[k];
-            }
-        }
+        for (int s = 0; s < 4; ++s) store(s, out - row_out, live_rows == a.rows);
+        cur = nxt;
+        cur_at = nxt_at;
     }
     __builtin_amdgcn_s_waitcnt(0);
+#endif
 }
 
 bool stem_pool_applicable(int dtype, int n, int h, int w, int cus)
@@ -492,15 +545,30 @@ bool stem_pool_applicable(int dtype, int n, int h, int w, int cus)
 std::atomic<int> g_stem_pool_force{-1};
 void stem_pool_force(int v) { g_stem_pool_force = v; }
 
-void pack_stem_rows(const float* oihw, uint16_t* out)
+void pack_stem_rows(const float* oihw, const float* scale, const float* shift, uint16_t* out)
 {
-    // [64][176]: tap row r occupies 24 elements, element 1 + 3s + c is tap (r, s) of input channel c
-    std::fill(out, out + 64 * kPackedK, (uint16_t)0);
-    for (int k = 0; k < 64; ++k)
-        for (int c = 0; c < 3; ++c)
-            for (int r = 0; r < 7; ++r)
-                for (int s2 = 0; s2 < 7; ++s2)
-                    out[k * kPackedK + r * 24 + 1 + 3 * s2 + c] = f32_to_bf16_bits(oihw[((k * 3 + c) * 7 + r) * 7 + s2]);
+    // Fragment [odd, even][K-step][channel tile] of 64 lanes x 8 elements: lane l has channel 32 tile + l % 32 of K group l / 32.
+    // K groups (tap row, part of 8 elements): steps 0 .. 6 are parts 0 and 1 of tap row `step`; steps 7 .. 10 tap rows 2 (step - 7) and the
+    // next one, part 2 for odd columns and part -1 for even ones.  Element e of an odd column's run is tap (e - 1) / 3, channel (e - 1) % 3;
+    // the run of the even column before it starts 6 elements earlier.
+    std::fill(out, out + kStemRowsElems, (uint16_t)0);
+    for (int f = 0; f < kFragments; ++f)
+        for (int l = 0; l < 64; ++l) {
+            const int even = f / 22, ks = f % 22 / 2, k = 32 * (f % 2) + l % 32, half = l / 32;
+            const int r = ks < 7 ? ks : 2 * (ks - 7) + half, part = ks < 7 ? half : even ? -1 : 2;
+            if (r >= 7) continue;
+            for (int v = 0; v < 8; ++v) {
+                const int e = part * 8 + v + (even ? 6 : 0) - 1;
+                if (e < 0 || e >= 21) continue;
+                const uint16_t bits = f32_to_bf16_bits(oihw[((k * 3 + e % 3) * 7 + r) * 7 + e / 3]);
+                out[(f * 64 + l) * 8 + v] = bits ^ (std::signbit(scale[k]) ? 0x8000 : 0);
+            }
+        }
+    for (int k = 0; k < 64; ++k) {
+        const float table[2] = {std::fabs(scale[k]), shift[k]};
+        memcpy(out + kFragments * 512 + 2 * k, table, 4);
+        memcpy(out + kFragments * 512 + 128 + 2 * k, table + 1, 4);
+    }
 }
 
 int launch_stem_pool(int dtype, int n, int h, int w, const void* x, const void* wts, const void* wts_rows,
@@ -526,15 +594,33 @@ int launch_stem_pool(int dtype, int n, int h, int w, const void* x, const void* 
                         g_stem_pool_force.load() != 1;
     if (prof && prof->on && (rc = prof->begin(stream, kKindStemPool, packed ? 2 : dtype, flops, bytes))) return rc;
     if (packed) {
-        a.w = (const unsigned char*)wts_rows;
-        constexpr int lds_rows = 2 * kPatchPitch + 256 * (64 * 2 + 16) + 512;
+        StemRowsArgs r;
+        memset(&r, 0, sizeof(r));
+        r.x = a.x; r.w = (const unsigned char*)wts_rows; r.y = a.y;
+        r.H = h; r.W = w; r.P = a.P; r.PP = a.PP; r.PQ = a.PQ;
+        r.strips_q = (a.PQ + kStripCols - 1) / kStripCols;
+        r.cols = ((a.PQ + r.strips_q - 1) / r.strips_q + 1) & ~1;  // even: a strip's rows begin on 16 bytes
+        // The fewest conv rows one after the other (a strip computes 2 * rows + 1 and costs about one more); of equal ones the lower strips.
+        double best = 1e30;
+        for (int rows = 1; rows <= kStripRows; ++rows) {
+            const long long strips = (long long)n * r.strips_q * ((a.PP + rows - 1) / rows), rounds = (strips + 4ll * cus - 1) / (4ll * cus);
+            const double cost = (double)rounds * (2 * rows + 2);
+            if (cost < best) { best = cost; r.rows = rows; }
+        }
+        r.ahead = std::min(kAhead, r.rows + 2);
+        r.strips_p = (a.PP + r.rows - 1) / r.rows;
+        const long long strips = (long long)n * r.strips_p * r.strips_q;
+        if (strips >= 1ll << 30) return fail(SGPRS_ERR_UNSUPPORTED, "too many stem strips");
+        r.strips = (int)strips;
+        r.per_die = (r.strips + 7) / 8;
+        div_constants(r.strips_q, &r.q_mul, &r.q_sh);
+        div_constants(r.strips_p, &r.p_mul, &r.p_sh);
         if (!raised[1]) {
-            SGPRS_HIP(hipFuncSetAttribute((const void*)stem_pool_packed_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                          lds_rows));
+            SGPRS_HIP(hipFuncSetAttribute((const void*)stem_pool_packed_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kPackedLds));
             raised[1] = true;
         }
-        SGPRS_LAUNCH(stem_pool_packed_kernel, dim3((int)std::min<long long>(nt, 2ll * cus)), dim3(256), lds_rows, stream, a,
-                     (unsigned)x_bytes);
+        const int grid = 8 * std::max(1, std::min(cus / 8, r.per_die));  // a partition's CUs are a multiple of eight
+        SGPRS_LAUNCH(stem_pool_packed_kernel, dim3(grid), dim3(256), kPackedLds, stream, r);
     } else if (dtype == SGPRS_BF16) {
         constexpr int patch = kInR * kInC * 4 * 2, stg = 256 * (64 * 2 + 16);
         constexpr int lds = 64 * (kStemK * 2 + 16) + (patch > stg ? patch : stg), occ = lds <= 80 * 1024 ? 2 : 1;

@@ -301,8 +301,8 @@ int sgprs_task_create_resnet18(int device, int dtype, int max_batch, const sgprs
         if ((rc = upload(t, shift.data(), cs.cout * sizeof(float), (void**)&t->conv[i].shift))) break;
         fragment_bytes += fragment_order(d) ? bytes : split_weight_bytes(d);
         if (i == 0 && dtype == SGPRS_BF16) {
-            std::vector<uint16_t> rows((size_t)64 * kStemRowsK);
-            pack_stem_rows(hp->conv_w[0], rows.data());
+            std::vector<uint16_t> rows(kStemRowsElems);
+            pack_stem_rows(hp->conv_w[0], scale.data(), shift.data(), rows.data());
             rc = upload(t, rows.data(), rows.size() * 2, &t->stem_w_rows);
         }
     }

@@ -341,6 +341,40 @@ def test_stage0_bf16_packed_row_and_four_slot_kernels_elementwise():
             pool.destroy()
 
 
+@pytest.mark.parametrize("nb, cus", [(1, 32), (1, 16), (2, 24), (1, 8), (4, 24), (3, 16), (2, 8), (3, 8), (5, 8), (7, 8), (9, 8)])
+def test_stage0_bf16_strips(nb, cus):
+    """The packed-row kernel's strips of every height, 1 to 7 pooled rows (the first seven cases), that do and do not divide
+    the image's 56, and then several of them per wavefront: against the four-slot kernel at one bf16 step (the same bf16 grid, fp32
+    sums in another order), with channels of negative and of zero scale; the last image against the oracle."""
+    dtype = S.SGPRS_BF16
+    params = make_resnet18_params(6, 2, bf16=True)
+    params["gamma"][0][::3] *= -1
+    params["gamma"][0][4] = 0
+    x = make_input(6, nb, (nb, 3, 224, 224), bf16=True)
+    xd = dev_nhwc(x, dtype)
+    pool = S.Pool(1, cus)
+    task = S.Task(params, dtype, nb, BN_EPS)
+    task.set_profiling(True)
+    outs = []
+    try:
+        for kind, name in ((-1, "stem_pool_packed_kernel"), (4, "stem_pool_kernel<1>")):
+            S.sgprs_conv_tuning_override(kind, 0, 1)
+            o = dev_empty(stage_shape(0, nb), dtype)
+            o.fill_(float("nan"))
+            task.stage_run(0, nb, xd.data_ptr(), o.data_ptr(), pool, 0)
+            pool.sync()
+            assert [r["name"] for r in task.kernel_times(0)] == [name]
+            outs.append(o)
+    finally:
+        S.sgprs_conv_tuning_override(-1, 0, 1)
+    a, b = (o.float().cpu().numpy() for o in outs)
+    d = np.abs(a - b)
+    assert np.all(d <= np.maximum(np.abs(b), 1e-3) * 2.0 ** -7), float(np.nanmax(d))
+    assert_close(host_nchw(outs[0])[-1:], oracle.resnet18_stage(0, params, BN_EPS, x[-1:]), dtype, f"last of {nb} images on {cus} CUs")
+    task.destroy()
+    pool.destroy()
+
+
 # ------------------------------------------------------------- config 3
 def test_config3_eight_bf16_instances_on_8x32_pool():
     dtype = S.SGPRS_BF16
