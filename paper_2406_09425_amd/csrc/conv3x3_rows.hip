@@ -38,12 +38,12 @@ typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 struct RowsArgs {
     const unsigned char* x;
-    const unsigned char* w;   // [64][3][3][64] bf16
+    const unsigned char* w;   // bf16, [64][3][3][64] or (tasks) in fragment order
     unsigned char* y;
     const float* scale;
     const float* shift;
     const unsigned char* res;  // nullable
-    int N, H, S, njobs, jpi, relu;
+    int N, H, S, njobs, jpi, relu, fragments;
     unsigned x_bytes, w_bytes, y_bytes;
 };
 
@@ -86,14 +86,19 @@ __device__ __forceinline__ void rows_body(const RowsArgs& a, unsigned char* smem
     const int j16 = lane & 15, g = lane >> 4;
     const int S = a.S;
 
-    // stationary weights: A operand, row j16 -> output channel 16q + j16, K group g
+    // stationary weights: A operand, row j16 -> output channel 16q + j16, K group g.  In fragment order a load is one KiB on end; out of
+    // rows, four neighbouring lanes are four cache lines and it takes longer, up to four times (us per launch inside the network, out of
+    // rows / in fragment order: batch 64 21.3 / 19.0, batch 128 32.7 / 30.5; in fragment order once per CU through LDS 20.1 at batch 64,
+    // behind the first rows instead of in front of them 20.4).
     const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, (int)a.w_bytes, 0x00020000);
+    const unsigned w_lane = a.fragments ? q * 1024 + lane * 16 : (q * 16 + j16) * 1152 + g * 16;
+    const int w_step = a.fragments ? 4096 : 64;
     u32x4_t wf[9][2];
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
-            wf[tap][ks] = __builtin_amdgcn_raw_buffer_load_b128(w_rs, (unsigned)((((q * 16 + j16) * 9 + tap) * 64 + ks * 32 + g * 8) * 2), 0, 0);
+            wf[tap][ks] = __builtin_amdgcn_raw_buffer_load_b128(w_rs, w_lane, (2 * tap + ks) * w_step, 0);
 
     // loader table: unit u = it * 512 + tid of a step's rows is 16-byte piece u % UPP of pixel slot u / UPP; slot
     // k * (WIDTH + 1) is a zero pixel, the WIDTH slots behind it are stream k; packed as stream << 16 | byte offset
@@ -330,13 +335,13 @@ bool plan_rows(const sgprs_conv_desc_t& d, int cus, int* rows_per_stream)
     return true;
 }
 
-int launch_conv3x3_rows(const sgprs_conv_desc_t& d, int S, const void* x, const void* w, const float* scale,
+int launch_conv3x3_rows(const sgprs_conv_desc_t& d, int S, const void* x, const void* w, const void* w_fragments, const float* scale,
                         const float* shift, const void* residual, void* y, hipStream_t stream, int cus, Profiler* prof)
 {
     if (d.w != kRowsWidth || d.cin != 64 || d.cout != 64 || S < 2 || d.h % (2 * S))
         return fail(SGPRS_ERR_INVALID_ARG, "internal: row-streaming plan does not match the shape");
     RowsArgs a;
-    a.x = (const unsigned char*)x; a.w = (const unsigned char*)w; a.y = (unsigned char*)y;
+    a.x = (const unsigned char*)x; a.w = (const unsigned char*)(w_fragments ? w_fragments : w); a.fragments = w_fragments != nullptr; a.y = (unsigned char*)y;
     a.scale = scale; a.shift = shift; a.res = (const unsigned char*)residual;
     a.N = d.n; a.H = d.h; a.S = S; a.jpi = d.h / (2 * S); a.njobs = d.n * a.jpi; a.relu = d.relu;
     a.x_bytes = a.y_bytes = (unsigned)((size_t)d.n * d.h * d.w * 128);

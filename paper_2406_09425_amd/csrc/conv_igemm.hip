@@ -617,7 +617,7 @@ int launch_conv(const sgprs_conv_desc_t& d, const void* x, const void* w, const 
         return launch_conv_split(d, p.variant, x, w, w_fragments, scale, shift, residual, y, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, stream, prof);
     if (p.kind == 6) return launch_conv3x3_kpatch(d, p.variant, x, w, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 5) return launch_conv3x3_wtile(d, p.variant, x, w_fragments, scale, shift, residual, y, stream, cus, prof);
-    if (p.kind == 3) return launch_conv3x3_rows(d, p.variant, x, w, scale, shift, residual, y, stream, cus, prof);
+    if (p.kind == 3) return launch_conv3x3_rows(d, p.variant, x, w, w_fragments, scale, shift, residual, y, stream, cus, prof);
     if (p.kind == 2) {
         return launch_conv3x3s2_patch(d, p.variant, x, w, scale, shift, y, nullptr, nullptr, nullptr, nullptr, nullptr, stream, cus,
                                       prof);

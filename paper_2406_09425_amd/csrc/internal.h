@@ -302,7 +302,7 @@ int launch_conv3x3s2_patch(const sgprs_conv_desc_t& d, int variant, const void* 
 // row-streaming 3x3 kernel (bf16, 64 -> 64 channels, 56-pixel rows)
 bool plan_rows(const sgprs_conv_desc_t& d, int cus, int* rows_per_stream);
 void rows_force_off(bool off);
-int launch_conv3x3_rows(const sgprs_conv_desc_t& d, int rows_per_stream, const void* x, const void* w, const float* scale,
+int launch_conv3x3_rows(const sgprs_conv_desc_t& d, int rows_per_stream, const void* x, const void* w, const void* w_fragments, const float* scale,
                         const float* shift, const void* residual, void* y, hipStream_t stream, int cus, Profiler* prof);
 // implicit GEMM with the K range split over the wavefronts of a workgroup (few output tiles)
 bool plan_ksplit(const sgprs_conv_desc_t& d, int cus, int* variant, double* cost_us);

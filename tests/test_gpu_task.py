@@ -375,6 +375,32 @@ def test_stage0_bf16_strips(nb, cus):
     pool.destroy()
 
 
+@pytest.mark.parametrize("nb", [2, 4])
+def test_stage1_bf16_rows_with_weights_in_fragment_order(nb):
+    """The row-streaming kernel of a task's layer 1 takes its weights in fragment order (jobs of 7 and of 14 rows, with and
+    without a residual): against the oracle, and next to the same task without that kernel."""
+    dtype = S.SGPRS_BF16
+    params = make_resnet18_params(6, 3, bf16=True)
+    x = np.maximum(make_input(6, nb, (nb, 64, 56, 56), bf16=True), 0)
+    ref = oracle.resnet18_stage(1, params, BN_EPS, x)
+    xd = dev_nhwc(x, dtype)
+    pool = S.Pool(1, 8)
+    task = S.Task(params, dtype, nb, BN_EPS)
+    task.set_profiling(True)
+    try:
+        for kind, rows in ((-1, True), (5, False)):
+            S.sgprs_conv_tuning_override(kind, 0, 1)
+            o = dev_empty(stage_shape(1, nb), dtype)
+            task.stage_run(1, nb, xd.data_ptr(), o.data_ptr(), pool, 0)
+            pool.sync()
+            assert [r["name"] == "conv3x3_rows_kernel" for r in task.kernel_times(1)] == [rows] * 4
+            assert_close(host_nchw(o), ref, dtype, f"bf16 stage 1, batch {nb}, row-streaming kernel {rows}")
+    finally:
+        S.sgprs_conv_tuning_override(-1, 0, 1)
+    task.destroy()
+    pool.destroy()
+
+
 # ------------------------------------------------------------- config 3
 def test_config3_eight_bf16_instances_on_8x32_pool():
     dtype = S.SGPRS_BF16
