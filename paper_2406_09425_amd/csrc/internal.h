@@ -270,6 +270,7 @@ int launch_mfma_probe(int cus, int steps, int random_data, unsigned long long* o
 int launch_load_probe(int cus, const void* buf, size_t buf_bytes, unsigned region, int iters, unsigned* out, hipStream_t stream);
 // fp32 stem on packed input rows, alone (pool false) or with the max-pool; no profiling record of its own
 bool stem_f32_applicable(int n, int h, int w);
+bool stem_f32_one_round(int n, int h, int w, int cus);  // with the pool: at most one tile per CU
 int launch_stem_f32(int n, int h, int w, const void* x, const void* wts, const float* scale, const float* shift, void* y,
                     int relu, bool pool, hipStream_t stream, int cus);
 // stage 0 fused: conv7x7/2 + BN + ReLU + max-pool 3x3/2

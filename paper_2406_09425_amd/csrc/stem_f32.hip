@@ -268,6 +268,15 @@ bool stem_f32_applicable(int n, int h, int w)
     return w % 4 == 0 && (long long)n * h * w * 12 < (1ll << 31);
 }
 
+// Tiles of `rows` x 8 pooled pixels.
+static long long pooled_tiles(int n, int h, int w, int rows)
+{
+    const int pp = (out_dim(h, 7, 2, 3) - 1) / 2 + 1, pq = (out_dim(w, 7, 2, 3) - 1) / 2 + 1;
+    return (long long)n * ((pp + rows - 1) / rows) * ((pq + 7) / 8);
+}
+
+bool stem_f32_one_round(int n, int h, int w, int cus) { return pooled_tiles(n, h, w, 4) <= cus; }
+
 int launch_stem_f32(int n, int h, int w, const void* x, const void* wts, const float* scale, const float* shift, void* y,
                     int relu, bool pool, hipStream_t stream, int cus)
 {
@@ -280,12 +289,16 @@ int launch_stem_f32(int n, int h, int w, const void* x, const void* wts, const f
     a.x_bytes = (unsigned)((long long)n * h * w * 12);
     // alone, 8 rows of 16 pixels unless that leaves CUs idle
     const int tall = pool || (long long)n * ((a.P + 7) / 8) * ((a.Q + 15) / 16) >= 2ll * cus;
-    const int tp = !pool && tall ? 8 : 4;
+    // with the pool, 4 rows of pooled pixels unless tiles of 2 (more conv pixels computed twice) all run at once: the chain of
+    // one tile is 6 x 37 MFMAs instead of 10 x 37
+    const bool low = pool && pooled_tiles(n, h, w, 2) <= cus;
+    const int tp = pool ? (low ? 2 : 4) : tall ? 8 : 4;
     a.tiles_p = ((pool ? a.PP : a.P) + tp - 1) / tp;
     a.tiles_q = pool ? (a.PQ + 7) / 8 : (a.Q + 15) / 16;
     const long long nt = (long long)n * a.tiles_p * a.tiles_q;
     if (nt >= (1ll << 31)) return fail(SGPRS_ERR_UNSUPPORTED, "too many stem tiles");
     a.ntiles = (int)nt;
+    if (low) return launch_tile<5, 17, true>(a, cus, stream);
     if (pool) return launch_tile<9, 17, true>(a, cus, stream);
     return tall ? launch_tile<8, 16, false>(a, cus, stream) : launch_tile<4, 16, false>(a, cus, stream);
 }

@@ -538,8 +538,9 @@ bool stem_pool_applicable(int dtype, int n, int h, int w, int cus)
     // smaller launches keep the finer-grained two-kernel path; in bf16 the fused kernel wins down
     // to one image (9.4 us against 8.5 + 4.9 us at batch 1); the line for fp32 is where its times cross
     // (us, two kernels and the gap between them against one, 256 CUs: 3 images 20 / 21, 5 images 24 / 21,
-    // 9 images 38 / 34), expressed in the 7x8 tiles counted here, not the 4x8 ones of its own kernel
-    return dtype == SGPRS_BF16 ? tiles >= 32 : tiles >= cus && stem_f32_applicable(n, h, w);
+    // 9 images 38 / 34), expressed in the 7x8 tiles counted here, not the 4x8 ones of its own kernel; and where
+    // its own tiles all run at once (the whole fp32 network, one image on 256 CUs: 115.5 us with two kernels, 112.8 fused)
+    return dtype == SGPRS_BF16 ? tiles >= 32 : (tiles >= cus || stem_f32_one_round(n, h, w, cus)) && stem_f32_applicable(n, h, w);
 }
 
 std::atomic<int> g_stem_pool_force{-1};

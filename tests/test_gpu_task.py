@@ -305,6 +305,26 @@ def test_stage0_fp32_fused_stem_pool_elementwise(cfg1):
         pool.destroy()
 
 
+@pytest.mark.parametrize("nb,cus", [(1, 256), (1, 224), (1, 192), (1, 128), (2, 224), (2, 256)])
+def test_stage0_fp32_one_round_of_tiles_elementwise(cfg1, nb, cus):
+    """Few images whose 4x8 tiles of pooled pixels (98 an image) all run at once take the fused kernel too, with
+    2x8 tiles where those do (196 an image): element by element against the oracle, two different inputs in turn."""
+    pool = S.Pool(1, cus)
+    task = S.Task(cfg1[0], S.SGPRS_F32, nb, BN_EPS)
+    task.set_profiling(True)
+    for seed in (17, 18):
+        x = make_input(1, seed, (nb, 3, 224, 224))
+        xd = dev_nhwc(x, S.SGPRS_F32)
+        o = dev_empty(stage_shape(0, nb), S.SGPRS_F32)
+        task.stage_run(0, nb, xd.data_ptr(), o.data_ptr(), pool, 0)
+        pool.sync()
+        assert [r["kind"] for r in task.kernel_times(0)] == [9]
+        # the bound of the fused kernel's other test
+        assert assert_close(host_nchw(o), oracle.resnet18_stage(0, cfg1[0], BN_EPS, x), S.SGPRS_F32, "fp32 stage 0") < 2e-5
+    task.destroy()
+    pool.destroy()
+
+
 def test_stage0_bf16_packed_row_and_four_slot_kernels_elementwise():
     """bf16 stage 0 runs the packed-row stem + pool kernel (kernel name recorded by the task); the
     tuning override switches to the 4-slot kernel.  Both, element by element against the oracle,
