@@ -232,7 +232,8 @@ int sgprs_add_relu(int dtype, size_t count, const void *a, const void *b, void *
  * w [cout][cin] (dtype, DEVICE), bias NULL or fp32[cout], logits fp32 [n][cout].
  * workspace: DEVICE fp32[n*cin] for the pooled vectors.  cin is 512, 1024 or 2048.
  * Up to 8 images with cin 512 or 1024 take one fused launch that leaves the
- * workspace untouched; its logits are bit-identical to the two-kernel path's. */
+ * workspace untouched (with cin 512 up to 31 may: beyond 8 it fills the
+ * workspace too); its logits are bit-identical to the two-kernel path's. */
 int sgprs_avgpool_fc(int dtype, int n, int hw, int cin, int cout, const void *x, const void *w,
                      const float *bias, float *logits, float *workspace, sgprs_pool_t *pool,
                      int partition);

@@ -183,6 +183,48 @@ __global__ __launch_bounds__(256) void add_relu_kernel(const void* __restrict__ 
     s.store_nt(y, idx);
 }
 
+// 16 bytes as floats.
+template <int DT> __device__ __forceinline__ void add_vec(float (&s)[Vec<DT>::N], const u32x4_t t)
+{
+#pragma unroll
+    for (int i = 0; i < Vec<DT>::N; ++i)
+        s[i] += DT == SGPRS_F32 ? __uint_as_float(t[i % 4]) : __uint_as_float(i % 2 ? t[i / 2] & 0xffff0000u : t[i / 2] << 16);
+}
+
+// Sums of the positions j = wave (mod 4) of one image [HW][CV vectors], VB * 64 channel vectors from c on, in rising order: all 13 of
+// a 7x7 map in one round trip instead of four at a time (one image, whole network: bf16 73.4 -> 72.5 us, fp32 112.3 -> 111.0).
+// A position past the image in a group of four reads as +0, which changes no sum that began at +0.
+template <int DT, int VB> __device__ __forceinline__ void pool_positions(const void* image, int HW, int CV, int c, int wave, float (&s)[VB][Vec<DT>::N])
+{
+#pragma unroll
+    for (int v = 0; v < VB; ++v)
+#pragma unroll
+        for (int i = 0; i < Vec<DT>::N; ++i) s[v][i] = 0.f;
+#if __HIP_DEVICE_COMPILE__  // the buffer-resource builtins exist in the device pass only
+    for (int j0 = 0; j0 < HW; j0 += 64) {
+        const unsigned char* block = (const unsigned char*)image + (size_t)j0 * CV * 16;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)block, 0, min(HW - j0, 64) * CV * 16, 0x00020000);
+        u32x4_t t[VB][16];
+#pragma unroll
+        for (int v = 0; v < VB; ++v)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) t[v][u] = u32x4_t{0, 0, 0, 0};
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            if (j0 + 16 * g + wave < HW)
+#pragma unroll
+                for (int v = 0; v < VB; ++v)
+#pragma unroll
+                    for (int u = 4 * g; u < 4 * g + 4; ++u)
+                        t[v][u] = __builtin_amdgcn_raw_buffer_load_b128(rs, ((wave + 4 * u) * CV + c + 64 * v) * 16, 0, 0);
+#pragma unroll
+        for (int v = 0; v < VB; ++v)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) add_vec<DT>(s[v], t[v][u]);
+    }
+#endif
+}
+
 // ---- global average pool: x [n][hw][c] -> v [n][c] fp32 ---------------------
 // One workgroup per (image, 64 channel vectors): the four wavefronts take
 // every fourth position, partial sums meet in LDS and are added in wavefront
@@ -268,89 +310,75 @@ __global__ __launch_bounds__(256) void avgpool_stream_kernel(const void* __restr
 // ---- avg-pool + FC in one launch, for a few images ---------------------------------
 // Every workgroup pools its image once more (the 50 KB come from the L2) with exactly the
 // arithmetic of avgpool_kernel, keeps the vector in LDS, and its four wavefronts then compute
-// four output rows each with exactly the arithmetic of fc_kernel: one kernel less at batch 1-8,
-// the same bits.
-template <int DT, int CPL /* 512-element passes */>
+// R output rows each with exactly the arithmetic of fc_kernel: one kernel less, the same bits.
+// Weights wait as they are in memory (4 or 8 registers a row), and the R sums go through the
+// shuffles together (one after the other, one image on 256 CUs took 4.3 us instead of 3.8).  What
+// bounds it: one chain of a round trip, LDS and shuffles for few images, the 50 KB (fp32 100) per
+// workgroup out of the L2 for more.
+template <int DT, int CPL /* 512-element passes */, int R /* output rows per wavefront */>
 __global__ __launch_bounds__(256) void avgpool_fc_kernel(const void* __restrict__ x, const void* __restrict__ w,
-                                                         const float* __restrict__ bias, float* __restrict__ y, int HW,
-                                                         int Cout)
+                                                         const float* __restrict__ bias, float* __restrict__ y,
+                                                         float* __restrict__ pooled_out, int HW, int Cout)
 {
-    constexpr int N = Vec<DT>::N, C = CPL * 512, CV = C / N, VP = CV / 64, R = 4;
+    constexpr int N = Vec<DT>::N, C = CPL * 512, CV = C / N, VP = CV / 64, WV = 8 / N;
+    constexpr int VB = VP == 2 && CPL == 1 && R == 4 ? 2 : 1;  // channel vectors of a lane whose positions are in flight together
     __shared__ float part[4][CV][N];
     __shared__ __align__(16) float pooled[C];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t n = blockIdx.y;
+    const int o0 = (blockIdx.x * 4 + wave) * R, o = o0 + lane;  // (lane r < R stores row r)
+    const float b = bias && lane < R && o < Cout ? bias[o] : 0.f;
     // the weight rows do not depend on the pooling: fetch them first so both latencies overlap
-    float wr[R][CPL][8];
+    u32x4_t wr[R][CPL][WV];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int o = min((int)(blockIdx.x * 4 + wave) * R + r, Cout - 1);
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int j = 0; j < CPL; ++j) {
-            const size_t e0 = (size_t)o * C + j * 512 + lane * 8;
-            if constexpr (DT == SGPRS_BF16) {
-                Vec<SGPRS_BF16> t;
-                t.load(w, e0 / 8);
+        for (int j = 0; j < CPL; ++j)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) wr[r][j][i] = t.v[i];
-            } else {
-                Vec<SGPRS_F32> t0, t1;
-                t0.load(w, e0 / 4);
-                t1.load(w, e0 / 4 + 1);
+            for (int u = 0; u < WV; ++u)
+                wr[r][j][u] = ((const u32x4_t*)w)[((size_t)min(o0 + r, Cout - 1) * C + j * 512 + lane * 8) / N + u];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { wr[r][j][i] = t0.v[i]; wr[r][j][4 + i] = t1.v[i]; }
-            }
-        }
-    }
+    for (int vp = 0; vp < VP; vp += VB) {
+        float s[VB][N];
+        pool_positions<DT, VB>((const u32x4_t*)x + n * HW * CV, HW, CV, vp * 64 + lane, wave, s);
 #pragma unroll
-    for (int vp = 0; vp < VP; ++vp) {
-        const int c = vp * 64 + lane;
-        float s[N];
+        for (int v = 0; v < VB; ++v)
 #pragma unroll
-        for (int i = 0; i < N; ++i) s[i] = 0.f;
-        int j = wave;
-        for (; j + 12 < HW; j += 16) {
-            Vec<DT> t[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) t[u].load(x, (n * HW + j + 4 * u) * CV + c);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int i = 0; i < N; ++i) s[i] += t[u].v[i];
-        }
-        for (; j < HW; j += 4) {
-            Vec<DT> t;
-            t.load(x, (n * HW + j) * CV + c);
-#pragma unroll
-            for (int i = 0; i < N; ++i) s[i] += t.v[i];
-        }
-#pragma unroll
-        for (int i = 0; i < N; ++i) part[wave][c][i] = s[i];
+            for (int i = 0; i < N; ++i) part[wave][(vp + v) * 64 + lane][i] = s[v][i];
     }
     __syncthreads();
     const float hw = (float)HW;
     for (int e = threadIdx.x; e < C; e += 256) {
         const int c = e / N, i = e % N;
-        pooled[e] = (((part[0][c][i] + part[1][c][i]) + part[2][c][i]) + part[3][c][i]) / hw;
+        const float v = (((part[0][c][i] + part[1][c][i]) + part[2][c][i]) + part[3][c][i]) / hw;
+        pooled[e] = v;
+        if (pooled_out && blockIdx.x == 0) pooled_out[n * C + e] = v;
     }
     __syncthreads();
+    float sum[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int o = (blockIdx.x * 4 + wave) * R + r;
-        if (o >= Cout) break;
-        float sum = 0.f;
+        sum[r] = 0.f;
 #pragma unroll
         for (int j = 0; j < CPL; ++j) {
             const f32x4_t v0 = *(const f32x4_t*)(pooled + j * 512 + lane * 8), v1 = *(const f32x4_t*)(pooled + j * 512 + lane * 8 + 4);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) sum += wr[r][j][i] * v0[i];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sum += wr[r][j][4 + i] * v1[i];
+            for (int i = 0; i < 8; ++i) {
+                float wv;
+                if constexpr (DT == SGPRS_BF16) wv = __uint_as_float(i % 2 ? wr[r][j][0][i / 2] & 0xffff0000u : wr[r][j][0][i / 2] << 16);
+                else wv = __uint_as_float(wr[r][j][i / 4][i % 4]);
+                sum[r] += wv * (i < 4 ? v0[i & 3] : v1[i & 3]);
+            }
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-        if (lane == 0) y[n * Cout + o] = sum + (bias ? bias[o] : 0.f);
     }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+        for (int r = 0; r < R; ++r) sum[r] += __shfl_xor(sum[r], off, 64);
+    float mine = sum[0];
+#pragma unroll
+    for (int r = 1; r < R; ++r) mine = lane == r ? sum[r] : mine;
+    if (lane < R && o < Cout) y[n * Cout + o] = mine + b;
 }
 
 // ---- FC: logits[n][o] = sum_c w[o][c] v[n][c] + b[o] ------------------------
@@ -532,16 +560,30 @@ int launch_avgpool_fc(int dtype, int n, int hw, int cin, int cout, const void* x
 {
     const int vec = dtype == SGPRS_BF16 ? 8 : 4;
     const size_t es = dtype_size(dtype);
-    if (n <= 8 && (cin == 512 || cin == 1024)) {  // a few images: one launch (its bits equal the two-kernel path's)
-        const dim3 fgrid((cout + 15) / 16, n);
+    // One launch for few images.  8 output rows per wavefront instead of 4 pool an image 32 times instead of 63, in a longer chain:
+    // better once workgroups of 4 rows share the CUs (us with 4 / 8 rows: bf16 1 image on 256 CUs 3.8 / 4.1, 8 images 4.3 / 4.3, on
+    // 96 CUs 6.7 / 5.4, on 32 CUs 12.6 / 9.4; fp32, twice the bytes, 4 images on 256 CUs 4.1 / 4.5, 8 on 256 5.1 / 4.8, on 96 9.8 / 6.7).
+    // Beyond 8 images against two launches (us, two / one): bf16 16 images on 256 CUs 7.0 / 4.9, on 64 9.8 / 9.5, 13 on 96 8.7 / 7.2,
+    // 24 on 64 11.8 / 12.8, 31 on 160 9.4 / 8.7, on 96 11.3 / 11.9; fp32 16 on 256 6.5 / 6.0, 20 on 256 7.0 / 7.6, 16 on 160 7.4 / 8.0.
+    // From 32 images the matrix cores' FC is faster (40 images on 256 CUs: bf16 6.9 / 7.8, fp32 8.2 / 11.7).  The bits are the two launches'.
+    const long long wgs4 = (long long)((cout + 15) / 16) * n, wgs8 = (long long)((cout + 31) / 32) * n;
+    const bool wide = n <= 8 ? wgs4 > (dtype == SGPRS_BF16 ? 2ll : 1ll) * cus
+                             : cin == 512 && n < 32 && wgs8 <= (dtype == SGPRS_BF16 ? 10ll : 2ll) * cus;
+    if ((wide || n <= 8) && (cin == 512 || cin == 1024)) {
+        const dim3 fgrid(wide ? (cout + 31) / 32 : (cout + 15) / 16, n);
+        float* const pooled = n > 8 ? ws : nullptr;  // up to 8 images the workspace stays as it is
         PROF_BEGIN(kKindFc, 2 + dtype, 2.0 * n * cin * cout,
                    (double)cin * cout * es + (double)n * hw * cin * es + (double)n * cout * 4);
         if (dtype == SGPRS_BF16) {
-            if (cin == 512) SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_BF16, 1>), fgrid, dim3(256), 0, stream, x, w, bias, logits, hw, cout);
-            else SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_BF16, 2>), fgrid, dim3(256), 0, stream, x, w, bias, logits, hw, cout);
+            if (wide && cin == 512) SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_BF16, 1, 8>), fgrid, dim3(256), 0, stream, x, w, bias, logits, pooled, hw, cout);
+            else if (wide) SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_BF16, 2, 8>), fgrid, dim3(256), 0, stream, x, w, bias, logits, pooled, hw, cout);
+            else if (cin == 512) SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_BF16, 1, 4>), fgrid, dim3(256), 0, stream, x, w, bias, logits, pooled, hw, cout);
+            else SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_BF16, 2, 4>), fgrid, dim3(256), 0, stream, x, w, bias, logits, pooled, hw, cout);
         } else {
-            if (cin == 512) SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_F32, 1>), fgrid, dim3(256), 0, stream, x, w, bias, logits, hw, cout);
-            else SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_F32, 2>), fgrid, dim3(256), 0, stream, x, w, bias, logits, hw, cout);
+            if (wide && cin == 512) SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_F32, 1, 8>), fgrid, dim3(256), 0, stream, x, w, bias, logits, pooled, hw, cout);
+            else if (wide) SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_F32, 2, 8>), fgrid, dim3(256), 0, stream, x, w, bias, logits, pooled, hw, cout);
+            else if (cin == 512) SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_F32, 1, 4>), fgrid, dim3(256), 0, stream, x, w, bias, logits, pooled, hw, cout);
+            else SGPRS_LAUNCH((avgpool_fc_kernel<SGPRS_F32, 2, 4>), fgrid, dim3(256), 0, stream, x, w, bias, logits, pooled, hw, cout);
         }
         SGPRS_HIP(hipGetLastError());
         PROF_END();

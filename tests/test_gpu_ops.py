@@ -273,6 +273,41 @@ def test_avgpool_fc_one_launch_equals_two(pools, dtype, cin, hw):
     assert_close(one.cpu().numpy().astype(np.float64), ref[:8], dtype, "one launch")
 
 
+@pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
+@pytest.mark.parametrize("cin,cout", [(512, 1000), (512, 1), (512, 31), (512, 33), (1024, 1000), (1024, 33)])
+def test_avgpool_fc_rows_per_wavefront_same_bits(dtype, cin, cout):
+    """The images of one tensor in calls of 1 to 31 on 8, 32 and 256 CUs (4 or 8 output rows per wavefront,
+    one launch or two, ragged output blocks): logits and, beyond 8 images, pooled vectors are the same bits."""
+    td = torch.bfloat16 if dtype == S.SGPRS_BF16 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(cout)
+    x = torch.randn((31, 21, cin), generator=g, device="cuda").to(td)
+    w = torch.randn((cout, cin), generator=g, device="cuda").to(td)
+    b = torch.randn((cout,), generator=g, device="cuda")
+    pooled = x.double().mean(1)
+    ref = pooled @ w.double().t() + b.double()
+    torch.cuda.synchronize()
+    first = None
+    for cus in (8, 32, 256):
+        pool = S.Pool(1, cus)
+        for n in (31, 17, 16, 9, 8, 4, 1):
+            y = torch.full((n + 1, cout), float("nan"), device="cuda")
+            ws = torch.full((n * cin,), float("nan"), device="cuda")
+            torch.cuda.synchronize()
+            S.sgprs_avgpool_fc(dtype, n, 21, cin, cout, x.data_ptr(), w.data_ptr(), b.data_ptr(), y.data_ptr(), ws.data_ptr(), pool, 0)
+            pool.sync()
+            first = y[:n].clone() if first is None else first
+            assert torch.equal(y[:n], first[:n]), (cus, n)
+            assert torch.isnan(y[n]).all()
+            # cin fp32 products and their sums: 2^-24 each, of terms whose size is that of the products
+            bound = 2.0 ** -24 * (cin + 18) * (pooled[:n].abs() @ w.double().abs().t() + b.double().abs())
+            assert ((y[:n].double() - ref[:n]).abs() <= bound).all(), (cus, n)
+            if n > 8:
+                assert (ws.double() - pooled[:n].flatten()).abs().max() < 1e-6
+            else:
+                assert torch.isnan(ws).all()
+        pool.destroy()
+
+
 def test_error_paths_enqueue_nothing(pools):
     pool = pools["full"]
     x = torch.zeros(64, device="cuda")
