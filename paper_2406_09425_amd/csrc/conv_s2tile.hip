@@ -23,7 +23,6 @@
 
 namespace sgprs {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
@@ -80,7 +79,7 @@ __device__ __forceinline__ unsigned s2_min16(unsigned a, unsigned b)
 
 // Four wavefronts: two tiles of pixels (KS = 1) or two halves of the input channels (KS = 2), times two channel tiles of 64.
 template <int TM, int KS>
-__global__ __launch_bounds__(256, s2_workgroups(TM, KS)) void conv_igemm_pair_kernel(const S2tileArgs a)
+__global__ __launch_bounds__(256, s2_workgroups(TM, KS)) void conv_s2tile_kernel(const S2tileArgs a)
 {
 #if __HIP_DEVICE_COMPILE__
     constexpr int TN = kS2TN, AHEAD = s2_ahead(TM, KS), STEPS = kS2Steps, CAP = s2_cap(TM), PATCH = CAP * 64, BUF = s2_buffer(TM);
@@ -398,7 +397,7 @@ const char* s2tile_variant_name(int v)
 {
     static char buf[kS2tileVariants][48];
     if (v < 0 || v >= kS2tileVariants) return "?";
-    snprintf(buf[v], 48, "conv_igemm_pair_kernel<%d, %d>", s2_tm(v), s2_ks(v));
+    snprintf(buf[v], 48, "conv_s2tile_kernel<%d, %d>", s2_tm(v), s2_ks(v));
     return buf[v];
 }
 
@@ -406,10 +405,10 @@ template <int TM, int KS> static int launch_s2(const S2tileArgs& a, int grid, hi
 {
     static std::atomic<bool> raised{false};
     if (!raised) {
-        SGPRS_HIP(hipFuncSetAttribute((const void*)conv_igemm_pair_kernel<TM, KS>, hipFuncAttributeMaxDynamicSharedMemorySize, s2_lds(TM)));
+        SGPRS_HIP(hipFuncSetAttribute((const void*)conv_s2tile_kernel<TM, KS>, hipFuncAttributeMaxDynamicSharedMemorySize, s2_lds(TM)));
         raised = true;
     }
-    SGPRS_LAUNCH((conv_igemm_pair_kernel<TM, KS>), dim3(grid), dim3(256), s2_lds(TM), stream, a);
+    SGPRS_LAUNCH((conv_s2tile_kernel<TM, KS>), dim3(grid), dim3(256), s2_lds(TM), stream, a);
     SGPRS_HIP(hipGetLastError());
     return SGPRS_OK;
 }

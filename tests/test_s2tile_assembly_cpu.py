@@ -10,7 +10,7 @@ from paper_2406_09425_amd import build
 
 from test_wtile_assembly_cpu import check
 
-KERNEL = re.compile(r"^(_ZN5sgprs22conv_igemm_pair_kernelILi(\d)ELi(\d)E\w+):.*?^\.Lfunc_end", re.S | re.M)
+KERNEL = re.compile(r"^(_ZN5sgprs18conv_s2tile_kernelILi(\d)ELi(\d)E\w+):.*?^\.Lfunc_end", re.S | re.M)
 
 
 def patch_waits(text, left):
