@@ -3,19 +3,21 @@
 //
 // What bounds the paired implicit GEMM is its operands' way: tiles of 64 or 128 pixels fetch every input pixel
 // 2.25 times and every weight once per tile through the LDS, with a barrier per k-tile, and inside a network the weights
-// come cold (64 images on 256 CUs, 14x14x256 -> 512: 19 us in a loop, 27 with inputs that change).  Here
+// come cold (64 images on 256 CUs, 14x14x256 -> 512: 19 us in a loop, 28 with inputs that change).  Here
 //   * a wavefront owns 98 (or up to 64) output pixels x 64 channels of both convolutions: 7 x 4 (4 x 4) MFMA tiles
 //     each, in accumulator registers; the shortcut is one more step, on the centre tap's pixels, which are there;
-//   * weights are one coalesced KiB per fragment from the L2 to registers, requested five steps ahead;
+//   * weights are one coalesced KiB per fragment from the L2 to registers, requested five steps ahead (two in the 4 x 1 variant,
+//     whose two workgroups on a CU cover for each other and leave room for no more);
 //   * two channel tiles share a patch of 32 input channels, fetched once, double buffered, the next one requested in the
-//     first steps of the ten that this one takes: one barrier per 280 MFMAs.  Four planes (rows and columns even
-//     or odd) make consecutive output pixels read consecutive pixels; 64 bytes of each, groups permuted against conflicts;
+//     first steps of the ten that this one takes: one barrier per 280 MFMAs of a wavefront (4 x 4 tiles: 160).  Four planes (rows
+//     and columns even or odd) make consecutive output pixels read consecutive pixels; 64 bytes of each, groups permuted against conflicts;
 //   * where pixels are few, two wavefronts share a tile by input channels (their sums meet in LDS).
-// Timestamps, 64 images on 256 CUs, 56x56x64 -> 128 (us): 5.5 until the first patch is there (25.7 MB for the launch: the
-// memory's rate), two stages of 3.5 (2.7 of MFMAs at the clock they leave), 3.5 for the stores.
-// Inside networks whose inputs change, us per launch, paired implicit GEMM / this, the three blocks: 64 images on 256 CUs 21.8
-// / 19.0, 19.9 / 17.2, 27.2 / 18.0; 128 images 37.9 / 36, 28.5 / 25, 32.0 / 24.7; 48 images on 192 CUs 20.7 / 17.7, 19.1 / 16.5,
-// 26.4 / 17.5; 16 on 64 18.0 / 16.2, 15.7 / 15.2, 18.6 / 13.9.  Whole inferences: 64 images 364.1 -> 347.8, 128 images 582.1 -> 570.7.
+// Timestamps, 64 images on 256 CUs, 56x56x64 -> 128, 7 x 1 tiles (us): 5.5 until the first patch is there (25.7 MB for the
+// launch: the memory's rate), two stages of 3.5 (2.7 of MFMAs at the clock they leave), 3.5 for the stores.
+// Inside networks whose inputs change, us per launch, paired implicit GEMM / this, the three blocks: 64 images on 256 CUs 22.8
+// / 19.6, 20.8 / 17.8, 28.1 / 18.6; 128 images 39.0 / 37.8, 29.2 / 26.0, 33.0 / 25.9; 48 images on 192 CUs 21.7 / 17.8, 19.9 / 17.6,
+// 27.4 / 17.9; 16 on 64 18.6 / 15.1, 16.2 / 16.5 (not chosen), 20.1 / 14.4; 68 on 256 23.3 / 24.8, 20.6 / 24.2, 28.4 / 24.0
+// (not chosen, the last one for its few items).
 #include <algorithm>
 #include <type_traits>
 
@@ -368,28 +370,36 @@ bool s2tile_fits(const sgprs_conv_desc_t& d, const sgprs_conv_desc_t& d1, int v)
            v >= 0 && v < kS2tileVariants && (d.cin / 64) % s2_ks(v) == 0 && s2tile_shape(d, s2_tm(v), &t);
 }
 
-// Estimated time (us) inside a network whose inputs change: launch, then rounds of items, each a fixed part and its
-// stages, at the clock that the share of the chip in use leaves, and a part of the memory traffic.  Two workgroups on a CU
-// share its matrix cores.  Fitted to the three blocks, 13 to 128 images on 64 to 256 CUs: within 10 %.
+// Estimated time (us) inside a network whose inputs change: a fixed part, what the busiest CU's items take (a part of their own and their
+// stages, at the clock that the share of the chip in use leaves) and a part of the memory traffic.  Whole items on the busiest
+// CU: one more than the others have takes as long as one on each (4 x 1 tiles, 56x56x64 -> 128 on 256 CUs: 64 images 19.6, 68 images 24.8).
+// Two 4 x 1 items share a CU's matrix cores: 7.9 for the pair, 4.8 for one that is left.  Fitted to the three blocks, 1 to 512
+// images on 8 to 256 CUs: 4 to 5 % off rms, 16 % at most.
 bool plan_s2tile(const sgprs_conv_desc_t& d, const sgprs_conv_desc_t& d1, int cus, int* variant, double* cost_us)
 {
-    *cost_us = 1e30;
+    double best = 1e30;
     for (int v = 0; v < kS2tileVariants; ++v) {
         S2tileShape t;
         const int ks = s2_ks(v), tm = s2_tm(v), stages = d.cin / 32 / ks;
-        if (!s2tile_fits(d, d1, v) || !s2tile_shape(d, tm, &t)) continue;
+        // 4 x 1 tiles only where a wavefront has two stages: with four (28x28x128 -> 256) the other tiles or the implicit GEMM are as fast
+        // or faster at 156 of 167 sizes (by 46 % at most) and slower by 6 % at most
+        if (!s2tile_fits(d, d1, v) || !s2tile_shape(d, tm, &t) || (v == 2 && stages > 2)) continue;
         const double mb = 2e-6 * ((double)d.n * d.h * d.w * d.cin + 10.0 * d.cin * d.cout + 2.0 * d.n * out_dim(d.h, 3, 2, 1) * out_dim(d.w, 3, 2, 1) * d.cout);
         const long long items = (ks == 2 ? t.gm : (t.gm + 1) / 2) * (d.cout / 128), per_die = (items + 7) / 8;
-        const int cus_die = std::max(1, cus / 8);
-        const double active = (double)std::min<long long>(items, cus) / 256, rounds = (double)((per_die + cus_die - 1) / cus_die), per_cu = (double)per_die / cus_die;
-        const double each = 8.5 + stages * (2.05 + 0.8 * active) * (1.0 + 0.7 * std::max(0.0, std::min(per_cu, 2.0) - 1.0));  // (4 x 1 tiles)
-        const double cost = tm == 7 ? 2.0 + rounds * (7.4 + stages * (2.55 + 0.35 * active)) + 0.07 * mb
-                          : ks == 2 ? 2.0 + rounds * (4.5 + stages * (1.65 + 0.75 * active)) + 0.07 * mb
-                                    : each * std::max(1.0, per_cu / 2.0) + 0.03 * mb;
+        const int cus_die = std::max(1, cus / 8), busiest = (int)((per_die + cus_die - 1) / cus_die);
+        const double active = (double)std::min<long long>(items, cus) / 256;
+        const double cost = v == 0 ? 6.5 + busiest * (2.7 + stages * 2.85) + 0.11 * mb
+                          : v == 1 ? 7.5 + busiest * (3.5 + stages * (2.25 + 0.7 * active)) + 0.063 * mb
+                          : v == 2 ? 5.2 + busiest / 2 * 7.9 + busiest % 2 * 4.8 + 0.126 * mb
+                                   : 4.9 + busiest * (2.4 + stages * (1.75 + 0.6 * active)) + 0.058 * mb;
         // with fewer items every CU waits for cold weights: 6 images on 96 CUs, 48 items, 13.6 us against 10.3
-        if (items * 5 >= cus * 3 && cost < *cost_us) { *cost_us = cost; *variant = v; }
+        if (items * 5 < cus * 3) continue;
+        // Each of two workgroups on a CU fetches the weights, and on the whole chip the launches after this one pay for it (56x56x64 -> 128, 128
+        // images on 256 CUs, 4 x 1 / 7 x 1 tiles: traced 35.7 / 37.8 us, whole network 551.1 / 548.5).
+        const double rank = cost + (v == 2 ? 0.2 * busiest * active : 0.0);
+        if (rank < best) { best = rank; *cost_us = cost; *variant = v; }
     }
-    return *cost_us < 1e30;
+    return best < 1e30;
 }
 
 // Name as a profiler prints it.

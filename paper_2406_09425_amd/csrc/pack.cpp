@@ -194,6 +194,22 @@ static ConvPlan plan_conv_uncached(const sgprs_conv_desc_t& d, int cus, bool has
     return best;
 }
 
+// What a paired launch whose estimate in a loop is `cost` takes inside a network whose inputs change, where its weights are cold and it
+// has the clock that the launches around it leave (bf16).  Implicit GEMM by tile: fixed, k-tiles of a workgroup, workgroups per CU, k-tiles
+// of the busiest CU, the same in steps of two thirds of a round (where the time of the 128x128 tiles jumps), k-tiles times the share of
+// the chip in use, MB.
+static double pair_in_network(const ConvPlan& p, const sgprs_conv_desc_t& d0, const sgprs_conv_desc_t& d1, int cus, double cost)
+{
+    if (p.kind != 0) return 1.05 * cost;
+    const double blocks = (double)p.grid_m * p.grid_n, rounds = blocks / cus, active = std::min(rounds, 1.0) * cus / 256;
+    if (p.variant > 2) return 0.9 * cost + 5.4 * active;
+    static const double kNet[3][7] = {{4.5, 0.05, 1.8, 0.216, 0.142, 0.0, 0.094}, {2.3, 0.02, 1.2, 0.235, 0.0, 0.26, 0.04}, {-3.3, 0.40, 1.8, 0.03, 0.0, 0.29, 0.0}};
+    const double* c = kNet[p.variant];
+    const double mb = 2e-6 * ((double)d0.n * d0.h * d0.w * d0.cin + 10.0 * d0.cin * d0.cout + 2.0 * d0.n * out_dim(d0.h, 3, 2, 1) * out_dim(d0.w, 3, 2, 1) * d0.cout);
+    return c[0] + c[2] * std::max(1.0, 2.0 * rounds) + c[6] * mb +
+           p.ktiles * (c[1] + c[3] * std::ceil(rounds) + c[4] * std::ceil(1.5 * rounds) / 1.5 + c[5] * active);
+}
+
 // A down-sampling block's first 3x3 convolution and its 1x1 shortcut in one launch: the tile that is
 // best for the two together.  The single-convolution estimates do not rank these launches: the
 // implicit-GEMM workgroups of the shortcut run beside the main problem's (three to five fit a CU)
@@ -261,12 +277,12 @@ static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs
             best.kind = 7; best.variant = v; best.bm = 1;
         }
     }
-    // The estimates above are of launches in a loop, whose weights stay in the L2: inside a network these take 0.8 to 1.0 times
-    // that on 64 to 96 CUs and 1.05 to 1.4 times on 128 to 256 (64 images on 256 CUs, the three blocks: 18.7 / 16.6 / 19.3
-    // estimated, 21.8 / 19.9 / 27.2 measured with inputs that change; with the kernel chosen here 19.0 / 17.2 / 18.0).
+    // Near a tie the launch chosen so far stays.  Of the three blocks' launches at 167 sizes (1 to 512 images, 8 to 256 CUs, inputs that change)
+    // this choice is more than 2 % slower than the implicit GEMM and the K-split kernel at 6, by 1 to 9 % (25 images on 224 CUs, 56x56x64 -> 128:
+    // 13.6 / 14.9 us), and leaves 1 % of all their time to the best launch of each size.
     int variant;
     double cost;
-    if (fragments && plan_s2tile(d0, d1, cus, &variant, &cost) && cost < best_cost * (0.9 + 0.3 * std::min(cus, 256) / 256)) {
+    if (fragments && plan_s2tile(d0, d1, cus, &variant, &cost) && cost < 0.98 * pair_in_network(best, d0, d1, cus, best_cost)) {
         best = ConvPlan();
         best.kind = 8; best.variant = variant; best.bm = 1;
     }
