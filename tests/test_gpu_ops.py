@@ -250,7 +250,8 @@ def test_avgpool_fc_parity(pools, dtype, n):
 @pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
 @pytest.mark.parametrize("cin,hw", [(512, 49), (1024, 21), (512, 3)])
 def test_avgpool_fc_one_launch_equals_two(pools, dtype, cin, hw):
-    """Up to 8 images take the single fused launch, more take avg-pool then FC: the same bits."""
+    """Up to 8 images take the single fused launch, 9 on 8 CUs avg-pool then FC (test_avgpool_fc_launches_by_size has the
+    names): the same bits."""
     bf = dtype == S.SGPRS_BF16
     x = make_input(96, cin + hw, (9, cin, hw, 1), bf16=bf)
     w = make_conv_weight(96, cin + hw, 1, 1000, cin, 1, bf16=bf)[:, :, 0, 0]
@@ -262,9 +263,10 @@ def test_avgpool_fc_one_launch_equals_two(pools, dtype, cin, hw):
     two = torch.full((9, 1000), float("nan"), dtype=torch.float32, device="cuda")
     one = torch.full((8, 1000), float("nan"), dtype=torch.float32, device="cuda")
     S.sgprs_avgpool_fc(dtype, 9, hw, cin, 1000, xd.data_ptr(), wd.data_ptr(), bd.data_ptr(), two.data_ptr(),
-                       ws.data_ptr(), pools["full"], 0)
+                       ws.data_ptr(), pools[8], 0)
     S.sgprs_avgpool_fc(dtype, 8, hw, cin, 1000, xd.data_ptr(), wd.data_ptr(), bd.data_ptr(), one.data_ptr(),
                        ws.data_ptr(), pools["full"], 0)
+    pools[8].sync()
     pools["full"].sync()
     assert torch.isfinite(one).all()
     assert torch.equal(one, two[:8])
@@ -274,13 +276,16 @@ def test_avgpool_fc_one_launch_equals_two(pools, dtype, cin, hw):
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=DT_ID.get)
-@pytest.mark.parametrize("cin,cout", [(512, 1000), (512, 1), (512, 31), (512, 33), (1024, 1000), (1024, 33)])
-def test_avgpool_fc_rows_per_wavefront_same_bits(dtype, cin, cout):
-    """The images of one tensor in calls of 1 to 31 on 8, 32 and 256 CUs (4 or 8 output rows per wavefront,
-    one launch or two, ragged output blocks): logits and, beyond 8 images, pooled vectors are the same bits."""
+@pytest.mark.parametrize("cin,cout,hw", [(512, 1000, 21), (512, 1, 21), (512, 31, 21), (512, 33, 21), (1024, 1000, 21), (1024, 33, 21),
+                                         (512, 1000, 49), (512, 33, 1), (512, 31, 3), (512, 33, 64), (512, 33, 65), (512, 31, 130),
+                                         (1024, 33, 49), (1024, 33, 65)])
+def test_avgpool_fc_rows_per_wavefront_same_bits(dtype, cin, cout, hw):
+    """The images of one tensor in calls of 1 to 31 on 8, 32 and 256 CUs (4 or 8 output rows per wavefront, one launch or two,
+    ragged output blocks; maps smaller than the four wavefronts, 7x7, and around the 64 positions that are requested at
+    once): logits and, beyond 8 images, pooled vectors are the same bits."""
     td = torch.bfloat16 if dtype == S.SGPRS_BF16 else torch.float32
     g = torch.Generator(device="cuda").manual_seed(cout)
-    x = torch.randn((31, 21, cin), generator=g, device="cuda").to(td)
+    x = torch.randn((31, hw, cin), generator=g, device="cuda").to(td)
     w = torch.randn((cout, cin), generator=g, device="cuda").to(td)
     b = torch.randn((cout,), generator=g, device="cuda")
     pooled = x.double().mean(1)
@@ -293,13 +298,15 @@ def test_avgpool_fc_rows_per_wavefront_same_bits(dtype, cin, cout):
             y = torch.full((n + 1, cout), float("nan"), device="cuda")
             ws = torch.full((n * cin,), float("nan"), device="cuda")
             torch.cuda.synchronize()
-            S.sgprs_avgpool_fc(dtype, n, 21, cin, cout, x.data_ptr(), w.data_ptr(), b.data_ptr(), y.data_ptr(), ws.data_ptr(), pool, 0)
+            S.sgprs_avgpool_fc(dtype, n, hw, cin, cout, x.data_ptr(), w.data_ptr(), b.data_ptr(), y.data_ptr(), ws.data_ptr(), pool, 0)
             pool.sync()
             first = y[:n].clone() if first is None else first
             assert torch.equal(y[:n], first[:n]), (cus, n)
             assert torch.isnan(y[n]).all()
-            # cin fp32 products and their sums: 2^-24 each, of terms whose size is that of the products
-            bound = 2.0 ** -24 * (cin + 18) * (pooled[:n].abs() @ w.double().abs().t() + b.double().abs())
+            # cin fp32 products and their sums: 2^-24 each, of terms whose size is that of the products; and the sums of a quarter of the
+            # positions, of the four quarters and the division, of terms whose size is that of the inputs
+            bound = 2.0 ** -24 * ((cin + 18) * (pooled[:n].abs() @ w.double().abs().t() + b.double().abs()) +
+                                  (hw / 4 + 5) * (x[:n].double().abs().mean(1) @ w.double().abs().t()))
             assert ((y[:n].double() - ref[:n]).abs() <= bound).all(), (cus, n)
             if n > 8:
                 assert (ws.double() - pooled[:n].flatten()).abs().max() < 1e-6

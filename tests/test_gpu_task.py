@@ -423,6 +423,27 @@ def test_stage1_bf16_rows_with_weights_in_fragment_order(nb):
     pool.destroy()
 
 
+@pytest.mark.parametrize("dtype", [S.SGPRS_F32, S.SGPRS_BF16], ids=DT_ID.get)
+def test_avgpool_fc_launches_by_size(cfg1, dtype):
+    """Stage 5 is one launch up to 8 images and, where its workgroups do not wait for CUs, up to 31; else avg-pool and FC."""
+    task = S.Task(cfg1[0], dtype, 32, BN_EPS)
+    task.set_profiling(True)
+    x = torch.zeros((32, 7, 7, 512), device="cuda").to(torch.bfloat16 if dtype == S.SGPRS_BF16 else torch.float32)
+    o = torch.zeros((32, 1000), device="cuda")
+    torch.cuda.synchronize()
+    for cus in (8, 256):
+        pool = S.Pool(1, cus)
+        for n in (1, 8, 9, 31, 32):
+            task.stage_run(5, n, x.data_ptr(), o.data_ptr(), pool, 0)
+            pool.sync()
+            names = [r["name"] for r in task.kernel_times(5)]
+            one = n <= 8 or (cus == 256 and n <= (31 if dtype == S.SGPRS_BF16 else 9))
+            fc = "fc_gemm_kernel" if n == 32 and (dtype == S.SGPRS_BF16 or cus == 8) else "fc_kernel"
+            assert names == (["avgpool_fc_kernel"] if one else ["avgpool_kernel", fc]), (cus, n)
+        pool.destroy()
+    task.destroy()
+
+
 # ------------------------------------------------------------- config 3
 def test_config3_eight_bf16_instances_on_8x32_pool():
     dtype = S.SGPRS_BF16
