@@ -566,6 +566,10 @@ int launch_avgpool_fc(int dtype, int n, int hw, int cin, int cout, const void* x
     // Beyond 8 images against two launches (us, two / one): bf16 16 images on 256 CUs 7.0 / 4.9, on 64 9.8 / 9.5, 13 on 96 8.7 / 7.2,
     // 24 on 64 11.8 / 12.8, 31 on 160 9.4 / 8.7, on 96 11.3 / 11.9; fp32 16 on 256 6.5 / 6.0, 20 on 256 7.0 / 7.6, 16 on 160 7.4 / 8.0.
     // From 32 images the matrix cores' FC is faster (40 images on 256 CUs: bf16 6.9 / 7.8, fp32 8.2 / 11.7).  The bits are the two launches'.
+    // Two lines that are not where the times cross.  Few CUs want the matrix cores' FC far below 32 images (fp32, 512 inputs: 8 CUs 9 / 31 / 32
+    // images 39 / 77 / 18.5, 32 CUs 20 / 32 images 18.5 / 8.5; bf16 8 CUs 31 / 32 images 73 / 14.2); in bf16 its sums are further off (2.3e-6
+    // against 9e-8), and in fp32 the bits would no longer be the one launch's.  And up to 8 images take one launch, which leaves the workspace as
+    // it is, also where two are faster (fp32, 1024 inputs: 8 CUs 8 / 9 images 93 / 57, 32 CUs 28 / 18).
     const long long wgs4 = (long long)((cout + 15) / 16) * n, wgs8 = (long long)((cout + 31) / 32) * n;
     const bool wide = n <= 8 ? wgs4 > (dtype == SGPRS_BF16 ? 2ll : 1ll) * cus
                              : cin == 512 && n < 32 && wgs8 <= (dtype == SGPRS_BF16 ? 10ll : 2ll) * cus;
