@@ -248,8 +248,10 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
 // workgroups per CU before it): batch 64 22.6 / 35.6, batch 128 40.4 / 66.4, 13 images on 96 CUs 11.5 / 18.9, 16 images 9.1 / 15.9,
 // one image 6.0 / 9.3, one on 32 CUs 5.9 / 11.2.
 // The elements of a run beside its taps (0 / 22 / 23, of even columns the three before and none behind) are real neighbouring inputs
-// multiplied by zero weights: the result equals the plain definition for finite inputs (a non-finite input pixel would also
-// reach the output columns next to its window).
+// multiplied by zero weights: the result equals the plain definition for finite inputs.  A pixel that is NaN or infinite also makes the sums of
+// these columns NaN: odd ones whose window begins right of it (its channel 2) or ends left of it (channels 0 and 1), even ones whose window
+// begins right of it.  (An infinite one in a window's last row, too, meets the zero weights of the last K group: at the right end of odd columns'
+// windows, at the left end of even ones'.)  NaN sums count as 0 (the ReLU's result) in the maximum over a window, the others as they are.
 constexpr int kStripCols = 30, kStripRows = 7;       // pooled columns and rows of a strip, at most
 constexpr int kRowPitch = 24 * kStripCols + 48;      // bytes of an input row in LDS: 48 pieces of 16
 constexpr int kGroupBytes = 4 * kRowPitch;           // rows are loaded by fours: three instructions
@@ -281,6 +283,34 @@ template <int N> __device__ __forceinline__ void stem_wait_vmcnt()
 {
     static_assert(N <= 63, "vmcnt range");
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+}
+
+// Maxima that leave NaN out, as the ReLU does that comes after them: a NaN sum counts as 0, the others of its window as they are.  (As assembly: the
+// builtin would first quieten each operand that no instruction known to it has written, one more instruction apiece; in pairs, or with the
+// neighbour's value as an operand, because the compiler keeps what reads a result of assembly an instruction away from it.)
+__device__ __forceinline__ float max_of(float a, float b)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+// b = max(a, b, v), a = max(a, v)
+__device__ __forceinline__ void max_both(float& a, float& b, float v)
+{
+    asm("v_max_f32 %0, %0, %2\n\tv_max_f32 %1, %1, %0" : "+&v"(a), "+v"(b) : "v"(v));
+}
+// With the lane before: its value (0 for lane 0) and this one's.
+__device__ __forceinline__ float max_neighbours(float v)
+{
+    float r;
+    asm("v_max_f32_dpp %0, %1, %1 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(r) : "v"(v));
+    return r;
+}
+__device__ __forceinline__ float max_neighbours(float v, float a)
+{
+    float r;
+    asm("v_max_f32_dpp %0, %1, %1 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\tv_max_f32 %0, %0, %2" : "=&v"(r) : "v"(v), "v"(a));
+    return r;
 }
 
 __global__ __launch_bounds__(256, 1) void stem_pool_packed_kernel(const StemRowsArgs a)
@@ -423,21 +453,12 @@ __global__ __launch_bounds__(256, 1) void stem_pool_packed_kernel(const StemRows
         };
         // Accumulator register e: column lane%32 = pixel, row 8*(e/4) + 4*(lane/32) + e%4 = channel.  Registers of both channel tiles
         // one after the other: x = 16 i + e.
-        auto neighbour = [](float v) {
-            return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x138 /* wave_shr:1 */, 0xf, 0xf, true));
-        };
-        float before[2];
         // Odd rows of the conv output are the last of a pooled row and the first of the next one.
-        auto last_odd = [&](int k) {      // 64
-            const int x = (k >> 2) * 2 + (k & 1), i = x >> 4, e = x & 15;
-            if (!(k & 2)) before[k & 1] = neighbour(acc[0][i][e]);
-            else odd[i][e] = __builtin_elementwise_maximum(before[k & 1], acc[0][i][e]);
-        };
-        auto last_even = [&](int k) {     // 96: m becomes the result
-            const int x = k / 3, i = x >> 4, e = x & 15;
-            if (k % 3 == 0) odd[i][e] = __builtin_elementwise_maximum(odd[i][e], acc[1][i][e]);
-            if (k % 3 == 1) m[i][e] = __builtin_elementwise_maximum(m[i][e], odd[i][e]);
-            if (k % 3 == 2) m[i][e] = m[i][e] * sc[x >> 2][e & 3] + sh[x >> 2][e & 3];
+        auto last_odd = [&](int x) { odd[x >> 4][x & 15] = max_neighbours(acc[0][x >> 4][x & 15]); };  // 32
+        auto last_even = [&](int k) {     // 66: m becomes the result, an element behind its maxima
+            const int x = k / 2, y = x - 1;
+            if (k % 2 == 0 && x < 32) max_both(odd[x >> 4][x & 15], m[x >> 4][x & 15], acc[1][x >> 4][x & 15]);
+            if (k % 2 == 1 && y >= 0) m[y >> 4][y & 15] = m[y >> 4][y & 15] * sc[y >> 2][y & 3] + sh[y >> 2][y & 3];
         };
         // A finished row goes to LDS, pixel by pixel, and from there eight pixels a store (straight from the lanes that have them, 16 bytes of a
         // pixel each, a store took four times as long).
@@ -450,12 +471,11 @@ __global__ __launch_bounds__(256, 1) void stem_pool_packed_kernel(const StemRows
             const auto s1 = __builtin_amdgcn_permlane32_swap(o[1], o[3], false, false);
             *(lds_w16_t)(unsigned long)(staged + frow * kOutPitch + fhalf * 16 + x * 4) = u32x4_t{s0[0], s1[0], s0[1], s1[1]};
         };
-        auto middle_odd = [&](int k) {    // 96: packs the result, then m is the maximum of the next pooled row
-            const int x = k / 6 * 2, i = x >> 4, e = (x & 15) + (k & 1);
-            if (k % 6 == 0) pack(x);
-            if (k % 6 == 1 && x % 8 == 6) stage(x - 6);
-            if (k % 6 == 2 || k % 6 == 3) before[k & 1] = neighbour(acc[0][i][e]);
-            if (k % 6 >= 4) m[i][e] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(before[k & 1], acc[0][i][e]), odd[i][e]);
+        auto middle_odd = [&](int k) {    // 64: packs the result, then m is the maximum of the next pooled row
+            const int x = k / 4 * 2, i = x >> 4, e = (x & 15) + (k & 1);
+            if (k % 4 == 0) pack(x);
+            if (k % 4 == 1 && x % 8 == 6) stage(x - 6);
+            if (k % 4 >= 2) m[i][e] = max_neighbours(acc[0][i][e], odd[i][e]);
         };
         u32x4_t line[4];
         auto fetch = [&](int s) {         // lane l has 16 bytes of the pixels 8 s + l / 8; the first one of the strip is pixel 1
@@ -470,9 +490,10 @@ __global__ __launch_bounds__(256, 1) void stem_pool_packed_kernel(const StemRows
         const auto nothing = [](int) {};
         constexpr std::integral_constant<int, 0> odds, n0;
         constexpr std::integral_constant<int, 1> evens;
+        constexpr std::integral_constant<int, 32> n32;
         constexpr std::integral_constant<int, 40> n40;
         constexpr std::integral_constant<int, 64> n64;
-        constexpr std::integral_constant<int, 96> n96;
+        constexpr std::integral_constant<int, 66> n66;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -492,19 +513,19 @@ __global__ __launch_bounds__(256, 1) void stem_pool_packed_kernel(const StemRows
 #pragma unroll
         for (int k = 0; k < 3; ++k) both[k] = read(b0.s0, k * kRowPitch);
         multiply(odds, b0, 0, n0, nothing);
-        multiply(evens, b0, shared + r1, n64, last_odd);
+        multiply(evens, b0, shared + r1, n32, last_odd);
         for (int j = 0; j < a.rows; ++j) {
             wait_for_rows();
             const Bases b1 = bases(r1), b2 = bases(conv_row(2 * j + 2));
             r1 = conv_row(2 * j + 3);
-            multiply(odds, b1, 0, n96, last_even);
-            multiply(evens, b1, b2.s0, n96, middle_odd);
+            multiply(odds, b1, 0, n66, last_even);
+            multiply(evens, b1, b2.s0, n64, middle_odd);
             multiply(odds, b2, 0, n40, [&](int k) {
-                if (k < 32) m[k >> 4][k & 15] = __builtin_elementwise_maximum(m[k >> 4][k & 15], acc[1][k >> 4][k & 15]);
+                if (k < 32) m[k >> 4][k & 15] = max_of(m[k >> 4][k & 15], acc[1][k >> 4][k & 15]);
                 if (k % 8 == 1 && k < 32) fetch(k / 8);
                 if (k >= 32 && k % 2) store((k - 32) / 2, out - row_out, j > 0 && j <= live_rows);
             });
-            multiply(evens, b2, shared + r1, n64, last_odd);
+            multiply(evens, b2, shared + r1, n32, last_odd);
             load_next(j + a.ahead);
             out += row_out;
         }
@@ -513,7 +534,7 @@ __global__ __launch_bounds__(256, 1) void stem_pool_packed_kernel(const StemRows
         // The hazard recogniser does not see into the assembly: what reads the last sums keeps its distance (elsewhere MFMAs lie between).
         asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[1][0]), "+v"(acc[1][1]));
 #pragma unroll
-        for (int k = 0; k < 96; ++k) last_even(k);
+        for (int k = 0; k < 66; ++k) last_even(k);
 #pragma unroll
         for (int x = 0; x < 32; x += 2) {
             pack(x);

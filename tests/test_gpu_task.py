@@ -397,6 +397,59 @@ def test_stage0_bf16_strips(nb, cus):
     pool.destroy()
 
 
+def test_stage0_bf16_pixels_that_are_not_finite():
+    """One pixel that is NaN or infinite, in an image each: at the image's corners, in both columns of a conv column pair and at the
+    edge between two strips.  A conv output that it makes NaN counts as 0 in its windows, and the others as they are.  Beside the 7x7
+    windows that hold it, it reaches (times zero weights) odd conv columns whose window is one pixel to its left, and right of channel
+    2, and even ones whose window is to its right; and in the last row of a window it meets zero weights as well, in odd columns at the
+    window's right end, in even ones at its left end: these count as 0 too.  Elsewhere every bit is that of the clean image."""
+    dtype = S.SGPRS_BF16
+    params = make_resnet18_params(6, 2, bf16=True)
+    params["gamma"][0][::3] *= -1
+    at = [(0, 0), (223, 223), (0, 223), (100, 100), (100, 101), (101, 102), (101, 103), (57, 111), (58, 112), (57, 113), (58, 114), (57, 116)]
+    bad = [(h, w, (i + j) % 3, v) for i, (h, w) in enumerate(at) for j, v in enumerate((float("nan"), float("inf"), -float("inf")))]
+    nb = len(bad)
+    x = torch.from_numpy(make_input(6, 1, (1, 3, 224, 224), bf16=True)).double()
+    wt = torch.from_numpy(params["conv_w"][0]).double()
+    scale, shift = (torch.from_numpy(v).double()[:, None, None] for v in S.sgprs_fold_bn(*(params[k][0] for k in ("gamma", "beta", "mean", "var")), BN_EPS))
+    task = S.Task(params, dtype, nb, BN_EPS)
+    task.set_profiling(True)
+    xs = x.repeat(nb, 1, 1, 1)
+    for i, (h, w, c, v) in enumerate(bad):
+        xs[i, c, h, w] = v
+    outs = []
+    for images, n in ((x, 1), (xs, nb)):
+        xd = images.permute(0, 2, 3, 1).to(torch.bfloat16).cuda().contiguous()
+        o = dev_empty(stage_shape(0, n), dtype)
+        torch.cuda.synchronize()
+        pool = S.Pool(1, 256)
+        task.stage_run(0, n, xd.data_ptr(), o.data_ptr(), pool, 0)
+        pool.sync()
+        pool.destroy()
+        assert [r["name"] for r in task.kernel_times(0)] == ["stem_pool_packed_kernel"]
+        outs.append(o.cpu().reshape(n, 56, 56, 64).permute(0, 3, 1, 2))
+    task.destroy()
+    clean, got = outs
+    # 147 fp32 products and their sums (the rounding to bf16, half of 2^-7, is counted below)
+    slack = 2.0 ** -24 * 150 * float((torch.nn.functional.conv2d(x.abs(), wt.abs(), stride=2, padding=3) * scale.abs()).max())
+    col = torch.arange(112)
+    for i, (h, w, c, v) in enumerate(bad):
+        conv = torch.nn.functional.conv2d(xs[i:i + 1], wt, stride=2, padding=3)[0] * scale + shift
+        left, right = 2 * col - w == 4, w - 2 * col == 4         # of the column's window
+        beside = torch.where(col % 2 == 1, (left & (c == 2)) | (right & (c < 2)), left)
+        touched = ((2 * col - h).abs() <= 3)[:, None] & (((2 * col - w).abs() <= 3) | beside)
+        end = torch.where(col % 2 == 1, (w - 2 * col == 2) | (w - 2 * col == 3), (2 * col - w == 3) | (2 * col - w == 2) & (c < 2))
+        lost = ((2 * col - h).abs() <= 3)[:, None] & beside | (2 * col - h == -3)[:, None] & end
+        counted = torch.where(torch.isnan(conv) | lost, 0.0, conv.clamp_min(0))
+        ref = torch.nn.functional.max_pool2d(counted[None], 3, 2, 1)[0]
+        reached = torch.nn.functional.max_pool2d(touched[None].double(), 3, 2, 1)[0].bool()
+        g = got[i].double()
+        assert torch.equal(got[i][:, ~reached], clean[0][:, ~reached]), bad[i]
+        inf = torch.isinf(ref)
+        assert not (torch.isinf(g) ^ inf).any() and not torch.isnan(g).any(), (bad[i], (torch.isinf(g) ^ inf).nonzero()[:4].tolist())
+        assert ((g - ref).abs()[~inf] <= 2.0 ** -8 * ref[~inf] + slack).all(), (bad[i], float((g - ref).abs()[~inf].max()))
+
+
 @pytest.mark.parametrize("nb", [2, 4])
 def test_stage1_bf16_rows_with_weights_in_fragment_order(nb):
     """The row-streaming kernel of a task's layer 1 takes its weights in fragment order (jobs of 7 and of 14 rows, with and

@@ -1,7 +1,8 @@
 """The bf16 stem kernel writes its MFMAs as inline assembly, which the compiler's hazard recogniser does not look into.
 What the source relies on is checked in the assembly: between the last MFMA that writes a register and whatever else touches it
-lie two more MFMAs or the fence of wait states, around the loops too; operands come from LDS; nothing is spilled; and the
-waits for input rows are those that the source counts."""
+lie two more MFMAs or the fence of wait states, around the loops too; operands come from LDS; what an inline maximum reads from
+the lane before was not written by the two instructions in front of it; nothing is spilled; and the waits for input rows are those
+that the source counts."""
 import os
 import re
 import subprocess
@@ -32,9 +33,12 @@ def unrolled(text):
 
 def check(text):
     """Number of inline MFMAs in the order of the text."""
-    count, fence, written, loaded = 0, 0, {}, {}
+    count, fence, written, loaded, recent = 0, 0, {}, {}, [set(), set()]
     for inline, t in instructions(text):
         name, _, operands = t.partition(" ")
+        if inline and name.endswith("_dpp"):
+            assert not registers(operands.partition(",")[2]) & (recent[0] | recent[1]), t
+        recent = [recent[1], registers(operands.partition(",")[0]) if name.startswith("v_") and not name.startswith("v_mfma") else set()]
         if inline and name.startswith("v_mfma"):
             m = MFMA.match(t)
             assert m, t  # starts from zero or accumulates in place
@@ -71,10 +75,12 @@ def test_the_check_sees_what_it_looks_for():
     mfma = lambda d: f"\t;;#ASMSTART\n\tv_mfma_f32_32x32x16_bf16 v[{d}:{d + 15}], a[0:3], a[4:7], 0\n\t;;#ASMEND\n"
     load, use = "\tds_read_b128 a[0:3], v99\n\tds_read_b128 a[4:7], v99\n", "\tv_add_f32_e32 v98, v97, v3\n"
     assert check(load + mfma(0) + mfma(16) + mfma(32) + use) == 3
+    shifted = "\t;;#ASMSTART\n\tv_max_f32_dpp v96, v98, v98 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t;;#ASMEND\n"
+    assert check(use + "\ts_add_u32 s0, s0, s1\n" * 2 + shifted) == 0
     loop = load + ".LBB0_1:\n" + mfma(0) + mfma(16) + mfma(32) + "\ts_cbranch_scc1 .LBB0_1\n" + mfma(16) + use
     assert unrolled(loop).count("v_mfma") == 7 and check(unrolled(loop)) == 7
     for bad in (load + mfma(0) + mfma(16) + use, load + use + mfma(0) + mfma(16) + "\tv_accvgpr_write_b32 a1, v3\n" + mfma(32),
-                unrolled(load + ".LBB0_1:\n" + use + mfma(16) + mfma(0) + "\ts_cbranch_scc1 .LBB0_1\n")):
+                unrolled(load + ".LBB0_1:\n" + use + mfma(16) + mfma(0) + "\ts_cbranch_scc1 .LBB0_1\n"), use + "\ts_add_u32 s0, s0, s1\n" + shifted):
         try:
             check(bad)
         except (AssertionError, KeyError):
