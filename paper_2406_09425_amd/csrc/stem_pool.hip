@@ -1,10 +1,12 @@
 // Stage 0 in one kernel, bf16 (fp32: stem_f32.hip): conv 7x7/2 (3 -> 64) + folded BN + ReLU + max-pool 3x3/2.
 //
-// The stem's 64 x 112 x 112 output is the largest tensor of the network; written
-// out and read back by a separate pooling kernel it costs more HBM traffic than
-// everything else in the stage.  Here a workgroup owns 7 x 8 pooled pixels.  It
-// computes the 15 x 17 conv pixels they depend on (255 rows of a 256-row MFMA
-// tile; the overlap between neighbouring tiles is recomputed), keeps them in
+// The stem's 64 x 112 x 112 output is the largest tensor of the network; written out and read back by a
+// separate pooling kernel it costs more HBM traffic than everything else in the stage.  Two kernels:
+// stem_pool_packed_kernel, further down, is what tasks run; stem_pool_kernel takes images whose rows are not
+// whole 16-byte pieces, and is what the other one is compared with (a task runs it under the tuning override only).
+//
+// stem_pool_kernel: a workgroup owns 7 x 8 pooled pixels.  It computes the 15 x 17 conv pixels they depend on
+// (255 rows of a 256-row MFMA tile; the overlap between neighbouring tiles is recomputed), keeps them in
 // LDS, pools there and writes only the pooled 16-byte vectors.
 //
 // As in the stand-alone stem kernel the input patch is staged in LDS with 4
@@ -31,7 +33,6 @@ typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef short i16x2_t __attribute__((ext_vector_type(2)));
 
 struct StemPoolArgs {
     const unsigned char* x;
@@ -239,14 +240,15 @@ __global__ __launch_bounds__(256) void stem_pool_kernel(const StemPoolArgs a)
 //    odd column and the even one before it: 15 reads per conv row, not 22 (8-aligned reads give 73 bytes a cycle and CU, and with
 //    scale and shift read from there as well they were the bound).
 //  * A SIMD starts an MFMA every 32 cycles and up to six other instructions of the same wavefront are free behind it (measured;
-//    eight: 43 cycles).  A conv row has 44 MFMAs and about 230 others, laid behind them five at a time.
-//  * Groups of four input rows are loaded as far ahead as their latency asks for, not as soon as there is room: a wavefront
+//    eight: 43 cycles).  A conv row has 44 MFMAs and about 220 others, laid behind them five at a time.
+//  * Groups of four input rows are loaded one or two row pairs ahead, as their latency asks for, not as soon as there is room: a wavefront
 //    that requests more than the memory takes waits at the request (all 27 loads of a strip first: 5 us instead of 2 before the
 //    first MFMA at batch 64).
 // Bound: the MFMAs (22 GFLOP with padding and what is computed twice at batch 64) at the clock they leave: 2816 cycles of MFMAs in
 // 3660 per row pair, at 1.7 GHz.  Measured (us per launch inside the network, this kernel / the one of 8x7 patches with two
-// workgroups per CU before it): batch 64 22.6 / 35.6, batch 128 40.4 / 66.4, 13 images on 96 CUs 11.5 / 18.9, 16 images 9.1 / 15.9,
-// one image 6.0 / 9.3, one on 32 CUs 5.9 / 11.2.
+// workgroups per CU before it): batch 64 23.2 / 37.0, batch 128 41.0 / 67.6, 13 images on 96 CUs 11.8 / 19.6, 16 images 9.8 / 14.2,
+// one image 5.9 / 6.0, on 64 CUs 6.2 / 6.0, on 32 CUs 6.3 / 7.8.  (The first pass of a new task, one image, weights and code cold: 6.8 / 7.0,
+// on 32 CUs 7.2 / 8.7.)
 // The elements of a run beside its taps (0 / 22 / 23, of even columns the three before and none behind) are real neighbouring inputs
 // multiplied by zero weights: the result equals the plain definition for finite inputs.  A pixel that is NaN or infinite also makes the sums of
 // these columns NaN: odd ones whose window begins right of it (its channel 2) or ends left of it (channels 0 and 1), even ones whose window
@@ -256,7 +258,7 @@ constexpr int kStripCols = 30, kStripRows = 7;       // pooled columns and rows 
 constexpr int kRowPitch = 24 * kStripCols + 48;      // bytes of an input row in LDS: 48 pieces of 16
 constexpr int kGroupBytes = 4 * kRowPitch;           // rows are loaded by fours: three instructions
 constexpr int kStripLds = (kStripRows + 2) * kGroupBytes;
-constexpr int kAhead = 5;                            // groups of rows loaded before the first is used: two row pairs, 3.5 us
+constexpr int kAhead = 5;                            // groups of rows loaded before the first is used
 constexpr int kFragments = 44;                       // [odd, even][K-step 0 .. 10][channel tile], 1024 bytes each; then scale and shift
 constexpr int kFragmentLds = 48 * 1024;              // (what the wavefronts load of them, twelve instructions each)
 constexpr int kOutPitch = 144;                       // a pixel of a finished row, where the fragments were
@@ -399,7 +401,9 @@ __global__ __launch_bounds__(256, 1) void stem_pool_packed_kernel(const StemRows
     asm volatile("" ::: "memory");
 
     // Groups are loaded `ahead` of the first one of a conv row, one every two rows (more at once only wait in the wavefront's way):
-    // the three that a row reads have landed when all but the last ahead - 3 have.
+    // the three that a strip's first row reads have landed when all but the last ahead - 3 have.  From the second row pair on the
+    // stores of a finished row lie between the loads and count as well: what is left in flight is one group and three stores, so
+    // that a group has one row pair to land, 2.2 us.
     auto wait_for_rows = [&] {
         __builtin_amdgcn_sched_barrier(0);
         if (a.ahead >= kAhead) stem_wait_vmcnt<3 * (kAhead - 3)>();
@@ -557,7 +561,7 @@ bool stem_pool_applicable(int dtype, int n, int h, int w, int cus)
     const int PP = (P - 1) / 2 + 1, PQ = (Q - 1) / 2 + 1;
     const long long tiles = (long long)n * ((PP + kPoolTP - 1) / kPoolTP) * ((PQ + kPoolTQ - 1) / kPoolTQ);
     // smaller launches keep the finer-grained two-kernel path; in bf16 the fused kernel wins down
-    // to one image (9.4 us against 8.5 + 4.9 us at batch 1); the line for fp32 is where its times cross
+    // to one image (5.9 us, the stem alone 8.5); the line for fp32 is where its times cross
     // (us, two kernels and the gap between them against one, 256 CUs: 3 images 20 / 21, 5 images 24 / 21,
     // 9 images 38 / 34), expressed in the 7x8 tiles counted here, not the 4x8 ones of its own kernel; and where
     // its own tiles all run at once (the whole fp32 network, one image on 256 CUs: 115.5 us with two kernels, 112.8 fused)
