@@ -196,7 +196,10 @@ int sgprs_conv2d_plan(const sgprs_conv_desc_t *d, int partition_cus, int has_res
  * x: [n][h][w][cin]; w_packed: DEVICE copy of the packed weights; scale, shift:
  * DEVICE fp32[cout]; residual: NULL or [n][p][q][cout] in dtype; y: same shape.
  * workspace: DEVICE, at least sgprs_conv2d_workspace() bytes (may be NULL if 0).
- * x, residual and y must not overlap. */
+ * x, residual and y must not overlap.
+ * The kernels that read the weights in another order (a task packs them so once, beside the
+ * packed layout: large bf16 batches' stride-1 layers and paired down-sampling layers, fp32 layers
+ * as three bf16 planes) are the tasks' alone; this entry point runs the others. */
 int sgprs_conv2d(const sgprs_conv_desc_t *d, const void *x, const void *w_packed,
                  const float *scale, const float *shift, const void *residual, void *y,
                  void *workspace, size_t workspace_bytes, sgprs_pool_t *pool, int partition);
