@@ -373,7 +373,7 @@ bool s2tile_fits(const sgprs_conv_desc_t& d, const sgprs_conv_desc_t& d1, int v)
 // Estimated time (us) inside a network whose inputs change: a fixed part, what the busiest CU's items take (a part of their own and their
 // stages, at the clock that the share of the chip in use leaves) and a part of the memory traffic.  Whole items on the busiest
 // CU: one more than the others have takes as long as one on each (4 x 1 tiles, 56x56x64 -> 128 on 256 CUs: 64 images 19.6, 68 images 24.8).
-// Two 4 x 1 items share a CU's matrix cores: 7.9 for the pair, 4.8 for one that is left.  Fitted to the three blocks, 1 to 512
+// Two 4 x 1 items share a CU's matrix cores: 8.2 for the pair, 5.2 for one that is left.  Fitted to the three blocks, 1 to 512
 // images on 8 to 256 CUs: 4 to 5 % off rms, 16 % at most.
 bool plan_s2tile(const sgprs_conv_desc_t& d, const sgprs_conv_desc_t& d1, int cus, int* variant, double* cost_us)
 {
@@ -390,10 +390,12 @@ bool plan_s2tile(const sgprs_conv_desc_t& d, const sgprs_conv_desc_t& d1, int cu
         const double active = (double)std::min<long long>(items, cus) / 256;
         const double cost = v == 0 ? 6.5 + busiest * (2.7 + stages * 2.85) + 0.11 * mb
                           : v == 1 ? 7.5 + busiest * (3.5 + stages * (2.25 + 0.7 * active)) + 0.063 * mb
-                          : v == 2 ? 5.2 + busiest / 2 * 7.9 + busiest % 2 * 4.8 + 0.126 * mb
+                          : v == 2 ? 4.6 + busiest / 2 * 8.2 + busiest % 2 * 5.2 + (busiest == 1 ? 4.0 * active : 0.0) + 0.126 * mb
                                    : 4.9 + busiest * (2.4 + stages * (1.75 + 0.6 * active)) + 0.058 * mb;
-        // with fewer items every CU waits for cold weights: 6 images on 96 CUs, 48 items, 13.6 us against 10.3
-        if (items * 5 < cus * 3) continue;
+        // With fewer items every CU waits for cold weights: 6 images on 96 CUs, 48 items, 13.6 us against 10.3.  One 4 x 1 item on a CU
+        // has nothing that covers for it either, the less the more CUs ask for weights (whole networks with the implicit GEMM / with this:
+        // 20 images on 256 CUs 198.5 / 201.5 us, 19 on 160 214.7 / 217.8, 10 on 96 198.5 / 199.8; 8 on 64 200.7 / 199.8).
+        if (items * 5 < cus * (v == 2 && busiest == 1 ? 4 : 3)) continue;
         // Each of two workgroups on a CU fetches the weights, and on the whole chip the launches after this one pay for it (56x56x64 -> 128, 128
         // images on 256 CUs, 4 x 1 / 7 x 1 tiles: traced 35.7 / 37.8 us, whole network 551.1 / 548.5).
         const double rank = cost + (v == 2 ? 0.2 * busiest * active : 0.0);

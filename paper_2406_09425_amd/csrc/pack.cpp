@@ -278,8 +278,8 @@ static ConvPlan plan_conv_pair_uncached(const sgprs_conv_desc_t& d0, const sgprs
         }
     }
     // Near a tie the launch chosen so far stays.  Of the three blocks' launches at 167 sizes (1 to 512 images, 8 to 256 CUs, inputs that change)
-    // this choice is more than 2 % slower than the implicit GEMM and the K-split kernel at 6, by 1 to 9 % (25 images on 224 CUs, 56x56x64 -> 128:
-    // 13.6 / 14.9 us), and leaves 1 % of all their time to the best launch of each size.
+    // this choice is more than 2 % slower than the implicit GEMM and the K-split kernel at 4, by 2 to 9 % (27 images on 64 CUs, 28x28x128 -> 256:
+    // 22.2 / 24.2 us), and leaves 1 % of all their time to the best launch of each size.
     int variant;
     double cost;
     if (fragments && plan_s2tile(d0, d1, cus, &variant, &cost) && cost < 0.98 * pair_in_network(best, d0, d1, cus, best_cost)) {
